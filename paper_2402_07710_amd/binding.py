@@ -1,18 +1,24 @@
-"""ctypes binding of libsc.so: the same calls as include/sc.h, taking torch tensors.
+"""Python binding of libsc.so: the same calls as include/sc.h, taking torch tensors.
 
 Argument marshalling only - every step of the path runs in the library's HIP kernels.  PyTorch
 supplies device memory (tensors) and the stream.  There is no CPU fallback: if the library has
 not been built, or no GPU is present when a call needs one, the call raises.
+
+The calls a layer makes every frame go through the CPython module `_native` (csrc/sc_python.cpp),
+which reads the tensors itself; size queries, read-back and the measurement aids use ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("SC_LIB_PATH", os.path.join(HERE, "libsc.so"))   # override: development builds
+NATIVE_PATH = os.path.join(HERE, "_native.so")
 
 SC_OK, SC_EINVAL, SC_ERANGE, SC_EDUP, SC_ECAP, SC_EHIP, SC_EFULL = 0, -1, -2, -3, -4, -5, -6
 SC_SUBM, SC_STRIDED, SC_INVERSE = 0, 1, 2
@@ -61,9 +67,10 @@ def load(build_if_missing: bool = True) -> ctypes.CDLL:
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    missing = [p for p in (LIB_PATH, NATIVE_PATH) if not os.path.exists(p)]
+    if missing:
         if not build_if_missing:
-            raise FileNotFoundError(f"{LIB_PATH} has not been built")
+            raise FileNotFoundError(f"{missing[0]} has not been built")
         from . import build as _build
         _build.build()
     lib = ctypes.CDLL(LIB_PATH)
@@ -103,8 +110,35 @@ def load(build_if_missing: bool = True) -> ctypes.CDLL:
     for name, (res, args) in sig.items():
         fn = getattr(lib, name)
         fn.restype, fn.argtypes = res, args
+    _load_native(lib)
     _lib = lib
     return lib
+
+
+# the functions _native calls, in the order its bind() takes their addresses
+_NATIVE_CALLS = ["sc_hash_build", "sc_hash_rebuild", "sc_kmap_build", "sc_kmap_build_noalloc", "sc_kmap_transpose", "sc_conv_fwd",
+                 "sc_conv_fwd_packed", "sc_conv_up_fwd", "sc_conv_fwd_grid", "sc_grid_build", "sc_kmap_build_grid"]
+
+
+class _NativeOnFirstUse:
+    """Stands in for the module until a call needs it: loads the library, which replaces this object."""
+
+    def __getattr__(self, name):
+        load()
+        return getattr(_native, name)
+
+
+_native = _NativeOnFirstUse()
+
+
+def _load_native(lib: ctypes.CDLL):
+    global _native
+    loader = importlib.machinery.ExtensionFileLoader("_native", NATIVE_PATH)
+    spec = importlib.util.spec_from_loader("_native", loader)
+    module = importlib.util.module_from_spec(spec)
+    loader.exec_module(module)
+    module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS))
+    _native = module
 
 
 def strerror(code: int) -> str:
@@ -155,16 +189,16 @@ def sc_conv_workspace_bytes(K: int, C_in: int, C_out: int, dtype) -> int:
 
 def sc_hash_build(coords, table, counts, stream=None):
     """coords int32 [n,4] (device), table uint8 [>= sc_hash_bytes(n)], counts uint8 [COUNTS_BYTES]."""
-    n = coords.shape[0]
-    _check(load().sc_hash_build(_ptr(coords), n, _ptr(table), table.numel() * table.element_size(),
-                                _ptr(counts), _stream(stream)), "sc_hash_build")
+    rc = _native.hash_build(coords, table, counts, stream)
+    if rc:
+        _check(rc, "sc_hash_build")
 
 
 def sc_hash_rebuild(coords, table, epoch, counts, stream=None):
     """Build again, without the filling pass, into a table that sc_hash_build initialised (same n)."""
-    n = coords.shape[0]
-    _check(load().sc_hash_rebuild(_ptr(coords), n, _ptr(table), table.numel() * table.element_size(), epoch,
-                                  _ptr(counts), _stream(stream)), "sc_hash_rebuild")
+    rc = _native.hash_rebuild(coords, table, epoch, counts, stream)
+    if rc:
+        _check(rc, "sc_hash_rebuild")
 
 
 def sc_hash_lookup(table, n_table, query, rows, stream=None):
@@ -173,19 +207,16 @@ def sc_hash_lookup(table, n_table, query, rows, stream=None):
 
 
 def sc_kmap_build(coords, table, K, stride, mode, out_coords, kmap, scratch, counts, stream=None):
-    n = coords.shape[0]
-    _check(load().sc_kmap_build(_ptr(coords), n, _ptr(table), K, stride, MODES[mode], _ptr(out_coords),
-                                _ptr(kmap), kmap.numel() * kmap.element_size(),
-                                _ptr(scratch), 0 if scratch is None else scratch.numel() * scratch.element_size(),
-                                _ptr(counts), _stream(stream)), "sc_kmap_build")
+    rc = _native.kmap_build(coords, table, K, stride, MODES[mode], out_coords, kmap, scratch, counts, stream)
+    if rc:
+        _check(rc, "sc_kmap_build")
 
 
 def sc_kmap_build_noalloc(coords, table, K, stride, mode, out_coords, kmap, counts, stream=None):
     """sc_kmap_build with the scratch buffer inside the library (no device allocation anywhere)."""
-    n = coords.shape[0]
-    _check(load().sc_kmap_build_noalloc(_ptr(coords), n, _ptr(table), K, stride, MODES[mode], _ptr(out_coords),
-                                        _ptr(kmap), kmap.numel() * kmap.element_size(), _ptr(counts),
-                                        _stream(stream)), "sc_kmap_build_noalloc")
+    rc = _native.kmap_build_noalloc(coords, table, K, stride, MODES[mode], out_coords, kmap, counts, stream)
+    if rc:
+        _check(rc, "sc_kmap_build_noalloc")
 
 
 def sc_grid_bytes(B: int, X: int, Y: int, Z: int) -> int:
@@ -198,8 +229,9 @@ def sc_grid_clear(grid, dims, stream=None):
 
 def sc_grid_build(coords, grid, dims, epoch, counts, stream=None):
     """coords int32 [n,4] (device), grid uint8 [>= sc_grid_bytes(*dims)], dims = (B, X, Y, Z)."""
-    _check(load().sc_grid_build(_ptr(coords), coords.shape[0], _ptr(grid), grid.numel() * grid.element_size(), *dims,
-                                epoch, _ptr(counts), _stream(stream)), "sc_grid_build")
+    rc = _native.grid_build(coords, grid, dims, epoch, counts, stream)
+    if rc:
+        _check(rc, "sc_grid_build")
 
 
 def sc_grid_lookup(grid, dims, epoch, query, rows, stream=None):
@@ -208,51 +240,38 @@ def sc_grid_lookup(grid, dims, epoch, query, rows, stream=None):
 
 
 def sc_kmap_build_grid(coords, grid, dims, epoch, K, kmap, counts, stream=None):
-    _check(load().sc_kmap_build_grid(_ptr(coords), coords.shape[0], _ptr(grid), grid.numel() * grid.element_size(),
-                                     *dims, epoch, K, _ptr(kmap), kmap.numel() * kmap.element_size(), _ptr(counts),
-                                     _stream(stream)), "sc_kmap_build_grid")
+    rc = _native.kmap_build_grid(coords, grid, dims, epoch, K, kmap, counts, stream)
+    if rc:
+        _check(rc, "sc_kmap_build_grid")
 
 
 def sc_conv_up_fwd(feat_coarse, n_map, weight, feat_fine, kmap, counts, K, stream=None):
     """Inverse layer of a K == stride layer from that layer's own map: feat_coarse [n_out, C_in],
     weight [K^3, C_in, C_out], feat_fine [n_map, C_out]."""
-    C_in, C_out = weight.shape[1], weight.shape[2]
-    if tuple(weight.shape) != (K ** 3, C_in, C_out) or weight.dtype != feat_coarse.dtype or \
-            feat_coarse.shape[1] != C_in or tuple(feat_fine.shape) != (n_map, C_out):
-        raise ScError(SC_EINVAL, "sc_conv_up_fwd")
-    _check(load().sc_conv_up_fwd(_ptr(feat_coarse), n_map, _ptr(weight), _ptr(feat_fine), _ptr(kmap),
-                                 kmap.numel() * kmap.element_size(), _ptr(counts), K, C_in, C_out,
-                                 DTYPES[feat_coarse.dtype], DTYPES[feat_fine.dtype], _stream(stream)), "sc_conv_up_fwd")
+    rc = _native.conv_up_fwd(feat_coarse, n_map, weight, feat_fine, kmap, counts, K, stream)
+    if rc:
+        _check(rc, "sc_conv_up_fwd")
 
 
 def sc_conv_fwd_grid(feat_in, coords, grid, dims, epoch, weight, feat_out, K, workspace, stream=None):
     """Fused 3x3x3 submanifold layer over the dense table: no kernel map."""
-    C_in, C_out = weight.shape[1], weight.shape[2]
-    _check(load().sc_conv_fwd_grid(_ptr(feat_in), _ptr(coords), coords.shape[0], _ptr(grid),
-                                   grid.numel() * grid.element_size(), *dims, epoch, _ptr(weight), _ptr(feat_out), K,
-                                   C_in, C_out, DTYPES[feat_in.dtype], DTYPES[feat_out.dtype], _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream(stream)), "sc_conv_fwd_grid")
+    rc = _native.conv_fwd_grid(feat_in, coords, grid, dims, epoch, weight, feat_out, K, workspace, stream)
+    if rc:
+        _check(rc, "sc_conv_fwd_grid")
 
 
 def sc_kmap_transpose(kmap, n, K, stride, counts, kmap_inv, stream=None):
-    _check(load().sc_kmap_transpose(_ptr(kmap), n, K, stride, _ptr(counts), _ptr(kmap_inv),
-                                    kmap_inv.numel() * kmap_inv.element_size(), _stream(stream)), "sc_kmap_transpose")
+    rc = _native.kmap_transpose(kmap, n, K, stride, counts, kmap_inv, stream)
+    if rc:
+        _check(rc, "sc_kmap_transpose")
 
 
 def sc_conv_fwd(feat_in, weight, feat_out, kmap, counts, K, stride, mode, workspace=None, stream=None, n_map=None):
     """feat_in [rows,C_in], weight [K^3,C_in,C_out] (same dtype), feat_out [n_out_cap,C_out];
     n_map = the n the map was built with (default: rows of feat_in)."""
-    n_in, C_in = feat_in.shape
-    n_out_cap, C_out = feat_out.shape
-    if n_map is None:
-        n_map = n_in
-    if tuple(weight.shape) != (K ** 3, C_in, C_out) or weight.dtype != feat_in.dtype:
-        raise ValueError("weight must be [K^3, C_in, C_out] in the feature dtype")
-    _check(load().sc_conv_fwd(_ptr(feat_in), n_map, _ptr(weight), _ptr(feat_out), n_out_cap, _ptr(kmap),
-                              kmap.numel() * kmap.element_size(), _ptr(counts), K, stride, MODES[mode],
-                              C_in, C_out, DTYPES[feat_in.dtype], DTYPES[feat_out.dtype], _ptr(workspace),
-                              0 if workspace is None else workspace.numel() * workspace.element_size(),
-                              _stream(stream)), "sc_conv_fwd")
+    rc = _native.conv_fwd(feat_in, n_map, weight, feat_out, kmap, counts, K, stride, MODES[mode], workspace, stream)
+    if rc:
+        _check(rc, "sc_conv_fwd")
 
 
 def sc_conv_packed_bytes(K: int, C_in: int, C_out: int, dtype) -> int:
@@ -275,16 +294,9 @@ def sc_conv_weight_pack(weight, K, packed=None, stream=None):
 
 def sc_conv_fwd_packed(feat_in, packed, C_out, feat_out, kmap, counts, K, stride, mode, stream=None, n_map=None):
     """sc_conv_fwd with weights packed by sc_conv_weight_pack."""
-    n_in, C_in = feat_in.shape
-    n_out_cap = feat_out.shape[0]
-    if n_map is None:
-        n_map = n_in
-    if feat_out.shape[1] != C_out:
-        raise ValueError("feat_out must have C_out columns")
-    _check(load().sc_conv_fwd_packed(_ptr(feat_in), n_map, _ptr(packed), _ptr(feat_out), n_out_cap, _ptr(kmap),
-                                     kmap.numel() * kmap.element_size(), _ptr(counts), K, stride, MODES[mode],
-                                     C_in, C_out, DTYPES[feat_in.dtype], DTYPES[feat_out.dtype], _stream(stream)),
-           "sc_conv_fwd_packed")
+    rc = _native.conv_fwd_packed(feat_in, n_map, packed, C_out, feat_out, kmap, counts, K, stride, MODES[mode], stream)
+    if rc:
+        _check(rc, "sc_conv_fwd_packed")
 
 
 def sc_counts_read(counts, kmap=None, n=0, K=1, stride=1, mode="subm", stream=None, check=True) -> ScCounts:

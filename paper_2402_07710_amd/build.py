@@ -1,15 +1,18 @@
-"""Compile the HIP sources under csrc/ into libsc.so for gfx950 (in-tree, next to this file)."""
+"""Compile the HIP sources under csrc/ into libsc.so for gfx950, and csrc/sc_python.cpp into the
+CPython module that hands torch tensors to it (both in-tree, next to this file)."""
 from __future__ import annotations
 
 import concurrent.futures
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsc.so")
+NATIVE = os.path.join(HERE, "_native.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -23,6 +26,25 @@ FLAGS = [
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-option-ignored",
 ]
+
+
+CXX = os.environ.get("CXX", "g++")
+
+
+def native_command() -> list[str]:
+    """Host compiler call for the CPython module (no device code in it)."""
+    import torch
+    home = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    return [
+        CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+        f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+        "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+        "-isystem", os.path.join(home, "include"), "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
+        "-isystem", os.path.join(rocm, "include"),
+        os.path.join(CSRC, "sc_python.cpp"), "-o", NATIVE,
+        "-L", os.path.join(home, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+    ]
 
 
 def sources() -> list[str]:
@@ -46,20 +68,23 @@ def build(force: bool = False, verbose: bool = False) -> str:
         objs.append(obj)
         if force or _stale(obj, [src] + headers):
             jobs.append([HIPCC, *FLAGS, "-c", src, "-o", obj])
+    lib_stale = force or bool(jobs)
+    if force or _stale(NATIVE, [os.path.join(CSRC, "sc_python.cpp")] + headers):
+        jobs.append(native_command())
 
     def run(cmd):
         if verbose:
             print(" ".join(cmd), flush=True)
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+            raise RuntimeError(f"compiler failed:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
         return r.stderr
 
     with concurrent.futures.ThreadPoolExecutor(max_workers=4) as ex:
         for warn in ex.map(run, jobs):
             if verbose and warn.strip():
                 print(warn)
-    if force or jobs or _stale(LIB, objs):
+    if lib_stale or _stale(LIB, objs):
         run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     return LIB
 
