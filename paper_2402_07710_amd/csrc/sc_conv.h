@@ -1,0 +1,68 @@
+// Definitions shared by the convolution kernels (sc_conv*.hip).
+#pragma once
+
+#include "sc_internal.h"
+
+namespace sc {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Packed weights: W [K3][C_in][C_out] (16-bit elements) as MFMA A-operand tiles of W[k]^T.  A tile
+// is 64 lanes x 16 bytes: lane l of tile (k, cb, ks) holds W[k][ks*32 + 8*(l/16) + j][cb*16 + l%16],
+// j = 0..7.  Inside one offset k the tiles are ordered by 64-channel half of C_in first, then
+// output block, then 32-channel slice of the half, so the tiles a kernel needs for one half of the
+// input channels are one contiguous piece: tile number wtile(KS, CB, cb, ks) below (for C_in = 32
+// there is one slice and the order is just cb).
+__host__ __device__ constexpr int wtile(int KS, int CB, int cb, int ks) {
+    return KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1);
+}
+// Workgroup barrier for data exchanged through LDS only.  __syncthreads() also waits until every
+// outstanding global load of the wavefront has returned (vmcnt(0)), which would drain the gathers
+// and weight fetches that were issued ahead on purpose; here only the wavefront's LDS operations
+// have to be complete before it arrives.
+__device__ inline void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int DT>
+__device__ inline f32x4 mfma16x16x32(uint4 a, uint4 b, f32x4 c) {
+    if constexpr (DT == SC_F16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+__device__ inline uint32_t f32_to_bf16_rne(float f) {
+    uint32_t u = __builtin_bit_cast(uint32_t, f);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;     // NaN stays NaN
+    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+}
+template <int DT>
+__device__ inline uint32_t pack2(float lo, float hi) {
+    if constexpr (DT == SC_F16) {
+        const _Float16 a = (_Float16)lo, b = (_Float16)hi;              // round to nearest even
+        return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+    } else {
+        return f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
+    }
+}
+
+// Store one accumulator block: the lane holds channels cb*16 + 4*qq .. +3 of output row `row`.
+template <int DT>
+__device__ inline void store_acc(void* __restrict__ out, int out_f32, int64_t row, int C_out, int col, f32x4 d) {
+    if (out_f32) {
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + row * C_out + col) = make_float4(d[0], d[1], d[2], d[3]);
+    } else {
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + row * C_out + col) =
+            make_uint2(pack2<DT>(d[0], d[1]), pack2<DT>(d[2], d[3]));
+    }
+}
+
+// The general 16-bit kernel (sc_conv_gather.hip): any K^3 <= 343, C_in 32 / 64 / 128 / 256, C_out a multiple of 16.
+int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const uint16_t* feat,
+                  const uint4* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap);
+
+}  // namespace sc

@@ -13,24 +13,10 @@
 // A layer of ~10^5 voxels is a few microseconds of matrix work, so what decides its time is how
 // many loads are in flight: the kernels below issue the offset-table reads of all K^3 offsets,
 // then all feature gathers, before the first multiply.
-#include "sc_internal.h"
+#include "sc_conv.h"
 
 namespace sc {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// Packed weights: W [K3][C_in][C_out] (16-bit elements) as MFMA A-operand tiles of W[k]^T.  A tile
-// is 64 lanes x 16 bytes: lane l of tile (k, cb, ks) holds W[k][ks*32 + 8*(l/16) + j][cb*16 + l%16],
-// j = 0..7.  Inside one offset k the tiles are ordered by 64-channel half of C_in first, then
-// output block, then 32-channel slice of the half, so the tiles a kernel needs for one half of the
-// input channels are one contiguous piece: tile number wtile(KS, CB, cb, ks) below (for C_in = 32
-// there is one slice and the order is just cb).
-__host__ __device__ constexpr int wtile(int KS, int CB, int cb, int ks) {
-    return KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1);
-}
 __global__ void __launch_bounds__(256)
 k_weight_pack(const uint16_t* __restrict__ w, uint4* __restrict__ wp, int K3, int C_in, int C_out) {
     const int KS = C_in / 32, CB = C_out / 16;
@@ -50,48 +36,6 @@ k_weight_pack(const uint16_t* __restrict__ w, uint4* __restrict__ wp, int K3, in
     for (int j = 0; j < 4; ++j)
         v[j] = (uint32_t)src[(int64_t)(2 * j) * C_out] | ((uint32_t)src[(int64_t)(2 * j + 1) * C_out] << 16);
     wp[((int64_t)k * CB * KS + wtile(KS, CB, cb, ks)) * 64 + lane] = make_uint4(v[0], v[1], v[2], v[3]);
-}
-
-// Workgroup barrier for data exchanged through LDS only.  __syncthreads() also waits until every
-// outstanding global load of the wavefront has returned (vmcnt(0)), which would drain the gathers
-// and weight fetches that were issued ahead on purpose; here only the wavefront's LDS operations
-// have to be complete before it arrives.
-__device__ inline void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-template <int DT>
-__device__ inline f32x4 mfma16x16x32(uint4 a, uint4 b, f32x4 c) {
-    if constexpr (DT == SC_F16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-__device__ inline uint32_t f32_to_bf16_rne(float f) {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;     // NaN stays NaN
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
-template <int DT>
-__device__ inline uint32_t pack2(float lo, float hi) {
-    if constexpr (DT == SC_F16) {
-        const _Float16 a = (_Float16)lo, b = (_Float16)hi;              // round to nearest even
-        return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
-    } else {
-        return f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
-    }
-}
-
-// Store one accumulator block: the lane holds channels cb*16 + 4*qq .. +3 of output row `row`.
-template <int DT>
-__device__ inline void store_acc(void* __restrict__ out, int out_f32, int64_t row, int C_out, int col, f32x4 d) {
-    if (out_f32) {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + row * C_out + col) = make_float4(d[0], d[1], d[2], d[3]);
-    } else {
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + row * C_out + col) =
-            make_uint2(pack2<DT>(d[0], d[1]), pack2<DT>(d[2], d[3]));
-    }
 }
 
 // ---- small layers: all of W resident in LDS ----------------------------------------------------
@@ -821,57 +765,7 @@ k_conv_direct64(const uint16_t* __restrict__ feat, const uint4* wp, void* __rest
     SC_MARK(5);
 }
 
-// ---- any shape: weights read from global memory, offsets walked by mask bit --------------------
-// One wavefront per 16 output rows, one tile per workgroup.  C_in = 32*KS (KS <= 8),
-// C_out = 16*CB (CB <= 16), any K3 <= 343.
-constexpr int KS_MAX = 8, CB_MAX = 16;
-template <int DT>
-__global__ void __launch_bounds__(256)
-k_conv_rows16_any(const uint16_t* __restrict__ feat, const uint4* __restrict__ wp, void* __restrict__ out,
-                  int out_f32, const uint32_t* __restrict__ gmask, const int32_t* __restrict__ nbr, int K3, int mw,
-                  int KS, int CB, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
-    const int C_in = KS * 32, C_out = CB * 16;
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int r = lane & 15, qq = lane >> 4;
-    const int64_t tile = blockIdx.x;
-    int64_t n_out = *n_out_ptr;
-    if (n_out > n_out_cap) n_out = n_out_cap;
-    const int64_t row = tile * TILE + q * 16 + r;
-    if (tile * TILE + q * 16 >= n_out) return;                       // uniform per wavefront
-
-    f32x4 acc[CB_MAX];
-#pragma unroll
-    for (int cb = 0; cb < CB_MAX; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int32_t* line = nbr + tile * (int64_t)K3 * TILE + q * 16 + r;
-    for (int wi = 0; wi < mw; ++wi) {
-        uint32_t m = gmask[(tile * 4 + q) * mw + wi];
-        while (m) {
-            const int k = wi * 32 + __builtin_ctz(m);
-            m &= m - 1;
-            const int32_t e = line[(int64_t)k * TILE];
-            uint4 fb[KS_MAX];
-            const uint4* frow = reinterpret_cast<const uint4*>(feat + (int64_t)(e < 0 ? 0 : e) * C_in) + qq;
-#pragma unroll
-            for (int ks = 0; ks < KS_MAX; ++ks)
-                if (ks < KS) fb[ks] = e >= 0 ? frow[ks * 4] : make_uint4(0, 0, 0, 0);
-            const uint4* wk = wp + (int64_t)k * CB * KS * 64 + lane;
-#pragma unroll
-            for (int cb = 0; cb < CB_MAX; ++cb) {
-                if (cb < CB) {
-#pragma unroll
-                    for (int ks = 0; ks < KS_MAX; ++ks)
-                        if (ks < KS) acc[cb] = mfma16x16x32<DT>(wk[wtile(KS, CB, cb, ks) * 64], fb[ks], acc[cb]);
-                }
-            }
-        }
-    }
-    if (row < n_out) {
-#pragma unroll
-        for (int cb = 0; cb < CB_MAX; ++cb)
-            if (cb < CB) store_acc<DT>(out, out_f32, row, C_out, cb * 16 + qq * 4, acc[cb]);
-    }
-}
-
+constexpr int CB_MAX = 16;
 // ---- fp32 features and weights -------------------------------------------------------------------
 // Same scheme with the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: true fp32 products and
 // sums): one wavefront per 16 output rows, offsets walked by mask bit, operands read straight from
@@ -1068,22 +962,24 @@ static int launch_stream(int64_t tiles, hipStream_t s, const uint16_t* feat, con
     return SC_OK;
 }
 
+// Compute units of the current device, asked once (a race between host threads stores the same value).
+static int compute_units() {
+    static int cu_count[MAX_DEVICES] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return 256;
+    if (cu_count[dev] == 0) {
+        int n = 0;
+        cu_count[dev] = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
+    }
+    return cu_count[dev];
+}
+
 // Tiles per workgroup for k_conv_direct64: its wavefronts are independent, so any count up to 8
 // (two wavefronts per SIMD at its register use) works; the workgroups should land on the CUs evenly.
 // Up to 8 tiles per CU: one workgroup per CU with ceil(tiles / CUs) wavefronts (measured on ~110 k
 // voxels: 31.4 us with 7, 33.3 with 8, 35.1 with 4); beyond that, four (261 k voxels: 62.6 us
 // with 4, 64.0 with 8, 78.1 with 7).
-static int direct_tiles_per_workgroup(int64_t tiles, int* cu_count_out) {
-    static int cu_count[MAX_DEVICES] = {};      // per device, asked once (a race between host threads stores the same value)
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES) {
-        if (cu_count[dev] == 0) {
-            int n = 0;
-            cu_count[dev] = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
-        }
-        cus = cu_count[dev];
-    }
-    *cu_count_out = cus;
+static int direct_tiles_per_workgroup(int64_t tiles, int cus) {
     if (tiles > (int64_t)cus * 8) return 4;
     const int64_t per_cu = (tiles + cus - 1) / cus;
     return per_cu < 1 ? 1 : (int)per_cu;
@@ -1108,8 +1004,7 @@ static int launch_direct64_as(int64_t tiles, int nwv, hipStream_t s, const uint1
 template <int DT, int K3, int FUSED>
 static int launch_direct64(int64_t tiles, hipStream_t s, const uint16_t* feat, const uint4* wp, void* out, int out_f32,
                            const MapSource& ms, const int64_t* counts, int64_t n_out_cap) {
-    int cus = 256;
-    const int nwv = direct_tiles_per_workgroup(tiles, &cus);
+    const int cus = compute_units(), nwv = direct_tiles_per_workgroup(tiles, cus);
     if (tiles <= (int64_t)cus * 4)
         return launch_direct64_as<DT, K3, FUSED, 0>(tiles, nwv, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
     return launch_direct64_as<DT, K3, FUSED, 1>(tiles, nwv, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
@@ -1209,13 +1104,7 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
                                                              n_out_ptr, n_out_cap, feat_small, &handled);
     if (handled || rc != SC_OK) return rc;
     if (FUSED) return SC_EINVAL;
-    if (dtype_in == SC_F16)
-        SC_LAUNCH(KID_CONV_MFMA, k_conv_rows16_any<SC_F16>, dim3((unsigned)tiles), dim3(256), 0, s, feat, wp, d_feat_out, out_f32,
-                  ms.gmask, ms.nbr, K3, mw, C_in / 32, C_out / 16, n_out_ptr, n_out_cap);
-    else
-        SC_LAUNCH(KID_CONV_MFMA, k_conv_rows16_any<SC_BF16>, dim3((unsigned)tiles), dim3(256), 0, s, feat, wp, d_feat_out, out_f32,
-                  ms.gmask, ms.nbr, K3, mw, C_in / 32, C_out / 16, n_out_ptr, n_out_cap);
-    return SC_OK;
+    return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
 }
 
 }  // namespace sc

@@ -1,0 +1,28 @@
+"""GPU tests of single kernels and dispatch branches at the sizes where they can go wrong (edges of
+tiles, remainders, the smallest and largest of a range), against the CPU oracle."""
+import numpy as np
+import pytest
+
+from paper_2402_07710_amd import synth
+from tests.test_gpu_parity import check_layer, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K,C_in,C_out", [(3, 256, 256), (3, 256, 80), (3, 128, 48), (3, 64, 16), (3, 32, 144), (5, 32, 32), (5, 64, 64),
+                                          (5, 256, 16), (7, 32, 48)])
+@pytest.mark.parametrize("n,dtype", [(1, "f16"), (65, "bf16"), (2000, "f16")])
+def test_general_kernel(K, C_in, C_out, n, dtype):
+    """Every number of input slices, output blocks that do and do not fill a workgroup's share, offsets
+    beyond one mask word, and tiles with fewer offsets than a step holds."""
+    say(f"general kernel K={K} {C_in}->{C_out} {dtype} n={n}")
+    coords = synth.uniform_cells(n, 10 if n < 1000 else 20, seed=K + C_in + n)
+    coords[:, 0] = np.arange(n) % 2
+    check_layer(coords, K, 1, "subm", C_in, C_out, dtype, seed=n, out_dtype="f32" if n == 65 else None)
+
+
+def test_general_kernel_with_two_output_blocks_per_wavefront():
+    say("general kernel, many tiles, 96 and 256 output channels")
+    coords = synth.lidar_scene(4)[:26000]
+    check_layer(coords, 3, 1, "subm", 32, 96, "f16", seed=1, threads=16)
+    check_layer(coords[:13000], 3, 1, "subm", 32, 256, "bf16", seed=1, threads=16)
