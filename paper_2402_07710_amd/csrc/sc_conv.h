@@ -61,8 +61,9 @@ __device__ inline void store_acc(void* __restrict__ out, int out_f32, int64_t ro
     }
 }
 
-// The general 16-bit kernel (sc_conv_gather.hip): any K^3 <= 343, C_in 32 / 64 / 128 / 256, C_out a multiple of 16.
-int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const uint16_t* feat,
-                  const uint4* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap);
+// The general kernel (sc_conv_gather.hip): any K^3 <= 343, C_out a multiple of 16; 16-bit layers with C_in 32, 64,
+// 128 or 256 and packed weights, fp32 layers with C_in 16, 32, 64, 128 or 256 and weights as they are.
+int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const void* feat,
+                  const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap);
 
 }  // namespace sc

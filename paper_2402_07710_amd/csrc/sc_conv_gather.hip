@@ -1,5 +1,5 @@
-// The general 16-bit convolution kernel: every shape without a kernel of its own in sc_conv.hip
-// (kernel sizes other than 3, 256 channels, unequal channel counts).
+// The general convolution kernel: every shape without a kernel of its own in sc_conv.hip (kernel sizes
+// other than 3, 256 channels, unequal channel counts), and fp32 layers with enough work for it.
 #include "sc_conv.h"
 
 namespace sc {
@@ -14,71 +14,89 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory");
 }
 
-// One workgroup of four wavefronts per 64-row tile and block of output channels.  The sum over
-// (offset, input channel) is walked in steps of SL 32-channel slices: one offset of 256 or 128 channels, 2
-// of 64 or 4 of 32 per step, only the offsets at which the tile has a neighbour.
+// One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
+// input channel) is walked in steps of SL slices of 64 bytes of a row (32 16-bit or 16 fp32 channels):
+// four slices per step (one offset of 256 bytes, 2 of 128, 4 of 64, a part of a longer one; eight
+// for 16-bit rows of 512 bytes), only the offsets at which the tile has a neighbour.
 //  * The rows of the next step are gathered straight into the other half of a double LDS buffer
-//    while this step multiplies, each wavefront fetching its 16-row group with eight (four at 32
-//    channels) consecutive lanes on one row: whole lines, a quarter of the address cycles of a
-//    gather in operand order.  The 16-byte pieces of a row are placed XOR-ed with the row number, so
-//    the operand reads (16 rows x one piece) use all banks.
-//  * The weight operands of the next step go from the packed tiles in global memory (whole lines,
-//    the same for all tiles: cache hits) to a second set of registers.  A wavefront owns CT
-//    16-channel output blocks, so no two wavefronts of a tile load the same weights unless the layer
-//    has fewer than 64 output channels (then they split the rows: WR).
-//  * One wait for everything and one barrier per step.
-// Groups without a neighbour are skipped where an offset is at least four slices (KS >= 4); below that
-// the test costs more than the multiplies: they read the row of zeros, and the places of the last
-// step that have no offset are fetched like the others (of offset 0, rows of zeros) and not multiplied.
-// Before (one wavefront per 16 rows, weights and rows loaded at their use): 14 k voxels 256 -> 256
-// 555 us, 53 k voxels K = 5 32 -> 32 116 us.
-template <int DT, int KS, int WR, int CT, int SL>
-__global__ void __launch_bounds__(256, 2)
-k_conv_gather(const uint16_t* feat, const uint4* wp, void* __restrict__ out, int out_f32, const uint32_t* __restrict__ gmask,
+//    while this step multiplies, with eight (four in 64-byte rows) consecutive lanes on one row: whole
+//    lines, a quarter of the address cycles of a gather in operand order.  The 16-byte pieces of a row
+//    are placed XOR-ed with the row number, so the operand reads (16 rows x one piece) use all banks.
+//  * 16-bit weights of the next step go from the packed tiles in global memory (whole lines, the same
+//    for all tiles: cache hits) to a second set of registers.  A wavefront owns CT 16-channel output
+//    blocks, so no two wavefronts of a tile load the same weights unless the layer has fewer than 64
+//    output channels (then they split the rows: WR).
+//  * fp32 weights are used as they lie in memory, so an operand is 4-byte reads of four rows: loaded
+//    straight to registers they cost as many address cycles as the gathers save (104 us at the size
+//    below); they go through LDS instead.  An fp32 multiply takes eight times as long per byte, so the
+//    wavefronts (eight) split rows as well as channels.
+//  * One wait for everything and one barrier per step.  What a step costs is issuing its loads (17
+//    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
+// Groups without a neighbour are skipped where an offset has at least 128 cycles of multiplies (fp32, or four
+// slices and more); below that the test costs more: they read the row of zeros, and the places of the
+// last step that have no offset are fetched like the others (of offset 0, rows of zeros) and not multiplied.
+// Measured, before (one wavefront per 16 rows, rows and weights loaded at their use) -> now: 14 k
+// voxels 256 -> 256 f16 480-555 -> 44 us; 53 k voxels K = 5 32 -> 32 bf16 116 -> 38 us; 53 k voxels 64 -> 64
+// fp32 118 -> 80 us.
+template <int DT, int KS, int NW, int WR, int CT, int SL>
+__global__ void __launch_bounds__(64 * NW, NW / 2)
+k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const uint32_t* __restrict__ gmask,
               const int32_t* __restrict__ nbr, int K3, int mw, int CB, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
-    constexpr int C_in = KS * 32;
-    constexpr int OPS = SL / KS;                       // offsets per step
-    constexpr int CH = KS == 1 ? 1 : KS / 2;           // chunks per offset: 64 rows x 64 (32) channels
+    constexpr bool F32 = DT == SC_F32;
+    constexpr int KP = KS < SL ? KS : SL, PARTS = KS / KP;     // slices of an offset taken in one step, steps per offset
+    constexpr int OPS = SL / KP;                       // offsets per step
+    constexpr int CH = KP == 1 ? 1 : KP / 2;           // chunks per offset and step: 64 rows x 128 (64) bytes
     constexpr int CHB = KS == 1 ? 4096 : 8192;         // bytes per chunk
-    constexpr int NI = KS == 1 ? 1 : 2;                // gather instructions per wavefront and chunk
+    constexpr int NI = KS == 1 || NW == 8 ? 1 : 2;     // gather instructions per wavefront and chunk
     constexpr int STEP_BYTES = SL * 4096;
-    constexpr int WC = 4 / WR, RG = 4 / WR;            // wavefronts across channels, 16-row groups per wavefront
-    constexpr bool SKIP = KS >= 4;
-    static_assert(SL % KS == 0, "a step is whole offsets");
-    extern __shared__ __align__(16) char smem[];       // [2][STEP_BYTES]
+    constexpr int WC = NW / WR, RG = 4 / WR;           // wavefronts across channels, 16-row groups per wavefront
+    constexpr bool SKIP = F32 || KS >= 4;
+    static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
+    constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
+    constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
+    extern __shared__ __align__(16) char smem[];       // rows[2][STEP_BYTES] | weights[2][W_BYTES]
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, qq = lane >> 4;
     const int wr = wv / WC, cb0 = (int)blockIdx.y * (WC * CT) + (wv % WC) * CT;
     int64_t n_out = n_out_cap;
     if (*n_out_ptr < n_out) n_out = *n_out_ptr;
-    const int64_t tile = xcd_unit_of(blockIdx.x, (n_out + TILE - 1) / TILE);
+    const int64_t tile = xcd_run_of(blockIdx.x, (n_out + TILE - 1) / TILE);
     if (tile < 0) return;                              // the whole workgroup
 
-    // the offsets the tile takes part in, in increasing order: number and 4-bit pattern of groups.  The
-    // tile's mask words are held by the lanes of one register.
+    // the offsets the tile takes part in, in increasing order: number (times PARTS, plus
+    // the part) and 4-bit pattern of groups.  The tile's mask words are held by the lanes of one register.
     const uint32_t mvec = lane < 4 * mw ? gmask[tile * (4 * mw) + lane] : 0u;
-    uint32_t mg[4] = {0u, 0u, 0u, 0u}, rest = 0u;
-    int wi = -1;
+    uint32_t mg[4] = {0u, 0u, 0u, 0u}, rest = 0u, pat_now = 0u;
+    int wi = -1, k_now = -1;
     auto next_offset = [&](int& k, uint32_t& pat) __attribute__((always_inline)) {
+        if (PARTS > 1 && k_now >= 0 && (k_now + 1) % PARTS != 0) {
+            k = ++k_now;
+            pat = pat_now;
+            return;
+        }
         while (rest == 0u && wi + 1 < mw) {
             ++wi;
 #pragma unroll
             for (int g = 0; g < 4; ++g) mg[g] = __builtin_amdgcn_readlane(mvec, g * mw + wi);
             rest = mg[0] | mg[1] | mg[2] | mg[3];
         }
-        k = -1;
-        pat = 0u;
+        k_now = -1;
+        pat_now = 0u;
         if (rest != 0u) {
             const int b = __builtin_ctz(rest);
             rest &= rest - 1u;
-            k = wi * 32 + b;
+            k_now = (wi * 32 + b) * PARTS;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) pat |= ((mg[g] >> b) & 1u) << g;
+            for (int g = 0; g < 4; ++g) pat_now |= ((mg[g] >> b) & 1u) << g;
         }
+        k = k_now;
+        pat = pat_now;
     };
 
-    // gathers: this wavefront fetches group wv; its lane's row inside the group and 16-byte piece
+    // gathers: this wavefront fetches group gw (of eight wavefronts, two share a group: each takes every other
+    // offset, or half of the rows); its lane's row inside the group and 16-byte piece
+    const int gw = NW == 4 ? wv : KS == 1 ? wv & 3 : wv >> 1, half = NW == 4 ? 0 : KS == 1 ? wv >> 2 : wv & 1;
     int grow[NI], gpiece;
     if constexpr (KS == 1) {
         const int logical = (lane & 7) ^ (lane >> 3);  // line = two 64-byte rows, slots XOR-ed with the line number
@@ -86,10 +104,10 @@ k_conv_gather(const uint16_t* feat, const uint4* wp, void* __restrict__ out, int
         gpiece = logical & 3;
     } else {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) grow[i] = i * 8 + (lane >> 3);
+        for (int i = 0; i < NI; ++i) grow[i] = (NW == 8 ? half : i) * 8 + (lane >> 3);
         gpiece = (lane & 7) ^ (lane >> 3);
     }
-    const int32_t* line = nbr + tile * (int64_t)K3 * TILE + wv * 16;
+    const int32_t* line = nbr + tile * (int64_t)K3 * TILE + gw * 16;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const char* fbase = reinterpret_cast<const char*>(feat) + gpiece * 16;
     const char* zbase = reinterpret_cast<const char*>(g_zero_row) + gpiece * 16;
@@ -102,36 +120,59 @@ k_conv_gather(const uint16_t* feat, const uint4* wp, void* __restrict__ out, int
         for (int o = 0; o < OPS; ++o)
 #pragma unroll
             for (int i = 0; i < NI; ++i)
-                if (!SKIP || k[o] >= 0) ev[o][i] = line[(int64_t)(k[o] >= 0 ? k[o] : 0) * TILE + grow[i]];
+                if (!SKIP || k[o] >= 0) ev[o][i] = line[(int64_t)(k[o] >= 0 ? k[o] / PARTS : 0) * TILE + grow[i]];
     };
-    auto gather = [&](const int (&k)[OPS], const uint32_t (&p)[OPS], int buf) {
+    auto gather = [&](const int (&k)[OPS], const uint32_t (&p)[OPS], int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int o = 0; o < OPS; ++o) {
-            if (!SKIP || ((p[o] >> wv) & 1u) != 0u) {
+            if ((!SKIP || ((p[o] >> gw) & 1u) != 0u) && (NW == 4 || KS > 1 || (o & 1) == half)) {
 #pragma unroll
                 for (int i = 0; i < NI; ++i) {
-                    const char* src = (SKIP || k[o] >= 0) && ev[o][i] >= 0 ? fbase + (int64_t)ev[o][i] * (C_in * 2) : zbase;
+                    const char* src = (SKIP || k[o] >= 0) && ev[o][i] >= 0 ? fbase + (int64_t)ev[o][i] * (KS * 64) + k[o] % PARTS * (KP * 64) : zbase;
 #pragma unroll
                     for (int c = 0; c < CH; ++c)
                         load_to_lds(src + c * 128, __builtin_amdgcn_readfirstlane(lds_base + buf * STEP_BYTES + (o * CH + c) * CHB +
-                                                                                  wv * (CHB / 4) + i * 1024));
+                                                                                  gw * (CHB / 4) + (NW == 8 && KS > 1 ? half : i) * 1024));
                 }
             }
         }
     };
+    // 16-bit weights: operand tiles, straight into the registers of the next step
     auto weights = [&](u32x4 (&a)[SL][CT], const int (&k)[OPS]) {
 #pragma unroll
         for (int o = 0; o < OPS; ++o)
             if (!SKIP || k[o] >= 0) {
-                const u32x4* wk = reinterpret_cast<const u32x4*>(wp) + (int64_t)(k[o] >= 0 ? k[o] : 0) * (CB * KS * 64) + lane;
+                const u32x4* w = reinterpret_cast<const u32x4*>(wp) + (int64_t)(k[o] >= 0 ? k[o] : 0) * (CB * KP * 64) + lane;
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
+                for (int ks = 0; ks < KP; ++ks)
 #pragma unroll
                     for (int ct = 0; ct < CT; ++ct) {
                         const int cb = cb0 + ct < CB ? cb0 + ct : CB - 1;      // past the last block: not stored
-                        a[o * KS + ks][ct] = wk[(KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1)) * 64];
+                        a[o * KP + ks][ct] = w[(KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1)) * 64];
                     }
             }
+    };
+    // fp32 weights: rows of W[k] as they lie in memory, into LDS.  Of a slice's 16 input channels
+    // 4 q + j (q the operand's lane quarter, j the multiply) goes to row 4 j + q, and its 16-channel blocks are
+    // XOR-ed with q as far as the row is long, so that the four quarters of an operand read use different banks.
+    auto swizzle = [&](int q) -> int { return NC == 16 ? 0 : NC == 32 ? q >> 1 : q; };
+    auto weights_lds = [&](const int (&k)[OPS], int buf) __attribute__((always_inline)) {
+        constexpr int PS = WC * CT;                    // instructions per slice
+        const int prow = lane / (NC / 4), piece = lane % (NC / 4);
+#pragma unroll
+        for (int i = 0; i < (SL * PS + NW - 1) / NW; ++i) {
+            const int t = i * NW + wv, sl = t / PS, row = t % PS * (16 / PS) + prow;
+            const int q = row & 3, j = row >> 2;
+            int kk = k[0];                             // of offset sl / KP: a chain of selects, the array stays in registers
+#pragma unroll
+            for (int o = 1; o < OPS; ++o) kk = sl >= o * KP ? k[o] : kk;
+            if (t < SL * PS && kk >= 0) {
+                int col = (int)blockIdx.y * NC + ((piece ^ (swizzle(q) << 2)) << 2);
+                if (col > CB * 16 - 4) col = CB * 16 - 4;      // past the last block: not stored
+                const float* src = reinterpret_cast<const float*>(wp) + ((int64_t)kk * (KP * 16) + sl % KP * 16 + 4 * q + j) * (CB * 16) + col;
+                load_to_lds(src, __builtin_amdgcn_readfirstlane(lds_base + 2 * STEP_BYTES + buf * W_BYTES + t * 1024));
+            }
+        }
     };
     f32x4 acc[RG][CT];
 #pragma unroll
@@ -147,19 +188,43 @@ k_conv_gather(const uint16_t* feat, const uint4* wp, void* __restrict__ out, int
 #pragma unroll
         for (int o = 0; o < OPS; ++o) {
             if (p[o] == 0u) continue;
+            f32x4 af[F32 ? KP : 1][CT];
+            if constexpr (F32) {
+#pragma unroll
+                for (int ks = 0; ks < KP; ++ks)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) {
+                        const int block = ((wv % WC) * CT + ct) ^ swizzle(qq);
+                        const float* w = reinterpret_cast<const float*>(smem + 2 * STEP_BYTES + buf * W_BYTES) + (o * KP + ks) * (16 * NC) +
+                                         qq * NC + block * 16 + r;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) af[ks][ct][j] = w[j * (4 * NC)];
+                    }
+            }
 #pragma unroll
             for (int g = 0; g < RG; ++g) {
                 const int gg = wr * RG + g;
                 if (SKIP && ((p[o] >> gg) & 1u) == 0u) continue;
                 const char* rows = smem + buf * STEP_BYTES + o * CH * CHB + gg * (CHB / 4);
-                uint4 b[KS];
+                uint4 b[KP];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) b[ks] = *reinterpret_cast<const uint4*>(rows + (ks >> 1) * CHB + ((ks & 1) ? op1 : op0));
+                for (int ks = 0; ks < KP; ++ks) b[ks] = *reinterpret_cast<const uint4*>(rows + (ks >> 1) * CHB + ((ks & 1) ? op1 : op0));
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
+                for (int ks = 0; ks < KP; ++ks) {
+                    if constexpr (F32) {
+                        // component j of both operands: input channel 16 ks + 4 qq + j at position qq of multiply j
+                        const f32x4 fb = __builtin_bit_cast(f32x4, b[ks]);
 #pragma unroll
-                    for (int ct = 0; ct < CT; ++ct)
-                        acc[g][ct] = mfma16x16x32<DT>(__builtin_bit_cast(uint4, a[o * KS + ks][ct]), b[ks], acc[g][ct]);
+                        for (int j = 0; j < 4; ++j)
+#pragma unroll
+                            for (int ct = 0; ct < CT; ++ct)
+                                acc[g][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[ks][ct][j], fb[j], acc[g][ct], 0, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int ct = 0; ct < CT; ++ct)
+                            acc[g][ct] = mfma16x16x32<DT>(__builtin_bit_cast(uint4, a[o * KP + ks][ct]), b[ks], acc[g][ct]);
+                    }
+                }
             }
         }
     };
@@ -178,7 +243,8 @@ k_conv_gather(const uint16_t* feat, const uint4* wp, void* __restrict__ out, int
     entries(k1);
     next_step(k2, p2);
     gather(k1, p1, 0);
-    weights(a0, k1);
+    if constexpr (F32) weights_lds(k1, 0);
+    else weights(a0, k1);
     entries(k2);
     step_end();
     // one step: request the next one's rows and weights and the entries of the one after, multiply
@@ -191,7 +257,8 @@ k_conv_gather(const uint16_t* feat, const uint4* wp, void* __restrict__ out, int
         }
         next_step(k2, p2);
         gather(k1, p1, buf ^ 1);
-        weights(a_next, k1);
+        if constexpr (F32) weights_lds(k1, buf ^ 1);
+        else weights(a_next, k1);
         entries(k2);
         __builtin_amdgcn_sched_barrier(0);             // requested here, not next to their use
         compute(a, p0, buf);
@@ -214,31 +281,35 @@ k_conv_gather(const uint16_t* feat, const uint4* wp, void* __restrict__ out, int
     }
 }
 
-template <int DT, int KS, int WR, int CT, int SL>
-static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s, const uint16_t* feat, const uint4* wp, void* out,
+template <int DT, int KS, int NW, int WR, int CT, int SL>
+static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-    const unsigned blocks_y = (unsigned)((CB + 4 / WR * CT - 1) / (4 / WR * CT));
-    SC_LAUNCH(KID_CONV_MFMA, (k_conv_gather<DT, KS, WR, CT, SL>), dim3(xcd_grid(tiles), blocks_y), dim3(256), 2 * SL * 4096, s, feat, wp,
+    constexpr size_t lds = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0);
+    static_assert(lds <= 65536, "within the LDS a kernel may use without asking");
+    const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
+    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL>), dim3(xcd_run_grid(tiles), blocks_y), dim3(64 * NW), lds, s, feat, wp,
               out, out_f32, ms.gmask, ms.nbr, K3, mw, CB, n_out_ptr, n_out_cap);
     return SC_OK;
 }
 
 template <int DT, int KS, int SL>
-static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int cus, hipStream_t s, const uint16_t* feat, const uint4* wp, void* out,
+static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-#define SC_GATHER(WR, CT) return launch_gather_as<DT, KS, WR, CT, SL>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
-    if (CB == 1) SC_GATHER(4, 1);
-    if (CB == 2) SC_GATHER(2, 1);
+#define SC_GATHER(NW, WR, CT) return launch_gather_as<DT, KS, NW, WR, CT, SL>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+    constexpr bool F32 = DT == SC_F32;
+    if (CB == 1) SC_GATHER(4, 4, 1);
+    if (CB == 2) SC_GATHER(F32 ? 8 : 4, F32 ? 4 : 2, 1);
     // two output blocks per wavefront halve how often a tile's rows are gathered; one, where the
     // launch would otherwise leave CUs idle (256 input channels, 219 tiles: -> 128 29.0 us with one,
     // 34.2 with two; -> 256, twice the workgroups, 49.1 and 44.1)
-    if (CB <= 4 || 2 * tiles * ((CB + 7) / 8) < 3 * (int64_t)cus) SC_GATHER(1, 1);
-    SC_GATHER(1, 2);
+    if (DT == SC_F32 || CB <= 4 || 2 * tiles * ((CB + 7) / 8) < 3 * (int64_t)cus) SC_GATHER(F32 ? 8 : 4, F32 ? 2 : 1, 1);
+    if constexpr (DT != SC_F32) SC_GATHER(4, 1, 2);
+    return SC_EINVAL;
 #undef SC_GATHER
 }
 
-int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const uint16_t* feat,
-                  const uint4* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
+int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const void* feat,
+                  const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const int CB = C_out / 16;
     // slices per step: a whole offset at 256 channels; four elsewhere, where twice as many workgroups
     // per CU (32 KB of LDS each) are worth more than fewer barriers (53 k voxels K = 5 32 -> 32: 39.3 us,
@@ -247,6 +318,19 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
     return dtype_in == SC_F16                                                                                                     \
                ? launch_gather_ks<SC_F16, KS, SL>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
                : launch_gather_ks<SC_BF16, KS, SL>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+    if (dtype_in == SC_F32) {
+#define SC_GATHER_F32(KS, SL) \
+    return launch_gather_ks<SC_F32, KS, SL>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+        switch (C_in) {
+            case 16: SC_GATHER_F32(1, 4);
+            case 32: SC_GATHER_F32(2, 4);
+            case 64: SC_GATHER_F32(4, 4);
+            case 128: SC_GATHER_F32(8, 4);
+            case 256: SC_GATHER_F32(16, 4);
+        }
+#undef SC_GATHER_F32
+        return SC_EINVAL;
+    }
     switch (C_in) {
         case 32: SC_GATHER_KS(1, 4);
         case 64: SC_GATHER_KS(2, 4);

@@ -26,3 +26,12 @@ def test_general_kernel_with_two_output_blocks_per_wavefront():
     coords = synth.lidar_scene(4)[:26000]
     check_layer(coords, 3, 1, "subm", 32, 96, "f16", seed=1, threads=16)
     check_layer(coords[:13000], 3, 1, "subm", 32, 256, "bf16", seed=1, threads=16)
+
+
+@pytest.mark.parametrize("K,C_in,C_out,n", [(3, 16, 64, 17000), (3, 32, 32, 17000), (3, 64, 64, 1), (3, 64, 64, 65), (3, 64, 80, 1000),
+                                            (3, 128, 16, 700), (3, 256, 48, 300), (5, 16, 16, 700), (5, 32, 32, 65)])
+def test_general_kernel_fp32(K, C_in, C_out, n):
+    """fp32: weights through LDS for 16, 32 and 64 channels per workgroup, rows of one to sixteen slices."""
+    say(f"general kernel fp32 K={K} {C_in}->{C_out} n={n}")
+    coords = synth.lidar_scene(3)[:n] if n > 2000 else synth.uniform_cells(n, 10, seed=K + C_in + n)
+    check_layer(coords, K, 1, "subm", C_in, C_out, "f32", seed=n, threads=16)
