@@ -141,43 +141,51 @@ k_kmap_subm(const int4* __restrict__ coords, int64_t n, const uint4* __restrict_
     SC_MARK(5);
 }
 
-// ---- strided layers with K == stride ---------------------------------------------------------
-// scratch: output-cell table (key -> min input row of the cell), slot_of[n], flag words,
+// ---- strided layers ----------------------------------------------------------------------------
+// An input p pairs with output cell q at offset d whenever p = q*s + d, d in [0,K)^3 (eq. 1-5 for K ==
+// stride, in general the enumeration of Algorithm 1's getOutputCoord with no padding), so it belongs to
+// one cell if K == stride and to up to MAXC = ceil(K/s)^3 cells otherwise.  Its valid (offset, cell)
+// candidates are numbered j = 0.. in ascending offset order; candidate id c = i*MAXC + j therefore
+// orders all candidates by input row and then by offset, and a cell's number is the rank of its lowest
+// candidate id among all cells' lowest ids.
+// scratch: output-cell table (lowest candidate id of the cell), the candidates' slots, flag words,
 // in-block word prefix, block sums / prefixes.
 struct StridedScratch {
-    uint4* oslots;           // output-cell table: {key, min input row}
+    int32_t* oslots;         // output-cell table: smallest candidate id of the cell, or CELL_EMPTY
     uint32_t omask;
     int32_t* slot_of;        // [n]
-    uint64_t* flagword;      // [ceil(n/64)]  bit i%64 set iff input i is the first of its cell
+    uint64_t* flagword;      // [ceil(n/64)]  bit i%64 set iff candidate i is the first of its cell
     int32_t* word_prefix;    // [ceil(n/64)]  flags before this word inside its 1024-block
     int32_t* block_sum;      // [nblk]
     int32_t* block_prefix;   // [nblk]
+    int32_t* cells;          // [CELL_COUNTERS x 32] distinct output cells claimed so far, one 128-byte line per counter
     size_t bytes;
 };
-// n = entries of slot_of / flag bits (inputs, or candidates for K != stride); slots_per_key sizes
-// the output-cell table: 8 when every entry is a distinct cell at worst (K == stride: n cells),
-// 2 for candidate lists, whose n is a bound that real voxel sets stay far below
-inline StridedScratch strided_scratch(void* p, int64_t n, uint64_t slots_per_key = 8) {
+constexpr int CELL_COUNTERS = 64;
+constexpr int32_t CELL_EMPTY = 0x7fffffff;
+// n = candidates; slots_per_key sizes the output-cell table: 8 where every input is a distinct cell at
+// worst (K == stride), 2 for longer candidate lists, whose n is a bound that real voxel sets stay far below
+inline StridedScratch strided_scratch(void* p, int64_t n, uint64_t slots_per_key) {
     StridedScratch s;
     const uint64_t cap = hash_capacity(n, slots_per_key);
     const int64_t words = (n + 63) / 64, nblk = (n + 1023) / 1024;
     size_t off = 0;
     char* b = (char*)p;
-    s.oslots = (uint4*)(b + off); off = align_up(off + cap * 16, 256);
+    s.oslots = (int32_t*)(b + off); off = align_up(off + cap * 16, 256);
     s.omask = (uint32_t)(cap - 1);
     s.slot_of = (int32_t*)(b + off); off = align_up(off + (size_t)n * 4, 256);
     s.flagword = (uint64_t*)(b + off); off = align_up(off + (size_t)words * 8, 256);
     s.word_prefix = (int32_t*)(b + off); off = align_up(off + (size_t)words * 4, 256);
     s.block_sum = (int32_t*)(b + off); off = align_up(off + (size_t)nblk * 4, 256);
     s.block_prefix = (int32_t*)(b + off); off = align_up(off + (size_t)nblk * 4, 256);
+    s.cells = (int32_t*)(b + off); off = align_up(off + (size_t)CELL_COUNTERS * 128, 256);
     s.bytes = off + 256;
     return s;
 }
 
-// One pass that prepares a strided build: output table <- empty, offset table <- -1.
+// Prepares a strided build: output-cell table <- empty, claim counters <- 0.
 __global__ void __launch_bounds__(256)
-k_strided_fill(uint4* __restrict__ oslots, uint64_t cap, int4* __restrict__ nbr16, int64_t nbr_vec, sc_counts* counts,
-               int reset, int64_t n_in, const TableHeader* th) {
+k_strided_fill(int4* __restrict__ oslots4, uint64_t cap, int32_t* __restrict__ cells, sc_counts* counts, int reset, int64_t n_in, const TableHeader* th) {
     const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (reset && blockIdx.x == 0) {                  // a build without a location table starts the counts block itself
@@ -188,67 +196,209 @@ k_strided_fill(uint4* __restrict__ oslots, uint64_t cap, int4* __restrict__ nbr1
     }
     // after a location-table build that could not report into the counts block, report for it
     if (th != nullptr && tid == 0) fold_table_error(th, counts);
-    const uint4 empty = make_uint4(0xffffffffu, 0xffffffffu, 0x7fffffffu, 0u);
-    for (int64_t i = tid; i < (int64_t)cap; i += nthr) oslots[i] = empty;
-    for (int64_t i = tid; i < nbr_vec; i += nthr) nbr16[i] = make_int4(-1, -1, -1, -1);
+    if (cells != nullptr && tid < CELL_COUNTERS) cells[tid * 32] = 0;
+    for (int64_t i = tid; i < (int64_t)(cap / 4); i += nthr) oslots4[i] = make_int4(CELL_EMPTY, CELL_EMPTY, CELL_EMPTY, CELL_EMPTY);
 }
 
-// Each input claims (or finds) the slot of its output cell floor(p/s) (eq. 2, eq. 4) and
-// lowers the slot's value to its own row index.
-__global__ void __launch_bounds__(256)
-k_strided_insert(const int4* __restrict__ coords, int64_t n, int s, uint4* oslots, uint32_t omask,
-                 int32_t* __restrict__ slot_of, sc_counts* counts) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int4 c = coords[i];
-    int32_t myslot = -1;
-    if (!in_domain4(c.x, c.y, c.z, c.w)) {
-        latch_status(counts, SC_ERANGE);
-    } else {
-        const uint64_t key = pack_key(c.x, c.y / s, c.z / s, c.w / s);
-        for (uint32_t t = 0; t <= omask + REHASH_MAX; ++t) {
-            const uint32_t slot = probe_slot(key, t, omask);
-            const uint64_t cur = atomicCAS(reinterpret_cast<unsigned long long*>(&oslots[slot]),
-                                           (unsigned long long)KEY_EMPTY, (unsigned long long)key);
-            if (cur == KEY_EMPTY || cur == key) {
-                myslot = (int32_t)slot;
-                break;
+// Candidate j of the input at c, or k < 0 if it has fewer.  Along one axis the offsets that can
+// pair coordinate p with a cell are d = p mod s, p mod s + s, ... below K and not above p (the
+// cell coordinate (p - d)/s must not be negative); candidates are numbered with x slowest and z
+// fastest, offsets ascending, i.e. in ascending order of the offset number k.
+struct Candidate {
+    int k;                 // offset number, -1: no such candidate
+    int qx, qy, qz;        // the output cell
+};
+__device__ inline int axis_options(int p, int K, int s) {
+    const int top = p < K - 1 ? p : K - 1;
+    return (top - p % s) / s + 1;                  // p mod s <= top always: s <= K and p mod s <= p
+}
+__device__ inline Candidate candidate(const int4 c, int K, int s, int j) {
+    const int cy = axis_options(c.z, K, s), cz = axis_options(c.w, K, s), cx = axis_options(c.y, K, s);
+    Candidate r;
+    r.k = -1; r.qx = r.qy = r.qz = 0;
+    if (j >= cx * cy * cz) return r;
+    const int dz = c.w % s + (j % cz) * s, dy = c.z % s + ((j / cz) % cy) * s, dx = c.y % s + (j / (cz * cy)) * s;
+    r.k = (dx * K + dy) * K + dz;
+    r.qx = (c.y - dx) / s; r.qy = (c.z - dy) / s; r.qz = (c.w - dz) / s;
+    return r;
+}
+
+// Kernel size, stride and candidates per input of a strided layer.  The common shapes are compiled in: the
+// enumeration above is a dozen integer divisions, each ~40 instructions when the divisor is not a constant.
+template <int KT, int ST>
+struct StridedShape {
+    static constexpr int MT = ST ? ((KT + ST - 1) / ST) * ((KT + ST - 1) / ST) * ((KT + ST - 1) / ST) : 0;
+    int k_, s_, m_;
+    __device__ int K() const { return KT ? KT : k_; }
+    __device__ int s() const { return ST ? ST : s_; }
+    __device__ int maxc() const { return MT ? MT : m_; }
+};
+
+// The cell of candidate `id` (input id / maxc, its candidate id % maxc), as a key.
+template <class Shape>
+__device__ inline uint64_t candidate_key(const int4* __restrict__ coords, const Shape& sh, int32_t id) {
+    const int4 c = coords[(uint32_t)id / (uint32_t)sh.maxc()];
+    const Candidate q = candidate(c, sh.K(), sh.s(), (uint32_t)id % (uint32_t)sh.maxc());
+    return pack_key(c.x, q.qx, q.qy, q.qz);
+}
+
+// Claim (or find) the slot of output cell `key` for candidate `id`; returns the slot, or -1 if the table is
+// full.  `fresh`: this call claimed it.  A slot is one word, the smallest id seen of its cell: which cell
+// that is follows from the id's coordinates, so claiming a cell is a single compare-and-swap, and a
+// later entry with a larger id only reads.
+template <class Shape>
+__device__ inline int32_t claim_cell(int32_t* oslots, uint32_t omask, const int4* __restrict__ coords, const Shape& sh, uint64_t key,
+                                     int32_t id, bool& fresh) {
+    fresh = false;
+    for (uint32_t t = 0; t <= omask + REHASH_MAX; ++t) {
+        const uint32_t slot = probe_slot(key, t, omask);
+        int32_t cur = *const_cast<const volatile int32_t*>(&oslots[slot]);
+        if (cur == CELL_EMPTY) {
+            cur = atomicCAS(&oslots[slot], CELL_EMPTY, id);
+            if (cur == CELL_EMPTY) {
+                fresh = true;
+                return (int32_t)slot;
             }
         }
-        if (myslot >= 0) atomicMin(reinterpret_cast<int32_t*>(&oslots[myslot]) + 2, (int32_t)i);
-        else latch_status(counts, SC_EFULL);
+        if (candidate_key(coords, sh, cur) == key) {
+            if (id < cur) atomicMin(&oslots[slot], id);
+            return (int32_t)slot;
+        }
     }
-    slot_of[i] = myslot;
+    return -1;
 }
 
-// flag(i) = input i is the first (lowest row) of its cell; one bit per input, plus the
-// exclusive prefix of the flag counts of the 16 words of each 1024-input block.
-__global__ void __launch_bounds__(1024)
-k_strided_flags(int64_t n, const int32_t* __restrict__ slot_of, const uint4* __restrict__ oslots,
-                uint64_t* __restrict__ flagword, int32_t* __restrict__ word_prefix,
-                int32_t* __restrict__ block_sum) {
-    __shared__ int32_t wave_count[16];
-    const int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-    bool first = false;
-    if (i < n) {
-        const int32_t sl = slot_of[i];
-        first = sl >= 0 && (int32_t)oslots[sl].z == (int32_t)i;
+// The same for a workgroup's entries at once.  What claiming costs is the rate of global atomics
+// (~20 per ns on the whole chip), and entries that are close in order mostly share cells: the workgroup's
+// cells are first merged in LDS (key and smallest id; LDS atomics), and only distinct ones go to the table.
+// With
+// a compare-and-swap on the key and a minimum on the id per entry, 53 k rows took 18.0 us (K = 3, stride
+// 2) and 8.5 us (K = 2), 200 k rows 51.8 and 21.0; now 9.7, 7.1, 21.0 and 10.5.  `key` is KEY_EMPTY for a thread without an entry; ids rise
+// with the thread.  Returns the thread's slot, -1 if it has none or the table is full (l.full is then set);
+// l.fresh counts the cells this workgroup claimed first.
+constexpr int CLAIM_WG = 256;                          // with 1024 the fixed part (barriers, few workgroups) outweighs the merging: 10.6 us
+struct ClaimLds {
+    static constexpr int SLOTS = 2 * CLAIM_WG;              // at most half full
+    unsigned long long key[SLOTS];
+    int32_t id[SLOTS];                                 // smallest id, later the slot in the global table
+    int32_t fresh, full;
+};
+template <class Shape>
+__device__ inline int32_t claim_cells_of_workgroup(ClaimLds& l, int32_t* oslots, uint32_t omask, const int4* __restrict__ coords,
+                                                   const Shape& sh, uint64_t key, int32_t id) {
+    constexpr int SLOTS = ClaimLds::SLOTS;
+#pragma unroll
+    for (int i = 0; i < SLOTS / CLAIM_WG; ++i) {
+        l.key[i * CLAIM_WG + threadIdx.x] = KEY_EMPTY;
+        l.id[i * CLAIM_WG + threadIdx.x] = CELL_EMPTY;
     }
-    const uint64_t vote = __ballot(first);
+    if (threadIdx.x == 0) l.fresh = l.full = 0;
+    __syncthreads();
+    int at = -1;
+    bool owner = false;                                // the thread that brought the key in claims the cell
+    if (key != KEY_EMPTY) {
+        uint32_t e = mix_block((uint32_t)(key >> 32), (uint32_t)key, 0) % SLOTS;
+        for (;;) {                                     // ends: at most one key per thread, twice as many slots
+            const uint64_t cur = atomicCAS(&l.key[e], (unsigned long long)KEY_EMPTY, (unsigned long long)key);
+            owner = cur == KEY_EMPTY;
+            if (owner || cur == key) break;
+            e = (e + 1) % SLOTS;
+        }
+        atomicMin(&l.id[e], id);
+        at = (int)e;
+    }
+    __syncthreads();
+    bool fresh = false;
+    if (owner) {
+        const int32_t slot = claim_cell(oslots, omask, coords, sh, key, l.id[at], fresh);
+        if (slot < 0) l.full = 1;
+        l.id[at] = slot;
+    }
+    const uint64_t vote = __ballot(fresh);
+    if ((threadIdx.x & 63) == 0 && vote != 0ull) atomicAdd(&l.fresh, __popcll(vote));
+    __syncthreads();
+    return at >= 0 ? l.id[at] : -1;
+}
+
+// One thread per candidate (input i = id / maxc, candidate j = id % maxc; one per input for K == stride: the
+// cell floor(p/s) of eq. 2, eq. 4): the inputs' candidates are independent, and with a thread each their
+// claims are all in flight together.
+template <class Shape>
+__global__ void __launch_bounds__(CLAIM_WG)
+k_strided_insert(const int4* __restrict__ coords, int64_t n, Shape sh, int32_t* oslots, uint32_t omask, int32_t* __restrict__ cand_slot,
+                 int32_t* __restrict__ cells, sc_counts* counts) {
+    __shared__ ClaimLds l;
+    const int64_t id = (int64_t)blockIdx.x * CLAIM_WG + threadIdx.x, nc = n * sh.maxc();
+    uint64_t key = KEY_EMPTY;
+    if (id < nc) {
+        const uint32_t i = (uint32_t)id / (uint32_t)sh.maxc();         // candidate ids stay below 2^26
+        const int j = (int)((uint32_t)id - i * (uint32_t)sh.maxc());
+        const int4 c = coords[i];
+        if (!in_domain4(c.x, c.y, c.z, c.w)) {
+            if (j == 0) latch_status(counts, SC_ERANGE);
+        } else {
+            const Candidate q = candidate(c, sh.K(), sh.s(), j);
+            if (q.k >= 0) key = pack_key(c.x, q.qx, q.qy, q.qz);
+        }
+    }
+    const int32_t slot = claim_cells_of_workgroup(l, oslots, omask, coords, sh, key, (int32_t)id);
+    if (id < nc) cand_slot[id] = slot;
+    if (threadIdx.x == 0) {
+        if (l.full) latch_status(counts, SC_EFULL);
+        // how many cells there are, before they are numbered: the next kernel clears that many table rows
+        if (l.fresh != 0) atomicAdd(&cells[(blockIdx.x % CELL_COUNTERS) * 32], l.fresh);
+    }
+}
+
+// flag(c) = candidate c is the first (lowest id) of its cell; one bit per candidate, plus the exclusive
+// prefix of the flag counts of the words of each block of U x 1024 candidates.  Also clears the offset
+// table.  U = 4 for long lists: every workgroup of the pairs kernel scans the block counts for itself.
+template <int U>
+__global__ void __launch_bounds__(1024)
+k_strided_flags(int64_t n, const int32_t* __restrict__ slot_of, const int32_t* __restrict__ oslots, uint64_t* __restrict__ flagword,
+                int32_t* __restrict__ word_prefix, int32_t* __restrict__ block_sum, const int32_t* __restrict__ cells,
+                int4* __restrict__ nbr16, int K3) {
+    __shared__ int32_t count_s[16 * U], total_s;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) wave_count[wave] = __popcll(vote);
+    uint64_t vote[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t c = ((int64_t)blockIdx.x * U + u) * 1024 + threadIdx.x;
+        bool first = false;
+        if (c < n) {
+            const int32_t sl = slot_of[c];
+            first = sl >= 0 && oslots[sl] == (int32_t)c;
+        }
+        vote[u] = __ballot(first);
+        if (lane == 0) count_s[u * 16 + wave] = __popcll(vote[u]);
+    }
+    if (wave == 0) {
+        int32_t v = cells[lane * 32];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (lane == 0) total_s = v;
+    }
     __syncthreads();
     if (lane == 0) {
         int32_t before = 0;
-        for (int w = 0; w < wave; ++w) before += wave_count[w];
-        const int64_t word = (int64_t)blockIdx.x * 16 + wave;
-        if (word * 64 < n) {
-            flagword[word] = vote;
-            word_prefix[word] = before;
+        int w = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            for (; w < u * 16 + wave; ++w) before += count_s[w];
+            const int64_t word = ((int64_t)blockIdx.x * U + u) * 16 + wave;
+            if (word * 64 < n) {
+                flagword[word] = vote[u];
+                word_prefix[word] = before;
+            }
         }
-        if (wave == 15) block_sum[blockIdx.x] = before + wave_count[15];
+        if (wave == 15) block_sum[blockIdx.x] = before + count_s[16 * U - 1];
     }
+    // offset table <- -1 for the tiles of the output rows, which the insert kernel counted: the bound is
+    // ceil(K/s)^3 rows per input, real sets need about one
+    const int64_t vec = ((int64_t)total_s + TILE - 1) / TILE * K3 * (TILE / 4), nthr = (int64_t)gridDim.x * 1024;
+    for (int64_t v = (int64_t)blockIdx.x * 1024 + threadIdx.x; v < vec; v += nthr) nbr16[v] = make_int4(-1, -1, -1, -1);
 }
+static_assert(CELL_COUNTERS == 64, "one lane per counter");
 
 // Exclusive prefix of the block sums (one workgroup walks the array), total -> counts->n_out.
 __global__ void __launch_bounds__(1024)
@@ -279,9 +429,9 @@ k_scan_blocks(const int32_t* __restrict__ block_sum, int32_t* __restrict__ block
 }
 
 // Exclusive prefix of the per-block counts, computed by every workgroup for itself into LDS (the
-// counts of a few hundred to a few thousand 1024-input blocks: cheaper than a kernel of its own,
+// counts of up to a thousand blocks: cheaper than a kernel of its own,
 // which is one workgroup long).  Returns the total.  All threads of the workgroup call it.
-constexpr int SCAN_IN_PAIRS_MAX = 4096;              // blocks (4 M inputs); more: k_scan_blocks
+constexpr int SCAN_IN_PAIRS_MAX = 1024;              // blocks (4 M candidates); more: k_scan_blocks
 __device__ inline int32_t block_prefix_to_lds(const int32_t* __restrict__ block_sum, int nblk, int32_t* prefix_s,
                                               int32_t* wave_s) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
@@ -311,135 +461,38 @@ __device__ inline int32_t block_prefix_to_lds(const int32_t* __restrict__ block_
     return total;
 }
 
-// Every input finds its output row (rank of its cell's first input among all first inputs),
-// its in-cell offset (eq. 3) and kernel offset (eq. 5), and records itself in the offset table.
+// Every candidate finds its output row (rank of its cell's first candidate among all first candidates),
+// and its input's row goes to that row's entry at the candidate's offset (K == stride: in-cell offset,
+// eq. 3, kernel offset, eq. 5).
 // SCAN: the prefix of the block counts is made here (block_prefix is then unused) and workgroup 0
 // writes the number of output rows.
-template <int SCAN>
+template <int SCAN, int U, class Shape>
 __global__ void __launch_bounds__(256)
-k_strided_pairs(const int4* __restrict__ coords, int64_t n, int s, int K3,
-                const int32_t* __restrict__ slot_of, const uint4* __restrict__ oslots,
-                const uint64_t* __restrict__ flagword, const int32_t* __restrict__ word_prefix,
-                const int32_t* __restrict__ block_prefix, const int32_t* __restrict__ block_sum, int nblk,
-                int32_t* __restrict__ nbr, int4* __restrict__ out_coords, sc_counts* counts, KmapHeader* hdr,
-                KmapHeader hdr_value) {
+k_strided_pairs(const int4* __restrict__ coords, int64_t n, Shape sh, const int32_t* __restrict__ cand_slot,
+                const int32_t* __restrict__ oslots, const uint64_t* __restrict__ flagword, const int32_t* __restrict__ word_prefix,
+                const int32_t* __restrict__ block_prefix, const int32_t* __restrict__ block_sum, int nblk, int32_t* __restrict__ nbr,
+                int4* __restrict__ out_coords, sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
     __shared__ int32_t prefix_s[SCAN ? SCAN_IN_PAIRS_MAX : 1];
     __shared__ int32_t wave_s[4];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) *hdr = hdr_value;
-    if constexpr (SCAN) {
-        const int32_t total = block_prefix_to_lds(block_sum, nblk, prefix_s, wave_s);
-        if (i == 0) counts->n_out = total;
-        block_prefix = prefix_s;
-    }
-    if (i >= n) return;
-    const int32_t sl = slot_of[i];
-    if (sl < 0) return;
-    const int32_t r = (int32_t)oslots[sl].z;                   // first input of this cell
-    const int32_t o = block_prefix[r >> 10] + word_prefix[r >> 6] +
-                      __popcll(flagword[r >> 6] & ((1ull << (r & 63)) - 1ull));
-    const int4 c = coords[i];
-    const int qx = c.y / s, qy = c.z / s, qz = c.w / s;
-    const int k = ((c.y - qx * s) * s + (c.z - qy * s)) * s + (c.w - qz * s);
-    const int64_t tile = o >> 6;
-    const int j = o & 63;
-    // distinct inputs own distinct (output row, offset) cells, so a plain store is enough; repeated
-    // input coordinates are the location table's business (sc_hash_build latches SC_EDUP)
-    nbr[(tile * K3 + k) * TILE + j] = (int32_t)i;
-    if (r == (int32_t)i) out_coords[o] = make_int4(c.x, qx, qy, qz);
-}
-
-// ---- strided layers with K != stride -------------------------------------------------------------
-// An input p pairs with output cell q at offset d whenever p = q*s + d, d in [0,K)^3 (the
-// enumeration of Algorithm 1's getOutputCoord with no padding), so it can belong to up to
-// MAXC = ceil(K/s)^3 cells.  Its valid (offset, cell) candidates are numbered j = 0.. in
-// ascending offset order; candidate id c = i*MAXC + j therefore orders all candidates by input
-// row and then by offset, and a cell's number is the rank of its lowest candidate id among all
-// cells' lowest ids: the same first-occurrence numbering as for K == stride, found with the same
-// flag / prefix kernels run over candidates instead of inputs.
-// offset table <- -1 for the tiles that hold the counts->n_out output rows
-__global__ void __launch_bounds__(256)
-k_fill_rows(int4* __restrict__ nbr16, int K3, const sc_counts* __restrict__ counts) {
-    const int64_t vec = (counts->n_out + TILE - 1) / TILE * K3 * (TILE / 4);
-    const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < vec; i += nthr) nbr16[i] = make_int4(-1, -1, -1, -1);
-}
-
-// Candidate j of the input at c, or k < 0 if it has fewer.  Along one axis the offsets that can
-// pair coordinate p with a cell are d = p mod s, p mod s + s, ... below K and not above p (the
-// cell coordinate (p - d)/s must not be negative); candidates are numbered with x slowest and z
-// fastest, offsets ascending, i.e. in ascending order of the offset number k.
-struct Candidate {
-    int k;                 // offset number, -1: no such candidate
-    int qx, qy, qz;        // the output cell
-};
-__device__ inline int axis_options(int p, int K, int s) {
-    const int top = p < K - 1 ? p : K - 1;
-    return (top - p % s) / s + 1;                  // p mod s <= top always: s <= K and p mod s <= p
-}
-__device__ inline Candidate candidate(const int4 c, int K, int s, int j) {
-    const int cy = axis_options(c.z, K, s), cz = axis_options(c.w, K, s), cx = axis_options(c.y, K, s);
-    Candidate r;
-    r.k = -1; r.qx = r.qy = r.qz = 0;
-    if (j >= cx * cy * cz) return r;
-    const int dz = c.w % s + (j % cz) * s, dy = c.z % s + ((j / cz) % cy) * s, dx = c.y % s + (j / (cz * cy)) * s;
-    r.k = (dx * K + dy) * K + dz;
-    r.qx = (c.y - dx) / s; r.qy = (c.z - dy) / s; r.qz = (c.w - dz) / s;
-    return r;
-}
-
-// One thread per candidate (input i = id / maxc, candidate j = id % maxc): the inputs' candidates
-// are independent, and with a thread each their compare-and-swaps are all in flight together.
-__global__ void __launch_bounds__(256)
-k_gstrided_insert(const int4* __restrict__ coords, int64_t n, int K, int s, int maxc, uint4* oslots, uint32_t omask,
-                  int32_t* __restrict__ cand_slot, sc_counts* counts) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= n * maxc) return;
-    const int64_t i = id / maxc;
-    const int j = (int)(id - i * maxc);
-    const int4 c = coords[i];
-    int32_t myslot = -1;
-    if (!in_domain4(c.x, c.y, c.z, c.w)) {
-        if (j == 0) latch_status(counts, SC_ERANGE);
-    } else {
-        const Candidate q = candidate(c, K, s, j);
-        if (q.k >= 0) {
-            const uint64_t key = pack_key(c.x, q.qx, q.qy, q.qz);
-            for (uint32_t t = 0; t <= omask + REHASH_MAX; ++t) {
-                const uint32_t slot = probe_slot(key, t, omask);
-                const uint64_t cur = atomicCAS(reinterpret_cast<unsigned long long*>(&oslots[slot]),
-                                               (unsigned long long)KEY_EMPTY, (unsigned long long)key);
-                if (cur == KEY_EMPTY || cur == key) {
-                    myslot = (int32_t)slot;
-                    break;
-                }
-            }
-            if (myslot >= 0) atomicMin(reinterpret_cast<int32_t*>(&oslots[myslot]) + 2, (int32_t)id);
-            else latch_status(counts, SC_EFULL);
-        }
-    }
-    cand_slot[id] = myslot;
-}
-
-__global__ void __launch_bounds__(256)
-k_gstrided_pairs(const int4* __restrict__ coords, int64_t n, int K, int s, int maxc,
-                 const int32_t* __restrict__ cand_slot, const uint4* __restrict__ oslots,
-                 const uint64_t* __restrict__ flagword, const int32_t* __restrict__ word_prefix,
-                 const int32_t* __restrict__ block_prefix, int32_t* __restrict__ nbr,
-                 int4* __restrict__ out_coords, KmapHeader* hdr, KmapHeader hdr_value) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (id == 0) *hdr = hdr_value;
-    if (id >= n * maxc) return;
+    if constexpr (SCAN) {
+        const int32_t total = block_prefix_to_lds(block_sum, nblk, prefix_s, wave_s);
+        if (id == 0) counts->n_out = total;
+        block_prefix = prefix_s;
+    }
+    if (id >= n * sh.maxc()) return;
     const int32_t sl = cand_slot[id];
     if (sl < 0) return;
-    const int64_t i = id / maxc;
+    const uint32_t i = (uint32_t)id / (uint32_t)sh.maxc();
     const int4 c = coords[i];
-    const Candidate q = candidate(c, K, s, (int)(id - i * maxc));
-    const int32_t r = (int32_t)oslots[sl].z;                   // the cell's first candidate
-    const int32_t o = block_prefix[r >> 10] + word_prefix[r >> 6] +
+    const int32_t r = oslots[sl];                              // the cell's first candidate
+    const Candidate q = candidate(c, sh.K(), sh.s(), (int)((uint32_t)id - i * (uint32_t)sh.maxc()));
+    const int32_t o = block_prefix[r >> (U == 4 ? 12 : 10)] + word_prefix[r >> 6] +
                       __popcll(flagword[r >> 6] & ((1ull << (r & 63)) - 1ull));
-    // one input per (output row, offset): a plain store
-    nbr[((int64_t)(o >> 6) * (K * K * K) + q.k) * TILE + (o & 63)] = (int32_t)i;
+    // one input per (output row, offset): a plain store is enough; repeated input coordinates are the
+    // location table's business (sc_hash_build latches SC_EDUP)
+    nbr[((int64_t)(o >> 6) * (sh.K() * sh.K() * sh.K()) + q.k) * TILE + (o & 63)] = (int32_t)i;
     if (r == (int32_t)id) out_coords[o] = make_int4(c.x, q.qx, q.qy, q.qz);
 }
 
@@ -611,7 +664,47 @@ static bool kmap_args_ok(int64_t n, int K, int stride, int mode) {
     }
     return false;
 }
-static bool strided_fast(int K, int stride) { return K == stride && K <= 4; }
+// slots of the output-cell table per candidate
+static uint64_t strided_slots(int K, int stride) { return K == stride && K <= 4 ? 8 : 2; }
+
+// The strided build (arguments checked by the caller): clear the cell table -> claim cells -> flag first
+// candidates, clear the rows of the offset table -> number cells, write pairs -> group masks.
+template <class Shape>
+static int build_strided(const Shape& sh, const int32_t* d_coords, int64_t n, const void* d_table, int K, int stride, int32_t* d_out_coords,
+                         void* d_kmap, const KmapLayout& L, const KmapHeader& h, void* d_scratch, sc_counts* d_counts, hipStream_t s) {
+    uint32_t* gmask = (uint32_t*)((char*)d_kmap + L.off_mask);
+    int32_t* nbr = (int32_t*)((char*)d_kmap + L.off_nbr);
+    const int64_t nc = n * strided_maxc(K, stride);            // candidates
+    StridedScratch g = strided_scratch(d_scratch, nc, strided_slots(K, stride));
+    const uint64_t cap = (uint64_t)g.omask + 1;
+    unsigned fb = (unsigned)((cap / 4 + 255) / 256);
+    if (fb > 4096) fb = 4096;
+    SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(fb), dim3(256), 0, s, (int4*)g.oslots, cap, g.cells, d_counts,
+              d_table == nullptr ? 1 : 0, n, (const TableHeader*)d_table);
+    SC_LAUNCH(KID_STRIDED_INSERT, k_strided_insert<Shape>, dim3((unsigned)((nc + CLAIM_WG - 1) / CLAIM_WG)), dim3(CLAIM_WG), 0, s,
+              (const int4*)d_coords, n, sh, g.oslots, g.omask, g.slot_of, g.cells, d_counts);
+    const unsigned gp = (unsigned)((nc + 255) / 256);
+#define SC_STRIDED_NUMBER(SCAN, U)                                                                                                     \
+    do {                                                                                                                               \
+        const int64_t nblk = (nc + U * 1024 - 1) / (U * 1024);                                                                         \
+        SC_LAUNCH(KID_STRIDED_FLAGS, k_strided_flags<U>, dim3((unsigned)nblk), dim3(1024), 0, s, nc, (const int32_t*)g.slot_of,        \
+                  (const int32_t*)g.oslots, g.flagword, g.word_prefix, g.block_sum, (const int32_t*)g.cells, (int4*)nbr, L.K3);        \
+        if (!SCAN)                                                                                                                     \
+            SC_LAUNCH(KID_SCAN_BLOCKS, k_scan_blocks, dim3(1), dim3(1024), 0, s, (const int32_t*)g.block_sum, g.block_prefix, nblk,    \
+                      d_counts);                                                                                                       \
+        SC_LAUNCH(KID_STRIDED_PAIRS, (k_strided_pairs<SCAN, U, Shape>), dim3(gp), dim3(256), 0, s, (const int4*)d_coords, n, sh,       \
+                  (const int32_t*)g.slot_of, (const int32_t*)g.oslots, (const uint64_t*)g.flagword, (const int32_t*)g.word_prefix,     \
+                  (const int32_t*)g.block_prefix, (const int32_t*)g.block_sum, (int)nblk, nbr, (int4*)d_out_coords, d_counts,          \
+                  (KmapHeader*)d_kmap, h);                                                                                             \
+    } while (0)
+    if (nc <= 512 * 1024) SC_STRIDED_NUMBER(1, 1);
+    else if (nc <= (int64_t)SCAN_IN_PAIRS_MAX * 4096) SC_STRIDED_NUMBER(1, 4);
+    else SC_STRIDED_NUMBER(0, 4);
+#undef SC_STRIDED_NUMBER
+    SC_LAUNCH(KID_KMAP_FROM_OFT, k_masks_from_table, dim3((unsigned)L.tiles), dim3(256), 0, s, (const int32_t*)nbr, L.K3, L.mw, L.tiles, gmask,
+              (const sc_counts*)d_counts);
+    return SC_OK;
+}
 
 }  // namespace sc
 
@@ -630,9 +723,8 @@ extern "C" size_t sc_kmap_bytes(int64_t n, int K, int stride, int mode) {
 extern "C" size_t sc_kmap_scratch_bytes(int64_t n, int K, int stride, int mode) {
     if (!kmap_args_ok(n, K, stride, mode)) return 0;
     if (mode == SC_SUBM) return 256;
-    if (mode == SC_STRIDED && !strided_fast(K, stride))
-        return strided_scratch(nullptr, sc_out_bound(n, K, stride, mode), 2).bytes;    // one entry per candidate
-    return strided_scratch(nullptr, n).bytes;
+    if (mode == SC_INVERSE) return strided_scratch(nullptr, n, 8).bytes;
+    return strided_scratch(nullptr, sc_out_bound(n, K, stride, mode), strided_slots(K, stride)).bytes;    // one entry per candidate
 }
 
 static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, int K, int stride, int mode,
@@ -658,8 +750,8 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
     h.n_in = n; h.n_out_bound = bound; h.tiles = L.tiles; h.mw = L.mw;
     if (n == 0) {
         if (mode == SC_STRIDED && d_table == nullptr)
-            SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(1), dim3(256), 0, s, (uint4*)nullptr, (uint64_t)0, (int4*)nullptr,
-                      (int64_t)0, d_counts, 1, (int64_t)0, (const TableHeader*)nullptr);
+            SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(1), dim3(256), 0, s, (int4*)nullptr, (uint64_t)0,
+                      (int32_t*)nullptr, d_counts, 1, (int64_t)0, (const TableHeader*)nullptr);
         SC_LAUNCH(KID_KMAP_HEADER, k_kmap_header, dim3(1), dim3(64), 0, s, (KmapHeader*)d_kmap, h);
         SC_LAUNCH(KID_MISC, k_set_n_out, dim3(1), dim3(64), 0, s, d_counts, (int64_t)0);
         return SC_OK;
@@ -686,77 +778,13 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
         return SC_OK;
     }
 
-    const TableHeader* table_hdr = (const TableHeader*)d_table;
-    if (!strided_fast(K, stride)) {
-        // strided, general K and stride: the same pipeline over candidates (input, offset)
-        const int maxc = strided_maxc(K, stride);
-        const int64_t nc = n * maxc;
-        StridedScratch g = strided_scratch(d_scratch, nc, 2);
-        const uint64_t gcap = (uint64_t)g.omask + 1;
-        const int64_t gvec = (int64_t)((L.bytes - L.off_nbr) / 16);
-        {
-            // the offset table is filled further down, once the number of output rows is known: the
-            // bound is ceil(K/s)^3 rows per input, real sets need about one
-            unsigned fb = (unsigned)((gcap + 255) / 256);
-            if (fb > 4096) fb = 4096;
-            SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(fb), dim3(256), 0, s, g.oslots, gcap, (int4*)nbr, (int64_t)0,
-                      d_counts, d_table == nullptr ? 1 : 0, n, table_hdr);
-        }
-        const int64_t gblk = (nc + 1023) / 1024;
-        const unsigned gg = (unsigned)((nc + 255) / 256);
-        SC_LAUNCH(KID_STRIDED_INSERT, k_gstrided_insert, dim3(gg), dim3(256), 0, s, (const int4*)d_coords, n, K, stride,
-                  maxc, g.oslots, g.omask, g.slot_of, d_counts);
-        SC_LAUNCH(KID_STRIDED_FLAGS, k_strided_flags, dim3((unsigned)gblk), dim3(1024), 0, s, nc,
-                  (const int32_t*)g.slot_of, (const uint4*)g.oslots, g.flagword, g.word_prefix, g.block_sum);
-        SC_LAUNCH(KID_SCAN_BLOCKS, k_scan_blocks, dim3(1), dim3(1024), 0, s, (const int32_t*)g.block_sum,
-                  g.block_prefix, gblk, d_counts);
-        {
-            unsigned fb = (unsigned)((gvec + 255) / 256);
-            if (fb > 2048) fb = 2048;
-            SC_LAUNCH(KID_FILL_I32, k_fill_rows, dim3(fb), dim3(256), 0, s, (int4*)nbr, L.K3, (const sc_counts*)d_counts);
-        }
-        SC_LAUNCH(KID_STRIDED_PAIRS, k_gstrided_pairs, dim3(gg), dim3(256), 0, s, (const int4*)d_coords, n, K, stride,
-                  maxc, (const int32_t*)g.slot_of, (const uint4*)g.oslots, (const uint64_t*)g.flagword,
-                  (const int32_t*)g.word_prefix, (const int32_t*)g.block_prefix, nbr, (int4*)d_out_coords,
-                  (KmapHeader*)d_kmap, h);
-        SC_LAUNCH(KID_KMAP_FROM_OFT, k_masks_from_table, dim3((unsigned)L.tiles), dim3(256), 0, s,
-                  (const int32_t*)nbr, L.K3, L.mw, L.tiles, gmask, (const sc_counts*)d_counts);
-        return SC_OK;
-    }
-
-    // strided, K == stride
-    StridedScratch sc_ = strided_scratch(d_scratch, n);
-    const uint64_t cap = (uint64_t)sc_.omask + 1;
-    const int64_t nbr_vec = (int64_t)((L.bytes - L.off_nbr) / 16);
-    {
-        int64_t work = (int64_t)cap > nbr_vec ? (int64_t)cap : nbr_vec;
-        unsigned fb = (unsigned)((work + 255) / 256);
-        if (fb > 4096) fb = 4096;
-        SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(fb), dim3(256), 0, s, sc_.oslots, cap, (int4*)nbr, nbr_vec,
-                  d_counts, d_table == nullptr ? 1 : 0, n, table_hdr);
-    }
-    const int64_t nblk = (n + 1023) / 1024;
-    const unsigned gb = (unsigned)((n + 255) / 256);
-    SC_LAUNCH(KID_STRIDED_INSERT, k_strided_insert, dim3(gb), dim3(256), 0, s, (const int4*)d_coords, n, stride,
-              sc_.oslots, sc_.omask, sc_.slot_of, d_counts);
-    SC_LAUNCH(KID_STRIDED_FLAGS, k_strided_flags, dim3((unsigned)nblk), dim3(1024), 0, s, n,
-              (const int32_t*)sc_.slot_of, (const uint4*)sc_.oslots, sc_.flagword, sc_.word_prefix, sc_.block_sum);
-    if (nblk <= SCAN_IN_PAIRS_MAX) {
-        SC_LAUNCH(KID_STRIDED_PAIRS, k_strided_pairs<1>, dim3(gb), dim3(256), 0, s, (const int4*)d_coords, n, stride, L.K3,
-                  (const int32_t*)sc_.slot_of, (const uint4*)sc_.oslots, (const uint64_t*)sc_.flagword,
-                  (const int32_t*)sc_.word_prefix, (const int32_t*)nullptr, (const int32_t*)sc_.block_sum, (int)nblk, nbr,
-                  (int4*)d_out_coords, d_counts, (KmapHeader*)d_kmap, h);
-    } else {
-        SC_LAUNCH(KID_SCAN_BLOCKS, k_scan_blocks, dim3(1), dim3(1024), 0, s, (const int32_t*)sc_.block_sum,
-                  sc_.block_prefix, nblk, d_counts);
-        SC_LAUNCH(KID_STRIDED_PAIRS, k_strided_pairs<0>, dim3(gb), dim3(256), 0, s, (const int4*)d_coords, n, stride, L.K3,
-                  (const int32_t*)sc_.slot_of, (const uint4*)sc_.oslots, (const uint64_t*)sc_.flagword,
-                  (const int32_t*)sc_.word_prefix, (const int32_t*)sc_.block_prefix, (const int32_t*)sc_.block_sum,
-                  (int)nblk, nbr, (int4*)d_out_coords, d_counts, (KmapHeader*)d_kmap, h);
-    }
-    SC_LAUNCH(KID_KMAP_FROM_OFT, k_masks_from_table, dim3((unsigned)L.tiles), dim3(256), 0, s,
-              (const int32_t*)nbr, L.K3, L.mw, L.tiles, gmask, (const sc_counts*)d_counts);
-    return SC_OK;
+    // the common shapes are compiled in, the others take K and stride as arguments
+    if (K == 2 && stride == 2)
+        return build_strided(StridedShape<2, 2>{}, d_coords, n, d_table, K, stride, d_out_coords, d_kmap, L, h, d_scratch, d_counts, s);
+    if (K == 3 && stride == 2)
+        return build_strided(StridedShape<3, 2>{}, d_coords, n, d_table, K, stride, d_out_coords, d_kmap, L, h, d_scratch, d_counts, s);
+    return build_strided(StridedShape<0, 0>{K, stride, strided_maxc(K, stride)}, d_coords, n, d_table, K, stride, d_out_coords, d_kmap, L, h,
+                         d_scratch, d_counts, s);
 }
 
 extern "C" int sc_kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, int K, int stride, int mode,

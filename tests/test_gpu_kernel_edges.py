@@ -35,3 +35,32 @@ def test_general_kernel_fp32(K, C_in, C_out, n):
     say(f"general kernel fp32 K={K} {C_in}->{C_out} n={n}")
     coords = synth.lidar_scene(3)[:n] if n > 2000 else synth.uniform_cells(n, 10, seed=K + C_in + n)
     check_layer(coords, K, 1, "subm", C_in, C_out, "f32", seed=n, threads=16)
+
+
+@pytest.mark.parametrize("K,stride", [(2, 2), (3, 2), (3, 3), (4, 2), (5, 5)])
+@pytest.mark.parametrize("n", [1, 256, 257, 3000])
+def test_strided_build_claims(K, stride, n):
+    """The merged claims of output cells at the edges of a workgroup, for the compiled-in shapes and the
+    general one, on sets where many inputs share a cell (a full cube) and where none do (a lattice)."""
+    say(f"strided claims K={K} s={stride} n={n}")
+    side = int(np.ceil(n ** (1 / 3)))
+    cube = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)[:n]
+    for xyz in (cube, cube * 8 + 7):
+        coords = np.concatenate([np.arange(len(xyz))[:, None] % 2, xyz], axis=1).astype(np.int32)
+        check_layer(np.ascontiguousarray(coords), K, stride, "strided", 32, 32, "f16", seed=n)
+
+
+def test_strided_map_with_blocks_of_4096_candidates():
+    say("strided map, 560,000 and 4.5 M candidates")
+    from paper_2402_07710_amd import binding as sc
+    import oracle
+    import torch
+    from tests.test_gpu_parity import assert_maps_equal, exported_map
+    for n, K in ((70_000, 3), (560_000, 3), (600_000, 2)):
+        coords = synth.uniform_cells(n, 100, seed=n)
+        buf = sc.LayerBuffers(n, K, 2, "strided", 32, 32, "f16", device="cuda:0")
+        buf.kmap_build(torch.from_numpy(coords).to("cuda:0"), standalone=True)
+        h = buf.read_counts()
+        ref = oracle.kmap(coords, K, 2, "strided")
+        assert h.status == 0 and h.n_out == ref["n_out"] and h.n_pairs == ref["offset_start"][-1]
+        assert_maps_equal(exported_map(buf, h), buf.out_coords[:h.n_out].cpu().numpy(), ref, exact_order=True)
