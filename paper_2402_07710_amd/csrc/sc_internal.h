@@ -36,30 +36,41 @@ __host__ __device__ inline bool in_domain4(int b, int x, int y, int z) {
 
 // Probe sequence of a key.  The table is cut into regions of 64 slots; a 4x4x4 block of cells
 // owns one region per attempt t (a hash of the block's coordinates and t) and a cell sits at its
-// own place inside the region (its 6 low coordinate bits, turned by 6 bits of the same hash).  Cells of one block therefore never
-// collide with each other, the 27 neighbours of a voxel fall into at most 8 regions, and voxels
-// that are close in space read the same cache lines of the table.  After REHASH_MAX attempts the
+// own place inside the region (its 6 low coordinate bits, turned by 6 bits of the same hash).  Cells of one
+// block therefore never collide with each other, the 27 neighbours of a voxel fall into at most 8 regions,
+// and voxels that are close in space read the same cache lines of the table.  After REHASH_MAX attempts the
 // sequence continues linearly, so it visits every slot and always ends at an empty one.
 constexpr uint32_t REHASH_MAX = 32;
-__host__ __device__ inline uint32_t mix_block(uint32_t hi, uint32_t lo, uint32_t t) {
-    uint32_t h = hi * 0x85ebca6bu ^ lo * 0xc2b2ae35u ^ (t + 1u) * 0x9e3779b9u;
+// Hash of block (b, x >> 2 | y >> 2, z >> 2) for attempt t, in two parts: a sum of one product per
+// coordinate, which a caller that looks a whole neighbourhood up forms once per coordinate value, and
+// the mixing of the attempt.
+constexpr uint32_t BLOCK_MUL_HI = 0x85ebca6bu, BLOCK_MUL_LO = 0xc2b2ae35u, BLOCK_MUL_TRY = 0x9e3779b9u;
+__host__ __device__ inline uint32_t block_base(uint32_t hi, uint32_t lo) { return hi * BLOCK_MUL_HI ^ lo * BLOCK_MUL_LO; }
+__host__ __device__ inline uint32_t block_mix(uint32_t base, uint32_t t) {
+    uint32_t h = base ^ (t + 1u) * BLOCK_MUL_TRY;
     h ^= h >> 15; h *= 0x2c1b3c6du;
     h ^= h >> 12; h *= 0x297a2d39u;
     h ^= h >> 15;
     return h;
 }
+__host__ __device__ inline uint32_t mix_block(uint32_t hi, uint32_t lo, uint32_t t) { return block_mix(block_base(hi, lo), t); }
+// Place of a cell inside its block, from the two low bits of its coordinates: the high bits first, so that
+// the eight slots of a 128-byte line are a 2x2x2 cube and the four of its half a 2x2 square of one
+// height.  A surface through the block then lies in half as many lines as with one coordinate after the
+// other (level ground 4 of 8, not 8; inserts of 110 k voxels 9.9 -> 8.7 us, of 10^6 54.6 -> 46.5).
+__host__ __device__ inline uint32_t local_x(uint32_t x) { return ((x & 2u) << 4) | ((x & 1u) << 1); }
+__host__ __device__ inline uint32_t local_y(uint32_t y) { return ((y & 2u) << 3) | (y & 1u); }
+__host__ __device__ inline uint32_t local_z(uint32_t z) { return (z & 3u) << 2; }
+// the place inside the region is turned by six more bits of the block's hash: one turn for the
+// whole block and attempt, so its cells still never collide with each other, but voxel sets
+// on a coarse lattice (every coordinate a multiple of 2 or 4, as after down-sampling at the
+// original scale) no longer all ask for the same few places of every region
+__host__ __device__ inline uint32_t region_slot(uint32_t h, uint32_t local) { return (h << 6) | (local ^ (h >> 26)); }
 __host__ __device__ inline uint32_t probe_slot(uint64_t key, uint32_t t, uint32_t mask) {
-    const uint32_t hi = (uint32_t)(key >> 32) & 0xfffffffcu;          // b, x >> 2
-    const uint32_t lo = (uint32_t)key & 0xfffcfffcu;                  // y >> 2, z >> 2
-    const uint32_t local = (((uint32_t)(key >> 32) & 3u) << 4) | (((uint32_t)(key >> 16) & 3u) << 2) | ((uint32_t)key & 3u);
+    const uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key;
+    const uint32_t local = local_x(hi) | local_y(lo >> 16) | local_z(lo);
     const uint32_t tt = t < REHASH_MAX ? t : REHASH_MAX - 1;
-    // the place inside the region is turned by six more bits of the block's hash: one turn for the
-    // whole block and attempt, so its cells still never collide with each other, but voxel sets
-    // on a coarse lattice (every coordinate a multiple of 2 or 4, as after down-sampling at the
-    // original scale) no longer all ask for the same few places of every region
-    const uint32_t h = mix_block(hi, lo, tt);
-    const uint32_t slot = ((h << 6) | (local ^ (h >> 26))) + (t - tt);
-    return slot & mask;
+    return (region_slot(mix_block(hi & 0xfffffffcu /* b, x >> 2 */, lo & 0xfffcfffcu /* y >> 2, z >> 2 */, tt), local) + (t - tt)) & mask;
 }
 
 // Slots for n keys at `per_key` slots each: the next power of two, at least 1024.
