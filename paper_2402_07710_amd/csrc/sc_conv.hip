@@ -963,7 +963,7 @@ static int launch_stream(int64_t tiles, hipStream_t s, const uint16_t* feat, con
 }
 
 // Compute units of the current device, asked once (a race between host threads stores the same value).
-static int compute_units() {
+int compute_units() {
     static int cu_count[MAX_DEVICES] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return 256;

@@ -278,6 +278,7 @@ __device__ inline int64_t xcd_unit_of(unsigned block, int64_t units) {
     return (block / NUM_XCD < chunk && u < units) ? u : -1;
 }
 
+int compute_units();                       // of the current device
 // The same in short runs: an XCD takes every eighth run of XCD_RUN consecutive units.  For kernels
 // whose time follows the neighbours of their rows: rows come in scan order, the first eighth of a
 // sweep (near the sensor) has several times the neighbours of the last, and contiguous eighths

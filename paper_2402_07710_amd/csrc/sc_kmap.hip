@@ -30,7 +30,7 @@ k_set_n_out(sc_counts* counts, int64_t n_out) {
     if (threadIdx.x == 0 && blockIdx.x == 0) counts->n_out = n_out;
 }
 
-// Submanifold: output row = input row.  One workgroup of WPT wavefronts per 64-row tile; lane =
+// Submanifold, K = 1 and 7: output row = input row.  One workgroup of WPT wavefronts per 64-row tile; lane =
 // row, and the K^3 offsets are dealt to the wavefronts CH at a time.  The probes of a row do not
 // depend on each other, so a wavefront issues the loads of its CH offsets together and afterwards
 // re-probes only the offsets whose slot held another key: a tile's K^3 x 64 look-ups cost a few
@@ -139,6 +139,118 @@ k_kmap_subm(const int4* __restrict__ coords, int64_t n, const uint4* __restrict_
     SC_MARK(4);
     if (threadIdx.x < 4 * MW) gmask[tile * (4 * MW) + threadIdx.x] = mask_s[threadIdx.x];
     SC_MARK(5);
+}
+
+// K = 3 and 5, the same tile layout with far fewer instructions.  The kernel above hashes every one of
+// a row's K^3 keys from scratch; at about 155 vector instructions per look-up, many of them quarter-rate
+// multiplies, issuing them took 81 % of its cycles (300 k voxels).  The K cells of an axis lie in at
+// most two blocks of four, so here a wavefront takes one x offset of a tile and forms four block hashes
+// per attempt; a look-up is then a select, a few bit operations for its place and a comparison.  What
+// bounds it now is the address unit (a random slot per lane and look-up) and the table's lines from L2.
+// 10^6 indoor voxels: 104 -> 75 us; sweeps of 110 k: 15.6 -> 13.7, 261 k: 37.7 -> 35.0, 53 k with K = 5:
+// 28.2 -> 24.0, 6 k with K = 5: 12 -> 8.4.  All five y offsets of K = 5 at once spill or leave room for
+// too few wavefronts (35 us).
+template <int K, int YG, int YB>                       // YG wavefronts share an x offset's y offsets, each takes YB of its at a time
+__global__ void __launch_bounds__(64 * K * YG)
+k_kmap_subm_blocks(const int4* __restrict__ coords, int64_t n, const uint4* __restrict__ slots, const TableHeader* __restrict__ th,
+                   uint32_t* __restrict__ gmask, int32_t* __restrict__ nbr, sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
+    static_assert(K == 3 || K == 5, "K cells in a row lie in at most two blocks of four");
+    constexpr int K3 = K * K * K, pad = (K - 1) / 2, MW = (K3 + 31) / 32, YC = (K + YG - 1) / YG, U = YB * K;
+    static_assert(YC % YB == 0, "the passes of a wavefront are whole");
+    __shared__ uint32_t mask_s[4 * MW];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = wave % K, dy_first = wave / K * YC;
+    const int64_t tile = xcd_unit(blockIdx.x, gridDim.x);
+    if (tile * TILE >= n) return;                      // padding workgroup of the XCD-aware grid
+    if (threadIdx.x < 4 * MW) mask_s[threadIdx.x] = 0u;
+    const int64_t row = tile * TILE + lane;
+    const bool valid = row < n;
+    int4 c = make_int4(0, 0, 0, 0);
+    if (valid) c = coords[row];
+    const uint32_t mask = th->mask, tag = th->epoch << 24;             // slots of other epochs are free
+    if (tile == 0 && threadIdx.x == 0) {
+        counts->n_out = n;
+        *hdr = hdr_value;
+        fold_table_error(th, counts);
+    }
+    __syncthreads();
+
+    const int x = c.y + w - pad;
+    const bool x_ok = valid && in_domain(x);
+    const uint32_t hi = ((uint32_t)c.x << 16) | (uint32_t)x, want_hi = hi | tag, lx = local_x((uint32_t)x);
+    // the two blocks of an axis: that of the first and that of the last cell
+    const uint32_t y0 = (uint32_t)(c.z - pad) & ~3u, y1 = (uint32_t)(c.z + pad) & ~3u;
+    const uint32_t z0 = (uint32_t)(c.w - pad) & ~3u, z1 = (uint32_t)(c.w + pad) & ~3u;
+    const uint32_t px = (hi & ~3u) * BLOCK_MUL_HI, py0 = (y0 << 16) * BLOCK_MUL_LO, py1 = (y1 << 16) * BLOCK_MUL_LO;
+    const uint32_t pz0 = z0 * BLOCK_MUL_LO, pz1 = z1 * BLOCK_MUL_LO;
+    const uint32_t base[2][2] = {{px ^ (py0 + pz0), px ^ (py0 + pz1)}, {px ^ (py1 + pz0), px ^ (py1 + pz1)}};
+
+    uint32_t bits[4] = {0u, 0u, 0u, 0u};               // this wavefront's bits of the four groups
+#pragma unroll 1
+    for (int pass = 0; pass < YC / YB; ++pass) {
+        const int dy0 = dy_first + pass * YB;
+        if (dy0 >= K) break;
+        uint3 got[U];
+        bool pending[U];
+        int32_t found[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int dy = dy0 + u / K, dz = u % K;
+            const bool centre = w == pad && dy == pad && dz == pad;
+            found[u] = centre && valid ? (int32_t)row : -1;                      // the centre is the row itself
+            pending[u] = dy < K && !centre && x_ok && in_domain(c.z + dy - pad) && in_domain(c.w + dz - pad);
+        }
+        bool any = true;
+        for (uint32_t t = 0; any; ++t) {                   // ends: every probe sequence reaches a free slot
+            const uint32_t tt = t < REHASH_MAX ? t : REHASH_MAX - 1;
+            uint32_t h[2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) h[i][j] = block_mix(base[i][j], tt);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int dy = dy0 + u / K, dz = u % K;
+                if (t == 0 || pending[u]) {                // a look-up outside the domain reads a slot and ignores it
+                    const uint32_t y = (uint32_t)(c.z + dy - pad), z = (uint32_t)(c.w + dz - pad);
+                    const bool first_y = (y & ~3u) == y0, first_z = dz == 0 || (dz < K - 1 && (z & ~3u) == z0);
+                    const uint32_t hh = first_z ? (first_y ? h[0][0] : h[1][0]) : (first_y ? h[0][1] : h[1][1]);
+                    const uint32_t slot = (region_slot(hh, lx | local_y(y) | local_z(z)) + (t - tt)) & mask;
+                    got[u] = *reinterpret_cast<const uint3*>(&slots[slot]);
+                }
+            }
+            any = false;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int dy = dy0 + u / K, dz = u % K;
+                const uint32_t want_lo = ((uint32_t)(c.z + dy - pad) << 16) | (uint32_t)(c.w + dz - pad);
+                const bool hit = got[u].x == want_lo && got[u].y == want_hi, free_slot = ((got[u].y ^ tag) >> 24) != 0u;
+                if (pending[u] && hit) found[u] = (int32_t)got[u].z;
+                pending[u] = pending[u] && !hit && !free_slot;
+                any = any || pending[u];
+            }
+            any = __any(any);
+        }
+        int32_t* lines = nbr + tile * (int64_t)(K3 * TILE) + (int64_t)(w * K + dy0) * (K * TILE) + lane;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (dy0 + u / K < K) {
+                lines[u * TILE] = found[u];
+                const uint64_t vote = __ballot(found[u] >= 0);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) bits[g] |= ((vote >> (16 * g)) & 0xffffull) != 0ull ? 1u << ((pass * YB * K) + u) : 0u;
+            }
+    }
+    // they start at bit (w K + dy_first) K of the tile's masks
+    const int at = (w * K + dy_first) * K;
+    if (lane < 4) {
+        const uint32_t b = lane == 0 ? bits[0] : lane == 1 ? bits[1] : lane == 2 ? bits[2] : bits[3];
+        const uint64_t placed = (uint64_t)b << (at & 31);
+        atomicOr(&mask_s[lane * MW + (at >> 5)], (uint32_t)placed);
+        if (MW > 1 && (uint32_t)(placed >> 32) != 0u) atomicOr(&mask_s[lane * MW + (at >> 5) + 1], (uint32_t)(placed >> 32));
+    }
+    __syncthreads();
+    if (threadIdx.x < 4 * MW) gmask[tile * (4 * MW) + threadIdx.x] = mask_s[threadIdx.x];
 }
 
 // ---- strided layers ----------------------------------------------------------------------------
@@ -763,14 +875,25 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
     SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm<KV, WPT, CH, AT>), dim3(xcd_grid(L.tiles)), dim3(64 * WPT), 0, s,      \
               (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, d_counts,          \
               (KmapHeader*)d_kmap, h)
+#define SC_SUBM_BLOCKS(KV, YG, YB)                                                                                \
+    SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm_blocks<KV, YG, YB>), dim3(xcd_grid(L.tiles)), dim3(64 * KV * YG), 0, s,  \
+              (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, d_counts,    \
+              (KmapHeader*)d_kmap, h)
         switch (K) {
             case 1: SC_SUBM_LAUNCH(1, 1, 1, 1); break;
-            case 3: SC_SUBM_LAUNCH(3, 8, 4, 1); break;
-            case 5: SC_SUBM_LAUNCH(5, 8, 4, 1); break;
+            case 3:
+                // nine wavefronts a tile up to 16 tiles per CU, where their shorter chains still show (8 k rows:
+                // 5.3 against 6.8 us, 261 k: 35.0 against 37.4); past it the block hashes that the wavefronts of
+                // an x offset repeat cost more (300 k: 33.4 against 30.7, 10^6: 98 against 75)
+                if (L.tiles <= 16 * (int64_t)compute_units()) SC_SUBM_BLOCKS(3, 3, 1);
+                else SC_SUBM_BLOCKS(3, 1, 3);
+                break;
+            case 5: SC_SUBM_BLOCKS(5, 3, 1); break;
             case 7: SC_SUBM_LAUNCH(7, 8, 4, 1); break;
             default: return SC_EINVAL;
         }
 #undef SC_SUBM_LAUNCH
+#undef SC_SUBM_BLOCKS
         if (d_out_coords != nullptr && d_out_coords != d_coords) {
             if (hipMemcpyAsync(d_out_coords, d_coords, (size_t)n * 16, hipMemcpyDeviceToDevice, s) != hipSuccess)
                 return SC_EHIP;
@@ -898,7 +1021,6 @@ extern "C" int sc_kmap_export(const void* d_kmap, int64_t n, int K, int stride, 
     const int64_t tiles = ((mode == SC_INVERSE ? h_counts->n_in : h_counts->n_out) + TILE - 1) / TILE;
     if (tiles > 0 && acc > 0)
         SC_LAUNCH(KID_EXPORT, k_export, dim3((unsigned)L.K3), dim3(1024), 0, s,
-                  (const int32_t*)((const char*)d_kmap + L.off_nbr), L.K3, tiles, (const int32_t*)d_offset_start,
-                  d_pairs_in, d_pairs_out);
+                  (const int32_t*)((const char*)d_kmap + L.off_nbr), L.K3, tiles, (const int32_t*)d_offset_start, d_pairs_in, d_pairs_out);
     return SC_OK;
 }

@@ -64,3 +64,30 @@ def test_strided_map_with_blocks_of_4096_candidates():
         ref = oracle.kmap(coords, K, 2, "strided")
         assert h.status == 0 and h.n_out == ref["n_out"] and h.n_pairs == ref["offset_start"][-1]
         assert_maps_equal(exported_map(buf, h), buf.out_coords[:h.n_out].cpu().numpy(), ref, exact_order=True)
+
+
+@pytest.mark.parametrize("K", [3, 5])
+@pytest.mark.parametrize("n", [1, 65, 3000, 270_000])
+def test_submanifold_map_lookups(K, n):
+    """The look-ups of a submanifold map by block: sets at the ends of the coordinate domain, cubes that
+    cross every block boundary, and enough rows for the variant with one wavefront per x offset."""
+    say(f"submanifold look-ups K={K} n={n}")
+    from paper_2402_07710_amd import binding as sc
+    import oracle
+    import torch
+    from tests.test_gpu_parity import assert_maps_equal, exported_map
+    cells = synth.uniform_cells(n, 16 if n <= 3000 else 90, seed=K + n)
+    for base in (0, sc.SC_COORD_MAX - int(cells[:, 1:].max())):
+        coords = cells.copy()
+        coords[:, 0] = np.arange(n) % 2 * 255 if n <= 3000 else 3
+        coords[:, 1:] += base
+        buf = sc.LayerBuffers(n, K, 1, "subm", 32, 32, "f16", device="cuda:0")
+        dev = torch.from_numpy(coords).to("cuda:0")
+        buf.hash_build(dev)
+        buf.kmap_build(dev)
+        h = buf.read_counts()
+        ref = oracle.kmap(coords, K, 1, "subm")
+        assert h.status == 0 and h.n_out == n
+        assert_maps_equal(exported_map(buf, h), coords, ref, exact_order=True)
+        if n > 3000:
+            break
