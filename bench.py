@@ -431,7 +431,7 @@ def measure_layer(args, torch, sc, synth, workload: str, steps: int, warmup: int
 
     # Multiplies issued against multiplies that exist.  The matrix kernels keep an output row in its
     # place and skip a group of rows at an offset only if none of its rows has a neighbour there:
-    # 16 rows (v_mfma 16x16x32: k_conv_rows16, k_conv_stream) or 32 rows (32x32x16: k_conv_direct64).
+    # 16 rows (v_mfma 16x16x32: all kernels over a map).
     # Counted from the exported pair lists, outside the timed region.
     if conv_name == "k_conv_mfma" and args.table != "fused" and P > 0:
         _, p_out, ost = sc.sc_kmap_export(buf.kmap, N, K, stride, mode, h, stream)

@@ -1034,17 +1034,17 @@ static int launch_streamed(int K3, int C_in, int C_out, int64_t tiles, hipStream
                            const uint4* wp, void* out, int out_f32, const MapSource& ms, const int64_t* counts,
                            int64_t n_out_cap, bool feat_small, bool* handled) {
     *handled = true;
-    // 64 input channels: the kernel with 32-bit buffer offsets where the feature array allows it
-    if (K3 == 27 && C_in == 64 && C_out == 64 && feat_small)
-        return launch_direct64<DT, 27, FUSED>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
 #define SC_STREAM(K3V, KSV, CBV, NWV, DV) \
     return launch_stream<DT, K3V, KSV, CBV, NWV, DV, FUSED>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
-    if (K3 == 27 && C_in == 64 && C_out == 64) SC_STREAM(27, 2, 4, 4, 3);       // feature arrays of 4 GiB and more
     if (K3 == 27 && C_in == 128 && C_out == 128) SC_STREAM(27, 4, 8, 8, 1);
     if (K3 == 27 && C_in == 32 && C_out == 64) SC_STREAM(27, 1, 4, 4, 3);
-    if (K3 == 27 && C_in == 64 && C_out == 128) SC_STREAM(27, 2, 8, 4, 2);
-    if constexpr (!FUSED) {
-        if (K3 == 8 && C_in == 64 && C_out == 128) SC_STREAM(8, 2, 8, 4, 2);
+    if constexpr (FUSED) {
+        // 64 input channels: the kernel with 32-bit buffer offsets where the feature array allows it
+        if (C_in == 64 && C_out == 64 && feat_small)
+            return launch_direct64<DT, 27, 1>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
+        if (C_in == 64 && C_out == 64) SC_STREAM(27, 2, 4, 4, 3);       // feature arrays of 4 GiB and more
+        if (C_in == 64 && C_out == 128) SC_STREAM(27, 2, 8, 4, 2);
+    } else {
         if (K3 == 8 && C_in == 128 && C_out == 128) SC_STREAM(8, 4, 8, 8, 1);
     }
 #undef SC_STREAM
@@ -1068,7 +1068,7 @@ static int pack_weights(int K3, int C_in, int C_out, const void* d_weight, void*
 // which the resident kernels re-lay out themselves and the others have packed into the workspace
 // first.  FUSED (dense table, no map) always takes raw weights.
 template <int FUSED>
-static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, hipStream_t s, const void* d_feat_in,
+static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, hipStream_t s, const void* d_feat_in,
                       const void* d_weight, bool packed, void* d_workspace, void* d_feat_out,
                       int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap, int64_t feat_rows) {
     const uint16_t* feat = (const uint16_t*)d_feat_in;
@@ -1098,13 +1098,19 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     }
     // rows that a 32-bit byte offset can address, with room for the "no neighbour" offsets above them
     const bool feat_small = feat_rows * (int64_t)C_in * 2 < 0xFFFFFF80ll;
+    // 128 -> 128 with the map: the general kernel up to 20 tiles per CU.  A workgroup of the streaming kernel is eight
+    // tiles and takes ~75 us however few there are; full, it moves the weights once for them (us, general and
+    // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
+    // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
+    if (!FUSED && C_in == 128 && C_out == 128 && likely <= 20 * (int64_t)compute_units())
+        return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
     rc = dtype_in == SC_F16 ? launch_streamed<SC_F16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
                                                             n_out_ptr, n_out_cap, feat_small, &handled)
                             : launch_streamed<SC_BF16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
                                                              n_out_ptr, n_out_cap, feat_small, &handled);
     if (handled || rc != SC_OK) return rc;
     if (FUSED) return SC_EINVAL;
-    return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
+    return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
 }
 
 }  // namespace sc
@@ -1138,6 +1144,8 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     int64_t tiles = (n_out_cap + TILE - 1) / TILE;
     if (tiles > L.tiles) tiles = L.tiles;
     if (tiles == 0) return SC_OK;
+    // tiles to expect: strided layers on surfaces have about as many output rows as input rows, their bound is up to 8 times that
+    const int64_t n_map_tiles = (n_map + TILE - 1) / TILE, likely = tiles < n_map_tiles ? tiles : n_map_tiles;
     const uint32_t* gmask = (const uint32_t*)((const char*)d_kmap + L.off_mask);
     const int32_t* nbr = (const int32_t*)((const char*)d_kmap + L.off_nbr);
     hipStream_t s = (hipStream_t)stream;
@@ -1149,7 +1157,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         const bool slices = C_in == 16 || C_in == 32 || C_in == 64 || C_in == 128 || C_in == 256;
         if (slices && C_out % 16 == 0 && (C_in * C_out >= 2048 || (C_in * C_out >= 1024 && tiles >= compute_units()) || L.K3 > 32)) {
             const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
-            return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
+            return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, likely, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
                                  n_out_cap);
         }
         if (L.K3 <= 32 && C_in % 16 == 0 && C_in <= 64 && C_out % 16 == 0 && C_out <= 64) {
@@ -1177,7 +1185,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
     // rows of the input feature array: the map's inputs, or (inverse layers) at most the strided map's bound
     const int64_t feat_rows = n_map > bound ? n_map : bound;
-    return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, s, d_feat_in, d_weight, packed, d_workspace,
+    return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, s, d_feat_in, d_weight, packed, d_workspace,
                          d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap, feat_rows);
 }
 
@@ -1270,6 +1278,6 @@ extern "C" int sc_conv_fwd_grid(const void* d_feat_in, const int32_t* d_coords, 
     if (n == 0) return SC_OK;
     const MapSource ms{nullptr, nullptr, (const int4*)d_coords, (const unsigned long long*)d_grid, GridDims{B, X, Y, Z}, epoch};
     if (!mfma_channels_ok(C_in, C_out)) return SC_EINVAL;
-    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (hipStream_t)stream, d_feat_in, d_weight,
+    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, (hipStream_t)stream, d_feat_in, d_weight,
                          false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n, n);
 }

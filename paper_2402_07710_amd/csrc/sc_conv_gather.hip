@@ -1,5 +1,5 @@
-// The general convolution kernel: every shape without a kernel of its own in sc_conv.hip (kernel sizes
-// other than 3, 256 channels, unequal channel counts), and fp32 layers with enough work for it.
+// The general convolution kernel: 16-bit layers of 64 and more channels (128 -> 128 up to 20 tiles per CU), every
+// shape without a kernel of its own in sc_conv.hip, and fp32 layers with enough work for it.
 #include "sc_conv.h"
 
 namespace sc {
@@ -32,14 +32,18 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 //    wavefronts (eight) split rows as well as channels.
 //  * One wait for everything and one barrier per step.  What a step costs is issuing its loads (17
 //    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
-// Groups without a neighbour are skipped where an offset has at least 128 cycles of multiplies (fp32, or four
-// slices and more); below that the test costs more: they read the row of zeros, and the places of the
-// last step that have no offset are fetched like the others (of offset 0, rows of zeros) and not multiplied.
+//  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
+//    65 us with 2, 51.5 with 4, 50 with 6).  That also decides the step length, 16 KB of LDS for 64 channels.
+// SKIP: groups without a neighbour are skipped (64 channels: 62 -> 50 us at that size).  32-channel rows
+// are too short for the test: such groups read the row of zeros, and the places of the last step that have no
+// offset are fetched like the others (of offset 0, rows of zeros) and not multiplied.
 // Measured, before (one wavefront per 16 rows, rows and weights loaded at their use) -> now: 14 k
 // voxels 256 -> 256 f16 480-555 -> 44 us; 53 k voxels K = 5 32 -> 32 bf16 116 -> 38 us; 53 k voxels 64 -> 64
-// fp32 118 -> 80 us.
-template <int DT, int KS, int NW, int WR, int CT, int SL>
-__global__ void __launch_bounds__(64 * NW, NW / 2)
+// fp32 118 -> 80 us.  Against the kernels that shared W[k] in LDS or gave a wavefront 64 rows: 64 -> 64 2 k /
+// 20 k / 110 k / 262 k voxels 14.8 / 15.8 / 29.4 / 58.2 -> 10.7 / 14.1 / 28.6 / 50.3 us; 64 -> 128 4 k / 110 k 27.4 /
+// 47.1 -> 11.7 / 40.7; 128 -> 128 4 k / 53 k / 262 k 70.8 / 75.5 / 157 -> 16.8 / 43 / 127.5.
+template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC>
+__global__ void __launch_bounds__(64 * NW, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const uint32_t* __restrict__ gmask,
               const int32_t* __restrict__ nbr, int K3, int mw, int CB, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
     constexpr bool F32 = DT == SC_F32;
@@ -50,7 +54,6 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     constexpr int NI = KS == 1 || NW == 8 ? 1 : 2;     // gather instructions per wavefront and chunk
     constexpr int STEP_BYTES = SL * 4096;
     constexpr int WC = NW / WR, RG = 4 / WR;           // wavefronts across channels, 16-row groups per wavefront
-    constexpr bool SKIP = F32 || KS >= 4;
     static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
     constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
     constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
@@ -281,61 +284,71 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     }
 }
 
-template <int DT, int KS, int NW, int WR, int CT, int SL>
+template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC>
 static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     constexpr size_t lds = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0);
     static_assert(lds <= 65536, "within the LDS a kernel may use without asking");
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
-    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL>), dim3(xcd_run_grid(tiles), blocks_y), dim3(64 * NW), lds, s, feat, wp,
-              out, out_f32, ms.gmask, ms.nbr, K3, mw, CB, n_out_ptr, n_out_cap);
+    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC>), dim3(xcd_run_grid(tiles), blocks_y),
+              dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms.gmask, ms.nbr, K3, mw, CB, n_out_ptr, n_out_cap);
     return SC_OK;
 }
 
-template <int DT, int KS, int SL>
-static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out,
-                            int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-#define SC_GATHER(NW, WR, CT) return launch_gather_as<DT, KS, NW, WR, CT, SL>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
-    constexpr bool F32 = DT == SC_F32;
-    if (CB == 1) SC_GATHER(4, 4, 1);
-    if (CB == 2) SC_GATHER(F32 ? 8 : 4, F32 ? 4 : 2, 1);
-    // two output blocks per wavefront halve how often a tile's rows are gathered; one, where the
-    // launch would otherwise leave CUs idle (256 input channels, 219 tiles: -> 128 29.0 us with one,
-    // 34.2 with two; -> 256, twice the workgroups, 49.1 and 44.1)
-    if (DT == SC_F32 || CB <= 4 || 2 * tiles * ((CB + 7) / 8) < 3 * (int64_t)cus) SC_GATHER(F32 ? 8 : 4, F32 ? 2 : 1, 1);
-    if constexpr (DT != SC_F32) SC_GATHER(4, 1, 2);
-    return SC_EINVAL;
+// O1, O2: wavefronts per SIMD with one and with two output blocks per wavefront
+template <int DT, int KS, int SL, int SKIP, int O1, int O2>
+static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat, const void* wp,
+                            void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
+#define SC_GATHER(NW, WR, CT, OCC) \
+    return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+    if constexpr (DT == SC_F32) {
+        if (CB == 1) SC_GATHER(4, 4, 1, 2);
+        if (CB == 2) SC_GATHER(8, 4, 1, 4);
+        SC_GATHER(8, 2, 1, 4);
+    } else {
+        if (CB == 1) SC_GATHER(4, 4, 1, O1);
+        if (CB == 2) SC_GATHER(4, 2, 1, O1);
+        // two output blocks per wavefront halve how often a tile's rows are gathered; one, where that leaves CUs
+        // idle or, up to 128 channels either way, with few wavefronts (us with one and with two blocks: 256 -> 128 at
+        // 219 tiles 29.0, 34.2; 256 -> 256 49.1, 44.1; 64 -> 256 at 157 tiles 17.6, 19.3, at 250 22.9, 20.9; 128 -> 128 at
+        // 625 tiles 36.0, 38.2, at 4,088 132, 127.5; 64 -> 128 at 469 tiles 20.2, 21.4, at 834 26.9, 26.7)
+        if (CB <= 4 || (CB <= 8 && KS <= 4 ? likely <= 4 * (int64_t)cus : 2 * likely * ((CB + 7) / 8) < 3 * (int64_t)cus)) SC_GATHER(4, 1, 1, O1);
+        SC_GATHER(4, 1, 2, O2);
+    }
 #undef SC_GATHER
 }
 
-int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const void* feat,
+int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const int CB = C_out / 16;
-    // slices per step: a whole offset at 256 channels; four elsewhere, where twice as many workgroups
-    // per CU (32 KB of LDS each) are worth more than fewer barriers (53 k voxels K = 5 32 -> 32: 39.3 us,
-    // with eight 44.6; 14 k voxels 128 -> 256: 25.2, 26.3)
-#define SC_GATHER_KS(KS, SL)                                                                                                      \
+    // Slices per step, skipping, wavefronts per SIMD.  256 channels: a whole offset.  128: an offset (half of one,
+    // with more workgroups: 128 -> 64 at 53 k voxels 36.7 us instead of 28.8).  64: an offset; two for K = 5 and 7, whose
+    // tiles walk many more offsets (K = 3 -> 64 at 262 k voxels 50.3 us with one, 56.5 with two; K = 5 -> 64 at 53 k 55.1
+    // and 50.7).  32: four (K = 5 -> 32 at 53 k: 30.4 us; two 32.1, eight with half the workgroups 36).
+#define SC_GATHER_KS(KS, SL, SKIP, O1, O2)                                                                                        \
     return dtype_in == SC_F16                                                                                                     \
-               ? launch_gather_ks<SC_F16, KS, SL>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
-               : launch_gather_ks<SC_BF16, KS, SL>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
+               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if (dtype_in == SC_F32) {
-#define SC_GATHER_F32(KS, SL) \
-    return launch_gather_ks<SC_F32, KS, SL>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+#define SC_GATHER_F32(KS) \
+    return launch_gather_ks<SC_F32, KS, 4, 1, 4, 4>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
         switch (C_in) {
-            case 16: SC_GATHER_F32(1, 4);
-            case 32: SC_GATHER_F32(2, 4);
-            case 64: SC_GATHER_F32(4, 4);
-            case 128: SC_GATHER_F32(8, 4);
-            case 256: SC_GATHER_F32(16, 4);
+            case 16: SC_GATHER_F32(1);
+            case 32: SC_GATHER_F32(2);
+            case 64: SC_GATHER_F32(4);
+            case 128: SC_GATHER_F32(8);
+            case 256: SC_GATHER_F32(16);
         }
 #undef SC_GATHER_F32
         return SC_EINVAL;
     }
     switch (C_in) {
-        case 32: SC_GATHER_KS(1, 4);
-        case 64: SC_GATHER_KS(2, 4);
-        case 128: SC_GATHER_KS(4, 4);
-        case 256: SC_GATHER_KS(8, 8);
+        case 32: SC_GATHER_KS(1, 4, 0, 2, 2);
+        case 64:
+            if (K3 <= 32) SC_GATHER_KS(2, 2, 1, 6, 5);
+            SC_GATHER_KS(2, 4, 1, 5, 4);
+        case 128: SC_GATHER_KS(4, 4, 1, 4, 3);
+        case 256: SC_GATHER_KS(8, 8, 1, 2, 2);
     }
 #undef SC_GATHER_KS
     return SC_EINVAL;

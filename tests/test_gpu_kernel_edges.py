@@ -28,6 +28,19 @@ def test_general_kernel_with_two_output_blocks_per_wavefront():
     check_layer(coords[:13000], 3, 1, "subm", 32, 256, "bf16", seed=1, threads=16)
 
 
+@pytest.mark.parametrize("K,stride,C_in,C_out", [(3, 1, 64, 64), (3, 1, 64, 128), (3, 1, 128, 128), (2, 2, 64, 128), (2, 2, 128, 128), (3, 2, 64, 64)])
+@pytest.mark.parametrize("n,dtype", [(1, "bf16"), (64, "f16"), (129, "bf16"), (66000, "f16")])
+def test_general_kernel_64_and_128_channels(K, stride, C_in, C_out, n, dtype):
+    """One row, whole tiles, a tile of one row, and enough tiles for two output blocks per wavefront."""
+    say(f"general kernel K={K} s={stride} {C_in}->{C_out} {dtype} n={n}")
+    if n > 60000:
+        coords = np.concatenate([synth.lidar_scene(4)[:33000], synth.lidar_scene(5)[:33000]])
+        coords[33000:, 0] = 1
+    else:
+        coords = synth.uniform_cells(n, 9, seed=C_in + C_out + n)
+    check_layer(coords, K, stride, "subm" if stride == 1 else "strided", C_in, C_out, dtype, seed=n, threads=16)
+
+
 @pytest.mark.parametrize("K,C_in,C_out,n", [(3, 16, 64, 17000), (3, 32, 32, 17000), (3, 64, 64, 1), (3, 64, 64, 65), (3, 64, 80, 1000),
                                             (3, 128, 16, 700), (3, 256, 48, 300), (5, 16, 16, 700), (5, 32, 32, 65)])
 def test_general_kernel_fp32(K, C_in, C_out, n):
