@@ -66,5 +66,7 @@ __device__ inline void store_acc(void* __restrict__ out, int out_f32, int64_t ro
 // caller's row capacity, `likely` is how many of them to expect (the input's, where the output count is known on the device only).
 int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap);
+int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp,
+                        void* out, int out_f32, const MapSource& ms, int64_t n);
 
 }  // namespace sc

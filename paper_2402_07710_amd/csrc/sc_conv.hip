@@ -215,12 +215,11 @@ __device__ __align__(256) uint4 g_zero_row[32];      // 512 bytes: a row of up t
 // Accumulators (64 rows x C_out per wavefront) never leave the registers.  KS = C_in/32,
 // CB = C_out/16.
 // Rows are gathered in the operand's own lane order (16 rows x four 16-byte pieces of a 32-channel
-// slice per load: 64 contiguous bytes of a row).  Gathering whole 128-byte rows with eight
+// slice per load: 64 contiguous bytes of a row).  Gathering whole 128-byte lines with eight
 // consecutive lanes per row is cheaper for the address unit, but the rows then have to pass
-// through LDS to reach operand layout; k_conv_direct64 does that for 64 input channels, where a
-// row is one line.  For wider rows the extra LDS traffic costs more than the gather saves, and an
-// in-register shuffle (lane-swap + quad-permute instructions, 20 VALU operations per 16 bytes)
-// was measured slower than either.
+// through LDS to reach operand layout (k_conv_gather does), where this kernel's weights already
+// keep the LDS busy; an in-register shuffle (lane-swap + quad-permute instructions, 20 VALU
+// operations per 16 bytes) was measured slower than either.
 // FUSED: as in k_conv_rows16, the offset-table lines come from the dense location table directly.
 template <int DT, int K3, int KS, int CB, int NWV, int D, int FUSED>
 __global__ void __launch_bounds__(64 * NWV, 2)
@@ -382,382 +381,6 @@ k_conv_stream(const uint16_t* __restrict__ feat, const uint4* wp, void* __restri
             if (row < n_out) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) store_acc<DT>(out, out_f32, row, C_out, cb * 16 + qq * 4, acc[g][cb]);
-            }
-        }
-    }
-    SC_MARK(4);
-    SC_MARK(5);
-}
-
-// ---- 64 input channels: independent wavefronts, weights straight from global memory ---------------
-// One wavefront per 64-row tile as in k_conv_stream, but nothing is shared between the wavefronts
-// of a workgroup: no weight tile in LDS, no barrier.  A layer of ~10^5 voxels keeps every CU busy
-// with a handful of wavefronts, each of which walks its K^3 offsets as one chain; what a step of
-// that chain costs is the latency of what it has to wait for, so everything a step needs is
-// requested one to two steps ahead and a wavefront never waits for another one.
-//  * A wavefront walks only the offsets at which its tile has a neighbour at all (about 60 % of
-//    the 27 on surface-like sets), in increasing order, taken from the tile's masks bit by bit.
-//  * Multiplies are v_mfma_f32_32x32x16 on the two 32-row halves of the tile.  SKIP = 1: a half
-//    without a neighbour at offset k is skipped, and so are its loads (tests and branches in
-//    every step, exact wait counts that depend on the tile).  SKIP = 0: such a half is rows of
-//    zeros like any row without a neighbour, and a step is one straight line of code, the same
-//    for every offset and tile; the host picks the form by how full the CUs are.
-//  * The weight operand of that instruction (32 output channels x 16 input channels) is read
-//    straight from the packed 16x32 tiles in global memory, one step ahead: both forms keep 8
-//    input channels of one output channel in 16 bytes, so only the addresses differ, and a load
-//    touches eight whole 128-byte lines.  Every wavefront of the chip reads the same 8 KB per
-//    offset: L1 and L2 hits.
-//  * Gathers are buffer loads, eight lanes on the eight 16-byte pieces of one 128-byte row: the
-//    address is one shift-or (row << 7 | byte in row), and "no neighbour" (row -1) lands beyond
-//    the buffer's range, where the hardware returns zeros without touching memory.  The rows
-//    land in a ring of three register slots and pass through a 4 KB staging area in LDS (swizzled
-//    16-byte slots) to come back in operand layout, one step before they are multiplied.
-//  * Loads inside the loop are inline assembly, so that the compiler places no waits of its own
-//    for them: which loads are issued depends on the tile, and the one wait per step names the
-//    exact number of younger loads that may stay in flight (the counter retires in order).
-//    Registers written by such a load are handed back to the compiler through an empty asm
-//    statement right after the wait that covers them.
-//  * In program order the staging operations of offset k+1 sit between the multiplies of offset
-//    k: a wavefront's LDS operations then run in the shadow of its own matrix instructions.
-// The feature array must be smaller than 4 GiB (32-bit buffer offsets); the host checks and falls
-// back to k_conv_stream otherwise.  The number of tiles per workgroup is the launch's block size
-// / 64 (any value up to 8): the host picks it so that the workgroups spread evenly over the CUs.
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-template <int DT>
-__device__ inline f32x16 mfma32x32x16(u32x4 a, u32x4 b, f32x16 c) {
-    if constexpr (DT == SC_F16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-template <int N> struct IntC { static constexpr int value = N; };
-constexpr int DIRECT_LINES(int K3) { return K3 + 1; }                // table lines kept in LDS per wavefront
-constexpr int DIRECT_STAGE = 32 * 128;                               // bytes of a wavefront's staging area
-
-template <int DT, int K3, int FUSED, int SKIP>
-__global__ void __launch_bounds__(512, 1)
-k_conv_direct64(const uint16_t* __restrict__ feat, const uint4* wp, void* __restrict__ out, int out_f32,
-                const MapSource ms, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
-    static_assert(K3 <= 31, "one mask word per half, and one more bit that is never set");
-    static_assert(!FUSED || K3 == 27, "fused look-ups: 3x3x3 layers");
-    const uint32_t* __restrict__ gmask = ms.gmask;
-    const int32_t* __restrict__ nbr = ms.nbr;
-    constexpr int MB = 2, C_out = 64, RB = 128;       // 32-channel output blocks, bytes per feature row
-    constexpr int KE = DIRECT_LINES(K3);               // the real lines, then one line of "no neighbour"
-    extern __shared__ __align__(16) uint4 smem[];     // stage[NWV][32 rows x 128 B] | e_lds[NWV][KE][64]
-
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, NWV = blockDim.x >> 6;
-    const int r32 = lane & 31, hh = lane >> 5;
-    char* stage = reinterpret_cast<char*>(smem) + wv * DIRECT_STAGE;
-    int32_t* e_lds = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(smem) + NWV * DIRECT_STAGE) + wv * (KE * TILE);
-    int64_t n_out = n_out_cap;
-    if (!FUSED && *n_out_ptr < n_out) n_out = *n_out_ptr;
-    // a workgroup's tiles are spread over the whole row range (tile = wavefront * units + unit):
-    // neighbouring tiles are alike in how many offsets they take part in, and the kernel ends with
-    // its slowest workgroup
-    const int64_t units = (n_out + (int64_t)NWV * TILE - 1) / ((int64_t)NWV * TILE);
-    const int64_t unit = xcd_unit_of(blockIdx.x, units);
-    if (unit < 0) return;
-    SC_MARK(0);
-    const int64_t tile = wv * units + unit;
-    const bool tile_ok = tile * TILE < n_out;
-
-    uint32_t mg[2] = {0u, 0u};                         // which offsets each 32-row half takes part in (bits < K3)
-    if constexpr (FUSED) {
-        int32_t v[K3];
-        if (tile_ok) {
-            grid_neighbours<3>(ms, tile * TILE + lane, n_out, v);
-#pragma unroll
-            for (int k = 0; k < K3; ++k) {
-                const uint64_t vote = __ballot(v[k] >= 0);
-#pragma unroll
-                for (int g = 0; g < 2; ++g) mg[g] |= (((vote >> (32 * g)) & 0xffffffffull) != 0ull ? 1u : 0u) << k;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K3; ++k) v[k] = -1;
-        }
-#pragma unroll
-        for (int k = 0; k < K3; ++k) e_lds[k * TILE + lane] = v[k];
-    } else {
-        // the tile's K3 table lines are one contiguous piece of the map: 16 bytes per lane and load
-        constexpr int LINE16 = K3 * TILE / 4;          // 16-byte pieces
-        constexpr int PASSES = (LINE16 + 63) / 64;
-        u32x4 v[PASSES];
-        const u32x4* line = reinterpret_cast<const u32x4*>(nbr + tile * (int64_t)(K3 * TILE));
-#pragma unroll
-        for (int i = 0; i < PASSES; ++i)
-            v[i] = (tile_ok && i * 64 + lane < LINE16) ? line[i * 64 + lane] : u32x4{~0u, ~0u, ~0u, ~0u};
-        if (tile_ok) {
-#pragma unroll
-            for (int g = 0; g < 2; ++g) mg[g] = gmask[tile * 4 + 2 * g] | gmask[tile * 4 + 2 * g + 1];
-        }
-#pragma unroll
-        for (int i = 0; i < PASSES; ++i)
-            if (i * 64 + lane < LINE16) reinterpret_cast<u32x4*>(e_lds)[i * 64 + lane] = v[i];
-    }
-#pragma unroll
-    for (int k = K3; k < KE; ++k) e_lds[k * TILE + lane] = -1;
-#pragma unroll
-    for (int g = 0; g < 2; ++g) mg[g] = __builtin_amdgcn_readfirstlane(mg[g]);
-    auto pattern_at = [&](int k) -> uint32_t { return SKIP ? ((mg[0] >> k) & 1u) | (((mg[1] >> k) & 1u) << 1) : 3u; };
-    auto halves_at = [&](int k) -> uint32_t { return ((mg[0] >> k) & 1u) + ((mg[1] >> k) & 1u); };
-    // The wavefront walks only the offsets its tile takes part in, in increasing order; K3 stands
-    // for "no further offset": no bit of the masks, a table line of "no neighbour".  k0 is the
-    // offset of the step at hand, k1..k4 the ones after it (what is requested ahead).
-    uint32_t rest = mg[0] | mg[1];
-    const int n_steps = __builtin_popcount(rest);
-    auto next_offset = [&]() -> int {
-        const int k = rest != 0u ? __builtin_ctz(rest) : K3;
-        rest &= rest - 1u;
-        return k;
-    };
-    int k0 = next_offset(), k1 = next_offset(), k2 = next_offset(), k3 = next_offset(), k4 = next_offset();
-
-    // gathers: instruction i of a half reads its rows 8i .. 8i+7, eight lanes per row
-    const int row8 = lane >> 3, piece = lane & 7;
-    // buffer descriptor over the feature array: offsets at or above 0xFFFFFF80 (row -1) read as zeros
-    u32x4 rs;
-    {
-        const uint64_t fa = (uint64_t)feat;
-        rs[0] = __builtin_amdgcn_readfirstlane((uint32_t)fa);
-        rs[1] = __builtin_amdgcn_readfirstlane((uint32_t)(fa >> 32) & 0xffffu);
-        rs[2] = __builtin_amdgcn_readfirstlane(0xFFFFFF80u);
-        rs[3] = __builtin_amdgcn_readfirstlane(0x00020000u);
-    }
-    const uint32_t pbyte = piece << 4;
-    // staging area: [32 rows][128 bytes], the 16-byte slots of a row swizzled with the row number;
-    // the multiply's operand for 16-channel slice s is piece 2s + (lane / 32) of row lane % 32
-    int st_w[4], st_r[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        st_w[i] = (8 * i + row8) * RB + ((piece ^ row8) << 4);
-        st_r[i] = r32 * RB + (((2 * i + hh) ^ (r32 & 7)) << 4);
-    }
-    const int32_t* e_mine = e_lds + row8;
-    // row numbers of offset k for this lane's eight loads (read from LDS well ahead of their use), and
-    // the byte offsets made of them
-    auto row_numbers = [&](uint32_t (&e)[2][4], int k) {
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) e[g][i] = (uint32_t)e_mine[k * TILE + g * 32 + i * 8];
-    };
-    auto row_offsets = [&](uint32_t (&off)[2][4], const uint32_t (&e)[2][4]) {
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) off[g][i] = (e[g][i] << 7) | pbyte;
-    };
-    // the rows of one offset for the halves named by pat: four loads per half, skipped as a whole otherwise
-    auto gather = [&](u32x4 (&dst)[2][4], const uint32_t (&off)[2][4], uint32_t pat) {
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-            if constexpr (!SKIP)
-                asm volatile(
-                    "buffer_load_dwordx4 %[d0], %[o0], %[rs], 0 offen\n\t"
-                    "buffer_load_dwordx4 %[d1], %[o1], %[rs], 0 offen\n\t"
-                    "buffer_load_dwordx4 %[d2], %[o2], %[rs], 0 offen\n\t"
-                    "buffer_load_dwordx4 %[d3], %[o3], %[rs], 0 offen"
-                    : [d0] "+v"(dst[g][0]), [d1] "+v"(dst[g][1]), [d2] "+v"(dst[g][2]), [d3] "+v"(dst[g][3])
-                    : [o0] "v"(off[g][0]), [o1] "v"(off[g][1]), [o2] "v"(off[g][2]), [o3] "v"(off[g][3]), [rs] "s"(rs));
-            else
-            asm volatile(
-                "s_bitcmp1_b32 %[pat], %[bit]\n\t"
-                "s_cbranch_scc0 .Lsc_skip_%=\n\t"
-                "buffer_load_dwordx4 %[d0], %[o0], %[rs], 0 offen\n\t"
-                "buffer_load_dwordx4 %[d1], %[o1], %[rs], 0 offen\n\t"
-                "buffer_load_dwordx4 %[d2], %[o2], %[rs], 0 offen\n\t"
-                "buffer_load_dwordx4 %[d3], %[o3], %[rs], 0 offen\n"
-                ".Lsc_skip_%=:"
-                : [d0] "+v"(dst[g][0]), [d1] "+v"(dst[g][1]), [d2] "+v"(dst[g][2]), [d3] "+v"(dst[g][3])
-                : [o0] "v"(off[g][0]), [o1] "v"(off[g][1]), [o2] "v"(off[g][2]), [o3] "v"(off[g][3]), [rs] "s"(rs),
-                  [pat] "s"(pat), [bit] "n"(g)
-                : "scc");
-    };
-    // the eight weight operands of offset k (slice sl, output block mb), skipped if the tile takes no part
-    const int a_lane = 2048 * ((lane >> 4) & 1) + 256 * hh + 16 * (lane & 15);
-    const char* w_lane = reinterpret_cast<const char*>(wp) + a_lane;
-    auto load_weights = [&](u32x4 (&dst)[4][MB], int k, uint32_t pat) {
-        const char* p0 = w_lane + (int64_t)(k < K3 ? k : K3 - 1) * (4 * MB * 1024);
-        const char* p1 = p0 + 4096;
-        if constexpr (!SKIP)
-            asm volatile(
-                "global_load_dwordx4 %[d0], %[p0], off\n\t"
-                "global_load_dwordx4 %[d1], %[p1], off\n\t"
-                "global_load_dwordx4 %[d2], %[p0], off offset:512\n\t"
-                "global_load_dwordx4 %[d3], %[p1], off offset:512\n\t"
-                "global_load_dwordx4 %[d4], %[p0], off offset:1024\n\t"
-                "global_load_dwordx4 %[d5], %[p1], off offset:1024\n\t"
-                "global_load_dwordx4 %[d6], %[p0], off offset:1536\n\t"
-                "global_load_dwordx4 %[d7], %[p1], off offset:1536"
-                : [d0] "+v"(dst[0][0]), [d1] "+v"(dst[0][1]), [d2] "+v"(dst[1][0]), [d3] "+v"(dst[1][1]),
-                  [d4] "+v"(dst[2][0]), [d5] "+v"(dst[2][1]), [d6] "+v"(dst[3][0]), [d7] "+v"(dst[3][1])
-                : [p0] "v"(p0), [p1] "v"(p1));
-        else
-        asm volatile(
-            "s_cmp_eq_u32 %[pat], 0\n\t"
-            "s_cbranch_scc1 .Lsc_skipw_%=\n\t"
-            "global_load_dwordx4 %[d0], %[p0], off\n\t"
-            "global_load_dwordx4 %[d1], %[p1], off\n\t"
-            "global_load_dwordx4 %[d2], %[p0], off offset:512\n\t"
-            "global_load_dwordx4 %[d3], %[p1], off offset:512\n\t"
-            "global_load_dwordx4 %[d4], %[p0], off offset:1024\n\t"
-            "global_load_dwordx4 %[d5], %[p1], off offset:1024\n\t"
-            "global_load_dwordx4 %[d6], %[p0], off offset:1536\n\t"
-            "global_load_dwordx4 %[d7], %[p1], off offset:1536\n"
-            ".Lsc_skipw_%=:"
-            : [d0] "+v"(dst[0][0]), [d1] "+v"(dst[0][1]), [d2] "+v"(dst[1][0]), [d3] "+v"(dst[1][1]),
-              [d4] "+v"(dst[2][0]), [d5] "+v"(dst[2][1]), [d6] "+v"(dst[3][0]), [d7] "+v"(dst[3][1])
-            : [p0] "v"(p0), [p1] "v"(p1), [pat] "s"(pat)
-            : "scc");
-    };
-    // wait until at most 4 n loads are outstanding (n: halves fetched by the step before)
-    auto wait_younger = [&](uint32_t n) {
-        if (!SKIP || n == 2u) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if (n == 0u) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    };
-    // hand the registers of finished loads back to the compiler
-    auto pin = [&](u32x4 (&slot)[2][4]) {
-        asm volatile("" : "+v"(slot[0][0]), "+v"(slot[0][1]), "+v"(slot[0][2]), "+v"(slot[0][3]),
-                          "+v"(slot[1][0]), "+v"(slot[1][1]), "+v"(slot[1][2]), "+v"(slot[1][3]));
-    };
-    auto pin_w = [&](u32x4 (&w)[4][MB]) {
-        asm volatile("" : "+v"(w[0][0]), "+v"(w[0][1]), "+v"(w[1][0]), "+v"(w[1][1]),
-                          "+v"(w[2][0]), "+v"(w[2][1]), "+v"(w[3][0]), "+v"(w[3][1]));
-    };
-    u32x4 fb[3][2][4], a[2][4][MB];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) fb[j][g][i] = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int sl = 0; sl < 4; ++sl)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) a[j][sl][mb] = u32x4{0u, 0u, 0u, 0u};
-    // before the loop: the weights of the first offset and the rows of the first three, all complete at its start
-    load_weights(a[0], k0, pattern_at(k0));
-    {
-        const int kj[3] = {k0, k1, k2};
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            uint32_t e[2][4], off[2][4];
-            row_numbers(e, kj[j]);
-            row_offsets(off, e);
-            gather(fb[j], off, pattern_at(kj[j]));
-        }
-    }
-    uint32_t e_next[2][4];               // row numbers of the offset the next step fetches
-    row_numbers(e_next, k3);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int j = 0; j < 3; ++j) pin(fb[j]);
-    pin_w(a[0]);
-    f32x16 acc[2][MB];
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) acc[g][mb][j] = 0.f;
-    // rows of the first offset: load layout -> operand layout through the staging area (one half after
-    // the other through the same 4 KB: a wavefront's LDS operations execute in order)
-    {
-        const uint32_t pat0 = pattern_at(k0);
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            if ((pat0 >> g) & 1u) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(stage + st_w[i]) = fb[0][g][i];
-#pragma unroll
-                for (int sl = 0; sl < 4; ++sl) fb[0][g][sl] = *reinterpret_cast<const u32x4*>(stage + st_r[sl]);
-            }
-        }
-    }
-    SC_MARK(1);
-    SC_MARK(2);
-
-    // One step, for offset k0.  At its start the rows of k0 are in ring slot S in operand layout and
-    // its weights are in a[AB] (possibly still on their way: the wait comes first); the rows of k1
-    // are in slot S1 in load layout, those of k2 in flight.  Loads in issue order:
-    // ... weights k0, rows k2 | weights k1, rows k3: what may stay in flight at the top of the step
-    // are the rows of k2, four loads per half that takes part.  Then the weights of k1 are
-    // requested, the multiplies of k0 are issued slice by slice with the staging of k1 between
-    // them (half 0 is written in slice 0 and read back in slice 1, half 1 in slices 2 and 3), the
-    // freed slot is refilled with the rows of k3, and the row numbers of k4 are read from LDS.
-    auto step = [&](auto slot_c, auto ab_c) {
-        constexpr int S = decltype(slot_c)::value, S1 = (S + 1) % 3, AB = decltype(ab_c)::value;
-        const uint32_t pat = pattern_at(k0), pat1 = pattern_at(k1), pat3 = pattern_at(k3);
-        wait_younger(halves_at(k2));
-        // every LDS operation of the step before is complete from here on (staging reads, row
-        // numbers): said in a form the compiler's wait-count pass sees, it places no LDS waits
-        // between the multiplies below, where they would also wait for the staging of this step
-        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0), the other counters left alone
-        pin(fb[S1]);
-        pin_w(a[AB]);
-        load_weights(a[1 - AB], k1, pat1);
-#pragma unroll
-        for (int sl = 0; sl < 4; ++sl) {
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                if ((pat >> g) & 1u) {
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) acc[g][mb] = mfma32x32x16<DT>(a[AB][sl][mb], fb[S][g][sl], acc[g][mb]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (g == 0) {
-                    const int h = sl >> 1;          // the half whose staging falls into this slice
-                    if ((pat1 >> h) & 1u) {
-                        if ((sl & 1) == 0) {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(stage + st_w[i]) = fb[S1][h][i];
-                        } else {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) fb[S1][h][i] = *reinterpret_cast<const u32x4*>(stage + st_r[i]);
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-        uint32_t off[2][4];
-        row_offsets(off, e_next);
-        gather(fb[S], off, pat3);
-        row_numbers(e_next, k4);        // on their way while the next step starts
-        k0 = k1; k1 = k2; k2 = k3; k3 = k4;
-        k4 = next_offset();
-    };
-    // six steps per trip, so that ring slots (three) and weight registers (two sets) are constants;
-    // steps past the last offset find K3 everywhere and do nothing
-#pragma unroll 1
-    for (int i = 0; i < n_steps; i += 6) {
-        step(IntC<0>{}, IntC<0>{});
-        step(IntC<1>{}, IntC<1>{});
-        step(IntC<2>{}, IntC<0>{});
-        step(IntC<0>{}, IntC<1>{});
-        step(IntC<1>{}, IntC<0>{});
-        step(IntC<2>{}, IntC<1>{});
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing of the loop's loads is left in flight
-    SC_MARK(3);
-    // the accumulator block of a lane: output row lane % 32 of the half, channels
-    // 32 mb + 8 q + 4 (lane / 32) .. + 3 for q = 0..3
-    if (tile_ok) {
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            const int64_t row = tile * TILE + g * 32 + r32;
-            if (row < n_out) {
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        store_acc<DT>(out, out_f32, row, C_out, mb * 32 + 8 * q + 4 * hh,
-                                      f32x4{acc[g][mb][4 * q], acc[g][mb][4 * q + 1], acc[g][mb][4 * q + 2], acc[g][mb][4 * q + 3]});
             }
         }
     }
@@ -974,42 +597,6 @@ int compute_units() {
     return cu_count[dev];
 }
 
-// Tiles per workgroup for k_conv_direct64: its wavefronts are independent, so any count up to 8
-// (two wavefronts per SIMD at its register use) works; the workgroups should land on the CUs evenly.
-// Up to 8 tiles per CU: one workgroup per CU with ceil(tiles / CUs) wavefronts (measured on ~110 k
-// voxels: 31.4 us with 7, 33.3 with 8, 35.1 with 4); beyond that, four (261 k voxels: 62.6 us
-// with 4, 64.0 with 8, 78.1 with 7).
-static int direct_tiles_per_workgroup(int64_t tiles, int cus) {
-    if (tiles > (int64_t)cus * 8) return 4;
-    const int64_t per_cu = (tiles + cus - 1) / cus;
-    return per_cu < 1 ? 1 : (int)per_cu;
-}
-// SKIP = 1: halves of a tile without a neighbour at an offset are skipped together with their loads
-// (tests and branches in every step); SKIP = 0: a step is one straight line of code that treats
-// them as rows of zeros (about a sixth more loads, staging and multiplies on surface-like sets,
-// half the instructions).  The straight line wins while a CU has few wavefronts and the time is
-// one wavefront's walk over its offsets (14 k voxels: 15.2 against 19.2 us, 55 k: 20.8 against
-// 22.8), the skipping form once the CUs are full (110 k: 32.1 against 35.7, 261 k: 63.9 against 68.7).
-template <int DT, int K3, int FUSED, int SKIP>
-static int launch_direct64_as(int64_t tiles, int nwv, hipStream_t s, const uint16_t* feat, const uint4* wp, void* out,
-                              int out_f32, const MapSource& ms, const int64_t* counts, int64_t n_out_cap) {
-    auto fn = k_conv_direct64<DT, K3, FUSED, SKIP>;
-    const size_t per_wave = DIRECT_STAGE + DIRECT_LINES(K3) * TILE * sizeof(int32_t);
-    static bool allowed[MAX_DEVICES] = {};
-    if (int rc = allow_lds((const void*)fn, 8 * per_wave, allowed)) return rc;
-    SC_LAUNCH(KID_CONV_MFMA, fn, dim3(xcd_grid((tiles + nwv - 1) / nwv)), dim3(64 * nwv), nwv * per_wave, s, feat, wp, out,
-              out_f32, ms, counts, n_out_cap);
-    return SC_OK;
-}
-template <int DT, int K3, int FUSED>
-static int launch_direct64(int64_t tiles, hipStream_t s, const uint16_t* feat, const uint4* wp, void* out, int out_f32,
-                           const MapSource& ms, const int64_t* counts, int64_t n_out_cap) {
-    const int cus = compute_units(), nwv = direct_tiles_per_workgroup(tiles, cus);
-    if (tiles <= (int64_t)cus * 4)
-        return launch_direct64_as<DT, K3, FUSED, 0>(tiles, nwv, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
-    return launch_direct64_as<DT, K3, FUSED, 1>(tiles, nwv, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
-}
-
 // Up-sampling straight from the strided layer's map: shapes with a dedicated kernel.
 template <int DT>
 static int launch_up(int K3, int C_in, int C_out, int64_t tiles, hipStream_t s, const uint16_t* feat, const uint4* wp,
@@ -1032,19 +619,13 @@ static int launch_up(int K3, int C_in, int C_out, int64_t tiles, hipStream_t s, 
 template <int DT, int FUSED>
 static int launch_streamed(int K3, int C_in, int C_out, int64_t tiles, hipStream_t s, const uint16_t* feat,
                            const uint4* wp, void* out, int out_f32, const MapSource& ms, const int64_t* counts,
-                           int64_t n_out_cap, bool feat_small, bool* handled) {
+                           int64_t n_out_cap, bool* handled) {
     *handled = true;
 #define SC_STREAM(K3V, KSV, CBV, NWV, DV) \
     return launch_stream<DT, K3V, KSV, CBV, NWV, DV, FUSED>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
     if (K3 == 27 && C_in == 128 && C_out == 128) SC_STREAM(27, 4, 8, 8, 1);
     if (K3 == 27 && C_in == 32 && C_out == 64) SC_STREAM(27, 1, 4, 4, 3);
-    if constexpr (FUSED) {
-        // 64 input channels: the kernel with 32-bit buffer offsets where the feature array allows it
-        if (C_in == 64 && C_out == 64 && feat_small)
-            return launch_direct64<DT, 27, 1>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
-        if (C_in == 64 && C_out == 64) SC_STREAM(27, 2, 4, 4, 3);       // feature arrays of 4 GiB and more
-        if (C_in == 64 && C_out == 128) SC_STREAM(27, 2, 8, 4, 2);
-    } else {
+    if constexpr (!FUSED) {
         if (K3 == 8 && C_in == 128 && C_out == 128) SC_STREAM(8, 4, 8, 8, 1);
     }
 #undef SC_STREAM
@@ -1070,7 +651,7 @@ static int pack_weights(int K3, int C_in, int C_out, const void* d_weight, void*
 template <int FUSED>
 static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, hipStream_t s, const void* d_feat_in,
                       const void* d_weight, bool packed, void* d_workspace, void* d_feat_out,
-                      int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap, int64_t feat_rows) {
+                      int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const uint16_t* feat = (const uint16_t*)d_feat_in;
     bool handled = false;
     int rc;
@@ -1087,27 +668,25 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
                                                                         d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled);
         return rc;
     }
-    const bool stream_shape = (K3 == 27 && ((C_in == 64 && C_out == 64) || (C_in == 128 && C_out == 128) ||
-                                            (C_in == 32 && C_out == 64) || (C_in == 64 && C_out == 128))) ||
-                              (!FUSED && K3 == 8 && ((C_in == 64 && C_out == 128) || (C_in == 128 && C_out == 128)));
-    if (FUSED && !stream_shape) return SC_EINVAL;     // no fused kernel for this shape: use the three calls
+    const bool fused_gather = C_in == 64 && (C_out == 64 || C_out == 128), wide = C_in == 128 && C_out == 128;
+    if (FUSED && !fused_gather && !wide && !(C_in == 32 && C_out == 64)) return SC_EINVAL;     // no fused kernel for this shape: use the three calls
     const uint4* wp = (const uint4*)d_weight;
     if (!packed) {
         if (int prc = pack_weights(K3, C_in, C_out, d_weight, d_workspace, s)) return prc;
         wp = (const uint4*)d_workspace;
     }
-    // rows that a 32-bit byte offset can address, with room for the "no neighbour" offsets above them
-    const bool feat_small = feat_rows * (int64_t)C_in * 2 < 0xFFFFFF80ll;
-    // 128 -> 128 with the map: the general kernel up to 20 tiles per CU.  A workgroup of the streaming kernel is eight
+    // 128 -> 128: the general kernel up to 20 tiles per CU.  A workgroup of the streaming kernel is eight
     // tiles and takes ~75 us however few there are; full, it moves the weights once for them (us, general and
     // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
     // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
-    if (!FUSED && C_in == 128 && C_out == 128 && likely <= 20 * (int64_t)compute_units())
+    if ((FUSED && fused_gather) || (wide && likely <= 20 * (int64_t)compute_units())) {
+        if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
+    }
     rc = dtype_in == SC_F16 ? launch_streamed<SC_F16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
-                                                            n_out_ptr, n_out_cap, feat_small, &handled)
+                                                            n_out_ptr, n_out_cap, &handled)
                             : launch_streamed<SC_BF16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
-                                                             n_out_ptr, n_out_cap, feat_small, &handled);
+                                                             n_out_ptr, n_out_cap, &handled);
     if (handled || rc != SC_OK) return rc;
     if (FUSED) return SC_EINVAL;
     return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
@@ -1183,10 +762,8 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         if (d_workspace == nullptr || workspace_bytes < need) return SC_ECAP;
     }
     const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
-    // rows of the input feature array: the map's inputs, or (inverse layers) at most the strided map's bound
-    const int64_t feat_rows = n_map > bound ? n_map : bound;
     return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, s, d_feat_in, d_weight, packed, d_workspace,
-                         d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap, feat_rows);
+                         d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap);
 }
 
 extern "C" int sc_conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, void* d_feat_out,
@@ -1279,5 +856,5 @@ extern "C" int sc_conv_fwd_grid(const void* d_feat_in, const int32_t* d_coords, 
     const MapSource ms{nullptr, nullptr, (const int4*)d_coords, (const unsigned long long*)d_grid, GridDims{B, X, Y, Z}, epoch};
     if (!mfma_channels_ok(C_in, C_out)) return SC_EINVAL;
     return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, (hipStream_t)stream, d_feat_in, d_weight,
-                         false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n, n);
+                         false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n);
 }

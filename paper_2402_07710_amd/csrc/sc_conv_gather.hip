@@ -37,15 +37,22 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 // SKIP: groups without a neighbour are skipped (64 channels: 62 -> 50 us at that size).  32-channel rows
 // are too short for the test: such groups read the row of zeros, and the places of the last step that have no
 // offset are fetched like the others (of offset 0, rows of zeros) and not multiplied.
+// FUSED: there is no kernel map; the four wavefronts look up every fourth of the 27 offsets of the tile's rows in the
+// dense location table and leave entries and votes in LDS (7 KB).  Whole fused layers on 2 k / 53 k / 262 k voxels, against
+// the kernels that gave a wavefront 64 rows: 64 -> 64 21.2 / 33.6 / 95 -> 17.6 / 30.0 / 81 us, 64 -> 128 38.9 / 46.6 / 124 ->
+// 17.8 / 40.0 / 108, 128 -> 128 88.7 / 93.9 / 193 -> 22.4 / 55.3 / 160.
 // Measured, before (one wavefront per 16 rows, rows and weights loaded at their use) -> now: 14 k
 // voxels 256 -> 256 f16 480-555 -> 44 us; 53 k voxels K = 5 32 -> 32 bf16 116 -> 38 us; 53 k voxels 64 -> 64
 // fp32 118 -> 80 us.  Against the kernels that shared W[k] in LDS or gave a wavefront 64 rows: 64 -> 64 2 k /
 // 20 k / 110 k / 262 k voxels 14.8 / 15.8 / 29.4 / 58.2 -> 10.7 / 14.1 / 28.6 / 50.3 us; 64 -> 128 4 k / 110 k 27.4 /
 // 47.1 -> 11.7 / 40.7; 128 -> 128 4 k / 53 k / 262 k 70.8 / 75.5 / 157 -> 16.8 / 43 / 127.5.
-template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC>
+template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int FUSED>
 __global__ void __launch_bounds__(64 * NW, OCC)
-k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const uint32_t* __restrict__ gmask,
-              const int32_t* __restrict__ nbr, int K3, int mw, int CB, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
+k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
+              const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
+    static_assert(!FUSED || (DT != SC_F32 && NW == 4 && KS > 1), "fused look-ups: a quarter of the 27 offsets per wavefront");
+    const uint32_t* __restrict__ gmask = ms.gmask;
+    const int32_t* __restrict__ nbr = ms.nbr;
     constexpr bool F32 = DT == SC_F32;
     constexpr int KP = KS < SL ? KS : SL, PARTS = KS / KP;     // slices of an offset taken in one step, steps per offset
     constexpr int OPS = SL / KP;                       // offsets per step
@@ -57,19 +64,39 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
     constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
     constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
-    extern __shared__ __align__(16) char smem[];       // rows[2][STEP_BYTES] | weights[2][W_BYTES]
+    extern __shared__ __align__(16) char smem[];       // rows[2][STEP_BYTES] | weights[2][W_BYTES] | FUSED: entries[28][64], masks[4][4]
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, qq = lane >> 4;
     const int wr = wv / WC, cb0 = (int)blockIdx.y * (WC * CT) + (wv % WC) * CT;
     int64_t n_out = n_out_cap;
-    if (*n_out_ptr < n_out) n_out = *n_out_ptr;
+    if (!FUSED && *n_out_ptr < n_out) n_out = *n_out_ptr;
     const int64_t tile = xcd_run_of(blockIdx.x, (n_out + TILE - 1) / TILE);
     if (tile < 0) return;                              // the whole workgroup
 
     // the offsets the tile takes part in, in increasing order: number (times PARTS, plus
     // the part) and 4-bit pattern of groups.  The tile's mask words are held by the lanes of one register.
-    const uint32_t mvec = lane < 4 * mw ? gmask[tile * (4 * mw) + lane] : 0u;
+    uint32_t mvec = 0u;
+    int32_t* found = reinterpret_cast<int32_t*>(smem + 2 * STEP_BYTES);
+    if constexpr (FUSED) {
+        // lane = row; each wavefront looks up every fourth offset, its part of the masks is a vote
+        uint32_t* votes = reinterpret_cast<uint32_t*>(found + 28 * TILE);
+        int32_t part[7];
+        grid_neighbours_quarter<3>(ms, tile * TILE + lane, n_out, wv, part);
+        uint32_t vg[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 7; ++u) {
+            found[(wv + 4 * u) * TILE + lane] = part[u];
+            const uint64_t vote = __ballot(part[u] >= 0);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) vg[g] |= (((vote >> (16 * g)) & 0xffffull) != 0ull ? 1u : 0u) << (wv + 4 * u);
+        }
+        if (lane == 0) *reinterpret_cast<uint4*>(votes + 4 * wv) = make_uint4(vg[0], vg[1], vg[2], vg[3]);
+        __syncthreads();
+        if (lane < 4) mvec = votes[lane] | votes[4 + lane] | votes[8 + lane] | votes[12 + lane];
+    } else {
+        if (lane < 4 * mw) mvec = gmask[tile * (4 * mw) + lane];
+    }
     uint32_t mg[4] = {0u, 0u, 0u, 0u}, rest = 0u, pat_now = 0u;
     int wi = -1, k_now = -1;
     auto next_offset = [&](int& k, uint32_t& pat) __attribute__((always_inline)) {
@@ -110,7 +137,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         for (int i = 0; i < NI; ++i) grow[i] = (NW == 8 ? half : i) * 8 + (lane >> 3);
         gpiece = (lane & 7) ^ (lane >> 3);
     }
-    const int32_t* line = nbr + tile * (int64_t)K3 * TILE + gw * 16;
+    const int32_t* line = FUSED ? nullptr : nbr + tile * (int64_t)K3 * TILE + gw * 16;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const char* fbase = reinterpret_cast<const char*>(feat) + gpiece * 16;
     const char* zbase = reinterpret_cast<const char*>(g_zero_row) + gpiece * 16;
@@ -123,7 +150,10 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         for (int o = 0; o < OPS; ++o)
 #pragma unroll
             for (int i = 0; i < NI; ++i)
-                if (!SKIP || k[o] >= 0) ev[o][i] = line[(int64_t)(k[o] >= 0 ? k[o] / PARTS : 0) * TILE + grow[i]];
+                if (!SKIP || k[o] >= 0) {
+                    const int at = (k[o] >= 0 ? k[o] / PARTS : 0) * TILE + grow[i];
+                    ev[o][i] = FUSED ? found[gw * 16 + at] : line[at];
+                }
     };
     auto gather = [&](const int (&k)[OPS], const uint32_t (&p)[OPS], int buf) __attribute__((always_inline)) {
 #pragma unroll
@@ -284,30 +314,32 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     }
 }
 
-template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC>
+template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int FUSED>
 static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-    constexpr size_t lds = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0);
+    constexpr size_t lds = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (FUSED ? 28 * TILE * 4 + 64 : 0);
     static_assert(lds <= 65536, "within the LDS a kernel may use without asking");
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
-    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC>), dim3(xcd_run_grid(tiles), blocks_y),
-              dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms.gmask, ms.nbr, K3, mw, CB, n_out_ptr, n_out_cap);
+    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, FUSED>), dim3(xcd_run_grid(tiles), blocks_y),
+              dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB, n_out_ptr, n_out_cap);
     return SC_OK;
 }
 
 // O1, O2: wavefronts per SIMD with one and with two output blocks per wavefront
-template <int DT, int KS, int SL, int SKIP, int O1, int O2>
+template <int DT, int KS, int SL, int SKIP, int O1, int O2, int FUSED = 0>
 static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat, const void* wp,
                             void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
 #define SC_GATHER(NW, WR, CT, OCC) \
-    return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+    return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC, FUSED>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if constexpr (DT == SC_F32) {
         if (CB == 1) SC_GATHER(4, 4, 1, 2);
         if (CB == 2) SC_GATHER(8, 4, 1, 4);
         SC_GATHER(8, 2, 1, 4);
     } else {
-        if (CB == 1) SC_GATHER(4, 4, 1, O1);
-        if (CB == 2) SC_GATHER(4, 2, 1, O1);
+        if constexpr (!FUSED) {
+            if (CB == 1) SC_GATHER(4, 4, 1, O1);
+            if (CB == 2) SC_GATHER(4, 2, 1, O1);
+        }
         // two output blocks per wavefront halve how often a tile's rows are gathered; one, where that leaves CUs
         // idle or, up to 128 channels either way, with few wavefronts (us with one and with two blocks: 256 -> 128 at
         // 219 tiles 29.0, 34.2; 256 -> 256 49.1, 44.1; 64 -> 256 at 157 tiles 17.6, 19.3, at 250 22.9, 20.9; 128 -> 128 at
@@ -351,6 +383,21 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
         case 256: SC_GATHER_KS(8, 8, 1, 2, 2);
     }
 #undef SC_GATHER_KS
+    return SC_EINVAL;
+}
+
+// 3x3x3 layers that look their neighbours up in the dense table themselves: 64 and 128 channels, at least 64 out.
+int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp,
+                        void* out, int out_f32, const MapSource& ms, int64_t n) {
+    const int CB = C_out / 16;
+    if (CB < 4) return SC_EINVAL;
+#define SC_GATHER_FUSED(KS, SL, O1, O2)                                                                                                      \
+    return dtype_in == SC_F16                                                                                                                \
+               ? launch_gather_ks<SC_F16, KS, SL, 1, O1, O2, 1>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
+               : launch_gather_ks<SC_BF16, KS, SL, 1, O1, O2, 1>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+    if (C_in == 64) SC_GATHER_FUSED(2, 2, 6, 5);
+    if (C_in == 128) SC_GATHER_FUSED(4, 4, 4, 3);
+#undef SC_GATHER_FUSED
     return SC_EINVAL;
 }
 

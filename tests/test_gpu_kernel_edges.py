@@ -41,6 +41,27 @@ def test_general_kernel_64_and_128_channels(K, stride, C_in, C_out, n, dtype):
     check_layer(coords, K, stride, "subm" if stride == 1 else "strided", C_in, C_out, dtype, seed=n, threads=16)
 
 
+@pytest.mark.parametrize("C_in,C_out", [(64, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("n", [64, 129, 66000])
+def test_fused_general_kernel(C_in, C_out, n):
+    """Look-ups inside the general kernel: a workgroup's tile is full, has one row, and two output blocks per
+    wavefront; voxels on the faces of the box."""
+    say(f"fused general kernel {C_in}->{C_out} n={n}")
+    import oracle
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import TOL, rel_err, to_dev
+    side = 10 if n < 1000 else 50
+    coords = synth.uniform_cells(n, side, seed=n)
+    feat, weight = synth.features(n, C_in, "f16", 1), synth.weights(27, C_in, C_out, "f16", 1)
+    buf = sc.LayerBuffers(n, 3, 1, "subm", C_in, C_out, "f16", device="cuda:0", grid_dims=(1, side, side, side))
+    buf.feat_out.fill_(float("nan"))
+    buf.layer_fused(torch.from_numpy(coords).to("cuda:0"), to_dev(feat, "f16"), to_dev(weight, "f16"))
+    ref = oracle.conv(feat, weight, oracle.kmap(coords, 3, 1, "subm"), threads=16)
+    err = rel_err(buf.feat_out[:n].double().cpu().numpy(), ref)
+    assert err <= TOL["f16"], err
+
+
 @pytest.mark.parametrize("K,C_in,C_out,n", [(3, 16, 64, 17000), (3, 32, 32, 17000), (3, 64, 64, 1), (3, 64, 64, 65), (3, 64, 80, 1000),
                                             (3, 128, 16, 700), (3, 256, 48, 300), (5, 16, 16, 700), (5, 32, 32, 65)])
 def test_general_kernel_fp32(K, C_in, C_out, n):
