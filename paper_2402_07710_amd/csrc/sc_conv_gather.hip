@@ -43,7 +43,7 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 // 17.8 / 40.0 / 108, 128 -> 128 88.7 / 93.9 / 193 -> 22.4 / 55.3 / 160.
 // Measured, before (one wavefront per 16 rows, rows and weights loaded at their use) -> now: 14 k
 // voxels 256 -> 256 f16 480-555 -> 44 us; 53 k voxels K = 5 32 -> 32 bf16 116 -> 38 us; 53 k voxels 64 -> 64
-// fp32 118 -> 80 us.  Against the kernels that shared W[k] in LDS or gave a wavefront 64 rows: 64 -> 64 2 k /
+// fp32 118 -> 72 us.  Against the kernels that shared W[k] in LDS or gave a wavefront 64 rows: 64 -> 64 2 k /
 // 20 k / 110 k / 262 k voxels 14.8 / 15.8 / 29.4 / 58.2 -> 10.7 / 14.1 / 28.6 / 50.3 us; 64 -> 128 4 k / 110 k 27.4 /
 // 47.1 -> 11.7 / 40.7; 128 -> 128 4 k / 53 k / 262 k 70.8 / 75.5 / 157 -> 16.8 / 43 / 127.5.
 template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int FUSED>
@@ -332,9 +332,15 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
 #define SC_GATHER(NW, WR, CT, OCC) \
     return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC, FUSED>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if constexpr (DT == SC_F32) {
-        if (CB == 1) SC_GATHER(4, 4, 1, 2);
-        if (CB == 2) SC_GATHER(8, 4, 1, 4);
-        SC_GATHER(8, 2, 1, 4);
+        // 32 output channels per workgroup: gathering a tile's rows once more costs less than a workgroup of 64 channels
+        // that others wait for (a tile near the sensor is 27 offsets x 2,048 cycles of multiplies per SIMD; us with
+        // 64 and with 32: 64 -> 64 at 4 k / 53 k / 80 k voxels 28.8 / 82 / 105 and 20.3 / 72 / 99.5, 128 -> 128 at 4 k / 53 k
+        // 56 / 245 and 39 / 235).  16 where the CUs' last round is shorter then, up to four rounds of 32 (64 -> 64 at 4 k /
+        // 8 k / 12 k 18.0 / 25.5 / 27.6 us against 20.3 / 23.6 / 34.3 with 32).
+        const int64_t w = likely * CB;
+        const bool narrow = w <= 8 * (int64_t)cus && (w + cus - 1) / cus < 2 * ((w + 2 * cus - 1) / (2 * cus));
+        if (CB == 1 || narrow) SC_GATHER(4, 4, 1, 3);
+        SC_GATHER(8, 4, 1, 4);
     } else {
         if constexpr (!FUSED) {
             if (CB == 1) SC_GATHER(4, 4, 1, O1);
