@@ -449,6 +449,61 @@ k_conv_f32(const float* __restrict__ feat, const float* __restrict__ w, float* _
     }
 }
 
+// fp32 layers of at most four input channels (a network's first layer: coordinates, intensity), K = 2 or 3: the four
+// channels of an offset are exactly one 16x16x4 multiply, so the layer is K^3 multiplies per group and output block.
+// What it costs is latency, so a group's table lines, then all its rows (one 4-byte load per offset: the four
+// lanes of a row read 16 bytes), are in flight together, and the weights come from LDS.  Sums in the order
+// of k_conv_f32, whose table entry, row and weights were loaded at their use (whole layers 4 -> 32 on 3 k / 80 k sweep
+// voxels 25.2 / 51.3 -> 14.2 / 30.6 us).
+template <int K3, int CB>
+__global__ void __launch_bounds__(256)
+k_conv_f32_first(const float* __restrict__ feat, const float* __restrict__ w, float* __restrict__ out,
+                 const uint32_t* __restrict__ gmask, const int32_t* __restrict__ nbr, int C_in,
+                 const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
+    static_assert(K3 <= 32, "one mask word per group");
+    constexpr int C_out = 16 * CB;
+    __shared__ __align__(16) float w_s[K3 * 4 * C_out];              // [K3][4][C_out], zero past C_in
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int r = lane & 15, qq = lane >> 4;
+    int64_t n_out = *n_out_ptr;
+    if (n_out > n_out_cap) n_out = n_out_cap;
+    const int64_t tile = xcd_run_of(blockIdx.x, (n_out + TILE - 1) / TILE);
+    if (tile < 0) return;                                            // the whole workgroup
+    const int64_t row = tile * TILE + q * 16 + r;
+
+    const int32_t* line = nbr + tile * (int64_t)(K3 * TILE) + q * 16 + r;
+    int32_t e[K3];
+#pragma unroll
+    for (int k = 0; k < K3; ++k) e[k] = row < n_out ? line[k * TILE] : -1;
+    const uint32_t m = __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]);
+    for (int i = threadIdx.x; i < K3 * C_out; i += 256) {           // 16 bytes each
+        const int col = i % (C_out / 4), kc = i / (C_out / 4), ci = kc & 3;
+        reinterpret_cast<float4*>(w_s)[i] =
+            ci < C_in ? reinterpret_cast<const float4*>(w + ((kc >> 2) * C_in + ci) * C_out)[col] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    float f[K3];
+#pragma unroll
+    for (int k = 0; k < K3; ++k) f[k] = e[k] >= 0 && qq < C_in ? feat[(int64_t)e[k] * C_in + qq] : 0.f;
+    __syncthreads();
+    f32x4 acc[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < K3; ++k) {
+        if (m & (1u << k)) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w_s[(k * 4 + qq) * C_out + cb * 16 + r], f[k], acc[cb], 0, 0, 0);
+        }
+    }
+    if (row < n_out) {
+        float* orow = out + row * C_out;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+            *reinterpret_cast<float4*>(orow + cb * 16 + qq * 4) = make_float4(acc[cb][0], acc[cb][1], acc[cb][2], acc[cb][3]);
+    }
+}
+
 // fp32 layers with few channels (C_in = 16*CI16 <= 64, C_out = 16*CB <= 64, K^3 <= 32): the same
 // instruction, loads batched.  A lane reads 16 bytes (4 channels) of its row per 16-channel chunk
 // and feeds component j to the j-th of four multiplies, so input channel 16c + 4q + j sits at
@@ -738,6 +793,16 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
             const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
             return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, likely, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
                                  n_out_cap);
+        }
+        if (C_in <= 4) {
+#define SC_F32_FIRST(K3V, CBV)                                                                                                \
+    if (L.K3 == K3V && C_out == 16 * CBV) {                                                                                   \
+        SC_LAUNCH(KID_CONV_F32, (k_conv_f32_first<K3V, CBV>), dim3(xcd_run_grid(tiles)), dim3(256), 0, s, (const float*)d_feat_in, \
+                  (const float*)d_weight, (float*)d_feat_out, gmask, nbr, C_in, n_out_ptr, n_out_cap);                         \
+        return SC_OK;                                                                                                         \
+    }
+            SC_F32_FIRST(27, 1) SC_F32_FIRST(27, 2) SC_F32_FIRST(27, 4) SC_F32_FIRST(8, 1) SC_F32_FIRST(8, 2) SC_F32_FIRST(8, 4)
+#undef SC_F32_FIRST
         }
         if (L.K3 <= 32 && C_in % 16 == 0 && C_in <= 64 && C_out % 16 == 0 && C_out <= 64) {
 #define SC_F32_SMALL(CI, CBV)                                                                                         \

@@ -71,6 +71,15 @@ def test_general_kernel_fp32(K, C_in, C_out, n):
     check_layer(coords, K, 1, "subm", C_in, C_out, "f32", seed=n, threads=16)
 
 
+@pytest.mark.parametrize("K,stride,C_in,C_out", [(3, 1, 1, 16), (3, 1, 3, 64), (3, 1, 4, 32), (2, 2, 4, 16), (2, 2, 3, 32), (2, 2, 2, 64)])
+@pytest.mark.parametrize("n", [1, 64, 65, 3000])
+def test_first_layer_fp32(K, stride, C_in, C_out, n):
+    """At most four input channels: rows and weights short of four, tiles that are full and that have one row."""
+    say(f"first layer K={K} s={stride} {C_in}->{C_out} n={n}")
+    coords = synth.uniform_cells(n, 6 if n < 100 else 18, seed=C_in + n)
+    check_layer(coords, K, stride, "subm" if stride == 1 else "strided", C_in, C_out, "f32", seed=n)
+
+
 @pytest.mark.parametrize("K,stride", [(2, 2), (3, 2), (3, 3), (4, 2), (5, 5)])
 @pytest.mark.parametrize("n", [1, 256, 257, 3000])
 def test_strided_build_claims(K, stride, n):
