@@ -734,6 +734,10 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // tiles and takes ~75 us however few there are; full, it moves the weights once for them (us, general and
     // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
     // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
+    // 32 -> 64, K = 3, up to 1.5 tiles per CU: there the streaming kernel's walk over all offsets, four tiles in step, is the
+    // longer chain (2 k / 10 k / 53 k voxels: general 9.2 / 9.8 / 14.7 us, streaming 11.2 / 11.7 / 12.8).
+    if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && 2 * likely <= 3 * (int64_t)compute_units())
+        return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
     if ((FUSED && fused_gather) || (wide && likely <= 20 * (int64_t)compute_units())) {
         if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);

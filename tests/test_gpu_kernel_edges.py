@@ -28,7 +28,7 @@ def test_general_kernel_with_two_output_blocks_per_wavefront():
     check_layer(coords[:13000], 3, 1, "subm", 32, 256, "bf16", seed=1, threads=16)
 
 
-@pytest.mark.parametrize("K,stride,C_in,C_out", [(3, 1, 64, 64), (3, 1, 64, 128), (3, 1, 128, 128), (2, 2, 64, 128), (2, 2, 128, 128), (3, 2, 64, 64)])
+@pytest.mark.parametrize("K,stride,C_in,C_out", [(3, 1, 32, 64), (3, 1, 64, 64), (3, 1, 64, 128), (3, 1, 128, 128), (2, 2, 64, 128), (2, 2, 128, 128), (3, 2, 64, 64)])
 @pytest.mark.parametrize("n,dtype", [(1, "bf16"), (64, "f16"), (129, "bf16"), (66000, "f16")])
 def test_general_kernel_64_and_128_channels(K, stride, C_in, C_out, n, dtype):
     """One row, whole tiles, a tile of one row, and enough tiles for two output blocks per wavefront."""
