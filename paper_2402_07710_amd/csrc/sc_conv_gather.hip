@@ -8,10 +8,10 @@ namespace sc {
 static __device__ __align__(512) uint4 g_zero_row[32];
 
 // 16 bytes per lane from global memory straight into LDS: lane l's land at byte lds + 16 l.  The
-// instruction takes its LDS address from M0, which nothing else on this target uses.  Inline
+// instruction takes its LDS address from M0 and needs one wait state after a write of it (s_nop).  Inline
 // assembly, because the compiler would put a wait for all loads in front of every later LDS read.
 __device__ inline void load_to_lds(const void* src, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
 }
 
 // One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
