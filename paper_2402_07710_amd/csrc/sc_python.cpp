@@ -113,6 +113,10 @@ void* stream(PyObject* o) {
     if (p == nullptr && PyErr_Occurred()) throw PyFailure{};
     return p;
 }
+// [rows, channels] and no other number of dimensions: a row's channels are contiguous
+void check_matrix(PyObject* o, const char* what) {
+    if (tensor(o).dim() != 2) fail(PyExc_ValueError, what);
+}
 bool same_dtype(PyObject* a, PyObject* b) { return tensor(a).scalar_type() == tensor(b).scalar_type(); }
 // weight must be [K^3, C_in, C_out] in the feature type
 bool weight_fits(PyObject* weight, PyObject* feat, int K, int64_t C_in, int64_t C_out) {
@@ -153,6 +157,8 @@ int kmap_build_grid(Args a) {            // coords, grid, dims, epoch, K, kmap, 
 }
 int conv_fwd(Args a) {                   // feat_in, n_map, weight, feat_out, kmap, counts, K, stride, mode, workspace, stream
     const int K = small_int(a[6]);
+    check_matrix(a[0], "feat_in must be [rows, C_in]");
+    check_matrix(a[3], "feat_out must be [rows, C_out]");
     const int64_t n_in = size(a[0], 0), C_in = size(a[0], 1), n_out_cap = size(a[3], 0), C_out = size(a[3], 1);
     if (!weight_fits(a[2], a[0], K, C_in, C_out)) fail(PyExc_ValueError, "weight must be [K^3, C_in, C_out] in the feature dtype");
     return lib.conv_fwd(ptr(a[0]), a[1] == Py_None ? n_in : integer(a[1]), ptr(a[2]), ptr(a[3]), n_out_cap, ptr(a[4]), nbytes(a[4]),
@@ -160,6 +166,8 @@ int conv_fwd(Args a) {                   // feat_in, n_map, weight, feat_out, km
                         ptr(a[9]), nbytes(a[9]), stream(a[10]));
 }
 int conv_fwd_packed(Args a) {            // feat_in, n_map, packed, C_out, feat_out, kmap, counts, K, stride, mode, stream
+    check_matrix(a[0], "feat_in must be [rows, C_in]");
+    check_matrix(a[4], "feat_out must be [rows, C_out]");
     const int64_t n_in = size(a[0], 0), C_in = size(a[0], 1), n_out_cap = size(a[4], 0), C_out = integer(a[3]);
     if (size(a[4], 1) != C_out) fail(PyExc_ValueError, "feat_out must have C_out columns");
     return lib.conv_fwd_packed(ptr(a[0]), a[1] == Py_None ? n_in : integer(a[1]), ptr(a[2]), ptr(a[4]), n_out_cap, ptr(a[5]),
@@ -169,7 +177,7 @@ int conv_fwd_packed(Args a) {            // feat_in, n_map, packed, C_out, feat_
 int conv_up_fwd(Args a) {                // feat_coarse, n_map, weight, feat_fine, kmap, counts, K, stream
     const int K = small_int(a[6]);
     const int64_t n_map = integer(a[1]), C_in = size(a[2], 1), C_out = size(a[2], 2);
-    if (!weight_fits(a[2], a[0], K, C_in, C_out) || size(a[0], 1) != C_in || tensor(a[3]).dim() != 2 || size(a[3], 0) != n_map ||
+    if (!weight_fits(a[2], a[0], K, C_in, C_out) || tensor(a[0]).dim() != 2 || size(a[0], 1) != C_in || tensor(a[3]).dim() != 2 || size(a[3], 0) != n_map ||
         size(a[3], 1) != C_out)
         return SC_EINVAL;
     return lib.conv_up_fwd(ptr(a[0]), n_map, ptr(a[2]), ptr(a[3]), ptr(a[4]), nbytes(a[4]), (const sc_counts*)ptr(a[5]), K, (int)C_in,
