@@ -126,33 +126,44 @@ bool weight_fits(PyObject* weight, PyObject* feat, int K, int64_t C_in, int64_t 
 
 using Args = PyObject* const*;
 
+// The library's call with the interpreter lock released: a launch may block (full queue, first load of a code
+// object) and other Python threads go on meanwhile.  The arguments have been read under the lock, and the
+// caller's frame holds the tensors they point into.
+template <class F, class... A>
+int unlocked(F function, A... arguments) {
+    PyThreadState* const thread = PyEval_SaveThread();
+    const int rc = function(arguments...);
+    PyEval_RestoreThread(thread);
+    return rc;
+}
+
 int hash_build(Args a) {                 // coords, table, counts, stream
-    return lib.hash_build((const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), (sc_counts*)ptr(a[2]), stream(a[3]));
+    return unlocked(lib.hash_build, (const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), (sc_counts*)ptr(a[2]), stream(a[3]));
 }
 int hash_rebuild(Args a) {               // coords, table, epoch, counts, stream
-    return lib.hash_rebuild((const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), small_int(a[2]), (sc_counts*)ptr(a[3]),
+    return unlocked(lib.hash_rebuild, (const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), small_int(a[2]), (sc_counts*)ptr(a[3]),
                             stream(a[4]));
 }
 int kmap_build(Args a) {                 // coords, table, K, stride, mode, out_coords, kmap, scratch, counts, stream
-    return lib.kmap_build((const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), small_int(a[2]), small_int(a[3]), small_int(a[4]),
+    return unlocked(lib.kmap_build, (const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), small_int(a[2]), small_int(a[3]), small_int(a[4]),
                           (int32_t*)ptr(a[5]), ptr(a[6]), nbytes(a[6]), ptr(a[7]), nbytes(a[7]), (sc_counts*)ptr(a[8]), stream(a[9]));
 }
 int kmap_build_noalloc(Args a) {         // coords, table, K, stride, mode, out_coords, kmap, counts, stream
-    return lib.kmap_build_noalloc((const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), small_int(a[2]), small_int(a[3]), small_int(a[4]),
+    return unlocked(lib.kmap_build_noalloc, (const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), small_int(a[2]), small_int(a[3]), small_int(a[4]),
                                   (int32_t*)ptr(a[5]), ptr(a[6]), nbytes(a[6]), (sc_counts*)ptr(a[7]), stream(a[8]));
 }
 int kmap_transpose(Args a) {             // kmap, n, K, stride, counts, kmap_inv, stream
-    return lib.kmap_transpose(ptr(a[0]), integer(a[1]), small_int(a[2]), small_int(a[3]), (const sc_counts*)ptr(a[4]), ptr(a[5]),
+    return unlocked(lib.kmap_transpose, ptr(a[0]), integer(a[1]), small_int(a[2]), small_int(a[3]), (const sc_counts*)ptr(a[4]), ptr(a[5]),
                               nbytes(a[5]), stream(a[6]));
 }
 int grid_build(Args a) {                 // coords, grid, dims, epoch, counts, stream
     const Dims d = dims(a[2]);
-    return lib.grid_build((const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), d.B, d.X, d.Y, d.Z, epoch32(a[3]),
+    return unlocked(lib.grid_build, (const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), d.B, d.X, d.Y, d.Z, epoch32(a[3]),
                           (sc_counts*)ptr(a[4]), stream(a[5]));
 }
 int kmap_build_grid(Args a) {            // coords, grid, dims, epoch, K, kmap, counts, stream
     const Dims d = dims(a[2]);
-    return lib.kmap_build_grid((const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), d.B, d.X, d.Y, d.Z, epoch32(a[3]),
+    return unlocked(lib.kmap_build_grid, (const int32_t*)ptr(a[0]), size(a[0], 0), ptr(a[1]), nbytes(a[1]), d.B, d.X, d.Y, d.Z, epoch32(a[3]),
                                small_int(a[4]), ptr(a[5]), nbytes(a[5]), (sc_counts*)ptr(a[6]), stream(a[7]));
 }
 int conv_fwd(Args a) {                   // feat_in, n_map, weight, feat_out, kmap, counts, K, stride, mode, workspace, stream
@@ -161,7 +172,7 @@ int conv_fwd(Args a) {                   // feat_in, n_map, weight, feat_out, km
     check_matrix(a[3], "feat_out must be [rows, C_out]");
     const int64_t n_in = size(a[0], 0), C_in = size(a[0], 1), n_out_cap = size(a[3], 0), C_out = size(a[3], 1);
     if (!weight_fits(a[2], a[0], K, C_in, C_out)) fail(PyExc_ValueError, "weight must be [K^3, C_in, C_out] in the feature dtype");
-    return lib.conv_fwd(ptr(a[0]), a[1] == Py_None ? n_in : integer(a[1]), ptr(a[2]), ptr(a[3]), n_out_cap, ptr(a[4]), nbytes(a[4]),
+    return unlocked(lib.conv_fwd, ptr(a[0]), a[1] == Py_None ? n_in : integer(a[1]), ptr(a[2]), ptr(a[3]), n_out_cap, ptr(a[4]), nbytes(a[4]),
                         (const sc_counts*)ptr(a[5]), K, small_int(a[7]), small_int(a[8]), (int)C_in, (int)C_out, dtype(a[0]), dtype(a[3]),
                         ptr(a[9]), nbytes(a[9]), stream(a[10]));
 }
@@ -170,7 +181,7 @@ int conv_fwd_packed(Args a) {            // feat_in, n_map, packed, C_out, feat_
     check_matrix(a[4], "feat_out must be [rows, C_out]");
     const int64_t n_in = size(a[0], 0), C_in = size(a[0], 1), n_out_cap = size(a[4], 0), C_out = integer(a[3]);
     if (size(a[4], 1) != C_out) fail(PyExc_ValueError, "feat_out must have C_out columns");
-    return lib.conv_fwd_packed(ptr(a[0]), a[1] == Py_None ? n_in : integer(a[1]), ptr(a[2]), ptr(a[4]), n_out_cap, ptr(a[5]),
+    return unlocked(lib.conv_fwd_packed, ptr(a[0]), a[1] == Py_None ? n_in : integer(a[1]), ptr(a[2]), ptr(a[4]), n_out_cap, ptr(a[5]),
                                nbytes(a[5]), (const sc_counts*)ptr(a[6]), small_int(a[7]), small_int(a[8]), small_int(a[9]), (int)C_in,
                                (int)C_out, dtype(a[0]), dtype(a[4]), stream(a[10]));
 }
@@ -180,12 +191,12 @@ int conv_up_fwd(Args a) {                // feat_coarse, n_map, weight, feat_fin
     if (!weight_fits(a[2], a[0], K, C_in, C_out) || tensor(a[0]).dim() != 2 || size(a[0], 1) != C_in || tensor(a[3]).dim() != 2 || size(a[3], 0) != n_map ||
         size(a[3], 1) != C_out)
         return SC_EINVAL;
-    return lib.conv_up_fwd(ptr(a[0]), n_map, ptr(a[2]), ptr(a[3]), ptr(a[4]), nbytes(a[4]), (const sc_counts*)ptr(a[5]), K, (int)C_in,
+    return unlocked(lib.conv_up_fwd, ptr(a[0]), n_map, ptr(a[2]), ptr(a[3]), ptr(a[4]), nbytes(a[4]), (const sc_counts*)ptr(a[5]), K, (int)C_in,
                            (int)C_out, dtype(a[0]), dtype(a[3]), stream(a[7]));
 }
 int conv_fwd_grid(Args a) {              // feat_in, coords, grid, dims, epoch, weight, feat_out, K, workspace, stream
     const Dims d = dims(a[3]);
-    return lib.conv_fwd_grid(ptr(a[0]), (const int32_t*)ptr(a[1]), size(a[1], 0), ptr(a[2]), nbytes(a[2]), d.B, d.X, d.Y, d.Z,
+    return unlocked(lib.conv_fwd_grid, ptr(a[0]), (const int32_t*)ptr(a[1]), size(a[1], 0), ptr(a[2]), nbytes(a[2]), d.B, d.X, d.Y, d.Z,
                              epoch32(a[4]), ptr(a[5]), ptr(a[6]), small_int(a[7]), (int)size(a[5], 1), (int)size(a[5], 2), dtype(a[0]),
                              dtype(a[6]), ptr(a[8]), nbytes(a[8]), stream(a[9]));
 }
