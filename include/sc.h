@@ -265,6 +265,9 @@ size_t sc_conv_workspace_bytes(int K, int C_in, int C_out, int dtype_in);
  *   dtype_out   SC_F32 or the same as dtype_in (one round-to-nearest-even at the end)
  *   channels    SC_F32: any C_in >= 1, 1 <= C_out <= 256.  SC_F16 / SC_BF16: C_in one of 32, 64,
  *               128, 256 and C_out a multiple of 16, 16 <= C_out <= 256.
+ *   Not finite: an infinity or NaN in W[k] reaches the output rows that have a pair at offset k and may
+ *               reach other rows of the same 16 (rows 16g .. 16g + 15) if one of them has; no row outside.
+ *               One in a feature row reaches the rows it is paired with.
  *   d_workspace workspace_bytes >= sc_conv_workspace_bytes(...); contents undefined afterwards */
 int sc_conv_fwd(const void* d_feat_in, int64_t n_map,
                 const void* d_weight,

@@ -34,9 +34,12 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 //    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
 //  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
 //    65 us with 2, 51.5 with 4, 50 with 6).  That also decides the step length, 16 KB of LDS for 64 channels.
-// SKIP: groups without a neighbour are skipped (64 channels: 62 -> 50 us at that size).  32-channel rows
-// are too short for the test: such groups read the row of zeros, and the places of the last step that have no
-// offset are fetched like the others (of offset 0, rows of zeros) and not multiplied.
+// A group without a neighbour at an offset is not multiplied by its weights (a weight that is not finite stays out
+// of its sums).  SKIP: nor is it gathered and read (64 channels: 62 -> 50 us at that size).  32-channel rows are too short
+// for that: such groups read the row of zeros, and the places of the last step that have no offset are fetched
+// like the others (of offset 0, rows of zeros); the operands of an offset are read together, then the
+// multiplies tested (whole layers K = 5 32 -> 32 on 2 k / 53 k voxels and 32 -> 64 on 110 k: 30.0 / 63.4 / 116 us; with SKIP
+// 31.0 / 64.5 / 121, with zeroed weights instead of the test 30.3 / 64.2 / 120, all of a step's operands first 29.4 / 63.2 / 120).
 // FUSED: there is no kernel map; the four wavefronts look up every fourth of the 27 offsets of the tile's rows in the
 // dense location table and leave entries and votes in LDS (7 KB).  Whole fused layers on 2 k / 53 k / 262 k voxels, against
 // the kernels that gave a wavefront 64 rows: 64 -> 64 21.2 / 33.6 / 95 -> 17.6 / 30.0 / 81 us, 64 -> 128 38.9 / 46.6 / 124 ->
@@ -234,19 +237,25 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
                         for (int j = 0; j < 4; ++j) af[ks][ct][j] = w[j * (4 * NC)];
                     }
             }
+            uint4 b[RG][KP];
+            auto operands = [&](int g) __attribute__((always_inline)) {
+                const char* rows = smem + buf * STEP_BYTES + o * CH * CHB + (wr * RG + g) * (CHB / 4);
+#pragma unroll
+                for (int ks = 0; ks < KP; ++ks) b[g][ks] = *reinterpret_cast<const uint4*>(rows + (ks >> 1) * CHB + ((ks & 1) ? op1 : op0));
+            };
+            if constexpr (!SKIP) {
+#pragma unroll
+                for (int g = 0; g < RG; ++g) operands(g);
+            }
 #pragma unroll
             for (int g = 0; g < RG; ++g) {
-                const int gg = wr * RG + g;
-                if (SKIP && ((p[o] >> gg) & 1u) == 0u) continue;
-                const char* rows = smem + buf * STEP_BYTES + o * CH * CHB + gg * (CHB / 4);
-                uint4 b[KP];
-#pragma unroll
-                for (int ks = 0; ks < KP; ++ks) b[ks] = *reinterpret_cast<const uint4*>(rows + (ks >> 1) * CHB + ((ks & 1) ? op1 : op0));
+                if (((p[o] >> (wr * RG + g)) & 1u) == 0u) continue;
+                if constexpr (SKIP) operands(g);
 #pragma unroll
                 for (int ks = 0; ks < KP; ++ks) {
                     if constexpr (F32) {
                         // component j of both operands: input channel 16 ks + 4 qq + j at position qq of multiply j
-                        const f32x4 fb = __builtin_bit_cast(f32x4, b[ks]);
+                        const f32x4 fb = __builtin_bit_cast(f32x4, b[g][ks]);
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -255,7 +264,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
                     } else {
 #pragma unroll
                         for (int ct = 0; ct < CT; ++ct)
-                            acc[g][ct] = mfma16x16x32<DT>(__builtin_bit_cast(uint4, a[o * KP + ks][ct]), b[ks], acc[g][ct]);
+                            acc[g][ct] = mfma16x16x32<DT>(__builtin_bit_cast(uint4, a[o * KP + ks][ct]), b[g][ks], acc[g][ct]);
                     }
                 }
             }

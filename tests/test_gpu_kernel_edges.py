@@ -134,3 +134,36 @@ def test_submanifold_map_lookups(K, n):
         assert_maps_equal(exported_map(buf, h), coords, ref, exact_order=True)
         if n > 3000:
             break
+
+
+@pytest.mark.parametrize("K,C_in,C_out,dtype", [(5, 32, 32, "f16"), (5, 32, 48, "bf16"), (7, 32, 32, "f16"), (3, 32, 16, "f16"), (3, 32, 64, "f16"),
+                                                (3, 32, 144, "bf16"), (3, 32, 32, "f16"), (3, 64, 64, "f16"), (3, 128, 128, "bf16"),
+                                                (3, 256, 32, "f16"), (3, 32, 64, "f32"), (3, 16, 16, "f32"), (3, 4, 16, "f32")])
+def test_non_finite_weights_stay_in_their_groups(K, C_in, C_out, dtype):
+    """An infinite W[k] reaches the 16-row groups that have a neighbour at k, and no others: the same
+    bits there as without it, also in tiles whose other groups do have one."""
+    say(f"non-finite weights K={K} {C_in}->{C_out} {dtype}")
+    import oracle
+    import torch
+    from tests.test_gpu_parity import run_layer
+    n, K3 = 500, K ** 3
+    coords = synth.uniform_cells(n, 30, seed=K)
+    km = oracle.kmap(coords, K, 1, "subm")
+    feat, weight = synth.features(n, C_in, dtype, 2), synth.weights(K3, C_in, C_out, dtype, 2)
+    plain = run_layer(coords, feat, weight, K, 1, "subm", dtype)[3]
+    start = km["offset_start"]
+    has = np.zeros((K3, (n + 15) // 16), dtype=bool)           # [offset, group]
+    for k in range(K3):
+        has[k, km["pair_out"][start[k]:start[k + 1]] // 16] = True
+    mixed = [k for k in range(K3) if has[k].any() and not has[k].all()]
+    for k in mixed[::max(1, len(mixed) // 4)]:
+        for value in (np.inf, np.nan):
+            spoiled = weight.copy()
+            spoiled[k] = value
+            got = run_layer(coords, feat, spoiled, K, 1, "subm", dtype)[3]
+            outside = ~has[k][np.arange(n) // 16]
+            tiles = np.arange(n)[outside] // 64
+            assert any(has[k][4 * t:4 * t + 4].any() for t in tiles), "a tile with and without"
+            assert np.array_equal(got[outside], plain[outside]), k
+            pair_rows = np.unique(km["pair_out"][start[k]:start[k + 1]])
+            assert not np.isfinite(got[pair_rows]).all(axis=1).any()
