@@ -235,7 +235,8 @@ int sc_kmap_build_grid(const int32_t* d_coords, int64_t n,
  * coarse set and its place in the kernel, and receives parent_features . W[place].  The pairs are
  * those of the strided layer that made the coarse set, with input and output swapped, so the map
  * is made from that layer's map:
- *   d_kmap, n, K, stride   the strided layer's map and the arguments it was built with
+ *   d_kmap, n, K, stride   the strided layer's map and the arguments it was built with; K == stride,
+ *                          2 <= K <= 4 (SC_EINVAL otherwise)
  *   d_counts               the counts block of that build (n_out is read on the device)
  *   d_kmap_inv             receives the inverse map, kmap_inv_bytes >= sc_kmap_bytes(n, K,
  *                          stride, SC_INVERSE); must not alias d_kmap

@@ -954,7 +954,7 @@ extern "C" int sc_kmap_build_noalloc(const int32_t* d_coords, int64_t n, const v
 
 extern "C" int sc_kmap_transpose(const void* d_kmap, int64_t n, int K, int stride, const sc_counts* d_counts,
                                  void* d_kmap_inv, size_t kmap_inv_bytes, void* stream) {
-    if (!kmap_args_ok(n, K, stride, SC_STRIDED)) return SC_EINVAL;
+    if (!kmap_args_ok(n, K, stride, SC_INVERSE)) return SC_EINVAL;
     if (d_kmap == nullptr || d_kmap_inv == nullptr || d_counts == nullptr || d_kmap == d_kmap_inv) return SC_EINVAL;
     if (!aligned16(d_kmap) || !aligned16(d_kmap_inv) || !aligned16(d_counts)) return SC_EINVAL;
     if (kmap_inv_bytes < sc_kmap_bytes(n, K, stride, SC_INVERSE)) return SC_ECAP;

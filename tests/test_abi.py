@@ -121,6 +121,17 @@ def test_host_side_argument_errors(lib):
     assert binding.strerror(12345) == "unknown status"
 
 
+def test_inverse_maps_are_for_equal_kernel_and_stride_up_to_four(lib):
+    """sc_kmap_transpose packs an offset into 6 bits and takes both maps to have one layout: K == stride <= 4."""
+    for K, stride in ((5, 5), (7, 7), (3, 2), (2, 1), (4, 3), (1, 1)):
+        assert lib.sc_kmap_bytes(10, K, stride, binding.SC_INVERSE) == 0
+        for n in (0, 10):
+            assert lib.sc_kmap_transpose(16, n, K, stride, 32, 48, 1 << 20, None) == binding.SC_EINVAL, (K, stride, n)
+    for K in (2, 3, 4):
+        need = lib.sc_kmap_bytes(10, K, K, binding.SC_INVERSE)
+        assert lib.sc_kmap_transpose(16, 10, K, K, 32, 48, need - 1, None) == binding.SC_ECAP
+
+
 def _insert_probe_lengths(lib, coords, n):
     """Simulate the table build on the host with the library's own probe sequence: number of
     attempts every key needs until it finds a free slot."""
