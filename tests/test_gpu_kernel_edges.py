@@ -167,3 +167,60 @@ def test_non_finite_weights_stay_in_their_groups(K, C_in, C_out, dtype):
             assert np.array_equal(got[outside], plain[outside]), k
             pair_rows = np.unique(km["pair_out"][start[k]:start[k + 1]])
             assert not np.isfinite(got[pair_rows]).all(axis=1).any()
+
+
+@pytest.mark.parametrize("K", [2, 3, 4])
+@pytest.mark.parametrize("stale", ["inverse map", "zeros", "ones", "words of the rows", "words of other rows"])
+def test_inverse_map_of_rows_without_a_parent(K, stale):
+    """Rows outside the coordinate domain have no parent, so their place in the inverse map's buffer is never
+    written with one: whatever an earlier use left there must not become a pair."""
+    say(f"inverse map, rows without a parent, K={K}, buffer holds {stale}")
+    import oracle
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import TOL, rel_err, to_dev
+    n, K3 = 1000, K ** 3
+    coords = synth.uniform_cells(n, 30, seed=K)
+    out_of_domain = np.arange(n) % 7 == 3
+    out_of_domain[640:704] = True                              # a whole tile of the fine rows
+    broken = coords.copy()
+    broken[out_of_domain, 1] = sc.SC_COORD_MAX + 1
+
+    def inverse(rows, into):
+        buf = sc.LayerBuffers(n, K, K, "strided", 32, 32, "f16", device="cuda:0")
+        buf.kmap_build(torch.from_numpy(rows).to("cuda:0"), standalone=True)
+        h = buf.read_counts(check=False)
+        sc.sc_kmap_transpose(buf.kmap, n, K, K, buf.counts, into)
+        return buf, h
+    tiles, words = (n + 63) // 64, 4 * ((K3 + 31) // 32)
+    first_line = (256 + tiles * words * 4 + 255) // 256 * 256 // 4          # int32 index of row 0's entry at offset 0
+    into = torch.zeros(sc.sc_kmap_bytes(n, K, K, "inverse"), dtype=torch.uint8, device="cuda:0")
+    if stale == "ones":
+        into.fill_(255)
+    elif stale != "zeros":
+        _, h = inverse(coords, into)
+        assert h.status == 0
+        if stale != "inverse map":                             # (parent, offset) of every row as the first kernel writes it
+            km = oracle.kmap(coords, K, K, "strided")
+            word = np.zeros(n, dtype=np.int32)
+            word[km["pair_in"]] = km["pair_out"] * 64 + np.repeat(np.arange(K3), np.diff(km["offset_start"]))
+            if stale == "words of other rows":
+                word = np.roll(word, 1)
+            at = first_line + np.arange(n) // 64 * (K3 * 64) + np.arange(n) % 64
+            into.view(torch.int32)[torch.from_numpy(at).to("cuda:0")] = torch.from_numpy(word).to("cuda:0")
+    buf, h = inverse(broken, into)
+    assert h.status == sc.SC_ERANGE
+    kept = np.flatnonzero(~out_of_domain)
+    ref = oracle.transpose_map(oracle.kmap(coords[kept], K, K, "strided"))
+    h = sc.sc_counts_read(buf.counts, into, n, K, K, "inverse", check=False)
+    assert h.n_pairs == len(kept) and list(h.per_offset[:K3]) == list(np.diff(ref["offset_start"]))
+    pin, pout, _ = sc.sc_kmap_export(into, n, K, K, "inverse", h)
+    assert np.array_equal(pin.cpu().numpy(), ref["pair_in"]) and np.array_equal(pout.cpu().numpy(), kept[ref["pair_out"]])
+    # and the group masks: rows without a parent become zero, the others their products
+    feat, weight = synth.features(int(ref["n_in"]), 32, "f16", K), synth.weights(K3, 32, 32, "f16", K)
+    out = torch.full((n, 32), float("nan"), dtype=torch.float16, device="cuda:0")
+    ws = torch.empty(sc.sc_conv_workspace_bytes(K, 32, 32, "f16"), dtype=torch.uint8, device="cuda:0")
+    sc.sc_conv_fwd(to_dev(feat, "f16"), to_dev(weight, "f16"), out, into, buf.counts, K, K, "inverse", ws, n_map=n)
+    got = out.double().cpu().numpy()
+    assert np.all(got[out_of_domain] == 0)
+    assert rel_err(got[kept], oracle.conv(feat, weight, ref, threads=8)) <= TOL["f16"]
