@@ -735,7 +735,8 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
     // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
     // 32 -> 64, K = 3, up to 1.5 tiles per CU: there the streaming kernel's walk over all offsets, four tiles in step, is the
-    // longer chain (2 k / 10 k / 53 k voxels: general 9.2 / 9.8 / 14.7 us, streaming 11.2 / 11.7 / 12.8).
+    // longer chain (2 k / 10 k / 53 k voxels: general 9.2 / 9.8 / 14.7 us, streaming 11.2 / 11.7 / 12.8).  Not the fused
+    // form: the general kernel has no fused instantiation for 32 channels, so that one takes the walk at every size.
     if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && 2 * likely <= 3 * (int64_t)compute_units())
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
     if ((FUSED && fused_gather) || (wide && likely <= 20 * (int64_t)compute_units())) {
@@ -790,10 +791,20 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
 
     if (dtype_in == SC_F32) {           // fp32 weights are used as they are: packed == raw
         if (C_out > 256) return SC_EINVAL;
-        // the general kernel where a layer has enough work for it: 64 -> 64 at 53 k voxels 118 -> 80 us, 32 -> 32
-        // 38 -> 31; below that its steps are mostly latency (8 k voxels: 16 -> 16 5.7 and 9.2 us, 32 -> 32 8.4 and 9.7)
+        // The general kernel where a layer has enough work for it; its steps are mostly latency below that.  us of the convolution,
+        // the kernel of small layers (with an instantiation for 32 -> 64 and more) and the general one, on sweeps (K = 3), sets of
+        // random cells (few neighbours) and strided layers (K = 3, stride 2, rows of the input):
+        //   64 -> 64  sweeps 500 20.0 / 11.7, 4 k 43 / 18, 53 k 121 / 73; random 300 12.3 / 9.2, 16 k 17.6 / 18.7; strided 2 k 33 / 31, 53 k 160 / 114
+        //   32 -> 64  sweeps 500 11.6 / 8.6, 16 k 26.5 / 25.2, 53 k 66 / 45; random 300 7.7 / 6.8, 16 k 10.7 / 12.7
+        //   64 -> 32  sweeps 500 12.2 / 11.6, 8 k 27.8 / 18.3, 53 k 69 / 46; random 300 7.7 / 9.1, 16 k 10.7 / 13.5
+        //   32 -> 32  sweeps 500 7.7 / 8.5, 8 k 16.5 / 13.0, 24 k 25.6 / 19.4; random 2 k 5.8 / 6.9, 16 k 7.0 / 9.0; strided 8 k 15.6 / 12.8, 16 k 15.9 / 15.3
+        //   16 -> 64  sweeps 4 k 14.8 / 10.0, 16 k 16.3 / 19.3, 24 k 24.7 / 22.8; random 16 k 7.2 / 12.2; strided 8 k 15.3 / 16.9, 16 k 15.8 / 21.0, 24 k 25.1 / 24.0
+        //   64 -> 16  sweeps 8 k 18.4 / 18.0, 24 k 28.6 / 24.2; random 16 k 7.2 / 12.6; strided 16 k 17.3 / 18.3, 24 k 27.3 / 23.0
+        //   16 -> 16  random 8 k 5.7 / 9.2
+        // So from 2,048 channel products on at every size, and 1,024 from a tile per CU on: below that the small kernel loses
+        // up to a quarter on sweeps and wins that on random cells.
         const bool slices = C_in == 16 || C_in == 32 || C_in == 64 || C_in == 128 || C_in == 256;
-        if (slices && C_out % 16 == 0 && (C_in * C_out >= 2048 || (C_in * C_out >= 1024 && tiles >= compute_units()) || L.K3 > 32)) {
+        if (slices && C_out % 16 == 0 && (C_in * C_out >= 2048 || (C_in * C_out >= 1024 && likely >= compute_units()) || L.K3 > 32)) {
             const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
             return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, likely, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
                                  n_out_cap);
