@@ -23,7 +23,9 @@ def test_general_kernel(K, C_in, C_out, n, dtype):
 
 def test_general_kernel_with_two_output_blocks_per_wavefront():
     say("general kernel, many tiles, 96 and 256 output channels")
-    coords = synth.lidar_scene(4)[:26000]
+    # up to 128 channels from four tiles per CU (of 256) on, 256 output channels from 0.75 on
+    coords = np.concatenate([synth.lidar_scene(4)[:33000], synth.lidar_scene(5)[:33000]])
+    coords[33000:, 0] = 1
     check_layer(coords, 3, 1, "subm", 32, 96, "f16", seed=1, threads=16)
     check_layer(coords[:13000], 3, 1, "subm", 32, 256, "bf16", seed=1, threads=16)
 
@@ -39,6 +41,24 @@ def test_general_kernel_64_and_128_channels(K, stride, C_in, C_out, n, dtype):
     else:
         coords = synth.uniform_cells(n, 9, seed=C_in + C_out + n)
     check_layer(coords, K, stride, "subm" if stride == 1 else "strided", C_in, C_out, dtype, seed=n, threads=16)
+
+
+def test_streaming_kernel_strided_128_channels():
+    """K = 2, 128 -> 128 beyond 20 tiles per CU (of 256), where the streaming kernel takes over; the last
+    workgroup's eight tiles are not all there."""
+    say("streaming kernel K=2 128->128")
+    import oracle
+    from tests.test_gpu_parity import rel_err, run_layer, sampled_rows_reference
+    n = 350_000
+    coords = synth.uniform_cells(n, 110, seed=2)
+    feat, weight = synth.features(n, 128, "f16", 2), synth.weights(8, 128, 128, "f16", 2)
+    _, h, out_coords, out = run_layer(coords, feat, weight, 2, 2, "strided", "f16", out_dtype="f32")
+    km = oracle.kmap(coords, 2, 2, "strided")
+    assert h.n_out == km["n_out"] and np.array_equal(out_coords, km["out_coords"])
+    rows = np.unique(np.concatenate([np.random.default_rng(2).choice(h.n_out, 4000, replace=False), np.arange(200),
+                                     np.arange(h.n_out - 200, h.n_out)]))
+    err = rel_err(out[rows], sampled_rows_reference(feat, weight, km, rows)[rows])
+    assert err <= 1e-5, err
 
 
 @pytest.mark.parametrize("C_in,C_out", [(64, 64), (64, 128), (128, 128)])
@@ -63,9 +83,13 @@ def test_fused_general_kernel(C_in, C_out, n):
 
 
 @pytest.mark.parametrize("K,C_in,C_out,n", [(3, 16, 64, 17000), (3, 32, 32, 17000), (3, 64, 64, 1), (3, 64, 64, 65), (3, 64, 80, 1000),
-                                            (3, 128, 16, 700), (3, 256, 48, 300), (5, 16, 16, 700), (5, 32, 32, 65)])
+                                            (3, 128, 16, 700), (3, 256, 48, 300), (5, 16, 16, 700), (5, 32, 32, 65),
+                                            (3, 16, 64, 24500), (3, 32, 32, 16400), (3, 64, 64, 34000), (3, 64, 80, 5000),
+                                            (3, 128, 64, 5000), (3, 256, 48, 8000), (5, 32, 32, 30000)])
 def test_general_kernel_fp32(K, C_in, C_out, n):
-    """fp32: weights through LDS for 16, 32 and 64 channels per workgroup, rows of one to sixteen slices."""
+    """fp32: weights through LDS, rows of one to sixteen slices; 16 channels per workgroup of four wavefronts (the
+    first two rows of the list) and, where the last round of the 256 CUs is no shorter with 16, 32 per workgroup
+    of eight (the others), also with a last block that is not there (80, 48)."""
     say(f"general kernel fp32 K={K} {C_in}->{C_out} n={n}")
     coords = synth.lidar_scene(3)[:n] if n > 2000 else synth.uniform_cells(n, 10, seed=K + C_in + n)
     check_layer(coords, K, 1, "subm", C_in, C_out, "f32", seed=n, threads=16)

@@ -479,8 +479,8 @@ def test_strided_general_on_lidar_scene():
 @pytest.mark.parametrize("s", [2, 3])
 @pytest.mark.parametrize("dtype,n", [("f16", 700), ("bf16", 20000)])
 def test_strided_64_channel_layer(s, dtype, n):
-    """K = 3 strided layers of 64 -> 64 channels run the kernel of the 64-channel submanifold
-    layer: here its row count comes from the device and is far below the grid's row capacity."""
+    """K = 3 strided layers of 64 -> 64 channels run the general kernel like the 64-channel
+    submanifold layer: here its row count comes from the device and is far below the grid's row capacity."""
     say(f"strided K=3 s={s} 64->64 {dtype} n={n}")
     coords = synth.lidar_scene(6)[:n]
     check_layer(coords, 3, s, "strided", 64, 64, dtype, seed=n, threads=16)
@@ -806,9 +806,8 @@ def sampled_rows_reference(feat, weight, ref_km, rows, threads=16):
     return oracle.conv(feat, weight, sub, threads=threads)
 
 
-# The 64 -> 64 kernel puts 1..8 tiles into a workgroup depending on how many tiles there are per
-# CU (4 beyond 8 per CU), and spreads a workgroup's tiles over the row range: tile = wavefront *
-# units + unit.  One size per setting on a 256-CU device, fp32 output held to the fp32 tolerance.
+# The 64 -> 64 layer from one to nine tiles per CU on a 256-CU device, last tiles ragged, fp32 output held
+# to the fp32 tolerance.
 @pytest.mark.parametrize("n_tiles,dtype", [(t, "f16") for t in (255, 300, 600, 1000, 1200, 1500, 1700, 2040, 2300)] +
                          [(t, "bf16") for t in (300, 1700, 2300)])
 def test_64_channel_layer_at_every_tiles_per_workgroup(n_tiles, dtype):
@@ -825,8 +824,7 @@ def test_64_channel_layer_at_every_tiles_per_workgroup(n_tiles, dtype):
     assert h.n_pairs == ref_km["offset_start"][-1]
     assert_maps_equal(exported_map(buf, h), out_coords, ref_km, exact_order=True)
     rng = np.random.default_rng(n_tiles)
-    # a random sample, both ends, and whole tiles on either side of the places where one
-    # wavefront's share of the row range ends and the next one's begins
+    # a random sample, both ends, and whole tiles at equal shares of the row range
     per_cu = -(-n_tiles // 256)
     nwv = 4 if per_cu > 8 else per_cu
     units = -(-n_tiles // nwv)
@@ -841,8 +839,7 @@ def test_64_channel_layer_at_every_tiles_per_workgroup(n_tiles, dtype):
 @pytest.mark.parametrize("dims,C", [((257, 257, 257), 64), ((512, 256, 256), 32)])
 def test_layers_of_tens_of_millions_of_voxels(dims, C):
     """Table, map and convolution far beyond the named workloads.  (257, 257, 257), 64 channels:
-    34 M voxels, the feature array passes 4 GiB, where the 64 -> 64 layer leaves the kernel with
-    32-bit buffer offsets for the streaming kernel.  (512, 256, 256), 32 channels: exactly
+    34 M voxels, the feature array passes 4 GiB, so byte offsets do not fit 32 bits.  (512, 256, 256), 32 channels: exactly
     SC_N_MAX = 2^26 voxels, the largest input the library accepts.
     The voxel set has a closed form: cells (3i+1, 3j+1, 3k+1) and (3i+1, 3j+1, 3k+2) for
     (i, j, k) < dims, rows in that order, so row r has exactly one neighbour, row r^1, at dz = +1
