@@ -52,12 +52,19 @@ def algorithmic_bytes(kernel: str, st: dict) -> float | None:
     if kernel in ("k_conv_mfma", "k_conv_f32"):
         # features in once, features out once, weights once, 8 bytes of map per pair
         return N * C_in * e + N_out * C_out * e + K3 * C_in * C_out * e + P * 8
+    NC = N * st["candidates"]                             # places for (input, output cell) candidates; P of them exist
     if kernel == "k_strided_fill":
-        return 16.0 * cap + N * K3 * 4.0
+        slots = 1024                                      # of the output-cell table, one 4-byte word each
+        while slots < (8 if st["candidates"] == 1 and K3 <= 64 else 2) * NC:
+            slots *= 2
+        return 4.0 * slots
     if kernel == "k_strided_insert":
-        return N * (16 + 8 + 8 + 4 + 4)
+        return N * 16 + P * (4 + 4) + NC * 4              # coords, a cell's word claimed (read + write), the candidate's slot
+    if kernel == "k_strided_flags":
+        return NC * 4 + P * 4 + N_out * K3 * 4.0          # candidate's slot, its cell's word; the offset table cleared
     if kernel == "k_strided_pairs":
-        return N * (16 + 4 + 16 + 4 + 4 + 8 + 4) + N_out * 16
+        # candidate's slot, coords, its cell's word, flags and prefix, table entry; output coords
+        return NC * 4 + N * 16 + P * (4 + 8 + 4 + 4) + N_out * 16
     if kernel == "k_masks_from_table":
         return N_out * K3 * 4.0
     return None
@@ -367,7 +374,7 @@ def measure_layer(args, torch, sc, synth, workload: str, steps: int, warmup: int
         step()
     prof = sc.sc_profile_read()
     sc.sc_profile_enable(False)
-    st = dict(N=N, N_out=N_out, P=P, K3=K ** 3, cap=(sc.sc_hash_bytes(N) - 256) // 16, C_in=C_in, C_out=C_out,
+    st = dict(N=N, N_out=N_out, P=P, K3=K ** 3, candidates=(-(-K // stride)) ** 3, cap=(sc.sc_hash_bytes(N) - 256) // 16, C_in=C_in, C_out=C_out,
               elem_bytes=d_feat.element_size())
     traffic_table = {}
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic_per_launch.txt")
