@@ -802,9 +802,12 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         //   64 -> 16  sweeps 8 k 18.4 / 18.0, 24 k 28.6 / 24.2; random 16 k 7.2 / 12.6; strided 16 k 17.3 / 18.3, 24 k 27.3 / 23.0
         //   16 -> 16  random 8 k 5.7 / 9.2
         // So from 2,048 channel products on at every size, and 1,024 from a tile per CU on: below that the small kernel loses
-        // up to a quarter on sweeps and wins that on random cells.
+        // up to a quarter on sweeps and wins that on random cells.  Tiles are the ones to expect; the shapes that the small kernel
+        // does not have (16 -> 80 to 112, 32 -> 48) have only k_conv_f32 below the line and keep the bound, which draws it lower
+        // (strided 4 k rows, k_conv_f32 and general: 32 -> 48 95 / 16, 16 -> 80 72 / 19).
+        const int64_t line_tiles = C_out == 16 || C_out == 32 || C_out == 64 ? likely : tiles;
         const bool slices = C_in == 16 || C_in == 32 || C_in == 64 || C_in == 128 || C_in == 256;
-        if (slices && C_out % 16 == 0 && (C_in * C_out >= 2048 || (C_in * C_out >= 1024 && likely >= compute_units()) || L.K3 > 32)) {
+        if (slices && C_out % 16 == 0 && (C_in * C_out >= 2048 || (C_in * C_out >= 1024 && line_tiles >= compute_units()) || L.K3 > 32)) {
             const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
             return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, likely, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
                                  n_out_cap);

@@ -95,6 +95,15 @@ def test_general_kernel_fp32(K, C_in, C_out, n):
     check_layer(coords, K, 1, "subm", C_in, C_out, "f32", seed=n, threads=16)
 
 
+@pytest.mark.parametrize("C_in,C_out", [(16, 64), (32, 32), (64, 16), (32, 48), (16, 80)])
+@pytest.mark.parametrize("n", [1900, 4000, 17000])
+def test_strided_fp32_on_both_sides_of_the_line(C_in, C_out, n):
+    """fp32 layers of 1,024 to 2,047 channel products, K = 3, stride 2: bound and expected tiles on either side of
+    a tile per CU (of 256)."""
+    say(f"strided fp32 {C_in}->{C_out} n={n}")
+    check_layer(synth.lidar_scene(6)[:n], 3, 2, "strided", C_in, C_out, "f32", seed=n, threads=16)
+
+
 @pytest.mark.parametrize("K,stride,C_in,C_out", [(3, 1, 1, 16), (3, 1, 3, 64), (3, 1, 4, 32), (2, 2, 4, 16), (2, 2, 3, 32), (2, 2, 2, 64)])
 @pytest.mark.parametrize("n", [1, 64, 65, 3000])
 def test_first_layer_fp32(K, stride, C_in, C_out, n):
