@@ -52,7 +52,7 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int FUSED>
 __global__ void __launch_bounds__(64 * NW, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
-              const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
+              int blocks_y, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
     static_assert(!FUSED || (DT != SC_F32 && NW == 4 && KS > 1), "fused look-ups: a quarter of the 27 offsets per wavefront");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
@@ -71,11 +71,15 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, qq = lane >> 4;
-    const int wr = wv / WC, cb0 = (int)blockIdx.y * (WC * CT) + (wv % WC) * CT;
+    const int wr = wv / WC;
     int64_t n_out = n_out_cap;
     if (!FUSED && *n_out_ptr < n_out) n_out = *n_out_ptr;
-    const int64_t tile = xcd_run_of(blockIdx.x, (n_out + TILE - 1) / TILE);
+    // a tile's blocks of output channels follow each other on its XCD
+    const unsigned turn = blockIdx.x / NUM_XCD;
+    const int by = (int)(turn % (unsigned)blocks_y);
+    const int64_t tile = xcd_run_of(turn / (unsigned)blocks_y * NUM_XCD + blockIdx.x % NUM_XCD, (n_out + TILE - 1) / TILE);
     if (tile < 0) return;                              // the whole workgroup
+    const int cb0 = by * (WC * CT) + (wv % WC) * CT;
 
     // the offsets the tile takes part in, in increasing order: number (times PARTS, plus
     // the part) and 4-bit pattern of groups.  The tile's mask words are held by the lanes of one register.
@@ -203,7 +207,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
             for (int o = 1; o < OPS; ++o) kk = sl >= o * KP ? k[o] : kk;
             if (t < SL * PS && kk >= 0) {
-                int col = (int)blockIdx.y * NC + ((piece ^ (swizzle(q) << 2)) << 2);
+                int col = by * NC + ((piece ^ (swizzle(q) << 2)) << 2);
                 if (col > CB * 16 - 4) col = CB * 16 - 4;      // past the last block: not stored
                 const float* src = reinterpret_cast<const float*>(wp) + ((int64_t)kk * (KP * 16) + sl % KP * 16 + 4 * q + j) * (CB * 16) + col;
                 load_to_lds(src, __builtin_amdgcn_readfirstlane(lds_base + 2 * STEP_BYTES + buf * W_BYTES + t * 1024));
@@ -329,8 +333,8 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s
     constexpr size_t lds = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (FUSED ? 28 * TILE * 4 + 64 : 0);
     static_assert(lds <= 65536, "within the LDS a kernel may use without asking");
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
-    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, FUSED>), dim3(xcd_run_grid(tiles), blocks_y),
-              dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB, n_out_ptr, n_out_cap);
+    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, FUSED>), dim3(xcd_run_grid(tiles) * blocks_y),
+              dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB, (int)blocks_y, n_out_ptr, n_out_cap);
     return SC_OK;
 }
 
