@@ -61,6 +61,19 @@ __device__ inline void store_acc(void* __restrict__ out, int out_f32, int64_t ro
     }
 }
 
+// Large dynamic LDS has to be allowed per kernel, once on every device the kernel runs on: a flag
+// per device (a repeated call would be harmless, so a race between host threads is too).
+constexpr int MAX_DEVICES = 64;
+inline int allow_lds(const void* fn, size_t lds, bool (&done)[MAX_DEVICES]) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return SC_EHIP;
+    if (!done[dev]) {
+        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return SC_EHIP;
+        done[dev] = true;
+    }
+    return SC_OK;
+}
+
 // The general kernel (sc_conv_gather.hip): any K^3 <= 343, C_out a multiple of 16; 16-bit layers with C_in 32, 64,
 // 128 or 256 and packed weights, fp32 layers with C_in 16, 32, 64, 128 or 256 and weights as they are.  `tiles` covers the
 // caller's row capacity, `likely` is how many of them to expect (the input's, where the output count is known on the device only).

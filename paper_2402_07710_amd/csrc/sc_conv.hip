@@ -571,19 +571,6 @@ k_conv_f32_small(const float* __restrict__ feat, const float* __restrict__ w, fl
     }
 }
 
-// Large dynamic LDS has to be allowed per kernel, once on every device the kernel runs on: a flag
-// per device (a repeated call would be harmless, so a race between host threads is too).
-constexpr int MAX_DEVICES = 64;
-static int allow_lds(const void* fn, size_t lds, bool (&done)[MAX_DEVICES]) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return SC_EHIP;
-    if (!done[dev]) {
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return SC_EHIP;
-        done[dev] = true;
-    }
-    return SC_OK;
-}
-
 template <int DT, int K3, int KS, int CB, int NT, int FUSED, int UP = 0, int WPACKED = 0>
 static int launch_rows16(int64_t tiles, hipStream_t s, const uint16_t* feat, const uint4* wp, void* out, int out_f32,
                          const MapSource& ms, const int64_t* counts, int64_t n_out_cap) {
@@ -734,10 +721,11 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // tiles and takes ~75 us however few there are; full, it moves the weights once for them (us, general and
     // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
     // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
-    // 32 -> 64, K = 3, up to 1.5 tiles per CU: there the streaming kernel's walk over all offsets, four tiles in step, is the
-    // longer chain (2 k / 10 k / 53 k voxels: general 9.2 / 9.8 / 14.7 us, streaming 11.2 / 11.7 / 12.8).  Not the fused
-    // form: the general kernel has no fused instantiation for 32 channels, so that one takes the walk at every size.
-    if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && 2 * likely <= 3 * (int64_t)compute_units())
+    // 32 -> 64, K = 3, up to three tiles per CU: there the streaming kernel's walk over all offsets, four tiles in step, is the
+    // longer chain (us, general and streaming kernel: 3 k voxels strided 8.0 / 9.9, 20 k 9.0 / 11.4, 30 k 9.6 / 12.6, 53 k 13.9 /
+    // 13.8, 110 k 23.2 / 20.3, 800 k indoor 163 / 129).  Not the fused form: the general kernel has no fused instantiation for
+    // 32 channels, so that one takes the walk at every size.
+    if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && likely <= 3 * (int64_t)compute_units())
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
     if ((FUSED && fused_gather) || (wide && likely <= 20 * (int64_t)compute_units())) {
         if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);

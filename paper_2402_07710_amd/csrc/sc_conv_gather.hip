@@ -14,6 +14,8 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
 }
 
+constexpr int LIST_PAD = 12;                            // places of the list past the last offset: three steps of four
+
 // One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
 // input channel) is walked in steps of SL slices of 64 bytes of a row (32 16-bit or 16 fp32 channels):
 // four slices per step (one offset of 256 bytes, 2 of 128, 4 of 64, a part of a longer one; eight
@@ -30,6 +32,10 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 //    straight to registers they cost as many address cycles as the gathers save (104 us at the size
 //    below); they go through LDS instead.  An fp32 multiply takes eight times as long per byte, so the
 //    wavefronts (eight) split rows as well as channels.
+//  * The steps are read from a list of the tile's offsets that is made once, in LDS: walking the mask words in every step was
+//    a third of a step's instructions, and scalar ones issue once per four cycles for all wavefronts of a SIMD (us, before and
+//    with the list: K = 5 32 -> 32 4 k / 53 k voxels 22.7 / 32.1 -> 16.0 / 25.3, K = 5 64 -> 64 20 k 44.5 -> 34.2, 64 -> 64 4 k
+//    12.6 -> 10.3, 128 -> 256 5 k 19.4 -> 17.8, fp32 64 -> 64 8 k 23.4 -> 21.3, 32 -> 64 80 k 58.3 -> 55.3; 110 k and more the same).
 //  * One wait for everything and one barrier per step.  What a step costs is issuing its loads (17
 //    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
 //  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
@@ -67,7 +73,8 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
     constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
     constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
-    extern __shared__ __align__(16) char smem[];       // rows[2][STEP_BYTES] | weights[2][W_BYTES] | FUSED: entries[28][64], masks[4][4]
+    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD] | FUSED: entries[28][64], masks[4][4]
+    extern __shared__ __align__(16) char smem[];
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, qq = lane >> 4;
@@ -81,10 +88,16 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     if (tile < 0) return;                              // the whole workgroup
     const int cb0 = by * (WC * CT) + (wv % WC) * CT;
 
-    // the offsets the tile takes part in, in increasing order: number (times PARTS, plus
-    // the part) and 4-bit pattern of groups.  The tile's mask words are held by the lanes of one register.
-    uint32_t mvec = 0u;
-    int32_t* found = reinterpret_cast<int32_t*>(smem + 2 * STEP_BYTES);
+    // The offsets the tile takes part in, in increasing order, as a list in LDS: number and 4-bit pattern of groups, zeros past
+    // the last.  Every wavefront makes it for itself (lane = offset), all with the same contents.
+    uint32_t* list = reinterpret_cast<uint32_t*>(smem + 2 * STEP_BYTES + 2 * W_BYTES);
+    int32_t* found = reinterpret_cast<int32_t*>(list + 40);
+    int listed = 0;
+    auto add_to_list = [&](int k, uint32_t pat) __attribute__((always_inline)) {
+        const uint64_t in = __ballot(pat != 0u);
+        if (pat != 0u) list[listed + __popcll(in & ((1ull << lane) - 1ull))] = (uint32_t)k << 4 | pat;
+        listed += __popcll(in);
+    };
     if constexpr (FUSED) {
         // lane = row; each wavefront looks up every fourth offset, its part of the masks is a vote
         uint32_t* votes = reinterpret_cast<uint32_t*>(found + 28 * TILE);
@@ -100,35 +113,42 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         }
         if (lane == 0) *reinterpret_cast<uint4*>(votes + 4 * wv) = make_uint4(vg[0], vg[1], vg[2], vg[3]);
         __syncthreads();
-        if (lane < 4) mvec = votes[lane] | votes[4 + lane] | votes[8 + lane] | votes[12 + lane];
+        uint32_t pat = 0u;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) pat |= (((votes[g] | votes[4 + g] | votes[8 + g] | votes[12 + g]) >> (lane & 31)) & 1u) << g;
+        add_to_list(lane, lane < 27 ? pat : 0u);
     } else {
-        if (lane < 4 * mw) mvec = gmask[tile * (4 * mw) + lane];
+        for (int k = lane; k - lane < K3; k += WAVE) {
+            uint32_t pat = 0u;
+            if (k < K3) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
+            }
+            add_to_list(k, pat);
+        }
     }
-    uint32_t mg[4] = {0u, 0u, 0u, 0u}, rest = 0u, pat_now = 0u;
-    int wi = -1, k_now = -1;
-    auto next_offset = [&](int& k, uint32_t& pat) __attribute__((always_inline)) {
-        if (PARTS > 1 && k_now >= 0 && (k_now + 1) % PARTS != 0) {
-            k = ++k_now;
-            pat = pat_now;
-            return;
-        }
-        while (rest == 0u && wi + 1 < mw) {
-            ++wi;
+    if (lane < LIST_PAD) list[listed + lane] = 0u;
+    const uint32_t* next = list;
+    uint32_t fetched[OPS];                             // the list's entries of the next step, read a step before they are needed
+    int part = 0;
+    auto fetch = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) mg[g] = __builtin_amdgcn_readlane(mvec, g * mw + wi);
-            rest = mg[0] | mg[1] | mg[2] | mg[3];
-        }
-        k_now = -1;
-        pat_now = 0u;
-        if (rest != 0u) {
-            const int b = __builtin_ctz(rest);
-            rest &= rest - 1u;
-            k_now = (wi * 32 + b) * PARTS;
+        for (int o = 0; o < OPS; ++o) fetched[o] = next[o];
+    };
+    fetch();
+    // numbers (times PARTS, plus the part; -1: none) and patterns of the next step's offsets
+    auto next_step = [&](int (&k)[OPS], uint32_t (&p)[OPS]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) pat_now |= ((mg[g] >> b) & 1u) << g;
+        for (int o = 0; o < OPS; ++o) {
+            const uint32_t e = __builtin_amdgcn_readfirstlane(fetched[o]);
+            p[o] = e & 15u;
+            k[o] = e != 0u ? (int)(e >> 4) * PARTS + part : -1;
         }
-        k = k_now;
-        pat = pat_now;
+        if (PARTS == 1 || ++part == PARTS) {
+            part = 0;
+            next += OPS;
+        }
+        fetch();
     };
 
     // gathers: this wavefront fetches group gw (of eight wavefronts, two share a group: each takes every other
@@ -158,8 +178,8 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
             for (int i = 0; i < NI; ++i)
                 if (!SKIP || k[o] >= 0) {
-                    const int at = (k[o] >= 0 ? k[o] / PARTS : 0) * TILE + grow[i];
-                    ev[o][i] = FUSED ? found[gw * 16 + at] : line[at];
+                    const int32_t* at = (FUSED ? found + gw * 16 : line) + (k[o] >= 0 ? k[o] / PARTS : 0) * TILE;
+                    ev[o][i] = at[(uint32_t)grow[i]];
                 }
     };
     auto gather = [&](const int (&k)[OPS], const uint32_t (&p)[OPS], int buf) __attribute__((always_inline)) {
@@ -182,13 +202,13 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
         for (int o = 0; o < OPS; ++o)
             if (!SKIP || k[o] >= 0) {
-                const u32x4* w = reinterpret_cast<const u32x4*>(wp) + (int64_t)(k[o] >= 0 ? k[o] : 0) * (CB * KP * 64) + lane;
+                const char* w = reinterpret_cast<const char*>(wp) + (uint32_t)(k[o] >= 0 ? k[o] : 0) * (uint32_t)(CB * KP * 1024);
 #pragma unroll
                 for (int ks = 0; ks < KP; ++ks)
 #pragma unroll
                     for (int ct = 0; ct < CT; ++ct) {
                         const int cb = cb0 + ct < CB ? cb0 + ct : CB - 1;      // past the last block: not stored
-                        a[o * KP + ks][ct] = w[(KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1)) * 64];
+                        a[o * KP + ks][ct] = *reinterpret_cast<const u32x4*>(w + (KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1)) * 1024 + (uint32_t)lane * 16u);
                     }
             }
     };
@@ -247,14 +267,18 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
                 for (int ks = 0; ks < KP; ++ks) b[g][ks] = *reinterpret_cast<const uint4*>(rows + (ks >> 1) * CHB + ((ks & 1) ? op1 : op0));
             };
-            if constexpr (!SKIP) {
-#pragma unroll
-                for (int g = 0; g < RG; ++g) operands(g);
-            }
+            // two short groups (64 input channels) are read together, also one without a neighbour: its products are left
+            // out (4 k voxels 64 -> 64 11.3 -> 10.3 us; all four: 10.2, but 110 k 30.9 -> 31.5 and 10^6 324 -> 332)
+            constexpr int GB = !SKIP ? RG : KP == 2 && RG > 1 && CT == 1 ? 2 : 1;
 #pragma unroll
             for (int g = 0; g < RG; ++g) {
+                if (GB > 1 && g % GB == 0) {
+#pragma unroll
+                    for (int i = g; i < g + GB; ++i) operands(i);
+                    __builtin_amdgcn_sched_barrier(0);         // read here, not under the tests below
+                }
                 if (((p[o] >> (wr * RG + g)) & 1u) == 0u) continue;
-                if constexpr (SKIP) operands(g);
+                if (GB == 1) operands(g);
 #pragma unroll
                 for (int ks = 0; ks < KP; ++ks) {
                     if constexpr (F32) {
@@ -273,10 +297,6 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
                 }
             }
         }
-    };
-    auto next_step = [&](int (&k)[OPS], uint32_t (&p)[OPS]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int o = 0; o < OPS; ++o) next_offset(k[o], p[o]);
     };
     // everything requested has arrived (said in a form the compiler's own wait-count pass sees), and so it has for all four wavefronts
     auto step_end = [&]() {
@@ -330,8 +350,13 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int FUSED>
 static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-    constexpr size_t lds = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (FUSED ? 28 * TILE * 4 + 64 : 0);
-    static_assert(lds <= 65536, "within the LDS a kernel may use without asking");
+    constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (FUSED ? 28 * TILE * 4 + 64 : 0);
+    static_assert(fixed <= 65536, "loads into LDS land in the first 64 KB");
+    const size_t lds = fixed + (size_t)(K3 + LIST_PAD + 3) / 4 * 16;
+    if constexpr (fixed + (343 + LIST_PAD + 3) / 4 * 16 > 65536) {
+        static bool allowed[MAX_DEVICES] = {};
+        if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, FUSED>, fixed + (343 + LIST_PAD + 3) / 4 * 16, allowed)) return rc;
+    }
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
     SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, FUSED>), dim3(xcd_run_grid(tiles) * blocks_y),
               dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB, (int)blocks_y, n_out_ptr, n_out_cap);

@@ -21,6 +21,17 @@ def test_general_kernel(K, C_in, C_out, n, dtype):
     check_layer(coords, K, 1, "subm", C_in, C_out, dtype, seed=n, out_dtype="f32" if n == 65 else None)
 
 
+@pytest.mark.parametrize("K,C_in,dtype", [(7, 256, "f16"), (7, 64, "bf16"), (7, 32, "f16"), (5, 128, "f16"), (7, 16, "f32"), (3, 256, "f32")])
+@pytest.mark.parametrize("side", [1, 4, 9])
+def test_general_kernel_on_a_cube(K, C_in, dtype, side):
+    """Lists of offsets from one entry to all K^3 of them; with 256 input channels the list lies past 64 KB of LDS, in fp32
+    an offset is up to four steps."""
+    say(f"general kernel on a cube of {side}^3, K={K} C_in={C_in} {dtype}")
+    xyz = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    coords = np.concatenate([np.zeros((len(xyz), 1), dtype=np.int64), xyz], axis=1).astype(np.int32)
+    check_layer(np.ascontiguousarray(coords), K, 1, "subm", C_in, 16 if C_in != 256 else 32, dtype, seed=side, threads=16)
+
+
 def test_general_kernel_with_two_output_blocks_per_wavefront():
     say("general kernel, many tiles, 96 and 256 output channels")
     # up to 128 channels from four tiles per CU (of 256) on, 256 output channels from 0.75 on
