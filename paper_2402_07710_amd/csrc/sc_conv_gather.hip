@@ -245,6 +245,39 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     };
     const int op0 = operand(0), op1 = operand(1);
     auto compute = [&](const u32x4 (&a)[SL][CT], const uint32_t (&p)[OPS], int buf) {
+        if constexpr (!F32 && (KP == 1 || KP == 8)) {
+            // Operands are read a batch of groups ahead of its multiplies, also of a group without a neighbour: its products are
+            // left out.  Batches are all groups of an offset (32 channels) or one (256).  (us, before -> now: 256 -> 256 500 / 2 k /
+            // 5 k voxels 12.8 / 22.9 / 29.8 -> 11.2 / 20.8 / 26.0, K = 5 32 -> 32 4 k / 53 k 16.0 / 25.2 -> 15.3 / 24.4.  64 and 128
+            // channels, whose batches are short next to the latency, lose the registers: 110 k 64 -> 64 30.5 -> 32.3.)
+            constexpr int GB = KP == 1 ? RG : 1, NB = RG / GB, BATCHES = OPS * NB;
+            uint4 b[2][GB][KP];
+            auto read = [&](uint4 (&b)[GB][KP], int i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int g = 0; g < GB; ++g) {
+                    const char* rows = smem + buf * STEP_BYTES + i / NB * CH * CHB + (wr * RG + i % NB * GB + g) * (CHB / 4);
+#pragma unroll
+                    for (int ks = 0; ks < KP; ++ks) b[g][ks] = *reinterpret_cast<const uint4*>(rows + (ks >> 1) * CHB + ((ks & 1) ? op1 : op0));
+                }
+            };
+            read(b[0], 0);
+#pragma unroll
+            for (int i = 0; i < BATCHES; ++i) {
+                if (i + 1 < BATCHES) read(b[(i + 1) & 1], i + 1);
+                __builtin_amdgcn_sched_barrier(0);     // read here, not under the tests
+#pragma unroll
+                for (int gb = 0; gb < GB; ++gb) {
+                    const int o = i / NB, g = i % NB * GB + gb;
+                    if (((p[o] >> (wr * RG + g)) & 1u) == 0u) continue;
+#pragma unroll
+                    for (int ks = 0; ks < KP; ++ks)
+#pragma unroll
+                        for (int ct = 0; ct < CT; ++ct)
+                            acc[g][ct] = mfma16x16x32<DT>(__builtin_bit_cast(uint4, a[o * KP + ks][ct]), b[i & 1][gb][ks], acc[g][ct]);
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int o = 0; o < OPS; ++o) {
             if (p[o] == 0u) continue;
@@ -269,7 +302,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
             };
             // two short groups (64 input channels) are read together, also one without a neighbour: its products are left
             // out (4 k voxels 64 -> 64 11.3 -> 10.3 us; all four: 10.2, but 110 k 30.9 -> 31.5 and 10^6 324 -> 332)
-            constexpr int GB = !SKIP ? RG : KP == 2 && RG > 1 && CT == 1 ? 2 : 1;
+            constexpr int GB = KP == 2 && RG > 1 && CT == 1 ? 2 : 1;
 #pragma unroll
             for (int g = 0; g < RG; ++g) {
                 if (GB > 1 && g % GB == 0) {
@@ -387,8 +420,12 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
         // two output blocks per wavefront halve how often a tile's rows are gathered; one, where that leaves CUs
         // idle or, up to 128 channels either way, with few wavefronts (us with one and with two blocks: 256 -> 128 at
         // 219 tiles 29.0, 34.2; 256 -> 256 49.1, 44.1; 64 -> 256 at 157 tiles 17.6, 19.3, at 250 22.9, 20.9; 128 -> 128 at
-        // 625 tiles 36.0, 38.2, at 4,088 132, 127.5; 64 -> 128 at 469 tiles 20.2, 21.4, at 834 26.9, 26.7)
-        if (CB <= 4 || (CB <= 8 && KS <= 4 ? likely <= 4 * (int64_t)cus : 2 * likely * ((CB + 7) / 8) < 3 * (int64_t)cus)) SC_GATHER(4, 1, 1, O1);
+        // 625 tiles 36.0, 38.2, at 4,088 132, 127.5; 64 -> 128 at 469 tiles 20.2, 21.4, at 834 26.9, 26.7; and with 256 input
+        // channels, whose step is the longest, up to four workgroups of one block per CU: 256 -> 256 at 141 tiles 35.8, 35.4, at 219
+        // 45.3, 50.3, at 250 49.3, 51.1, at 469 82.6, 76.9)
+        const int64_t pairs = likely * ((CB + 7) / 8);
+        if (CB <= 4 || (CB <= 8 && KS <= 4 ? likely <= 4 * (int64_t)cus : KS == 8 ? pairs <= 2 * (int64_t)cus : 2 * pairs < 3 * (int64_t)cus))
+            SC_GATHER(4, 1, 1, O1);
         SC_GATHER(4, 1, 2, O2);
     }
 #undef SC_GATHER
