@@ -14,6 +14,8 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
 }
 
+// where a tile's table entries come from: the map's lines as they are needed, the same copied to LDS first, or look-ups
+enum { FROM_MAP, FROM_TABLE, FROM_LINES };
 constexpr int LIST_PAD = 12;                            // places of the list past the last offset: three steps of four
 
 // One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
@@ -36,6 +38,11 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 //    a third of a step's instructions, and scalar ones issue once per four cycles for all wavefronts of a SIMD (us, before and
 //    with the list: K = 5 32 -> 32 4 k / 53 k voxels 22.7 / 32.1 -> 16.0 / 25.3, K = 5 64 -> 64 20 k 44.5 -> 34.2, 64 -> 64 4 k
 //    12.6 -> 10.3, 128 -> 256 5 k 19.4 -> 17.8, fp32 64 -> 64 8 k 23.4 -> 21.3, 32 -> 64 80 k 58.3 -> 55.3; 110 k and more the same).
+//  * FROM_LINES (K <= 3, 16 bit, 64 and more channels): the tile's lines of the map are copied to LDS at the start, beside the
+//    masks' round trip.  Read from the map step by step, 32 bytes at a time, they were a third of the loads that the address unit
+//    serves at 17 cycles each, and the first gathers waited for them (us, before -> with: 64 -> 64 110 k / 262 k / 10^6 voxels
+//    30.7 / 58.0 / 326 -> 29.4 / 54.4 / 302, 128 -> 128 20 k / 53 k / 262 k 21.4 / 43.6 / 152 -> 20.2 / 42.2 / 147, 256 -> 256 14 k 45.7 ->
+//    43.5).  7 KB of LDS: fp32 would lose a workgroup per CU to them; 32 channels, an offset a quarter of a step, gain nothing.
 //  * One wait for everything and one barrier per step.  What a step costs is issuing its loads (17
 //    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
 //  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
@@ -46,7 +53,7 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 // like the others (of offset 0, rows of zeros); the operands of an offset are read together, then the
 // multiplies tested (whole layers K = 5 32 -> 32 on 2 k / 53 k voxels and 32 -> 64 on 110 k: 30.0 / 63.4 / 116 us; with SKIP
 // 31.0 / 64.5 / 121, with zeroed weights instead of the test 30.3 / 64.2 / 120, all of a step's operands first 29.4 / 63.2 / 120).
-// FUSED: there is no kernel map; the four wavefronts look up every fourth of the 27 offsets of the tile's rows in the
+// FROM_TABLE (fused layers): there is no kernel map; the four wavefronts look up every fourth of the 27 offsets of the tile's rows in the
 // dense location table and leave entries and votes in LDS (7 KB).  Whole fused layers on 2 k / 53 k / 262 k voxels, against
 // the kernels that gave a wavefront 64 rows: 64 -> 64 21.2 / 33.6 / 95 -> 17.6 / 30.0 / 81 us, 64 -> 128 38.9 / 46.6 / 124 ->
 // 17.8 / 40.0 / 108, 128 -> 128 88.7 / 93.9 / 193 -> 22.4 / 55.3 / 160.
@@ -55,11 +62,12 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 // fp32 118 -> 72 us.  Against the kernels that shared W[k] in LDS or gave a wavefront 64 rows: 64 -> 64 2 k /
 // 20 k / 110 k / 262 k voxels 14.8 / 15.8 / 29.4 / 58.2 -> 10.7 / 14.1 / 28.6 / 50.3 us; 64 -> 128 4 k / 110 k 27.4 /
 // 47.1 -> 11.7 / 40.7; 128 -> 128 4 k / 53 k / 262 k 70.8 / 75.5 / 157 -> 16.8 / 43 / 127.5.
-template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int FUSED>
+template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int SRC>
 __global__ void __launch_bounds__(64 * NW, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
               int blocks_y, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
-    static_assert(!FUSED || (DT != SC_F32 && NW == 4 && KS > 1), "fused look-ups: a quarter of the 27 offsets per wavefront");
+    constexpr bool FUSED = SRC == FROM_TABLE, HELD = SRC != FROM_MAP;      // HELD: the tile's entries are in LDS
+    static_assert(!HELD || (DT != SC_F32 && NW == 4 && KS > 1), "a quarter of the 27 offsets per wavefront");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
     constexpr bool F32 = DT == SC_F32;
@@ -73,7 +81,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
     constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
     constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
-    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD] | FUSED: entries[28][64], masks[4][4]
+    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD] | HELD: entries[28][64], masks[4][4]
     extern __shared__ __align__(16) char smem[];
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -118,6 +126,11 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         for (int g = 0; g < 4; ++g) pat |= (((votes[g] | votes[4 + g] | votes[8 + g] | votes[12 + g]) >> (lane & 31)) & 1u) << g;
         add_to_list(lane, lane < 27 ? pat : 0u);
     } else {
+        int32_t part[7];
+        if constexpr (HELD) {
+#pragma unroll
+            for (int u = 0; u < 7; ++u) part[u] = wv + 4 * u < K3 ? nbr[(tile * K3 + wv + 4 * u) * TILE + lane] : -1;
+        }
         for (int k = lane; k - lane < K3; k += WAVE) {
             uint32_t pat = 0u;
             if (k < K3) {
@@ -125,6 +138,11 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
                 for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
             }
             add_to_list(k, pat);
+        }
+        if constexpr (HELD) {
+#pragma unroll
+            for (int u = 0; u < 7; ++u) found[(wv + 4 * u) * TILE + lane] = part[u];
+            __syncthreads();
         }
     }
     if (lane < LIST_PAD) list[listed + lane] = 0u;
@@ -164,7 +182,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         for (int i = 0; i < NI; ++i) grow[i] = (NW == 8 ? half : i) * 8 + (lane >> 3);
         gpiece = (lane & 7) ^ (lane >> 3);
     }
-    const int32_t* line = FUSED ? nullptr : nbr + tile * (int64_t)K3 * TILE + gw * 16;
+    const int32_t* line = HELD ? nullptr : nbr + tile * (int64_t)K3 * TILE + gw * 16;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const char* fbase = reinterpret_cast<const char*>(feat) + gpiece * 16;
     const char* zbase = reinterpret_cast<const char*>(g_zero_row) + gpiece * 16;
@@ -178,7 +196,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
             for (int i = 0; i < NI; ++i)
                 if (!SKIP || k[o] >= 0) {
-                    const int32_t* at = (FUSED ? found + gw * 16 : line) + (k[o] >= 0 ? k[o] / PARTS : 0) * TILE;
+                    const int32_t* at = (HELD ? found + gw * 16 : line) + (k[o] >= 0 ? k[o] / PARTS : 0) * TILE;
                     ev[o][i] = at[(uint32_t)grow[i]];
                 }
     };
@@ -380,28 +398,28 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     }
 }
 
-template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int FUSED>
+template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int SRC>
 static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-    constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (FUSED ? 28 * TILE * 4 + 64 : 0);
-    static_assert(fixed <= 65536, "loads into LDS land in the first 64 KB");
+    constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (SRC != FROM_MAP ? 28 * TILE * 4 + 64 : 0);
+    static_assert(fixed <= 65536 + 28 * TILE * 4 + 64, "loads into LDS land in the first 64 KB");
     const size_t lds = fixed + (size_t)(K3 + LIST_PAD + 3) / 4 * 16;
     if constexpr (fixed + (343 + LIST_PAD + 3) / 4 * 16 > 65536) {
         static bool allowed[MAX_DEVICES] = {};
-        if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, FUSED>, fixed + (343 + LIST_PAD + 3) / 4 * 16, allowed)) return rc;
+        if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>, fixed + (343 + LIST_PAD + 3) / 4 * 16, allowed)) return rc;
     }
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
-    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, FUSED>), dim3(xcd_run_grid(tiles) * blocks_y),
+    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>), dim3(xcd_run_grid(tiles) * blocks_y),
               dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB, (int)blocks_y, n_out_ptr, n_out_cap);
     return SC_OK;
 }
 
 // O1, O2: wavefronts per SIMD with one and with two output blocks per wavefront
-template <int DT, int KS, int SL, int SKIP, int O1, int O2, int FUSED = 0>
+template <int DT, int KS, int SL, int SKIP, int O1, int O2, int SRC = FROM_MAP>
 static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat, const void* wp,
                             void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
 #define SC_GATHER(NW, WR, CT, OCC) \
-    return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC, FUSED>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+    return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC, SRC>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if constexpr (DT == SC_F32) {
         // 32 output channels per workgroup: gathering a tile's rows once more costs less than a workgroup of 64 channels
         // that others wait for (a tile near the sensor is 27 offsets x 2,048 cycles of multiplies per SIMD; us with
@@ -413,7 +431,7 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
         if (CB == 1 || narrow) SC_GATHER(4, 4, 1, 3);
         SC_GATHER(8, 4, 1, 4);
     } else {
-        if constexpr (!FUSED) {
+        if constexpr (SRC != FROM_TABLE) {
             if (CB == 1) SC_GATHER(4, 4, 1, O1);
             if (CB == 2) SC_GATHER(4, 2, 1, O1);
         }
@@ -438,10 +456,10 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
     // with more workgroups: 128 -> 64 at 53 k voxels 36.7 us instead of 28.8).  64: an offset; two for K = 5 and 7, whose
     // tiles walk many more offsets (K = 3 -> 64 at 262 k voxels 50.3 us with one, 56.5 with two; K = 5 -> 64 at 53 k 55.1
     // and 50.7).  32: four (K = 5 -> 32 at 53 k: 30.4 us; two 32.1, eight with half the workgroups 36).
-#define SC_GATHER_KS(KS, SL, SKIP, O1, O2)                                                                                        \
+#define SC_GATHER_KS(KS, SL, SKIP, O1, O2, SRC)                                                                                      \
     return dtype_in == SC_F16                                                                                                     \
-               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
-               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
+               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if (dtype_in == SC_F32) {
 #define SC_GATHER_F32(KS) \
     return launch_gather_ks<SC_F32, KS, 4, 1, 4, 4>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
@@ -455,13 +473,19 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
 #undef SC_GATHER_F32
         return SC_EINVAL;
     }
+    if (K3 <= 27) {
+        switch (C_in) {
+            case 32: break;
+            case 64: SC_GATHER_KS(2, 2, 1, 6, 5, FROM_LINES);
+            case 128: SC_GATHER_KS(4, 4, 1, 4, 3, FROM_LINES);
+            case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_LINES);
+        }
+    }
     switch (C_in) {
-        case 32: SC_GATHER_KS(1, 4, 0, 2, 2);
-        case 64:
-            if (K3 <= 32) SC_GATHER_KS(2, 2, 1, 6, 5);
-            SC_GATHER_KS(2, 4, 1, 5, 4);
-        case 128: SC_GATHER_KS(4, 4, 1, 4, 3);
-        case 256: SC_GATHER_KS(8, 8, 1, 2, 2);
+        case 32: SC_GATHER_KS(1, 4, 0, 2, 2, FROM_MAP);
+        case 64: SC_GATHER_KS(2, 4, 1, 5, 4, FROM_MAP);
+        case 128: SC_GATHER_KS(4, 4, 1, 4, 3, FROM_MAP);
+        case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_MAP);
     }
 #undef SC_GATHER_KS
     return SC_EINVAL;
@@ -474,8 +498,8 @@ int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cu
     if (CB < 4) return SC_EINVAL;
 #define SC_GATHER_FUSED(KS, SL, O1, O2)                                                                                                      \
     return dtype_in == SC_F16                                                                                                                \
-               ? launch_gather_ks<SC_F16, KS, SL, 1, O1, O2, 1>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
-               : launch_gather_ks<SC_BF16, KS, SL, 1, O1, O2, 1>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+               ? launch_gather_ks<SC_F16, KS, SL, 1, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
+               : launch_gather_ks<SC_BF16, KS, SL, 1, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
     if (C_in == 64) SC_GATHER_FUSED(2, 2, 6, 5);
     if (C_in == 128) SC_GATHER_FUSED(4, 4, 4, 3);
 #undef SC_GATHER_FUSED

@@ -21,7 +21,7 @@ def test_general_kernel(K, C_in, C_out, n, dtype):
     check_layer(coords, K, 1, "subm", C_in, C_out, dtype, seed=n, out_dtype="f32" if n == 65 else None)
 
 
-@pytest.mark.parametrize("K,C_in,dtype", [(7, 256, "f16"), (7, 64, "bf16"), (7, 32, "f16"), (5, 128, "f16"), (7, 16, "f32"), (3, 256, "f32")])
+@pytest.mark.parametrize("K,C_in,dtype", [(7, 256, "f16"), (7, 64, "bf16"), (7, 32, "f16"), (5, 128, "f16"), (7, 16, "f32"), (3, 256, "f32"), (1, 64, "f16"), (3, 64, "bf16")])
 @pytest.mark.parametrize("side", [1, 4, 9])
 def test_general_kernel_on_a_cube(K, C_in, dtype, side):
     """Lists of offsets from one entry to all K^3 of them; with 256 input channels the list lies past 64 KB of LDS, in fp32
