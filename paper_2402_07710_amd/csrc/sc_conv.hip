@@ -722,11 +722,14 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
     // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
     // 32 -> 64, K = 3, up to three tiles per CU: there the streaming kernel's walk over all offsets, four tiles in step, is the
-    // longer chain (us, general and streaming kernel: 3 k voxels strided 8.0 / 9.9, 20 k 9.0 / 11.4, 30 k 9.6 / 12.6, 53 k 13.9 /
-    // 13.8, 110 k 23.2 / 20.3, 800 k indoor 163 / 129).  Not the fused form: the general kernel has no fused instantiation for
-    // 32 channels, so that one takes the walk at every size.
-    if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && likely <= 3 * (int64_t)compute_units())
+    // longer chain (us, general and streaming kernel: 3 k voxels strided 7.6 / 9.9, 20 k 8.6 / 11.4, 30 k 9.6 / 12.6, 53 k 13.9 /
+    // 13.8, 110 k 23.2 / 20.3, 800 k indoor 163 / 129).  Fused, where the look-ups add to the walk of a wavefront with 64 rows, up to
+    // sixteen (whole layers: 2 k 13.1 / 22.3, 53 k 23.0 / 26.9, 200 k 52.5 / 64.4, 400 k 94 / 110; dense sets 300 k 77.4 / 72.8,
+    // 800 k 192 / 182).
+    if (K3 == 27 && C_in == 32 && C_out == 64 && likely <= (FUSED ? 16 : 3) * (int64_t)compute_units()) {
+        if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
+    }
     if ((FUSED && fused_gather) || (wide && likely <= 20 * (int64_t)compute_units())) {
         if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);

@@ -38,11 +38,11 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 //    a third of a step's instructions, and scalar ones issue once per four cycles for all wavefronts of a SIMD (us, before and
 //    with the list: K = 5 32 -> 32 4 k / 53 k voxels 22.7 / 32.1 -> 16.0 / 25.3, K = 5 64 -> 64 20 k 44.5 -> 34.2, 64 -> 64 4 k
 //    12.6 -> 10.3, 128 -> 256 5 k 19.4 -> 17.8, fp32 64 -> 64 8 k 23.4 -> 21.3, 32 -> 64 80 k 58.3 -> 55.3; 110 k and more the same).
-//  * FROM_LINES (K <= 3, 16 bit, 64 and more channels): the tile's lines of the map are copied to LDS at the start, beside the
+//  * FROM_LINES (K <= 3, 16 bit): the tile's lines of the map are copied to LDS at the start, beside the
 //    masks' round trip.  Read from the map step by step, 32 bytes at a time, they were a third of the loads that the address unit
 //    serves at 17 cycles each, and the first gathers waited for them (us, before -> with: 64 -> 64 110 k / 262 k / 10^6 voxels
 //    30.7 / 58.0 / 326 -> 29.4 / 54.4 / 302, 128 -> 128 20 k / 53 k / 262 k 21.4 / 43.6 / 152 -> 20.2 / 42.2 / 147, 256 -> 256 14 k 45.7 ->
-//    43.5).  7 KB of LDS: fp32 would lose a workgroup per CU to them; 32 channels, an offset a quarter of a step, gain nothing.
+//    43.5, 32 -> 64 2 k / 40 k 7.4 / 11.4 -> 7.1 / 11.1).  7 KB of LDS: fp32 would lose a workgroup per CU to them.
 //  * One wait for everything and one barrier per step.  What a step costs is issuing its loads (17
 //    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
 //  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(64 * NW, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
               int blocks_y, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
     constexpr bool FUSED = SRC == FROM_TABLE, HELD = SRC != FROM_MAP;      // HELD: the tile's entries are in LDS
-    static_assert(!HELD || (DT != SC_F32 && NW == 4 && KS > 1), "a quarter of the 27 offsets per wavefront");
+    static_assert(!HELD || (DT != SC_F32 && NW == 4), "a quarter of the 27 offsets per wavefront");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
     constexpr bool F32 = DT == SC_F32;
@@ -475,7 +475,7 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
     }
     if (K3 <= 27) {
         switch (C_in) {
-            case 32: break;
+            case 32: SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
             case 64: SC_GATHER_KS(2, 2, 1, 6, 5, FROM_LINES);
             case 128: SC_GATHER_KS(4, 4, 1, 4, 3, FROM_LINES);
             case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_LINES);
@@ -491,17 +491,18 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
     return SC_EINVAL;
 }
 
-// 3x3x3 layers that look their neighbours up in the dense table themselves: 64 and 128 channels, at least 64 out.
+// 3x3x3 layers that look their neighbours up in the dense table themselves: 32, 64 and 128 channels, at least 64 out.
 int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp,
                         void* out, int out_f32, const MapSource& ms, int64_t n) {
     const int CB = C_out / 16;
     if (CB < 4) return SC_EINVAL;
-#define SC_GATHER_FUSED(KS, SL, O1, O2)                                                                                                      \
+#define SC_GATHER_FUSED(KS, SL, SKIP, O1, O2)                                                                                                    \
     return dtype_in == SC_F16                                                                                                                \
-               ? launch_gather_ks<SC_F16, KS, SL, 1, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
-               : launch_gather_ks<SC_BF16, KS, SL, 1, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
-    if (C_in == 64) SC_GATHER_FUSED(2, 2, 6, 5);
-    if (C_in == 128) SC_GATHER_FUSED(4, 4, 4, 3);
+               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
+               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+    if (C_in == 32) SC_GATHER_FUSED(1, 4, 0, 2, 2);
+    if (C_in == 64) SC_GATHER_FUSED(2, 2, 1, 6, 5);
+    if (C_in == 128) SC_GATHER_FUSED(4, 4, 1, 4, 3);
 #undef SC_GATHER_FUSED
     return SC_EINVAL;
 }

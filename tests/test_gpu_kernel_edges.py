@@ -72,7 +72,7 @@ def test_streaming_kernel_strided_128_channels():
     assert err <= 1e-5, err
 
 
-@pytest.mark.parametrize("C_in,C_out", [(64, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("C_in,C_out", [(32, 64), (64, 64), (64, 128), (128, 128)])
 @pytest.mark.parametrize("n", [64, 129, 66000])
 def test_fused_general_kernel(C_in, C_out, n):
     """Look-ups inside the general kernel: a workgroup's tile is full, has one row, and two output blocks per
