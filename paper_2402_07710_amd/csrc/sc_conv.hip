@@ -666,8 +666,8 @@ static int launch_streamed(int K3, int C_in, int C_out, int64_t tiles, hipStream
 #define SC_STREAM(K3V, KSV, CBV, NWV, DV) \
     return launch_stream<DT, K3V, KSV, CBV, NWV, DV, FUSED>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
     if (K3 == 27 && C_in == 128 && C_out == 128) SC_STREAM(27, 4, 8, 8, 1);
-    if (K3 == 27 && C_in == 32 && C_out == 64) SC_STREAM(27, 1, 4, 4, 3);
     if constexpr (!FUSED) {
+        if (K3 == 27 && C_in == 32 && C_out == 64) SC_STREAM(27, 1, 4, 4, 3);
         if (K3 == 8 && C_in == 128 && C_out == 128) SC_STREAM(8, 4, 8, 8, 1);
     }
 #undef SC_STREAM
@@ -710,8 +710,8 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
                                                                         d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled);
         return rc;
     }
-    const bool fused_gather = C_in == 64 && (C_out == 64 || C_out == 128), wide = C_in == 128 && C_out == 128;
-    if (FUSED && !fused_gather && !wide && !(C_in == 32 && C_out == 64)) return SC_EINVAL;     // no fused kernel for this shape: use the three calls
+    const bool fused_gather = (C_in == 32 && C_out == 64) || (C_in == 64 && (C_out == 64 || C_out == 128)), wide = C_in == 128 && C_out == 128;
+    if (FUSED && !fused_gather && !wide) return SC_EINVAL;     // no fused kernel for this shape: use the three calls
     const uint4* wp = (const uint4*)d_weight;
     if (!packed) {
         if (int prc = pack_weights(K3, C_in, C_out, d_weight, d_workspace, s)) return prc;
@@ -721,15 +721,14 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // tiles and takes ~75 us however few there are; full, it moves the weights once for them (us, general and
     // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
     // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
-    // 32 -> 64, K = 3, up to three tiles per CU: there the streaming kernel's walk over all offsets, four tiles in step, is the
-    // longer chain (us, general and streaming kernel: 3 k voxels strided 7.6 / 9.9, 20 k 8.6 / 11.4, 30 k 9.6 / 12.6, 53 k 13.9 /
-    // 13.8, 110 k 23.2 / 20.3, 800 k indoor 163 / 129).  Fused, where the look-ups add to the walk of a wavefront with 64 rows, up to
-    // sixteen (whole layers: 2 k 13.1 / 22.3, 53 k 23.0 / 26.9, 200 k 52.5 / 64.4, 400 k 94 / 110; dense sets 300 k 77.4 / 72.8,
-    // 800 k 192 / 182).
-    if (K3 == 27 && C_in == 32 && C_out == 64 && likely <= (FUSED ? 16 : 3) * (int64_t)compute_units()) {
-        if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
+    // 32 -> 64, K = 3: the streaming kernel walks all offsets, four tiles in step, which is the longer chain of few tiles and the
+    // cheaper one of many dense ones.  The general kernel up to 13 tiles per CU, strided layers, whose rows have few neighbours
+    // each but most offsets, up to 7 (us, general and streaming kernel: 2 k voxels 7.1 / 9.1, 53 k 12.3 / 13.8, 110 k 20.3 / 20.2,
+    // 200 k 31.9 / 36.2, 262 k 39.4 / 39.0, indoor 100 k 23.1 / 22.9, 200 k 39.0 / 43.1, 800 k 144 / 130; strided 3 k 7.6 / 9.9, 53 k
+    // 14.7 / 18.2, 110 k 25.5 / 27.4, 150 k 31.6 / 29.1).  Fused, where the look-ups would add to the walk of a wavefront with 64
+    // rows, at every size (whole layers: 2 k 13.1 / 22.3, 53 k 22.5 / 27.0, 200 k 51.2 / 64.3, 400 k 88.5 / 108; indoor 800 k 184.7 / 182.7).
+    if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && likely <= (tiles == likely ? 13 : 7) * (int64_t)compute_units())
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
-    }
     if ((FUSED && fused_gather) || (wide && likely <= 20 * (int64_t)compute_units())) {
         if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);

@@ -449,6 +449,11 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
 #undef SC_GATHER
 }
 
+// 32-channel rows, K <= 3: steps of four offsets are the shorter walk as long as all workgroups are on the chip at once (39 KB of
+// LDS: four per CU); beyond two per CU steps of two (23 KB) and groups without a neighbour left out (us, four and two offsets:
+// 32 -> 64 20 k voxels 8.6 / 9.2, 40 k 11.1 / 10.9, 53 k 13.4 / 12.3, 200 k 34.9 / 31.9; strided 53 k 17.1 / 14.7; 32 -> 128 110 k 32.8 / 29.2).
+static bool likely_two_offsets(int64_t likely, int CB, int cus) { return likely * ((CB + 3) / 4) > 2 * (int64_t)cus; }
+
 int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const int CB = C_out / 16;
@@ -473,9 +478,12 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
 #undef SC_GATHER_F32
         return SC_EINVAL;
     }
+    const bool two_offsets = likely_two_offsets(likely, CB, cus);
     if (K3 <= 27) {
         switch (C_in) {
-            case 32: SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
+            case 32:
+                if (two_offsets) SC_GATHER_KS(1, 2, 1, 5, 4, FROM_LINES);
+                SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
             case 64: SC_GATHER_KS(2, 2, 1, 6, 5, FROM_LINES);
             case 128: SC_GATHER_KS(4, 4, 1, 4, 3, FROM_LINES);
             case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_LINES);
@@ -500,6 +508,7 @@ int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cu
     return dtype_in == SC_F16                                                                                                                \
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
                : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+    if (C_in == 32 && likely_two_offsets(tiles, CB, cus)) SC_GATHER_FUSED(1, 2, 1, 5, 4);
     if (C_in == 32) SC_GATHER_FUSED(1, 4, 0, 2, 2);
     if (C_in == 64) SC_GATHER_FUSED(2, 2, 1, 6, 5);
     if (C_in == 128) SC_GATHER_FUSED(4, 4, 1, 4, 3);

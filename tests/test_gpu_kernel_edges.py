@@ -72,6 +72,24 @@ def test_streaming_kernel_strided_128_channels():
     assert err <= 1e-5, err
 
 
+@pytest.mark.parametrize("stride,n", [(1, 213_100), (2, 114_800)])
+def test_streaming_kernel_32_to_64_channels(stride, n):
+    """The fewest tiles that take it: 13 per CU (of 256), strided layers 7 (rows of the input)."""
+    say(f"streaming kernel K=3 s={stride} 32->64")
+    import oracle
+    from tests.test_gpu_parity import rel_err, run_layer, sampled_rows_reference
+    mode = "subm" if stride == 1 else "strided"
+    coords = synth.uniform_cells(n, 90, seed=3)
+    feat, weight = synth.features(n, 32, "f16", 3), synth.weights(27, 32, 64, "f16", 3)
+    _, h, _, out = run_layer(coords, feat, weight, 3, stride, mode, "f16", out_dtype="f32")
+    km = oracle.kmap(coords, 3, stride, mode)
+    assert h.n_out == km["n_out"]
+    rows = np.unique(np.concatenate([np.random.default_rng(3).choice(h.n_out, 4000, replace=False), np.arange(200),
+                                     np.arange(h.n_out - 200, h.n_out)]))
+    err = rel_err(out[rows], sampled_rows_reference(feat, weight, km, rows)[rows])
+    assert err <= 1e-5, err
+
+
 @pytest.mark.parametrize("C_in,C_out", [(32, 64), (64, 64), (64, 128), (128, 128)])
 @pytest.mark.parametrize("n", [64, 129, 66000])
 def test_fused_general_kernel(C_in, C_out, n):
