@@ -593,15 +593,16 @@ static bool resident_shape(int K3, int C_in, int C_out, bool fused) {
                        (C_in == 64 && C_out == 32));
 }
 template <int DT, int FUSED, int WPACKED>
-static int launch_resident(int K3, int C_in, int C_out, int64_t tiles, hipStream_t s, const uint16_t* feat,
+static int launch_resident(int K3, int C_in, int C_out, int64_t tiles, int64_t likely, hipStream_t s, const uint16_t* feat,
                            const uint4* wp, void* out, int out_f32, const MapSource& ms, const int64_t* counts,
                            int64_t n_out_cap, bool* handled) {
     *handled = true;
 #define SC_ROWS16(K3V, KSV, CBV, NTV) \
     return launch_rows16<DT, K3V, KSV, CBV, NTV, FUSED, 0, WPACKED>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
-    // four tiles per workgroup once every CU still gets a workgroup: the weights are re-laid out
-    // half as often and no CU hosts two workgroups while another hosts one (cfg2: 11.9 -> 10.6 us)
-    if (K3 == 27 && C_in == 32 && C_out == 32 && tiles >= 512) SC_ROWS16(27, 1, 2, 4);
+    // four tiles per workgroup once the likely tiles still give two CUs one (half the copies of the weights, and no CU with
+    // two workgroups while another has one: 53 k voxels 11.9 -> 10.6 us with raw weights).  The likely ones: by the bound, 512
+    // tiles or more, strided layers of 10 k ... 30 k voxels took four and left most CUs idle (7.6 ... 8.1 us, now 6.1 ... 6.5).
+    if (K3 == 27 && C_in == 32 && C_out == 32 && likely >= 512) SC_ROWS16(27, 1, 2, 4);
     if (K3 == 27 && C_in == 32 && C_out == 32) SC_ROWS16(27, 1, 2, 2);
     if constexpr (!FUSED) {
         if (K3 == 8 && C_in == 32 && C_out == 64) SC_ROWS16(8, 1, 4, 2);
@@ -697,16 +698,24 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     const uint16_t* feat = (const uint16_t*)d_feat_in;
     bool handled = false;
     int rc;
-    if (resident_shape(K3, C_in, C_out, FUSED)) {
+    // From 9 tiles per CU the general kernel takes the square layers: by then the CUs run its workgroups in several rounds,
+    // one tile each, while the resident kernel's large workgroups end unevenly.  Packed weights only: raw ones would need a launch to pack
+    // them (us, resident and general kernel: 32 -> 32, K = 3: lidar 110 k 15.9 / 15.8, 131 k 16.3 / 17.7, 150 k 20.6 / 19.7, 200 k
+    // 24.8 / 24.2, indoor 200 k 34.7 / 31.1, 400 k 59.1 / 54.1, 800 k 108 / 104, strided 300 k 45.2 / 44.7; 64 -> 64, K = 2: 110 k
+    // 9.8 / 9.75, 150 k 15.0 / 11.6, 200 k 16.9 / 14.1, indoor 400 k 20.9 / 19.2, 500 k 27.8 / 21.1.  The other K = 2 shapes stay:
+    // 32 -> 32 200 k 6.3 / 8.1, 32 -> 64 9.7 / 12.3, indoor 500 k 16.0 / 17.05).
+    const bool outgrown = packed && !FUSED && likely > 9 * (int64_t)compute_units() &&
+                          ((K3 == 27 && C_in == 32 && C_out == 32) || (K3 == 8 && C_in == 64 && C_out == 64));
+    if (resident_shape(K3, C_in, C_out, FUSED) && !outgrown) {
         if (packed)
-            rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 1>(K3, C_in, C_out, tiles, s, feat, (const uint4*)d_weight,
+            rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
                                                                        d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled)
-                                    : launch_resident<SC_BF16, FUSED, 1>(K3, C_in, C_out, tiles, s, feat, (const uint4*)d_weight,
+                                    : launch_resident<SC_BF16, FUSED, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
                                                                         d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled);
         else
-            rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 0>(K3, C_in, C_out, tiles, s, feat, (const uint4*)d_weight,
+            rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 0>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
                                                                        d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled)
-                                    : launch_resident<SC_BF16, FUSED, 0>(K3, C_in, C_out, tiles, s, feat, (const uint4*)d_weight,
+                                    : launch_resident<SC_BF16, FUSED, 0>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
                                                                         d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled);
         return rc;
     }

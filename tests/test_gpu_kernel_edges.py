@@ -90,6 +90,32 @@ def test_streaming_kernel_32_to_64_channels(stride, n):
     assert err <= 1e-5, err
 
 
+@pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457),
+                                          (3, 2, 32, 32_640), (3, 2, 32, 32_705)])
+def test_packed_square_layers_beyond_the_resident_kernel(K, stride, C, n):
+    """Packed weights, the fewest tiles (9 per CU of 256, one row more) that go through the general kernel; strided
+    layers at 510 and 512 likely tiles, where the resident kernel takes two and four tiles per workgroup."""
+    say(f"packed K={K} s={stride} {C}->{C} n={n}")
+    import oracle
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import rel_err, sampled_rows_reference, to_dev
+    mode = "subm" if stride == 1 else "strided"
+    coords = synth.uniform_cells(n, 80, seed=5)
+    feat, weight = synth.features(n, C, "f16", 5), synth.weights(K ** 3, C, C, "f16", 5)
+    buf = sc.LayerBuffers(n, K, stride, mode, C, C, "f16", out_dtype="f32", device="cuda:0")
+    buf.feat_out.fill_(float("nan"))
+    buf.hash_build(torch.from_numpy(coords).to("cuda:0"))
+    buf.kmap_build(torch.from_numpy(coords).to("cuda:0"))
+    buf.conv_fwd_packed(to_dev(feat, "f16"), sc.sc_conv_weight_pack(to_dev(weight, "f16"), K))
+    km = oracle.kmap(coords, K, stride, mode)
+    assert buf.read_counts().n_out == km["n_out"]
+    rows = np.unique(np.concatenate([np.random.default_rng(5).choice(km["n_out"], 3000, replace=False), np.arange(200),
+                                     np.arange(km["n_out"] - 200, km["n_out"])]))
+    err = rel_err(buf.feat_out.cpu().numpy()[rows], sampled_rows_reference(feat, weight, km, rows)[rows])
+    assert err <= 1e-5, err
+
+
 @pytest.mark.parametrize("C_in,C_out", [(32, 64), (64, 64), (64, 128), (128, 128)])
 @pytest.mark.parametrize("n", [64, 129, 66000])
 def test_fused_general_kernel(C_in, C_out, n):
