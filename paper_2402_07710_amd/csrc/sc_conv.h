@@ -19,6 +19,15 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __host__ __device__ constexpr int wtile(int KS, int CB, int cb, int ks) {
     return KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1);
 }
+// Group masks from a line of the offset table (lane = row of the tile): bit of each group that has a neighbour.  Maps of
+// strided layers up to K^3 = 32 come without masks (MapSource::gmask null): the kernels read the lines anyway.
+__device__ inline uint32_t line_pattern(int32_t entry) {
+    const uint64_t vote = __ballot(entry >= 0);
+    uint32_t pat = 0u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) pat |= (((vote >> (16 * g)) & 0xffffull) != 0ull ? 1u : 0u) << g;
+    return pat;
+}
 // Workgroup barrier for data exchanged through LDS only.  __syncthreads() also waits until every
 // outstanding global load of the wavefront has returned (vmcnt(0)), which would drain the gathers
 // and weight fetches that were issued ahead on purpose; here only the wavefront's LDS operations

@@ -100,7 +100,12 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
         const int32_t* line = nbr + tile * (int64_t)(K3 * TILE) + q * 16 + r;
 #pragma unroll
         for (int k = 0; k < K3; ++k) e[k] = line[k * TILE];
-        m = gmask[tile * 4 + q];
+        if (gmask != nullptr) {
+            m = gmask[tile * 4 + q];
+        } else {
+#pragma unroll
+            for (int k = 0; k < K3; ++k) m |= (__ballot(e[k] >= 0) != 0ull ? 1u : 0u) << k;
+        }
     } else {
 #pragma unroll
         for (int k = 0; k < K3; ++k) e[k] = -1;
@@ -278,7 +283,15 @@ k_conv_stream(const uint16_t* __restrict__ feat, const uint4* wp, void* __restri
 #pragma unroll
             for (int k = 0; k < K3; ++k) v[k] = line[k * TILE];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) mg[g] = gmask[tile * 4 + g];
+            for (int g = 0; g < 4; ++g) mg[g] = gmask != nullptr ? gmask[tile * 4 + g] : 0u;
+            if (gmask == nullptr) {
+#pragma unroll
+                for (int k = 0; k < K3; ++k) {
+                    const uint32_t pat = line_pattern(v[k]);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) mg[g] |= ((pat >> g) & 1u) << k;
+                }
+            }
         } else {
 #pragma unroll
             for (int k = 0; k < K3; ++k) v[k] = -1;
@@ -389,6 +402,12 @@ k_conv_stream(const uint16_t* __restrict__ feat, const uint4* wp, void* __restri
 }
 
 constexpr int CB_MAX = 16;
+// The mask word of a 16-row group of a map without masks (K^3 <= 32): line = its first entry, at the lane's row.
+__device__ inline uint32_t vote_mask(const int32_t* line, int K3) {
+    uint32_t m = 0u;
+    for (int k = 0; k < K3; ++k) m |= (__ballot(line[(int64_t)k * TILE] >= 0) != 0ull ? 1u : 0u) << k;
+    return m;
+}
 // ---- fp32 features and weights -------------------------------------------------------------------
 // Same scheme with the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: true fp32 products and
 // sums): one wavefront per 16 output rows, offsets walked by mask bit, operands read straight from
@@ -412,7 +431,7 @@ k_conv_f32(const float* __restrict__ feat, const float* __restrict__ w, float* _
     for (int cb = 0; cb < CB_MAX; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int32_t* line = nbr + tile * (int64_t)K3 * TILE + q * 16 + r;
     for (int wi = 0; wi < mw; ++wi) {
-        uint32_t m = gmask[(tile * 4 + q) * mw + wi];
+        uint32_t m = gmask != nullptr ? gmask[(tile * 4 + q) * mw + wi] : vote_mask(line, K3);
         while (m) {
             const int k = wi * 32 + __builtin_ctz(m);
             m &= m - 1;
@@ -475,7 +494,13 @@ k_conv_f32_first(const float* __restrict__ feat, const float* __restrict__ w, fl
     int32_t e[K3];
 #pragma unroll
     for (int k = 0; k < K3; ++k) e[k] = row < n_out ? line[k * TILE] : -1;
-    const uint32_t m = __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]);
+    uint32_t m = 0u;
+    if (gmask != nullptr) {
+        m = __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < K3; ++k) m |= (__ballot(e[k] >= 0) != 0ull ? 1u : 0u) << k;
+    }
     for (int i = threadIdx.x; i < K3 * C_out; i += 256) {           // 16 bytes each
         const int col = i % (C_out / 4), kc = i / (C_out / 4), ci = kc & 3;
         reinterpret_cast<float4*>(w_s)[i] =
@@ -528,7 +553,7 @@ k_conv_f32_small(const float* __restrict__ feat, const float* __restrict__ w, fl
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int32_t* line = nbr + tile * (int64_t)K3 * TILE + q * 16 + r;
-    uint32_t m = __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]);
+    uint32_t m = gmask != nullptr ? __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]) : vote_mask(line, K3);
     while (m) {
         int kk[NB];
         int32_t e[NB];
@@ -784,7 +809,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     if (tiles == 0) return SC_OK;
     // tiles to expect: strided layers on surfaces have about as many output rows as input rows, their bound is up to 8 times that
     const int64_t n_map_tiles = (n_map + TILE - 1) / TILE, likely = tiles < n_map_tiles ? tiles : n_map_tiles;
-    const uint32_t* gmask = (const uint32_t*)((const char*)d_kmap + L.off_mask);
+    const uint32_t* gmask = kmap_masked(mode, L.K3) ? (const uint32_t*)((const char*)d_kmap + L.off_mask) : nullptr;
     const int32_t* nbr = (const int32_t*)((const char*)d_kmap + L.off_nbr);
     hipStream_t s = (hipStream_t)stream;
 
@@ -903,7 +928,7 @@ extern "C" int sc_conv_up_fwd(const void* d_feat_coarse, int64_t n_map, const vo
     const KmapLayout L = kmap_layout(sc_out_bound(n_map, K, K, SC_STRIDED), K);
     if (L.tiles == 0) return SC_OK;
     MapSource ms{};
-    ms.gmask = (const uint32_t*)((const char*)d_kmap + L.off_mask);
+    ms.gmask = kmap_masked(SC_STRIDED, L.K3) ? (const uint32_t*)((const char*)d_kmap + L.off_mask) : nullptr;
     ms.nbr = (const int32_t*)((const char*)d_kmap + L.off_nbr);
     bool handled = false;
     // the kernel walks the coarse rows: counts->n_out of them, at most the map's bound

@@ -131,18 +131,38 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
             for (int u = 0; u < 7; ++u) part[u] = wv + 4 * u < K3 ? nbr[(tile * K3 + wv + 4 * u) * TILE + lane] : -1;
         }
-        for (int k = lane; k - lane < K3; k += WAVE) {
-            uint32_t pat = 0u;
-            if (k < K3) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
-            }
-            add_to_list(k, pat);
-        }
-        if constexpr (HELD) {
+        auto hold = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < 7; ++u) found[(wv + 4 * u) * TILE + lane] = part[u];
+        };
+        if (gmask != nullptr) {
+            for (int k = lane; k - lane < K3; k += WAVE) {
+                uint32_t pat = 0u;
+                if (k < K3) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
+                }
+                add_to_list(k, pat);
+            }
+            if constexpr (HELD) {
+                hold();
+                __syncthreads();
+            }
+        } else {
+            // a map without masks (K^3 <= 32): its lines are voted on, every NWth by a wavefront, and the patterns traded through
+            // LDS, in the half of the rows' buffer that is filled second
+            uint32_t* patterns = reinterpret_cast<uint32_t*>(smem + STEP_BYTES);
+            if constexpr (HELD) hold();
+#pragma unroll
+            for (int u = 0; u < 32 / NW; ++u) {
+                const int k = wv + NW * u;
+                if (k < K3) {
+                    const uint32_t pat = line_pattern(HELD && u < 7 ? part[u] : nbr[(tile * K3 + k) * TILE + lane]);
+                    if (lane == 0) patterns[k] = pat;
+                }
+            }
             __syncthreads();
+            add_to_list(lane, lane < K3 ? patterns[lane] : 0u);
         }
     }
     if (lane < LIST_PAD) list[listed + lane] = 0u;
@@ -403,7 +423,7 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (SRC != FROM_MAP ? 28 * TILE * 4 + 64 : 0);
     static_assert(fixed <= 65536 + 28 * TILE * 4 + 64, "loads into LDS land in the first 64 KB");
-    const size_t lds = fixed + (size_t)(K3 + LIST_PAD + 3) / 4 * 16;
+    const size_t lds = fixed + (size_t)((SRC != FROM_MAP && K3 < 27 ? 27 : K3) + LIST_PAD + 3) / 4 * 16;     // entries lie behind a list of 27
     if constexpr (fixed + (343 + LIST_PAD + 3) / 4 * 16 > 65536) {
         static bool allowed[MAX_DEVICES] = {};
         if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>, fixed + (343 + LIST_PAD + 3) / 4 * 16, allowed)) return rc;

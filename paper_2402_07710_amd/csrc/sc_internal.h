@@ -230,7 +230,9 @@ __device__ inline void grid_neighbours_quarter(const MapSource& ms, int64_t row,
 // output row 64t+j at offset k, or -1: the paper's offset table (Section III-C.2), stored
 // offset-major inside a tile so that the 16 rows an MFMA group takes are 64 contiguous bytes.
 // Bit k of mask[t][q] (word k/32) says whether any of the rows 16q..16q+15 of tile t has a
-// neighbour at offset k; the convolution skips the groups whose bit is clear.
+// neighbour at offset k; the convolution skips the groups whose bit is clear.  Strided maps up to K^3 = 32 leave the masks
+// unwritten (kmap_masked): every kernel that reads such a map votes over its lines, which it reads anyway, and the pass
+// over the finished table that made the masks was a launch of 4.5 us in a chain of small kernels.
 struct KmapHeader {
     uint32_t magic;
     int32_t K, stride, mode;
@@ -246,6 +248,7 @@ struct KmapLayout {
     size_t off_nbr;
     size_t bytes;
 };
+inline bool kmap_masked(int mode, int K3) { return mode != SC_STRIDED || K3 > 32; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline KmapLayout kmap_layout(int64_t n_out_bound, int K) {
     KmapLayout L;

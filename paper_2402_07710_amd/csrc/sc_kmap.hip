@@ -782,7 +782,7 @@ static bool kmap_args_ok(int64_t n, int K, int stride, int mode) {
 static uint64_t strided_slots(int K, int stride) { return K == stride && K <= 4 ? 8 : 2; }
 
 // The strided build (arguments checked by the caller): clear the cell table -> claim cells -> flag first
-// candidates, clear the rows of the offset table -> number cells, write pairs -> group masks.
+// candidates, clear the rows of the offset table -> number cells, write pairs (-> group masks, K^3 > 32).
 template <class Shape>
 static int build_strided(const Shape& sh, const int32_t* d_coords, int64_t n, const void* d_table, int K, int stride, int32_t* d_out_coords,
                          void* d_kmap, const KmapLayout& L, const KmapHeader& h, void* d_scratch, sc_counts* d_counts, hipStream_t s) {
@@ -815,8 +815,9 @@ static int build_strided(const Shape& sh, const int32_t* d_coords, int64_t n, co
     else if (nc <= (int64_t)SCAN_IN_PAIRS_MAX * 4096) SC_STRIDED_NUMBER(1, 4);
     else SC_STRIDED_NUMBER(0, 4);
 #undef SC_STRIDED_NUMBER
-    SC_LAUNCH(KID_KMAP_FROM_OFT, k_masks_from_table, dim3((unsigned)L.tiles), dim3(256), 0, s, (const int32_t*)nbr, L.K3, L.mw, L.tiles, gmask,
-              (const sc_counts*)d_counts);
+    if (kmap_masked(SC_STRIDED, L.K3))
+        SC_LAUNCH(KID_KMAP_FROM_OFT, k_masks_from_table, dim3((unsigned)L.tiles), dim3(256), 0, s, (const int32_t*)nbr, L.K3, L.mw, L.tiles, gmask,
+                  (const sc_counts*)d_counts);
     return SC_OK;
 }
 

@@ -312,3 +312,13 @@ def test_inverse_map_of_rows_without_a_parent(K, stale):
     got = out.double().cpu().numpy()
     assert np.all(got[out_of_domain] == 0)
     assert rel_err(got[kept], oracle.conv(feat, weight, ref, threads=8)) <= TOL["f16"]
+
+
+@pytest.mark.parametrize("K,C_in,C_out,dtype", [(3, 3, 16, "f32"), (3, 5, 7, "f32"), (3, 16, 32, "f32"), (3, 64, 64, "f32"), (3, 32, 32, "f16"), (3, 32, 80, "bf16"),
+                                                (3, 128, 64, "f16"), (2, 5, 20, "f32"), (2, 32, 16, "f32"), (2, 128, 32, "f32"), (2, 32, 64, "f16"), (2, 256, 48, "bf16"),
+                                                (4, 64, 32, "f16"), (4, 16, 64, "f32")])
+@pytest.mark.parametrize("n", [1, 65, 1500])
+def test_strided_maps_with_and_without_masks(K, C_in, C_out, dtype, n):
+    """K <= 3: every kernel votes over the map's lines, also those of a last tile that is not full; K = 4: masks of two words."""
+    say(f"strided K={K} {C_in}->{C_out} {dtype} n={n}")
+    check_layer(synth.uniform_cells(n, 6 if n < 100 else 14, seed=C_in + n), K, 2, "strided", C_in, C_out, dtype, seed=n)
