@@ -191,7 +191,8 @@ size_t sc_kmap_scratch_bytes(int64_t n, int K, int stride, int mode);
  *                 Section III-C.2 (for every output row and offset the paired input row or -1),
  *                 tile-major: 64 consecutive output rows per tile, offset-major inside a tile,
  *                 plus one bit per (16-row group, offset) that tells whether the group has any
- *                 neighbour there.  Read it with sc_kmap_export; feed it to sc_conv_fwd (any
+ *                 neighbour there (strided maps: K^3 > 32 only) and, K == stride <= 4, every
+ *                 input's output row and offset.  Read it with sc_kmap_export; feed it to sc_conv_fwd (any
  *                 number of times: layers that share coordinates share the map).
  *   d_scratch     scratch_bytes >= sc_kmap_scratch_bytes(...); contents undefined afterwards.
  *   d_counts      n_out is written here (device side); errors are latched into status. */

@@ -803,7 +803,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     if (kmap_bytes < sc_kmap_bytes(n_map, K, stride, mode)) return SC_ECAP;
     // rows of the output: what the map build counted, or (inverse layers) the rows it was built from
     const int64_t* n_out_ptr = mode == SC_INVERSE ? &d_counts->n_in : &d_counts->n_out;
-    const KmapLayout L = kmap_layout(bound, K);
+    const KmapLayout L = kmap_layout(bound, K, stride, mode);
     int64_t tiles = (n_out_cap + TILE - 1) / TILE;
     if (tiles > L.tiles) tiles = L.tiles;
     if (tiles == 0) return SC_OK;
@@ -925,7 +925,7 @@ extern "C" int sc_conv_up_fwd(const void* d_feat_coarse, int64_t n_map, const vo
     if (dtype_in != SC_F16 && dtype_in != SC_BF16) return SC_EINVAL;
     if (dtype_out != SC_F32 && dtype_out != dtype_in) return SC_EINVAL;
     if (kmap_bytes < sc_kmap_bytes(n_map, K, K, SC_STRIDED)) return SC_ECAP;
-    const KmapLayout L = kmap_layout(sc_out_bound(n_map, K, K, SC_STRIDED), K);
+    const KmapLayout L = kmap_layout(sc_out_bound(n_map, K, K, SC_STRIDED), K, K, SC_STRIDED);
     if (L.tiles == 0) return SC_OK;
     MapSource ms{};
     ms.gmask = kmap_masked(SC_STRIDED, L.K3) ? (const uint32_t*)((const char*)d_kmap + L.off_mask) : nullptr;

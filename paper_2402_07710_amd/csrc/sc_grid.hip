@@ -199,7 +199,7 @@ extern "C" int sc_kmap_build_grid(const int32_t* d_coords, int64_t n, const void
     if (grid_bytes < need) return SC_ECAP;
     if (kmap_bytes < sc_kmap_bytes(n, K, 1, SC_SUBM)) return SC_ECAP;
     hipStream_t s = (hipStream_t)stream;
-    const KmapLayout L = kmap_layout(n, K);
+    const KmapLayout L = kmap_layout(n, K, 1, SC_SUBM);
     KmapHeader hv = {KMAP_MAGIC, K, 1, SC_SUBM, n, n, L.tiles, L.mw, 0};
     KmapHeader* hdr = (KmapHeader*)d_kmap;
     if (n == 0) {

@@ -225,7 +225,7 @@ __device__ inline void grid_neighbours_quarter(const MapSource& ms, int64_t row,
 }
 
 // ---- kernel-map blob ------------------------------------------------------------------------
-// header | mask[T][4][mw] (uint32) | nbr[T][K3][TILE] (int32)
+// header | mask[T][4][mw] (uint32) | nbr[T][K3][TILE] (int32) | strided maps, K == stride <= 4: parent[n] (uint32)
 // Outputs are cut into tiles of 64 consecutive rows.  nbr[t][k][j] is the input row paired with
 // output row 64t+j at offset k, or -1: the paper's offset table (Section III-C.2), stored
 // offset-major inside a tile so that the 16 rows an MFMA group takes are 64 contiguous bytes.
@@ -246,11 +246,13 @@ struct KmapLayout {
     int mw;               // mask words per (tile, quarter) = ceil(K3 / 32)
     size_t off_mask;      // byte offsets inside the blob
     size_t off_nbr;
+    size_t off_parent;    // 0: none
     size_t bytes;
 };
+// parent[i] = (output row << 6) | offset of input i, all ones where it has none: what sc_kmap_transpose makes the inverse map of.
 inline bool kmap_masked(int mode, int K3) { return mode != SC_STRIDED || K3 > 32; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
-inline KmapLayout kmap_layout(int64_t n_out_bound, int K) {
+inline KmapLayout kmap_layout(int64_t n_out_bound, int K, int stride, int mode) {
     KmapLayout L;
     L.K3 = K * K * K;
     L.mw = (L.K3 + 31) / 32;
@@ -258,6 +260,11 @@ inline KmapLayout kmap_layout(int64_t n_out_bound, int K) {
     L.off_mask = 256;
     L.off_nbr = align_up(L.off_mask + (size_t)L.tiles * 4 * L.mw * sizeof(uint32_t), 256);
     L.bytes = align_up(L.off_nbr + (size_t)L.tiles * L.K3 * TILE * sizeof(int32_t), 256);
+    L.off_parent = 0;
+    if (mode == SC_STRIDED && K == stride && K <= 4) {       // one output row at most per input: n_out_bound inputs
+        L.off_parent = L.bytes;
+        L.bytes = align_up(L.off_parent + (size_t)n_out_bound * sizeof(uint32_t), 256);
+    }
     return L;
 }
 

@@ -585,7 +585,7 @@ __global__ void __launch_bounds__(256)
 k_strided_pairs(const int4* __restrict__ coords, int64_t n, Shape sh, const int32_t* __restrict__ cand_slot,
                 const int32_t* __restrict__ oslots, const uint64_t* __restrict__ flagword, const int32_t* __restrict__ word_prefix,
                 const int32_t* __restrict__ block_prefix, const int32_t* __restrict__ block_sum, int nblk, int32_t* __restrict__ nbr,
-                int4* __restrict__ out_coords, sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
+                uint32_t* __restrict__ parent, int4* __restrict__ out_coords, sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
     __shared__ int32_t prefix_s[SCAN ? SCAN_IN_PAIRS_MAX : 1];
     __shared__ int32_t wave_s[4];
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -597,7 +597,10 @@ k_strided_pairs(const int4* __restrict__ coords, int64_t n, Shape sh, const int3
     }
     if (id >= n * sh.maxc()) return;
     const int32_t sl = cand_slot[id];
-    if (sl < 0) return;
+    if (sl < 0) {
+        if (parent != nullptr) parent[id] = ~0u;
+        return;
+    }
     const uint32_t i = (uint32_t)id / (uint32_t)sh.maxc();
     const int4 c = coords[i];
     const int32_t r = oslots[sl];                              // the cell's first candidate
@@ -607,6 +610,7 @@ k_strided_pairs(const int4* __restrict__ coords, int64_t n, Shape sh, const int3
     // one input per (output row, offset): a plain store is enough; repeated input coordinates are the
     // location table's business (sc_hash_build latches SC_EDUP)
     nbr[((int64_t)(o >> 6) * (sh.K() * sh.K() * sh.K()) + q.k) * TILE + (o & 63)] = (int32_t)i;
+    if (parent != nullptr) parent[id] = (uint32_t)o << 6 | (uint32_t)q.k;      // one candidate per input: id is its row
     if (r == (int32_t)id) out_coords[o] = make_int4(c.x, q.qx, q.qy, q.qz);
 }
 
@@ -715,42 +719,26 @@ k_write_starts(StartArg a, int count, int32_t* __restrict__ dst) {
     for (int i = threadIdx.x; i < count; i += blockDim.x) dst[i] = a.v[i];
 }
 
-// Inverse layer (Section III-E): the pairs of a strided map with input and output swapped.  Every fine
-// row has one parent (K == stride), so the inverse map is made from one word per fine row: a first
-// kernel scatters (coarse row, offset) to the place of the row's first table entry, a second one
-// expands the 64 words of a tile to its K^3 lines and group masks.  Against filling the table with -1,
-// scattering into it and reading it back for the masks that is a kernel less and 4 bytes per row
-// scattered into 1/K^3 of the table (calls back to back, K = 2, 10 k / 53 k / 200 k rows: 12.5 / 12.4 / 16.0 -> 5.6 / 5.4 / 7.0 us).
-// One wavefront per coarse tile and offset line.
+// Inverse layer (Section III-E): the pairs of a strided map with input and output swapped.  Every fine row has one parent
+// (K == stride); the strided build leaves (coarse row, offset) in one word per fine row, and this kernel expands the 64
+// words of a tile to its K^3 lines and group masks.  Finding the words again by scattering the strided table was a kernel of its
+// own, a launch of 4 us (transpose and 64 -> 32 convolution on 53 k rows 11.7 -> 9.2 us).
+// One wavefront per fine tile, lane = row.  A word counts only if the strided map confirms it: of inputs with the same
+// coordinate the map holds one.
 __global__ void __launch_bounds__(256)
-k_transpose_parents(const int32_t* __restrict__ nbr, int K3, const sc_counts* __restrict__ counts, int32_t* __restrict__ inv_nbr) {
-    const int lane = threadIdx.x & 63;
-    const int64_t tiles = (counts->n_out + TILE - 1) / TILE;
-    const int64_t items = tiles * K3;
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t it = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); it < items; it += nwaves) {
-        const int64_t t = it / K3;
-        const int k = (int)(it - t * K3);
-        const int32_t i = nbr[it * TILE + lane];
-        // row < 2^26, offset < 64: K <= 4
-        if (i >= 0) inv_nbr[(int64_t)(i >> 6) * (K3 * TILE) + (i & 63)] = (int32_t)(((uint32_t)(t * TILE + lane) << 6) | (uint32_t)k);
-    }
-}
-// One wavefront per fine tile, lane = row.  A row that the strided build left out (coordinate outside
-// the domain) has no word: what lies there counts only if the strided map confirms it.
-__global__ void __launch_bounds__(256)
-k_transpose_expand(const int32_t* __restrict__ nbr, int K3, int mw, int64_t n, const sc_counts* __restrict__ counts, int32_t* inv_nbr,
-                   uint32_t* __restrict__ inv_mask, KmapHeader* hdr, KmapHeader hdr_value) {
+k_transpose_expand(const int32_t* __restrict__ nbr, const uint32_t* __restrict__ parent, int K3, int mw, int64_t n,
+                   const sc_counts* __restrict__ counts, int32_t* __restrict__ inv_nbr, uint32_t* __restrict__ inv_mask, KmapHeader* hdr,
+                   KmapHeader hdr_value) {
     const int lane = threadIdx.x & 63;
     if (blockIdx.x == 0 && threadIdx.x == 0) *hdr = hdr_value;
     const int64_t tile = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (tile * TILE >= n) return;
     const int64_t row = tile * TILE + lane, n_out = counts->n_out;
     int32_t* lines = inv_nbr + tile * (int64_t)(K3 * TILE) + lane;
-    const uint32_t word = (uint32_t)lines[0];
+    const uint32_t word = row < n ? parent[row] : ~0u;
     const int64_t o = word >> 6;
     int k = (int)(word & 63u);
-    if (row >= n || o >= n_out || k >= K3 || nbr[((o >> 6) * K3 + k) * TILE + (o & 63)] != (int32_t)row) k = -1;
+    if (o >= n_out || k >= K3 || nbr[((o >> 6) * K3 + k) * TILE + (o & 63)] != (int32_t)row) k = -1;
     for (int w = 0; w < mw; ++w) {
         uint32_t bits = 0;                            // lanes 0..3: group `lane`
         for (int kk = w * 32; kk < K3 && kk < w * 32 + 32; ++kk) {
@@ -788,6 +776,7 @@ static int build_strided(const Shape& sh, const int32_t* d_coords, int64_t n, co
                          void* d_kmap, const KmapLayout& L, const KmapHeader& h, void* d_scratch, sc_counts* d_counts, hipStream_t s) {
     uint32_t* gmask = (uint32_t*)((char*)d_kmap + L.off_mask);
     int32_t* nbr = (int32_t*)((char*)d_kmap + L.off_nbr);
+    uint32_t* parent = L.off_parent != 0 ? (uint32_t*)((char*)d_kmap + L.off_parent) : nullptr;
     const int64_t nc = n * strided_maxc(K, stride);            // candidates
     StridedScratch g = strided_scratch(d_scratch, nc, strided_slots(K, stride));
     const uint64_t cap = (uint64_t)g.omask + 1;
@@ -808,7 +797,7 @@ static int build_strided(const Shape& sh, const int32_t* d_coords, int64_t n, co
                       d_counts);                                                                                                       \
         SC_LAUNCH(KID_STRIDED_PAIRS, (k_strided_pairs<SCAN, U, Shape>), dim3(gp), dim3(256), 0, s, (const int4*)d_coords, n, sh,       \
                   (const int32_t*)g.slot_of, (const int32_t*)g.oslots, (const uint64_t*)g.flagword, (const int32_t*)g.word_prefix,     \
-                  (const int32_t*)g.block_prefix, (const int32_t*)g.block_sum, (int)nblk, nbr, (int4*)d_out_coords, d_counts,          \
+                  (const int32_t*)g.block_prefix, (const int32_t*)g.block_sum, (int)nblk, nbr, parent, (int4*)d_out_coords, d_counts,          \
                   (KmapHeader*)d_kmap, h);                                                                                             \
     } while (0)
     if (nc <= 512 * 1024) SC_STRIDED_NUMBER(1, 1);
@@ -832,7 +821,7 @@ extern "C" int64_t sc_out_bound(int64_t n, int K, int stride, int mode) {
 
 extern "C" size_t sc_kmap_bytes(int64_t n, int K, int stride, int mode) {
     if (!kmap_args_ok(n, K, stride, mode)) return 0;
-    return kmap_layout(sc_out_bound(n, K, stride, mode), K).bytes;
+    return kmap_layout(sc_out_bound(n, K, stride, mode), K, stride, mode).bytes;
 }
 
 extern "C" size_t sc_kmap_scratch_bytes(int64_t n, int K, int stride, int mode) {
@@ -857,7 +846,7 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
 
     hipStream_t s = (hipStream_t)stream;
     const int64_t bound = sc_out_bound(n, K, stride, mode);
-    const KmapLayout L = kmap_layout(bound, K);
+    const KmapLayout L = kmap_layout(bound, K, stride, mode);
     uint32_t* gmask = (uint32_t*)((char*)d_kmap + L.off_mask);
     int32_t* nbr = (int32_t*)((char*)d_kmap + L.off_nbr);
     KmapHeader h{};
@@ -962,7 +951,7 @@ extern "C" int sc_kmap_transpose(const void* d_kmap, int64_t n, int K, int strid
     if (!aligned16(d_kmap) || !aligned16(d_kmap_inv) || !aligned16(d_counts)) return SC_EINVAL;
     if (kmap_inv_bytes < sc_kmap_bytes(n, K, stride, SC_INVERSE)) return SC_ECAP;
     hipStream_t s = (hipStream_t)stream;
-    const KmapLayout L = kmap_layout(n, K);          // same shape for both directions when K == stride
+    const KmapLayout L = kmap_layout(n, K, stride, SC_STRIDED);      // offset table and masks lie alike in both directions
     KmapHeader h{};
     h.magic = KMAP_MAGIC; h.K = K; h.stride = stride; h.mode = SC_INVERSE;
     h.n_in = n; h.n_out_bound = n; h.tiles = L.tiles; h.mw = L.mw;
@@ -973,11 +962,8 @@ extern "C" int sc_kmap_transpose(const void* d_kmap, int64_t n, int K, int strid
     const int32_t* nbr = (const int32_t*)((const char*)d_kmap + L.off_nbr);
     int32_t* inv_nbr = (int32_t*)((char*)d_kmap_inv + L.off_nbr);
     uint32_t* inv_mask = (uint32_t*)((char*)d_kmap_inv + L.off_mask);
-    int64_t items = L.tiles * L.K3;
-    unsigned gb = (unsigned)((items + 3) / 4);
-    if (gb > 4096) gb = 4096;
-    SC_LAUNCH(KID_MISC, k_transpose_parents, dim3(gb), dim3(256), 0, s, nbr, L.K3, d_counts, inv_nbr);
-    SC_LAUNCH(KID_KMAP_FROM_OFT, k_transpose_expand, dim3((unsigned)((L.tiles + 3) / 4)), dim3(256), 0, s, nbr, L.K3, L.mw, n, d_counts,
+    const uint32_t* parent = (const uint32_t*)((const char*)d_kmap + L.off_parent);
+    SC_LAUNCH(KID_KMAP_FROM_OFT, k_transpose_expand, dim3((unsigned)((L.tiles + 3) / 4)), dim3(256), 0, s, nbr, parent, L.K3, L.mw, n, d_counts,
               inv_nbr, inv_mask, (KmapHeader*)d_kmap_inv, h);
     return SC_OK;
 }
@@ -988,7 +974,7 @@ extern "C" int sc_counts_read(sc_counts* d_counts, sc_counts* h_counts, const vo
     hipStream_t s = (hipStream_t)stream;
     if (d_kmap != nullptr) {
         if (!kmap_args_ok(n, K, stride, mode)) return SC_EINVAL;
-        const KmapLayout L = kmap_layout(sc_out_bound(n, K, stride, mode), K);
+        const KmapLayout L = kmap_layout(sc_out_bound(n, K, stride, mode), K, stride, mode);
         SC_LAUNCH(KID_MISC, k_counts_clear_pairs, dim3(1), dim3(256), 0, s, d_counts);
         if (L.tiles > 0) {
             int64_t items = L.tiles * L.K3;
@@ -1011,7 +997,7 @@ extern "C" int sc_kmap_export(const void* d_kmap, int64_t n, int K, int stride, 
     if (h_counts->n_pairs > 0 && (d_pairs_in == nullptr || d_pairs_out == nullptr)) return SC_EINVAL;
     if (h_counts->n_pairs > 0x7fffffffLL) return SC_ECAP;
     hipStream_t s = (hipStream_t)stream;
-    const KmapLayout L = kmap_layout(sc_out_bound(n, K, stride, mode), K);
+    const KmapLayout L = kmap_layout(sc_out_bound(n, K, stride, mode), K, stride, mode);
     StartArg h_start{};
     int32_t acc = 0;
     for (int k = 0; k < L.K3; ++k) {

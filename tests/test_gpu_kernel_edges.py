@@ -322,3 +322,25 @@ def test_strided_maps_with_and_without_masks(K, C_in, C_out, dtype, n):
     """K <= 3: every kernel votes over the map's lines, also those of a last tile that is not full; K = 4: masks of two words."""
     say(f"strided K={K} {C_in}->{C_out} {dtype} n={n}")
     check_layer(synth.uniform_cells(n, 6 if n < 100 else 14, seed=C_in + n), K, 2, "strided", C_in, C_out, dtype, seed=n)
+
+
+@pytest.mark.parametrize("K", [2, 3, 4])
+@pytest.mark.parametrize("n", [1, 64, 700, 5000])
+def test_inverse_map_of_repeated_coordinates(K, n):
+    """A build without a location table takes repeated inputs: one of them is in the map, and the inverse map holds the same pairs."""
+    say(f"inverse map of repeated coordinates K={K} n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    coords = synth.uniform_cells(n, 24, seed=n)
+    coords[n // 2:] = coords[:n - n // 2]
+    buf = sc.LayerBuffers(n, K, K, "strided", 32, 32, "f16", device="cuda:0")
+    buf.kmap_build(torch.from_numpy(np.ascontiguousarray(coords)).to("cuda:0"), standalone=True)
+    h = buf.read_counts()
+    pin, pout, _ = (t.cpu().numpy() for t in buf.export(h))
+    into = torch.full((sc.sc_kmap_bytes(n, K, K, "inverse"),), 7, dtype=torch.uint8, device="cuda:0")
+    sc.sc_kmap_transpose(buf.kmap, n, K, K, buf.counts, into)
+    hi = sc.sc_counts_read(buf.counts, into, n, K, K, "inverse")
+    iin, iout, _ = (t.cpu().numpy() for t in sc.sc_kmap_export(into, n, K, K, "inverse", hi))
+    assert h.n_pairs == hi.n_pairs == len(np.unique(coords, axis=0)) and list(h.per_offset[:K ** 3]) == list(hi.per_offset[:K ** 3])
+    offset = np.repeat(np.arange(K ** 3), h.per_offset[:K ** 3])
+    assert sorted(zip(offset, pout, pin)) == sorted(zip(offset, iin, iout))
