@@ -297,9 +297,10 @@ inline StridedScratch strided_scratch(void* p, int64_t n, uint64_t slots_per_key
     return s;
 }
 
-// Prepares a strided build: output-cell table <- empty, claim counters <- 0.
+// Prepares a strided build: output-cell table <- empty, claim counters <- 0; short builds: flag words <- 0, offset table <- -1.
 __global__ void __launch_bounds__(256)
-k_strided_fill(int4* __restrict__ oslots4, uint64_t cap, int32_t* __restrict__ cells, sc_counts* counts, int reset, int64_t n_in, const TableHeader* th) {
+k_strided_fill(int4* __restrict__ oslots4, uint64_t cap, int32_t* __restrict__ cells, uint64_t* __restrict__ flagword, int64_t words,
+               int4* __restrict__ nbr16, int64_t nbr_vec, sc_counts* counts, int reset, int64_t n_in, const TableHeader* th) {
     const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (reset && blockIdx.x == 0) {                  // a build without a location table starts the counts block itself
@@ -312,6 +313,8 @@ k_strided_fill(int4* __restrict__ oslots4, uint64_t cap, int32_t* __restrict__ c
     if (th != nullptr && tid == 0) fold_table_error(th, counts);
     if (cells != nullptr && tid < CELL_COUNTERS) cells[tid * 32] = 0;
     for (int64_t i = tid; i < (int64_t)(cap / 4); i += nthr) oslots4[i] = make_int4(CELL_EMPTY, CELL_EMPTY, CELL_EMPTY, CELL_EMPTY);
+    for (int64_t i = tid; i < words; i += nthr) flagword[i] = 0ull;
+    for (int64_t i = tid; i < nbr_vec; i += nthr) nbr16[i] = make_int4(-1, -1, -1, -1);
 }
 
 // Candidate j of the input at c, or k < 0 if it has fewer.  Along one axis the offsets that can
@@ -357,13 +360,14 @@ __device__ inline uint64_t candidate_key(const int4* __restrict__ coords, const 
 }
 
 // Claim (or find) the slot of output cell `key` for candidate `id`; returns the slot, or -1 if the table is
-// full.  `fresh`: this call claimed it.  A slot is one word, the smallest id seen of its cell: which cell
+// full.  `fresh`: this call claimed it; `ousted`: the id that stood there until this call's smaller one took its place, or -1.  A slot is one word, the smallest id seen of its cell: which cell
 // that is follows from the id's coordinates, so claiming a cell is a single compare-and-swap, and a
 // later entry with a larger id only reads.
 template <class Shape>
 __device__ inline int32_t claim_cell(int32_t* oslots, uint32_t omask, const int4* __restrict__ coords, const Shape& sh, uint64_t key,
-                                     int32_t id, bool& fresh) {
+                                     int32_t id, bool& fresh, int32_t& ousted) {
     fresh = false;
+    ousted = -1;
     for (uint32_t t = 0; t <= omask + REHASH_MAX; ++t) {
         const uint32_t slot = probe_slot(key, t, omask);
         int32_t cur = *const_cast<const volatile int32_t*>(&oslots[slot]);
@@ -375,7 +379,10 @@ __device__ inline int32_t claim_cell(int32_t* oslots, uint32_t omask, const int4
             }
         }
         if (candidate_key(coords, sh, cur) == key) {
-            if (id < cur) atomicMin(&oslots[slot], id);
+            if (id < cur) {
+                const int32_t old = atomicMin(&oslots[slot], id);
+                if (id < old) ousted = old;
+            }
             return (int32_t)slot;
         }
     }
@@ -390,16 +397,20 @@ __device__ inline int32_t claim_cell(int32_t* oslots, uint32_t omask, const int4
 // 2) and 8.5 us (K = 2), 200 k rows 51.8 and 21.0; now 9.7, 7.1, 21.0 and 10.5.  `key` is KEY_EMPTY for a thread without an entry; ids rise
 // with the thread.  Returns the thread's slot, -1 if it has none or the table is full (l.full is then set);
 // l.fresh counts the cells this workgroup claimed first.
+// FLAGS: the bits of the ids that stand in the table, in flag words that start out zero: an id's bit is turned when it comes and
+// when a smaller one takes its place.  Turns commute, so the words are right when the last workgroup is done, and who comes
+// sets only bits of the workgroup's own ids, gathered in LDS.
 constexpr int CLAIM_WG = 256;                          // with 1024 the fixed part (barriers, few workgroups) outweighs the merging: 10.6 us
 struct ClaimLds {
     static constexpr int SLOTS = 2 * CLAIM_WG;              // at most half full
     unsigned long long key[SLOTS];
     int32_t id[SLOTS];                                 // smallest id, later the slot in the global table
     int32_t fresh, full;
+    uint32_t flags[CLAIM_WG / 32];
 };
-template <class Shape>
+template <int FLAGS, class Shape>
 __device__ inline int32_t claim_cells_of_workgroup(ClaimLds& l, int32_t* oslots, uint32_t omask, const int4* __restrict__ coords,
-                                                   const Shape& sh, uint64_t key, int32_t id) {
+                                                   const Shape& sh, uint64_t key, int32_t id, uint32_t* flags) {
     constexpr int SLOTS = ClaimLds::SLOTS;
 #pragma unroll
     for (int i = 0; i < SLOTS / CLAIM_WG; ++i) {
@@ -407,6 +418,7 @@ __device__ inline int32_t claim_cells_of_workgroup(ClaimLds& l, int32_t* oslots,
         l.id[i * CLAIM_WG + threadIdx.x] = CELL_EMPTY;
     }
     if (threadIdx.x == 0) l.fresh = l.full = 0;
+    if (FLAGS && threadIdx.x < CLAIM_WG / 32) l.flags[threadIdx.x] = 0u;
     __syncthreads();
     int at = -1;
     bool owner = false;                                // the thread that brought the key in claims the cell
@@ -424,23 +436,29 @@ __device__ inline int32_t claim_cells_of_workgroup(ClaimLds& l, int32_t* oslots,
     __syncthreads();
     bool fresh = false;
     if (owner) {
-        const int32_t slot = claim_cell(oslots, omask, coords, sh, key, l.id[at], fresh);
+        const int32_t first = l.id[at];
+        int32_t ousted;
+        const int32_t slot = claim_cell(oslots, omask, coords, sh, key, first, fresh, ousted);
         if (slot < 0) l.full = 1;
+        if (FLAGS && (fresh || ousted >= 0)) atomicXor(&l.flags[(uint32_t)first % CLAIM_WG / 32], 1u << ((uint32_t)first % 32));
+        if (FLAGS && ousted >= 0) atomicXor(&flags[(uint32_t)ousted / 32], 1u << ((uint32_t)ousted % 32));
         l.id[at] = slot;
     }
     const uint64_t vote = __ballot(fresh);
     if ((threadIdx.x & 63) == 0 && vote != 0ull) atomicAdd(&l.fresh, __popcll(vote));
     __syncthreads();
+    if (FLAGS && threadIdx.x < CLAIM_WG / 32 && l.flags[threadIdx.x] != 0u)
+        atomicXor(&flags[(size_t)blockIdx.x * (CLAIM_WG / 32) + threadIdx.x], l.flags[threadIdx.x]);
     return at >= 0 ? l.id[at] : -1;
 }
 
 // One thread per candidate (input i = id / maxc, candidate j = id % maxc; one per input for K == stride: the
 // cell floor(p/s) of eq. 2, eq. 4): the inputs' candidates are independent, and with a thread each their
 // claims are all in flight together.
-template <class Shape>
+template <int FLAGS, class Shape>
 __global__ void __launch_bounds__(CLAIM_WG)
 k_strided_insert(const int4* __restrict__ coords, int64_t n, Shape sh, int32_t* oslots, uint32_t omask, int32_t* __restrict__ cand_slot,
-                 int32_t* __restrict__ cells, sc_counts* counts) {
+                 int32_t* __restrict__ cells, uint32_t* flags, sc_counts* counts) {
     __shared__ ClaimLds l;
     const int64_t id = (int64_t)blockIdx.x * CLAIM_WG + threadIdx.x, nc = n * sh.maxc();
     uint64_t key = KEY_EMPTY;
@@ -455,12 +473,12 @@ k_strided_insert(const int4* __restrict__ coords, int64_t n, Shape sh, int32_t* 
             if (q.k >= 0) key = pack_key(c.x, q.qx, q.qy, q.qz);
         }
     }
-    const int32_t slot = claim_cells_of_workgroup(l, oslots, omask, coords, sh, key, (int32_t)id);
+    const int32_t slot = claim_cells_of_workgroup<FLAGS>(l, oslots, omask, coords, sh, key, (int32_t)id, flags);
     if (id < nc) cand_slot[id] = slot;
     if (threadIdx.x == 0) {
         if (l.full) latch_status(counts, SC_EFULL);
         // how many cells there are, before they are numbered: the next kernel clears that many table rows
-        if (l.fresh != 0) atomicAdd(&cells[(blockIdx.x % CELL_COUNTERS) * 32], l.fresh);
+        if (!FLAGS && l.fresh != 0) atomicAdd(&cells[(blockIdx.x % CELL_COUNTERS) * 32], l.fresh);
     }
 }
 
@@ -612,6 +630,72 @@ k_strided_pairs(const int4* __restrict__ coords, int64_t n, Shape sh, const int3
     nbr[((int64_t)(o >> 6) * (sh.K() * sh.K() * sh.K()) + q.k) * TILE + (o & 63)] = (int32_t)i;
     if (parent != nullptr) parent[id] = (uint32_t)o << 6 | (uint32_t)q.k;      // one candidate per input: id is its row
     if (r == (int32_t)id) out_coords[o] = make_int4(c.x, q.qx, q.qy, q.qz);
+}
+
+// The same for short builds with one candidate per input (K == stride), whose flag words the insert kernel has made: every
+// workgroup counts all words for itself, and there is no kernel between claiming and numbering (a launch of 4 us; whole layers K = 2
+// 32 -> 64, 2 k / 10 k / 53 k / 200 k voxels 18.3 / 19.8 / 21.7 / 33.9 -> 16.2 / 17.2 / 19.2 / 31.1 us).  Words and counts of the largest set that comes here are 48 KB of LDS.
+constexpr int SHORT_WORDS = 4096;                      // 262,144 inputs
+template <class Shape>
+__global__ void __launch_bounds__(1024)
+k_strided_pairs_short(const int4* __restrict__ coords, int n, Shape sh, const int32_t* __restrict__ cand_slot, const int32_t* __restrict__ oslots,
+                      const uint64_t* __restrict__ flagword, int32_t* __restrict__ nbr, uint32_t* __restrict__ parent, int4* __restrict__ out_coords,
+                      sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
+    __shared__ uint64_t word_s[SHORT_WORDS];
+    __shared__ int32_t before_s[SHORT_WORDS], wave_s[16];
+    const int id = (int)(blockIdx.x * 1024 + threadIdx.x), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (id == 0) *hdr = hdr_value;
+    // what does not need the words is requested before their barriers
+    const int32_t sl = id < n ? cand_slot[id] : -1;
+    int4 c = make_int4(0, 0, 0, 0);
+    int32_t r = 0;                                             // the cell's first input
+    if (sl >= 0) {
+        c = coords[id];
+        r = oslots[sl];
+    }
+    constexpr int PER = SHORT_WORDS / 1024;
+    const int words = (n + 63) / 64;
+    uint64_t word[PER];
+    int32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int w = threadIdx.x * PER + u;
+        word[u] = w < words ? flagword[w] : 0ull;
+        mine += __popcll(word[u]);
+    }
+    int32_t incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+    }
+    if (lane == 63) wave_s[wave] = incl;
+    __syncthreads();
+    int32_t run = incl - mine, total = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        const int32_t v = wave_s[w];
+        if (w < wave) run += v;
+        total += v;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        word_s[threadIdx.x * PER + u] = word[u];
+        before_s[threadIdx.x * PER + u] = run;
+        run += __popcll(word[u]);
+    }
+    __syncthreads();
+    if (id == 0) counts->n_out = total;
+    if (id >= n) return;
+    if (sl < 0) {
+        if (parent != nullptr) parent[id] = ~0u;
+        return;
+    }
+    const Candidate q = candidate(c, sh.K(), sh.s(), 0);
+    const int32_t o = before_s[r >> 6] + __popcll(word_s[r >> 6] & ((1ull << (r & 63)) - 1ull));
+    nbr[((int64_t)(o >> 6) * (sh.K() * sh.K() * sh.K()) + q.k) * TILE + (o & 63)] = id;
+    if (parent != nullptr) parent[id] = (uint32_t)o << 6 | (uint32_t)q.k;
+    if (r == id) out_coords[o] = make_int4(c.x, q.qx, q.qy, q.qz);
 }
 
 // Group masks of a finished offset table: one workgroup per tile; its four wavefronts share the
@@ -766,6 +850,9 @@ static bool kmap_args_ok(int64_t n, int K, int stride, int mode) {
     }
     return false;
 }
+// Bytes of table a short build clears at most: what is cleared for nothing grows with the table and the launch saved does not (K = 3
+// on 150 k inputs, 16 MiB, a whole 32 -> 64 layer: 37.1 us without and 35.2 with it).
+constexpr int64_t SHORT_TABLE_MAX = 16 << 20;
 // slots of the output-cell table per candidate
 static uint64_t strided_slots(int K, int stride) { return K == stride && K <= 4 ? 8 : 2; }
 
@@ -782,10 +869,28 @@ static int build_strided(const Shape& sh, const int32_t* d_coords, int64_t n, co
     const uint64_t cap = (uint64_t)g.omask + 1;
     unsigned fb = (unsigned)((cap / 4 + 255) / 256);
     if (fb > 4096) fb = 4096;
-    SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(fb), dim3(256), 0, s, (int4*)g.oslots, cap, g.cells, d_counts,
-              d_table == nullptr ? 1 : 0, n, (const TableHeader*)d_table);
-    SC_LAUNCH(KID_STRIDED_INSERT, k_strided_insert<Shape>, dim3((unsigned)((nc + CLAIM_WG - 1) / CLAIM_WG)), dim3(CLAIM_WG), 0, s,
-              (const int4*)d_coords, n, sh, g.oslots, g.omask, g.slot_of, g.cells, d_counts);
+    // Short builds: one candidate per input, its flags made as the cells are claimed.  All the table rows there could be are cleared
+    // with the cell table, before their number is known, so only where they are few bytes.
+    const int64_t nbr_vec = L.tiles * L.K3 * (TILE / 4);
+    const bool is_short = K == stride && n <= 64 * SHORT_WORDS && nbr_vec * 16 <= SHORT_TABLE_MAX;
+    SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(fb), dim3(256), 0, s, (int4*)g.oslots, cap, g.cells, is_short ? g.flagword : (uint64_t*)nullptr,
+              is_short ? (n + 63) / 64 : (int64_t)0, (int4*)nbr, is_short ? nbr_vec : (int64_t)0, d_counts, d_table == nullptr ? 1 : 0, n,
+              (const TableHeader*)d_table);
+#define SC_STRIDED_INSERT(FLAGS)                                                                                                       \
+    SC_LAUNCH(KID_STRIDED_INSERT, (k_strided_insert<FLAGS, Shape>), dim3((unsigned)((nc + CLAIM_WG - 1) / CLAIM_WG)), dim3(CLAIM_WG), 0, s, \
+              (const int4*)d_coords, n, sh, g.oslots, g.omask, g.slot_of, g.cells, (uint32_t*)g.flagword, d_counts)
+    if (is_short) {
+        SC_STRIDED_INSERT(1);
+        SC_LAUNCH(KID_STRIDED_PAIRS, k_strided_pairs_short<Shape>, dim3((unsigned)((n + 1023) / 1024)), dim3(1024), 0, s, (const int4*)d_coords, (int)n,
+                  sh, (const int32_t*)g.slot_of, (const int32_t*)g.oslots, (const uint64_t*)g.flagword, nbr, parent, (int4*)d_out_coords, d_counts,
+                  (KmapHeader*)d_kmap, h);
+        if (kmap_masked(SC_STRIDED, L.K3))
+            SC_LAUNCH(KID_KMAP_FROM_OFT, k_masks_from_table, dim3((unsigned)L.tiles), dim3(256), 0, s, (const int32_t*)nbr, L.K3, L.mw, L.tiles, gmask,
+                      (const sc_counts*)d_counts);
+        return SC_OK;
+    }
+    SC_STRIDED_INSERT(0);
+#undef SC_STRIDED_INSERT
     const unsigned gp = (unsigned)((nc + 255) / 256);
 #define SC_STRIDED_NUMBER(SCAN, U)                                                                                                     \
     do {                                                                                                                               \
@@ -854,8 +959,8 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
     h.n_in = n; h.n_out_bound = bound; h.tiles = L.tiles; h.mw = L.mw;
     if (n == 0) {
         if (mode == SC_STRIDED && d_table == nullptr)
-            SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(1), dim3(256), 0, s, (int4*)nullptr, (uint64_t)0,
-                      (int32_t*)nullptr, d_counts, 1, (int64_t)0, (const TableHeader*)nullptr);
+            SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(1), dim3(256), 0, s, (int4*)nullptr, (uint64_t)0, (int32_t*)nullptr,
+                      (uint64_t*)nullptr, (int64_t)0, (int4*)nullptr, (int64_t)0, d_counts, 1, (int64_t)0, (const TableHeader*)nullptr);
         SC_LAUNCH(KID_KMAP_HEADER, k_kmap_header, dim3(1), dim3(64), 0, s, (KmapHeader*)d_kmap, h);
         SC_LAUNCH(KID_MISC, k_set_n_out, dim3(1), dim3(64), 0, s, d_counts, (int64_t)0);
         return SC_OK;

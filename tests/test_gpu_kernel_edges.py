@@ -344,3 +344,24 @@ def test_inverse_map_of_repeated_coordinates(K, n):
     assert h.n_pairs == hi.n_pairs == len(np.unique(coords, axis=0)) and list(h.per_offset[:K ** 3]) == list(hi.per_offset[:K ** 3])
     offset = np.repeat(np.arange(K ** 3), h.per_offset[:K ** 3])
     assert sorted(zip(offset, pout, pin)) == sorted(zip(offset, iin, iout))
+
+
+@pytest.mark.parametrize("K,n", [(2, 1), (2, 63), (2, 1024), (2, 1025), (2, 262144), (2, 262145), (3, 155328), (3, 155329), (4, 65536), (4, 65537), (5, 33536), (7, 12224)])
+def test_strided_build_on_both_sides_of_the_short_one(K, n):
+    """K == stride: cells with one input and with many, in random order; the largest sets whose words are counted by every
+    workgroup or whose table is cleared ahead, and one row more."""
+    say(f"strided build K=s={K} n={n}")
+    import oracle
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    coords = synth.uniform_cells(n, max(4, int(round((n * 3) ** (1 / 3)))), seed=K + n)
+    km = oracle.kmap(coords, K, K, "strided")
+    buf = sc.LayerBuffers(n, K, K, "strided", 32, 32, "f16", device="cuda:0")
+    buf.scratch.fill_(0x5a)
+    buf.kmap.fill_(0x11)
+    buf.kmap_build(torch.from_numpy(coords).to("cuda:0"), standalone=True)
+    h = buf.read_counts()
+    pin, pout, start = (t.cpu().numpy() for t in buf.export(h))
+    assert h.n_out == km["n_out"] and np.array_equal(start, km["offset_start"])
+    assert np.array_equal(pin, km["pair_in"]) and np.array_equal(pout, km["pair_out"])
+    assert np.array_equal(buf.out_coords[:h.n_out].cpu().numpy(), km["out_coords"])
