@@ -754,7 +754,10 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // 128 -> 128: the general kernel up to 20 tiles per CU.  A workgroup of the streaming kernel is eight
     // tiles and takes ~75 us however few there are; full, it moves the weights once for them (us, general and
     // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
-    // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).
+    // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).  Beyond 20 tiles per CU the streaming kernel takes
+    // 86 us a round of eight tiles per CU, full or not, the general one 0.05 us a tile of a dense set and less of others: K = 3 layers
+    // whose rounds are less than four fifths full stay with it (whole layers, general and streaming: indoor 400 k, 0.76 full, 370 /
+    // 407, 500 k, 0.95, 466 / 428, 700 k, 0.89, 663 / 624; sweeps 400 k 287 / 371).
     // 32 -> 64, K = 3: the streaming kernel walks all offsets, four tiles in step, which is the longer chain of few tiles and the
     // cheaper one of many dense ones.  The general kernel up to 13 tiles per CU, strided layers, whose rows have few neighbours
     // each but most offsets, up to 7 (us, general and streaming kernel: 2 k voxels 7.1 / 9.1, 53 k 12.3 / 13.8, 110 k 20.3 / 20.2,
@@ -763,7 +766,9 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // rows, at every size (whole layers: 2 k 13.1 / 22.3, 53 k 22.5 / 27.0, 200 k 51.2 / 64.3, 400 k 88.5 / 108; indoor 800 k 184.7 / 182.7).
     if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && likely <= (tiles == likely ? 13 : 7) * (int64_t)compute_units())
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
-    if ((FUSED && fused_gather) || (wide && likely <= 20 * (int64_t)compute_units())) {
+    const int64_t round = 8 * (int64_t)compute_units();
+    const bool part_filled = K3 == 27 && 5 * likely < 4 * ((likely + round - 1) / round * round);
+    if ((FUSED && fused_gather) || (wide && (likely <= 20 * (int64_t)compute_units() || part_filled))) {
         if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
     }
