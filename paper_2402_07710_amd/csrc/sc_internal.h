@@ -294,12 +294,14 @@ int compute_units();                       // of the current device
 // sweep (near the sensor) has several times the neighbours of the last, and contiguous eighths
 // leave seven XCDs waiting for one (53 k voxels fp32 64 -> 64: 84 -> 80 us, 14 k voxels 256 -> 256 the same).
 constexpr int XCD_RUN = 4;
+template <int RUN = XCD_RUN>
 inline unsigned xcd_run_grid(int64_t units) {
-    return (unsigned)((units + NUM_XCD * XCD_RUN - 1) / (NUM_XCD * XCD_RUN) * (NUM_XCD * XCD_RUN));
+    return (unsigned)((units + NUM_XCD * RUN - 1) / (NUM_XCD * RUN) * (NUM_XCD * RUN));
 }
-__device__ inline int64_t xcd_run_of(unsigned block, int64_t units) {    // needs gridDim.x >= xcd_run_grid(units)
+template <int RUN = XCD_RUN>
+__device__ inline int64_t xcd_run_of(unsigned block, int64_t units) {    // needs gridDim.x >= xcd_run_grid<RUN>(units)
     const unsigned i = block / NUM_XCD;
-    const int64_t u = (int64_t)(i / XCD_RUN * NUM_XCD + block % NUM_XCD) * XCD_RUN + i % XCD_RUN;
+    const int64_t u = (int64_t)(i / RUN * NUM_XCD + block % NUM_XCD) * RUN + i % RUN;
     return u < units ? u : -1;
 }
 

@@ -150,7 +150,12 @@ k_kmap_subm(const int4* __restrict__ coords, int64_t n, const uint4* __restrict_
 // 10^6 indoor voxels: 104 -> 75 us; sweeps of 110 k: 15.6 -> 13.7, 261 k: 37.7 -> 35.0, 53 k with K = 5:
 // 28.2 -> 24.0, 6 k with K = 5: 12 -> 8.4.  All five y offsets of K = 5 at once spill or leave room for
 // too few wavefronts (35 us).
-template <int K, int YG, int YB>                       // YG wavefronts share an x offset's y offsets, each takes YB of its at a time
+// Tiles to the XCDs: contiguous eighths, runs of 16 (RUNS) from 2,300 tiles on (K = 5: 1,400), where the eighth nearest the sensor,
+// whose rows find more, ends last (us of the map, eighths -> runs: 100 k 13.6 -> 12.7, 170 k 24.4 -> 20.9, 262 k 36.1 -> 34.3, 10^6
+// indoor 76.1 -> 74.4, K = 5 on 100 k 58.2 -> 45.2; 53 k 8.5 -> 8.9; runs of 4 and 64 at 262 k 34.4 and 35.5, at 10^6 78.0 and 73.5).
+constexpr int MAP_RUN = 16;
+static bool map_in_runs(int64_t tiles, int K) { return tiles > (K == 5 ? 1400 : 2300); }
+template <int K, int YG, int YB, int RUNS>             // YG wavefronts share an x offset's y offsets, each takes YB of its at a time
 __global__ void __launch_bounds__(64 * K * YG)
 k_kmap_subm_blocks(const int4* __restrict__ coords, int64_t n, const uint4* __restrict__ slots, const TableHeader* __restrict__ th,
                    uint32_t* __restrict__ gmask, int32_t* __restrict__ nbr, sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
@@ -160,8 +165,8 @@ k_kmap_subm_blocks(const int4* __restrict__ coords, int64_t n, const uint4* __re
     __shared__ uint32_t mask_s[4 * MW];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = wave % K, dy_first = wave / K * YC;
-    const int64_t tile = xcd_unit(blockIdx.x, gridDim.x);
-    if (tile * TILE >= n) return;                      // padding workgroup of the XCD-aware grid
+    const int64_t tile = RUNS ? xcd_run_of<MAP_RUN>(blockIdx.x, (n + TILE - 1) / TILE) : xcd_unit(blockIdx.x, gridDim.x);
+    if (tile < 0 || tile * TILE >= n) return;                              // padding workgroup of the XCD-aware grid
     if (threadIdx.x < 4 * MW) mask_s[threadIdx.x] = 0u;
     const int64_t row = tile * TILE + lane;
     const bool valid = row < n;
@@ -972,10 +977,15 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
     SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm<KV, WPT, CH, AT>), dim3(xcd_grid(L.tiles)), dim3(64 * WPT), 0, s,      \
               (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, d_counts,          \
               (KmapHeader*)d_kmap, h)
-#define SC_SUBM_BLOCKS(KV, YG, YB)                                                                                \
-    SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm_blocks<KV, YG, YB>), dim3(xcd_grid(L.tiles)), dim3(64 * KV * YG), 0, s,  \
+#define SC_SUBM_BLOCKS_AS(KV, YG, YB, RUNS, GRID)                                                                  \
+    SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm_blocks<KV, YG, YB, RUNS>), dim3(GRID), dim3(64 * KV * YG), 0, s,         \
               (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, d_counts,    \
               (KmapHeader*)d_kmap, h)
+#define SC_SUBM_BLOCKS(KV, YG, YB)                                                                                 \
+    do {                                                                                                           \
+        if (map_in_runs(L.tiles, KV)) SC_SUBM_BLOCKS_AS(KV, YG, YB, 1, xcd_run_grid<MAP_RUN>(L.tiles));            \
+        else SC_SUBM_BLOCKS_AS(KV, YG, YB, 0, xcd_grid(L.tiles));                                                  \
+    } while (0)
         switch (K) {
             case 1: SC_SUBM_LAUNCH(1, 1, 1, 1); break;
             case 3:
@@ -991,6 +1001,7 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
         }
 #undef SC_SUBM_LAUNCH
 #undef SC_SUBM_BLOCKS
+#undef SC_SUBM_BLOCKS_AS
         if (d_out_coords != nullptr && d_out_coords != d_coords) {
             if (hipMemcpyAsync(d_out_coords, d_coords, (size_t)n * 16, hipMemcpyDeviceToDevice, s) != hipSuccess)
                 return SC_EHIP;

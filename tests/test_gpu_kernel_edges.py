@@ -365,3 +365,21 @@ def test_strided_build_on_both_sides_of_the_short_one(K, n):
     assert h.n_out == km["n_out"] and np.array_equal(start, km["offset_start"])
     assert np.array_equal(pin, km["pair_in"]) and np.array_equal(pout, km["pair_out"])
     assert np.array_equal(buf.out_coords[:h.n_out].cpu().numpy(), km["out_coords"])
+
+
+@pytest.mark.parametrize("K,n", [(3, 2300 * 64), (3, 2300 * 64 + 1), (3, 2304 * 64 + 63), (5, 1400 * 64 + 1)])
+def test_map_of_tiles_in_runs(K, n):
+    """The fewest tiles that go to the XCDs in runs, with a last run that is not full."""
+    say(f"map in runs K={K} n={n}")
+    import oracle
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    coords = synth.uniform_cells(n, 64, seed=K)
+    km = oracle.kmap(coords, K, 1, "subm")
+    buf = sc.LayerBuffers(n, K, 1, "subm", 32, 32, "f16", device="cuda:0")
+    c = torch.from_numpy(coords).to("cuda:0")
+    buf.kmap.fill_(0x11)
+    buf.hash_build(c)
+    buf.kmap_build(c)
+    pin, pout, start = (t.cpu().numpy() for t in buf.export())
+    assert np.array_equal(start, km["offset_start"]) and np.array_equal(pin, km["pair_in"]) and np.array_equal(pout, km["pair_out"])
