@@ -383,3 +383,29 @@ def test_map_of_tiles_in_runs(K, n):
     buf.kmap_build(c)
     pin, pout, start = (t.cpu().numpy() for t in buf.export())
     assert np.array_equal(start, km["offset_start"]) and np.array_equal(pin, km["pair_in"]) and np.array_equal(pout, km["pair_out"])
+
+
+@pytest.mark.parametrize("C_out,n", [(64, 768 * 64), (64, 768 * 64 + 1), (128, 384 * 64), (128, 384 * 64 + 1), (16, 33), (256, 193 * 64)])
+def test_64_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
+    """Steps of two offsets, with an odd number of offsets in a tile's list, and of one; with and without a map."""
+    say(f"64 -> {C_out}, n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import TOL, to_dev
+    side = max(4, int(round((n * 3) ** (1 / 3))))
+    coords = synth.uniform_cells(n, side, seed=C_out)
+    feat, weight = synth.features(n, 64, "bf16", 1), synth.weights(27, 64, C_out, "bf16", 1)
+    buf = sc.LayerBuffers(n, 3, 1, "subm", 64, C_out, "bf16", device="cuda:0")
+    c, f, w = torch.from_numpy(coords).to("cuda:0"), to_dev(feat, "bf16"), to_dev(weight, "bf16")
+    buf.feat_out.fill_(float("nan"))
+    buf.layer(c, f, w)
+    pin, pout, start = (t.long() for t in buf.export())
+    ref = torch.zeros((n, C_out), device="cuda:0")
+    for k in range(27):
+        at = slice(int(start[k]), int(start[k + 1]))
+        ref.index_add_(0, pout[at], f[pin[at]].float() @ w[k].float())
+    assert float((buf.feat_out.float() - ref).abs().max() / ref.abs().max()) <= TOL["bf16"]
+    if C_out in (64, 128):
+        fused = sc.LayerBuffers(n, 3, 1, "subm", 64, C_out, "bf16", device="cuda:0", grid_dims=(1, side, side, side))
+        fused.layer_fused(c, f, w)
+        assert torch.equal(fused.feat_out, buf.feat_out)
