@@ -260,8 +260,8 @@ size_t sc_conv_workspace_bytes(int K, int C_in, int C_out, int dtype_in);
  *   d_feat_in   [rows][C_in]  of dtype_in
  *   d_weight    [K^3][C_in][C_out] of dtype_in
  *   d_feat_out  [n_out_cap][C_out] of dtype_out; rows [0, n_out) are fully overwritten (a row
- *               with no pair becomes 0), rows >= n_out are left untouched.  n_out is read on
- *               the device from d_counts; n_out_cap >= sc_out_bound(...) is always enough.
+ *               with no pair becomes 0), rows >= n_out are left untouched.  n_out is n_map
+ *               (SC_STRIDED: read on the device from d_counts); n_out_cap >= sc_out_bound(...) is always enough.
  *   d_kmap      blob from sc_kmap_build (or sc_kmap_transpose) for the same (n_map, K, stride)
  *   dtype_in    SC_F32 (fp32 MFMA) or SC_F16 / SC_BF16 (16-bit MFMA, fp32 accumulation)
  *   dtype_out   SC_F32 or the same as dtype_in (one round-to-nearest-even at the end)

@@ -19,6 +19,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __host__ __device__ constexpr int wtile(int KS, int CB, int cb, int ks) {
     return KS == 1 ? cb : ((ks >> 1) * CB + cb) * 2 + (ks & 1);
 }
+// Rows of the output: counted on the device (strided layers) or known to the caller, who then spares the kernel a round trip in
+// front of everything else.
+__device__ inline int64_t output_rows(const int64_t* __restrict__ counted, int64_t cap) {
+    return counted != nullptr && *counted < cap ? *counted : cap;
+}
+
 // Group masks from a line of the offset table (lane = row of the tile): bit of each group that has a neighbour.  Maps of
 // strided layers up to K^3 = 32 come without masks (MapSource::gmask null): the kernels read the lines anyway.
 __device__ inline uint32_t line_pattern(int32_t entry) {

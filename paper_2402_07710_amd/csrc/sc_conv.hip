@@ -66,8 +66,7 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
     const int r = lane & 15, qq = lane >> 4;
     const int q = wv & 3;
     SC_MARK(0);
-    int64_t n_out = n_out_cap;
-    if (!FUSED && *n_out_ptr < n_out) n_out = *n_out_ptr;
+    const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
     // the grid covers the caller's row capacity; the rows that exist are spread over all XCDs and
     // a workgroup that gets none leaves at once (the whole workgroup, before any barrier)
     const int64_t unit = xcd_unit_of(blockIdx.x, (n_out + NT * TILE - 1) / (NT * TILE));
@@ -248,8 +247,7 @@ k_conv_stream(const uint16_t* __restrict__ feat, const uint4* wp, void* __restri
     uint4* w_lds = smem;
     int32_t* e_lds = reinterpret_cast<int32_t*>(smem + 2 * WK) + wv * (K3 * TILE);
     SC_MARK(0);
-    int64_t n_out = n_out_cap;
-    if (!FUSED && *n_out_ptr < n_out) n_out = *n_out_ptr;
+    const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
     // the grid covers the caller's row capacity; the rows that exist are spread over all XCDs and
     // a workgroup that gets none leaves at once (the same decision in every wavefront, before
     // any barrier)
@@ -421,8 +419,7 @@ k_conv_f32(const float* __restrict__ feat, const float* __restrict__ w, float* _
     const int r = lane & 15, qq = lane >> 4;
     const int CB = (C_out + 15) / 16;
     const int64_t tile = blockIdx.x;
-    int64_t n_out = *n_out_ptr;
-    if (n_out > n_out_cap) n_out = n_out_cap;
+    const int64_t n_out = output_rows(n_out_ptr, n_out_cap);
     const int64_t row = tile * TILE + q * 16 + r;
     if (tile * TILE + q * 16 >= n_out) return;                       // uniform per wavefront
 
@@ -484,8 +481,7 @@ k_conv_f32_first(const float* __restrict__ feat, const float* __restrict__ w, fl
     __shared__ __align__(16) float w_s[K3 * 4 * C_out];              // [K3][4][C_out], zero past C_in
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int r = lane & 15, qq = lane >> 4;
-    int64_t n_out = *n_out_ptr;
-    if (n_out > n_out_cap) n_out = n_out_cap;
+    const int64_t n_out = output_rows(n_out_ptr, n_out_cap);
     const int64_t tile = xcd_run_of(blockIdx.x, (n_out + TILE - 1) / TILE);
     if (tile < 0) return;                                            // the whole workgroup
     const int64_t row = tile * TILE + q * 16 + r;
@@ -544,8 +540,7 @@ k_conv_f32_small(const float* __restrict__ feat, const float* __restrict__ w, fl
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int r = lane & 15, qq = lane >> 4;
     const int64_t tile = blockIdx.x;
-    int64_t n_out = *n_out_ptr;
-    if (n_out > n_out_cap) n_out = n_out_cap;
+    const int64_t n_out = output_rows(n_out_ptr, n_out_cap);
     const int64_t row = tile * TILE + q * 16 + r;
     if (tile * TILE + q * 16 >= n_out) return;                       // uniform per wavefront
 
@@ -806,8 +801,9 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     const int64_t bound = sc_out_bound(n_map, K, stride, mode);
     if (bound < 0) return SC_EINVAL;
     if (kmap_bytes < sc_kmap_bytes(n_map, K, stride, mode)) return SC_ECAP;
-    // rows of the output: what the map build counted, or (inverse layers) the rows it was built from
-    const int64_t* n_out_ptr = mode == SC_INVERSE ? &d_counts->n_in : &d_counts->n_out;
+    // rows of the output: of a strided layer what the map build counted, otherwise the rows the map was built from
+    const int64_t* n_out_ptr = mode == SC_STRIDED ? &d_counts->n_out : nullptr;
+    if (mode != SC_STRIDED && n_out_cap > n_map) n_out_cap = n_map;
     const KmapLayout L = kmap_layout(bound, K, stride, mode);
     int64_t tiles = (n_out_cap + TILE - 1) / TILE;
     if (tiles > L.tiles) tiles = L.tiles;

@@ -87,8 +87,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, qq = lane >> 4;
     const int wr = wv / WC;
-    int64_t n_out = n_out_cap;
-    if (!FUSED && *n_out_ptr < n_out) n_out = *n_out_ptr;
+    const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
     // a tile's blocks of output channels follow each other on its XCD
     const unsigned turn = blockIdx.x / NUM_XCD;
     const int by = (int)(turn % (unsigned)blocks_y);
