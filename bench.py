@@ -57,7 +57,9 @@ def algorithmic_bytes(kernel: str, st: dict) -> float | None:
         slots = 1024                                      # of the output-cell table, one 4-byte word each
         while slots < (8 if st["candidates"] == 1 and K3 <= 64 else 2) * NC:
             slots *= 2
-        return 4.0 * slots
+        # short builds (one candidate per input) clear the offset table here, the others with the flags
+        short = st["candidates"] == 1 and N <= 262144 and (N + 63) // 64 * 64 * K3 * 4 <= 16 << 20
+        return 4.0 * slots + (N_out * K3 * 4.0 if short else 0.0)
     if kernel == "k_strided_insert":
         return N * 16 + P * (4 + 4) + NC * 4              # coords, a cell's word claimed (read + write), the candidate's slot
     if kernel == "k_strided_flags":
