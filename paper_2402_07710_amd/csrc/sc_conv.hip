@@ -109,25 +109,35 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
 #pragma unroll
         for (int k = 0; k < K3; ++k) e[k] = -1;
     }
-    // weights -> LDS as operand tiles (every thread helps, also wavefronts without rows): the
-    // thread that fills (tile, lane) reads its 8 input channels of one output channel (2-byte
-    // loads, 128 contiguous bytes per wavefront) and writes them as one 16-byte LDS store
+    // weights -> LDS as operand tiles (every thread helps, also wavefronts without rows): a thread reads four output
+    // channels of 8 input channels (8-byte loads) and writes four lanes' 16 bytes.  With a thread per lane, 2-byte loads, they were
+    // four times as many loads of 17 cycles each (us: up-sampling from the strided map 64 -> 32 53 k 6.1 -> 5.4, 64 -> 64 200 k 22.8 ->
+    // 20.8, 128 -> 64 53 k 12.8 -> 11.4; layers K = 2 64 -> 64 200 k 40.7 -> 38.6, fused 32 -> 32 53 k 15.1 -> 14.8)
     if constexpr (WPACKED) {
         // the caller packed the weights once (sc_conv_weight_pack): the tiles are copied as they are
         for (int i = threadIdx.x; i < K3 * CB * KS * 64; i += 256 * NT) w_lds[i] = wraw[i];
     } else {
         const uint16_t* w16 = reinterpret_cast<const uint16_t*>(wraw);
-        for (int i = threadIdx.x; i < K3 * CB * KS * 64; i += 256 * NT) {
-            const int ln = i & 63;
-            int rest = i >> 6;
+        for (int i = threadIdx.x; i < K3 * CB * KS * 16; i += 256 * NT) {
+            const int col = (i & 3) * 4, oct = (i >> 2) & 3;
+            int rest = i >> 4;
             const int ks = rest % KS; rest /= KS;
             const int cb = rest % CB;
             const int k = rest / CB;
-            const uint16_t* src = w16 + ((int64_t)k * C_in + ks * 32 + 8 * (ln >> 4)) * C_out + cb * 16 + (ln & 15);
-            uint32_t v[4];
+            const uint16_t* src = w16 + ((int64_t)k * C_in + ks * 32 + 8 * oct) * C_out + cb * 16 + col;
+            uint2 v[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = (uint32_t)src[(2 * j) * C_out] | ((uint32_t)src[(2 * j + 1) * C_out] << 16);
-            w_lds[i] = make_uint4(v[0], v[1], v[2], v[3]);
+            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const uint2*>(src + j * C_out);
+            uint4* dst = w_lds + ((k * CB + cb) * KS + ks) * 64 + oct * 16 + col;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t take = (c & 1) ? 0x07060302u : 0x05040100u;     // the upper or the lower halves of two words
+                uint32_t o[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    o[j] = c < 2 ? __builtin_amdgcn_perm(v[2 * j + 1].x, v[2 * j].x, take) : __builtin_amdgcn_perm(v[2 * j + 1].y, v[2 * j].y, take);
+                dst[c] = make_uint4(o[0], o[1], o[2], o[3]);
+            }
         }
     }
     SC_MARK(1);
