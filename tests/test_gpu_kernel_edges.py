@@ -324,14 +324,14 @@ def test_strided_maps_with_and_without_masks(K, C_in, C_out, dtype, n):
     check_layer(synth.uniform_cells(n, 6 if n < 100 else 14, seed=C_in + n), K, 2, "strided", C_in, C_out, dtype, seed=n)
 
 
-@pytest.mark.parametrize("K", [2, 3, 4])
-@pytest.mark.parametrize("n", [1, 64, 700, 5000])
+@pytest.mark.parametrize("K,n", [(K, n) for K in (2, 3, 4) for n in (1, 64, 700, 5000)] + [(2, 262145), (3, 155329)])
 def test_inverse_map_of_repeated_coordinates(K, n):
-    """A build without a location table takes repeated inputs: one of them is in the map, and the inverse map holds the same pairs."""
+    """A build without a location table takes repeated inputs: one of them is in the map, and the inverse map holds the same pairs.
+    The two largest sets take the longer build."""
     say(f"inverse map of repeated coordinates K={K} n={n}")
     import torch
     from paper_2402_07710_amd import binding as sc
-    coords = synth.uniform_cells(n, 24, seed=n)
+    coords = synth.uniform_cells(n, 24 if n < 10000 else 90, seed=n)
     coords[n // 2:] = coords[:n - n // 2]
     buf = sc.LayerBuffers(n, K, K, "strided", 32, 32, "f16", device="cuda:0")
     buf.kmap_build(torch.from_numpy(np.ascontiguousarray(coords)).to("cuda:0"), standalone=True)
