@@ -16,7 +16,7 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 
 // where a tile's table entries come from: the map's lines as they are needed, the same copied to LDS first, or look-ups
 enum { FROM_MAP, FROM_TABLE, FROM_LINES };
-constexpr int LIST_PAD = 12;                            // places of the list past the last offset: three steps of four
+constexpr int LIST_PAD = 12;                            // places of the list past the last offset: three steps of four, the longest
 
 // One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
 // input channel) is walked in steps of SL slices of 64 bytes of a row (32 16-bit or 16 fp32 channels):
@@ -73,6 +73,8 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     constexpr bool F32 = DT == SC_F32;
     constexpr int KP = KS < SL ? KS : SL, PARTS = KS / KP;     // slices of an offset taken in one step, steps per offset
     constexpr int OPS = SL / KP;                       // offsets per step
+    // the two steps after the last are read too: up to 3 OPS - 1 places past the last offset, which have to be zeros
+    static_assert(3 * OPS <= LIST_PAD, "the list's zeros reach as far as the steps read");
     constexpr int CH = KP == 1 ? 1 : KP / 2;           // chunks per offset and step: 64 rows x 128 (64) bytes
     constexpr int CHB = KS == 1 ? 4096 : 8192;         // bytes per chunk
     constexpr int NI = KS == 1 || NW == 8 ? 1 : 2;     // gather instructions per wavefront and chunk

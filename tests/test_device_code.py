@@ -46,3 +46,15 @@ def test_a_wait_state_between_writing_m0_and_a_load_to_lds(instructions):
                     bad.append((before, here))
     assert sites > 0
     assert not bad, f"{len(bad)} of {sites} loads into LDS directly behind a write of M0, e.g. {bad[0]}"
+
+
+def test_steps_longer_than_the_list_of_offsets_allows_do_not_compile(tmp_path):
+    """The general kernel reads its list of offsets two steps ahead; past the zeros behind the last offset it would gather at
+    offsets that are none.  With fewer zeros than its longest step needs it must be refused."""
+    path = os.path.join(build.CSRC, "sc_conv_gather.hip")
+    text = open(path).read()
+    zeros = re.search(r"LIST_PAD = (\d+);", text)
+    short = tmp_path / "sc_conv_gather.hip"
+    short.write_text(text.replace(zeros.group(0), f"LIST_PAD = {int(zeros.group(1)) - 1};"))
+    run = subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-fsyntax-only", str(short)], capture_output=True, text=True)
+    assert run.returncode != 0 and "static assertion failed" in run.stderr and "the list's zeros reach" in run.stderr, run.stderr[-2000:]
