@@ -15,6 +15,7 @@
 #include <cstdlib>
 
 #include "sc_internal.h"
+#include "sc_rules.h"
 
 namespace sc {
 
@@ -150,11 +151,9 @@ k_kmap_subm(const int4* __restrict__ coords, int64_t n, const uint4* __restrict_
 // 10^6 indoor voxels: 104 -> 75 us; sweeps of 110 k: 15.6 -> 13.7, 261 k: 37.7 -> 35.0, 53 k with K = 5:
 // 28.2 -> 24.0, 6 k with K = 5: 12 -> 8.4.  All five y offsets of K = 5 at once spill or leave room for
 // too few wavefronts (35 us).
-// Tiles to the XCDs: contiguous eighths, runs of 16 (RUNS) from 2,300 tiles on (K = 5: 1,400), where the eighth nearest the sensor,
-// whose rows find more, ends last (us of the map, eighths -> runs: 100 k 13.6 -> 12.7, 170 k 24.4 -> 20.9, 262 k 36.1 -> 34.3, 10^6
-// indoor 76.1 -> 74.4, K = 5 on 100 k 58.2 -> 45.2; 53 k 8.5 -> 8.9; runs of 4 and 64 at 262 k 34.4 and 35.5, at 10^6 78.0 and 73.5).
+// Tiles to the XCDs: contiguous eighths, or runs of MAP_RUN (map_in_runs; of 4 and 64 tiles at 262 k rows 34.4 and 35.5 us against 34.3
+// with 16, at 10^6 78.0 and 73.5 against 74.4).
 constexpr int MAP_RUN = 16;
-static bool map_in_runs(int64_t tiles, int K) { return tiles > (K == 5 ? 1400 : 2300); }
 template <int K, int YG, int YB, int RUNS>             // YG wavefronts share an x offset's y offsets, each takes YB of its at a time
 __global__ void __launch_bounds__(64 * K * YG)
 k_kmap_subm_blocks(const int4* __restrict__ coords, int64_t n, const uint4* __restrict__ slots, const TableHeader* __restrict__ th,
@@ -983,7 +982,7 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
               (KmapHeader*)d_kmap, h)
 #define SC_SUBM_BLOCKS(KV, YG, YB)                                                                                 \
     do {                                                                                                           \
-        if (map_in_runs(L.tiles, KV)) SC_SUBM_BLOCKS_AS(KV, YG, YB, 1, xcd_run_grid<MAP_RUN>(L.tiles));            \
+        if (map_in_runs(L.tiles, KV, compute_units())) SC_SUBM_BLOCKS_AS(KV, YG, YB, 1, xcd_run_grid<MAP_RUN>(L.tiles));            \
         else SC_SUBM_BLOCKS_AS(KV, YG, YB, 0, xcd_grid(L.tiles));                                                  \
     } while (0)
         switch (K) {

@@ -367,9 +367,10 @@ def test_strided_build_on_both_sides_of_the_short_one(K, n):
     assert np.array_equal(buf.out_coords[:h.n_out].cpu().numpy(), km["out_coords"])
 
 
-@pytest.mark.parametrize("K,n", [(3, 2300 * 64), (3, 2300 * 64 + 1), (3, 2304 * 64 + 63), (5, 1400 * 64 + 1)])
+@pytest.mark.parametrize("K,n", [(3, 1536 * 64), (3, 1536 * 64 + 1), (3, 2300 * 64), (3, 2300 * 64 + 1), (3, 2304 * 64 + 63), (5, 896 * 64),
+                                 (5, 896 * 64 + 1), (5, 1400 * 64 + 1)])
 def test_map_of_tiles_in_runs(K, n):
-    """The fewest tiles that go to the XCDs in runs, with a last run that is not full."""
+    """The most tiles that go to the XCDs in eighths, the fewest that go in runs (6 and 3.5 per CU of 256), last runs that are not full."""
     say(f"map in runs K={K} n={n}")
     import oracle
     import torch
