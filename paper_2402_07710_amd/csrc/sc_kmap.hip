@@ -639,7 +639,6 @@ k_strided_pairs(const int4* __restrict__ coords, int64_t n, Shape sh, const int3
 // The same for short builds with one candidate per input (K == stride), whose flag words the insert kernel has made: every
 // workgroup counts all words for itself, and there is no kernel between claiming and numbering (a launch of 4 us; whole layers K = 2
 // 32 -> 64, 2 k / 10 k / 53 k / 200 k voxels 18.3 / 19.8 / 21.7 / 33.9 -> 16.2 / 17.2 / 19.2 / 31.1 us).  Words and counts of the largest set that comes here are 48 KB of LDS.
-constexpr int SHORT_WORDS = 4096;                      // 262,144 inputs
 template <class Shape>
 __global__ void __launch_bounds__(1024)
 k_strided_pairs_short(const int4* __restrict__ coords, int n, Shape sh, const int32_t* __restrict__ cand_slot, const int32_t* __restrict__ oslots,
@@ -854,9 +853,6 @@ static bool kmap_args_ok(int64_t n, int K, int stride, int mode) {
     }
     return false;
 }
-// Bytes of table a short build clears at most: what is cleared for nothing grows with the table and the launch saved does not (K = 3
-// on 150 k inputs, 16 MiB, a whole 32 -> 64 layer: 37.1 us without and 35.2 with it).
-constexpr int64_t SHORT_TABLE_MAX = 16 << 20;
 // slots of the output-cell table per candidate
 static uint64_t strided_slots(int K, int stride) { return K == stride && K <= 4 ? 8 : 2; }
 
@@ -871,12 +867,14 @@ static int build_strided(const Shape& sh, const int32_t* d_coords, int64_t n, co
     const int64_t nc = n * strided_maxc(K, stride);            // candidates
     StridedScratch g = strided_scratch(d_scratch, nc, strided_slots(K, stride));
     const uint64_t cap = (uint64_t)g.omask + 1;
-    unsigned fb = (unsigned)((cap / 4 + 255) / 256);
-    if (fb > 4096) fb = 4096;
-    // Short builds: one candidate per input, its flags made as the cells are claimed.  All the table rows there could be are cleared
-    // with the cell table, before their number is known, so only where they are few bytes.
+    // Short builds clear all the table rows there could be beside the cell table.
     const int64_t nbr_vec = L.tiles * L.K3 * (TILE / 4);
-    const bool is_short = K == stride && n <= 64 * SHORT_WORDS && nbr_vec * 16 <= SHORT_TABLE_MAX;
+    const bool is_short = short_strided_build(n, K, stride, nbr_vec * 16);
+    // workgroups for the larger of the two (K = 5 on 5 k inputs, with workgroups for the cell table only 40.6 us, now 39.9; K = 7 on 3 k
+    // 69.3, now 66.1; K <= 3 the same)
+    const int64_t cell_vec = (int64_t)(cap / 4), fill_vec = is_short && nbr_vec > cell_vec ? nbr_vec : cell_vec;
+    unsigned fb = (unsigned)((fill_vec + 255) / 256);
+    if (fb > 4096) fb = 4096;
     SC_LAUNCH(KID_FILL_I32, k_strided_fill, dim3(fb), dim3(256), 0, s, (int4*)g.oslots, cap, g.cells, is_short ? g.flagword : (uint64_t*)nullptr,
               is_short ? (n + 63) / 64 : (int64_t)0, (int4*)nbr, is_short ? nbr_vec : (int64_t)0, d_counts, d_table == nullptr ? 1 : 0, n,
               (const TableHeader*)d_table);

@@ -10,3 +10,10 @@ static_assert(map_in_runs(tiles(64000), 5, 256) && !map_in_runs(tiles(53373), 5,
 // the first tile past the line, and the line goes with the compute units
 static_assert(!map_in_runs(1536, 3, 256) && map_in_runs(1537, 3, 256) && !map_in_runs(896, 5, 256) && map_in_runs(897, 5, 256), "first tile");
 static_assert(map_in_runs(385, 3, 64) && !map_in_runs(384, 3, 64) && !map_in_runs(1537, 3, 304), "per compute unit");
+
+// bytes of the offset table of a layer with K == stride
+constexpr int64_t table(int64_t rows, int K) { return tiles(rows) * K * K * K * 256; }
+constexpr bool is_short(int64_t rows, int K) { return short_strided_build(rows, K, K, table(rows, K)); }
+static_assert(is_short(1, 7) && is_short(200000, 2) && is_short(150000, 3) && is_short(49000, 4) && is_short(16000, 5) && is_short(3000, 7), "short");
+static_assert(!is_short(33000, 5) && !is_short(17000, 6) && !is_short(12000, 7) && !is_short(262145, 2) && !is_short(155329, 3), "general");
+static_assert(!short_strided_build(1000, 3, 2, 1), "one candidate per input only");

@@ -346,7 +346,8 @@ def test_inverse_map_of_repeated_coordinates(K, n):
     assert sorted(zip(offset, pout, pin)) == sorted(zip(offset, iin, iout))
 
 
-@pytest.mark.parametrize("K,n", [(2, 1), (2, 63), (2, 1024), (2, 1025), (2, 262144), (2, 262145), (3, 155328), (3, 155329), (4, 65536), (4, 65537), (5, 33536), (7, 12224)])
+@pytest.mark.parametrize("K,n", [(2, 1), (2, 63), (2, 1024), (2, 1025), (2, 262144), (2, 262145), (3, 155328), (3, 155329), (4, 65536), (4, 65537), (5, 16768), (5, 16769), (5, 33536), (6, 9664), (6, 9665), (7, 6080),
+                                 (7, 6081), (7, 12224)])
 def test_strided_build_on_both_sides_of_the_short_one(K, n):
     """K == stride: cells with one input and with many, in random order; the largest sets whose words are counted by every
     workgroup or whose table is cleared ahead, and one row more."""
@@ -410,3 +411,24 @@ def test_64_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
         fused = sc.LayerBuffers(n, 3, 1, "subm", 64, C_out, "bf16", device="cuda:0", grid_dims=(1, side, side, side))
         fused.layer_fused(c, f, w)
         assert torch.equal(fused.feat_out, buf.feat_out)
+
+
+@pytest.mark.parametrize("K,n", [(2, 262145), (3, 155329), (4, 65537), (5, 16769), (5, 33000), (6, 9665), (7, 6081)])
+def test_large_tables_are_cleared_where_rows_exist(K, n):
+    """K == stride: of a table that is more than a build should clear ahead, the rows that no cell has stay as they were."""
+    say(f"rows that do not exist K=s={K} n={n}")
+    import oracle
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    coords = synth.lidar_scene(1)
+    coords = np.ascontiguousarray(np.concatenate([np.concatenate([np.full((len(coords), 1), b), coords[:, 1:]], axis=1) for b in range(5)])[:n].astype(np.int32))
+    buf = sc.LayerBuffers(n, K, K, "strided", 32, 32, "f16", device="cuda:0")
+    buf.kmap.fill_(0x11)
+    buf.kmap_build(torch.from_numpy(coords).to("cuda:0"), standalone=True)
+    n_out = buf.read_counts().n_out
+    assert n_out == oracle.kmap(coords, K, K, "strided")["n_out"] < n
+    K3, tiles, used = K ** 3, (n + 63) // 64, (n_out + 63) // 64
+    first = (256 + tiles * 16 * ((K3 + 31) // 32) + 255) // 256 * 256 // 4       # int32 index of the table
+    table = buf.kmap[:(first + tiles * K3 * 64) * 4].view(torch.int32)[first:].view(tiles, K3 * 64)
+    assert used < tiles and bool((table[used:] == 0x11111111).all())
+    assert not bool((table[:used] == 0x11111111).any())
