@@ -14,6 +14,7 @@
 // many loads are in flight: the kernels below issue the offset-table reads of all K^3 offsets,
 // then all feature gathers, before the first multiply.
 #include "sc_conv.h"
+#include "sc_rules.h"
 
 namespace sc {
 
@@ -720,10 +721,11 @@ static int pack_weights(int K3, int C_in, int C_out, const void* d_weight, void*
 
 // A 16-bit layer.  `packed`: d_weight is what sc_conv_weight_pack made; otherwise the raw weights,
 // which the resident kernels re-lay out themselves and the others have packed into the workspace
-// first.  FUSED (dense table, no map) always takes raw weights.
+// first.  FUSED (dense table, no map) always takes raw weights.  `strided`: the number of output rows is known on the device only;
+// `overlapping`: strided with K != stride.
 template <int FUSED>
-static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, hipStream_t s, const void* d_feat_in,
-                      const void* d_weight, bool packed, void* d_workspace, void* d_feat_out,
+static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, bool strided, bool overlapping, hipStream_t s,
+                      const void* d_feat_in, const void* d_weight, bool packed, void* d_workspace, void* d_feat_out,
                       int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const uint16_t* feat = (const uint16_t*)d_feat_in;
     bool handled = false;
@@ -756,27 +758,17 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
         if (int prc = pack_weights(K3, C_in, C_out, d_weight, d_workspace, s)) return prc;
         wp = (const uint4*)d_workspace;
     }
-    // 128 -> 128: the general kernel up to 20 tiles per CU.  A workgroup of the streaming kernel is eight
-    // tiles and takes ~75 us however few there are; full, it moves the weights once for them (us, general and
-    // streaming kernel: 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276,
-    // 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k 110 / 82).  Beyond 20 tiles per CU the streaming kernel takes
-    // 86 us a round of eight tiles per CU, full or not, the general one 0.05 us a tile of a dense set and less of others: K = 3 layers
-    // whose rounds are less than four fifths full stay with it (whole layers, general and streaming: indoor 400 k, 0.76 full, 370 /
-    // 407, 500 k, 0.95, 466 / 428, 700 k, 0.89, 663 / 624; sweeps 400 k 287 / 371).
-    // 32 -> 64, K = 3: the streaming kernel walks all offsets, four tiles in step, which is the longer chain of few tiles and the
-    // cheaper one of many dense ones.  The general kernel up to 13 tiles per CU, strided layers, whose rows have few neighbours
-    // each but most offsets, up to 7 (us, general and streaming kernel: 2 k voxels 7.1 / 9.1, 53 k 12.3 / 13.8, 110 k 20.3 / 20.2,
-    // 200 k 31.9 / 36.2, 262 k 39.4 / 39.0, indoor 100 k 23.1 / 22.9, 200 k 39.0 / 43.1, 800 k 144 / 130; strided 3 k 7.6 / 9.9, 53 k
-    // 14.7 / 18.2, 110 k 25.5 / 27.4, 150 k 31.6 / 29.1).  Fused, where the look-ups would add to the walk of a wavefront with 64
-    // rows, at every size (whole layers: 2 k 13.1 / 22.3, 53 k 22.5 / 27.0, 200 k 51.2 / 64.3, 400 k 88.5 / 108; indoor 800 k 184.7 / 182.7).
-    if (!FUSED && K3 == 27 && C_in == 32 && C_out == 64 && likely <= (tiles == likely ? 13 : 7) * (int64_t)compute_units())
+    // general or streaming kernel (sc_rules.h).  Fused 32 -> 64, where the look-ups would add to the walk of a wavefront with 64 rows, through
+    // the general one at every size (whole layers, us, general and streaming: 2 k 13.1 / 22.3, 53 k 22.5 / 27.0, 200 k 60.3 / 77.6, 400 k 114 / 142, 10^6 257 /
+    // 309; indoor 200 k 50.2 / 58.2, 400 k 104 / 115, 800 k 213.6 / 216.9, 10^6 266.9 / 269.0)
+    const bool general = FUSED && fused_gather ? true
+                         : wide                ? general_128_to_128(K3 == 27 ? 3 : 2, likely, strided, compute_units())
+                                               : !FUSED && K3 == 27 && C_in == 32 && C_out == 64 &&
+                                                     general_32_to_64(likely, overlapping, compute_units());
+    if (general && FUSED)
+        return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
+    if (general)
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
-    const int64_t round = 8 * (int64_t)compute_units();
-    const bool part_filled = K3 == 27 && 5 * likely < 4 * ((likely + round - 1) / round * round);
-    if ((FUSED && fused_gather) || (wide && (likely <= 20 * (int64_t)compute_units() || part_filled))) {
-        if (FUSED) return launch_gather_fused(dtype_in, C_in, C_out, tiles, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
-        return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
-    }
     rc = dtype_in == SC_F16 ? launch_streamed<SC_F16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
                                                             n_out_ptr, n_out_cap, &handled)
                             : launch_streamed<SC_BF16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
@@ -880,8 +872,9 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         if (d_workspace == nullptr || workspace_bytes < need) return SC_ECAP;
     }
     const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
-    return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, s, d_feat_in, d_weight, packed, d_workspace,
-                         d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap);
+    const bool strided = mode == SC_STRIDED;
+    return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, strided, strided && K != stride, s, d_feat_in, d_weight, packed,
+                         d_workspace, d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap);
 }
 
 extern "C" int sc_conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, void* d_feat_out,
@@ -973,6 +966,6 @@ extern "C" int sc_conv_fwd_grid(const void* d_feat_in, const int32_t* d_coords, 
     if (n == 0) return SC_OK;
     const MapSource ms{nullptr, nullptr, (const int4*)d_coords, (const unsigned long long*)d_grid, GridDims{B, X, Y, Z}, epoch};
     if (!mfma_channels_ok(C_in, C_out)) return SC_EINVAL;
-    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, (hipStream_t)stream, d_feat_in, d_weight,
-                         false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n);
+    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, false, false, (hipStream_t)stream, d_feat_in,
+                         d_weight, false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n);
 }

@@ -26,4 +26,27 @@ constexpr bool short_strided_build(int64_t n, int K, int stride, int64_t table_b
     return K == stride && n <= 64 * SHORT_WORDS && table_bytes <= (K <= 4 ? 16 << 20 : 8 << 20);
 }
 
+// 32 -> 64, K = 3, 16 bit: general kernel or streaming kernel (false).  The streaming kernel walks all offsets, four tiles in step, which is the
+// longer chain of few tiles and the cheaper one of many dense ones.  `likely` tiles; `overlapping`: strided with K != stride, whose rows
+// have few neighbours each but most offsets.  Up to 13 tiles per CU, overlapping 7 (us of the whole layer, general / streaming, sweep
+// and indoor rows.  Submanifold: 53 k 27.6 / 28.5 and 27.3 / 27.9, 115 k 43.2 / 43.1 and 45.2 / 44.2, 150 k 52.5 / 55.7 and 54.6 / 57.5, 213 k 75.6 / 78.7 and 76.4 /
+// 78.1, 262 k 96.2 / 96.1 and 96.4 / 92.1.  K == stride = 3, a cell's rows in one place: 53 k 26.5 / 29.8 and 26.3 / 29.2, 150 k 34.2 / 35.2 and 31.6 / 34.0, 213 k
+// 39.0 / 39.1 and 34.7 / 36.9, 400 k 57.3 / 53.7 and 45.5 / 44.7.  Stride 2: 53 k 38.5 / 40.8 and 34.9 / 37.0, 85 k 53.9 / 51.9 and 45.9 / 46.6, 115 k 61.6 / 62.7 and
+// 51.0 / 50.5, 150 k 76.0 / 73.1 and 63.6 / 65.8, 180 k 87.6 / 86.6 and 71.8 / 69.7, 262 k 123 / 114 and 93.3 / 84.2; the convolution where the caller knows the rows, indoor:
+// 53 k 16.1 / 15.1, 69 k 18.6 / 21.0, 83 k 24.2 / 21.7, 121 k 28.0 / 22.4).
+constexpr bool general_32_to_64(int64_t likely, bool overlapping, int64_t cus) { return likely <= (overlapping ? 7 : 13) * cus; }
+
+// 128 -> 128, K = 2 and 3, 16 bit: general kernel or streaming kernel (false).  A workgroup of the streaming kernel is eight tiles and takes ~75 us
+// however few there are; full, it moves the weights once for them.  General up to 20 tiles per CU (us of the convolution, general / streaming:
+// 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276, 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k
+// 110 / 82).  Beyond, the streaming kernel takes 86 us a round of eight tiles per CU, full or not, the general one 0.05 us a tile of a
+// dense set and less of others: K = 3 layers whose rounds are less than four fifths full stay with it, where the rows are known to the caller
+// (whole layers: indoor 400 k, 0.76 full, 372 / 408, 500 k, 0.95, 464 / 427, 700 k, 0.89, 657 / 623; sweeps 400 k 282 / 366; inverse maps 400 k
+// sweeps 165 / 244, indoor 241 / 247).  Of strided layers only the inputs are known, and the rows decide how full the rounds are: stride 2 on 400 k
+// sweeps 396 / 386, indoor 270 / 267, stride 3 132 / 111 and 109.4 / 110.9.
+constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t cus) {
+    const int64_t round = 8 * cus;
+    return likely <= 20 * cus || (K == 3 && !strided && 5 * likely < 4 * ((likely + round - 1) / round * round));
+}
+
 }  // namespace sc

@@ -17,3 +17,11 @@ constexpr bool is_short(int64_t rows, int K) { return short_strided_build(rows, 
 static_assert(is_short(1, 7) && is_short(200000, 2) && is_short(150000, 3) && is_short(49000, 4) && is_short(16000, 5) && is_short(3000, 7), "short");
 static_assert(!is_short(33000, 5) && !is_short(17000, 6) && !is_short(12000, 7) && !is_short(262145, 2) && !is_short(155329, 3), "general");
 static_assert(!short_strided_build(1000, 3, 2, 1), "one candidate per input only");
+
+// 32 -> 64: 7 tiles per compute unit where strided cells overlap, however exactly the caller knows the rows; 13 elsewhere, K == stride = 3 too
+static_assert(general_32_to_64(tiles(115000), true, 256) == false && general_32_to_64(tiles(114000), true, 256), "stride 2");
+static_assert(general_32_to_64(tiles(150000), false, 256) && !general_32_to_64(tiles(213100), false, 256), "the others");
+// 128 -> 128: the rounds of a layer that is not strided count, a strided one's are not known
+static_assert(general_128_to_128(3, tiles(400000), false, 256) && !general_128_to_128(3, tiles(400000), true, 256), "part-filled rounds");
+static_assert(!general_128_to_128(3, tiles(500000), false, 256) && !general_128_to_128(2, tiles(400000), false, 256), "full rounds, K = 2");
+static_assert(general_128_to_128(3, 20 * 256, true, 256) && general_128_to_128(2, 20 * 256, true, 256), "up to 20 tiles per compute unit");

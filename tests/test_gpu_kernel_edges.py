@@ -432,3 +432,28 @@ def test_large_tables_are_cleared_where_rows_exist(K, n):
     table = buf.kmap[:(first + tiles * K3 * 64) * 4].view(torch.int32)[first:].view(tiles, K3 * 64)
     assert used < tiles and bool((table[used:] == 0x11111111).all())
     assert not bool((table[:used] == 0x11111111).any())
+
+
+@pytest.mark.parametrize("stride,C_in,C_out,n", [(2, 128, 128, 393_217), (3, 128, 128, 400_000), (2, 32, 64, 400_000)])
+def test_streaming_kernel_strided_rows_known_to_the_caller(stride, C_in, C_out, n):
+    """K = 3, the output holds exactly the rows there are.  128 -> 128: strided layers of inputs that would leave a round part-filled;
+    32 -> 64: stride 2, rows between 7 and 13 tiles per CU (of 256)."""
+    say(f"streaming kernel K=3 s={stride} {C_in}->{C_out} n={n}")
+    import oracle
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import rel_err, sampled_rows_reference, to_dev
+    coords = synth.uniform_cells(n, 80 if C_in == 128 else 110, seed=stride)
+    feat, weight = synth.features(n, C_in, "f16", 3), synth.weights(27, C_in, C_out, "f16", 3)
+    buf = sc.LayerBuffers(n, 3, stride, "strided", 32, 32, "f16", device="cuda:0")
+    buf.kmap_build(torch.from_numpy(coords).to("cuda:0"), standalone=True)
+    km = oracle.kmap(coords, 3, stride, "strided")
+    n_out = buf.read_counts().n_out
+    assert n_out == km["n_out"]
+    assert C_in == 128 or 7 * 256 < n_out / 64 <= 13 * 256
+    out = torch.full((n_out, C_out), float("nan"), dtype=torch.float32, device="cuda:0")
+    packed = sc.sc_conv_weight_pack(to_dev(weight, "f16"), 3)
+    sc.sc_conv_fwd_packed(to_dev(feat, "f16"), packed, C_out, out, buf.kmap, buf.counts, 3, stride, "strided", n_map=n)
+    rows = np.unique(np.concatenate([np.random.default_rng(3).choice(n_out, 3000, replace=False), np.arange(200), np.arange(n_out - 200, n_out)]))
+    err = rel_err(out.cpu().numpy()[rows], sampled_rows_reference(feat, weight, km, rows)[rows])
+    assert err <= 1e-5, err
