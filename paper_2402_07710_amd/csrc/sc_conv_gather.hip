@@ -1,6 +1,7 @@
 // The general convolution kernel: 16-bit layers of 64 and more channels (128 -> 128 up to 20 tiles per CU), every
 // shape without a kernel of its own in sc_conv.hip, and fp32 layers with enough work for it.
 #include "sc_conv.h"
+#include "sc_rules.h"
 
 namespace sc {
 
@@ -470,25 +471,13 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
 #undef SC_GATHER
 }
 
-// 32-channel rows, K <= 3: steps of four offsets are the shorter walk as long as all workgroups are on the chip at once (39 KB of
-// LDS: four per CU); beyond two per CU steps of two (23 KB) and groups without a neighbour left out (us, four and two offsets:
-// 32 -> 64 20 k voxels 8.6 / 9.2, 40 k 11.1 / 10.9, 53 k 13.4 / 12.3, 200 k 34.9 / 31.9; strided 53 k 17.1 / 14.7; 32 -> 128 110 k 32.8 / 29.2).
-static bool likely_two_offsets(int64_t likely, int CB, int cus) { return likely * ((CB + 3) / 4) > 2 * (int64_t)cus; }
-
-// 64-channel rows, K <= 3: steps of two offsets up to three workgroups per CU.  A workgroup's walk is bound by the instructions of its
-// steps there (list, loop and barrier once for two offsets), beyond by the loads, and 39 KB of LDS instead of 23 leave four
-// workgroups a CU instead of six (whole layers, us, one and two offsets: 64 -> 64 10 k / 20 k / 30 k / 46 k / 60 k / 72 k 21.3 / 25.2 / 27.1 /
-// 29.9 / 35.0 / 38.0 and 20.5 / 22.4 / 24.1 / 28.1 / 34.4 / 39.2; indoor 20 k / 40 k / 50 k 24.1 / 28.6 / 31.9 and 22.7 / 28.5 / 33.5; K = 3,
-// stride 2, 20 k / 53 k 33.4 / 43.6 and 29.8 / 45.2; 64 -> 128 20 k / 40 k 26.1 / 32.2 and 24.4 / 33.9; 64 -> 32 30 k 26.4 and 23.0).
-static bool few_workgroups(int64_t likely, int CB, int cus) { return likely * ((CB + 3) / 4) <= 3 * (int64_t)cus; }
-
 int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const int CB = C_out / 16;
     // Slices per step, skipping, wavefronts per SIMD.  256 channels: a whole offset.  128: an offset (half of one,
     // with more workgroups: 128 -> 64 at 53 k voxels 36.7 us instead of 28.8).  64: an offset; two for K = 5 and 7, whose
     // tiles walk many more offsets (K = 3 -> 64 at 262 k voxels 50.3 us with one, 56.5 with two; K = 5 -> 64 at 53 k 55.1
-    // and 50.7; K <= 3: few_workgroups).  32: four (K = 5 -> 32 at 53 k: 30.4 us; two 32.1, eight with half the workgroups 36).
+    // and 50.7).  32: four (K = 5 -> 32 at 53 k: 30.4 us; two 32.1, eight with half the workgroups 36).
 #define SC_GATHER_KS(KS, SL, SKIP, O1, O2, SRC)                                                                                      \
     return dtype_in == SC_F16                                                                                                     \
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
@@ -506,14 +495,14 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
 #undef SC_GATHER_F32
         return SC_EINVAL;
     }
-    const bool two_offsets = likely_two_offsets(likely, CB, cus);
+    const bool few = few_workgroups(likely, CB, cus);
     if (K3 <= 27) {
         switch (C_in) {
             case 32:
-                if (two_offsets) SC_GATHER_KS(1, 2, 1, 5, 4, FROM_LINES);
-                SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
+                if (few) SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
+                SC_GATHER_KS(1, 2, 1, 5, 4, FROM_LINES);
             case 64:
-                if (few_workgroups(likely, CB, cus)) SC_GATHER_KS(2, 4, 1, 4, 4, FROM_LINES);
+                if (few) SC_GATHER_KS(2, 4, 1, 4, 4, FROM_LINES);
                 SC_GATHER_KS(2, 2, 1, 6, 5, FROM_LINES);
             case 128: SC_GATHER_KS(4, 4, 1, 4, 3, FROM_LINES);
             case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_LINES);
@@ -538,9 +527,10 @@ int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cu
     return dtype_in == SC_F16                                                                                                                \
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
                : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
-    if (C_in == 32 && likely_two_offsets(tiles, CB, cus)) SC_GATHER_FUSED(1, 2, 1, 5, 4);
-    if (C_in == 32) SC_GATHER_FUSED(1, 4, 0, 2, 2);
-    if (C_in == 64 && few_workgroups(tiles, CB, cus)) SC_GATHER_FUSED(2, 4, 1, 4, 4);
+    const bool few = few_workgroups(tiles, CB, cus);
+    if (C_in == 32 && few) SC_GATHER_FUSED(1, 4, 0, 2, 2);
+    if (C_in == 32) SC_GATHER_FUSED(1, 2, 1, 5, 4);
+    if (C_in == 64 && few) SC_GATHER_FUSED(2, 4, 1, 4, 4);
     if (C_in == 64) SC_GATHER_FUSED(2, 2, 1, 6, 5);
     if (C_in == 128) SC_GATHER_FUSED(4, 4, 1, 4, 3);
 #undef SC_GATHER_FUSED

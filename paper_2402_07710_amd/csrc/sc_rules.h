@@ -49,4 +49,16 @@ constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t c
     return likely <= 20 * cus || (K == 3 && !strided && 5 * likely < 4 * ((likely + round - 1) / round * round));
 }
 
+// The general kernel, K <= 3, up to three workgroups per CU: steps of four offsets of 32-channel rows and of two of 64-channel ones, the shorter walk; 39 KB of LDS,
+// four workgroups a CU.  A workgroup's walk is bound by the instructions of its steps there (list, loop and barrier once for more offsets), beyond
+// by the loads, and steps of two and one (23 KB, six workgroups a CU; groups without a neighbour left out) are worth more.
+// us of whole layers, four and two offsets: 32 -> 64 sweeps 30 k / 38 k / 46 k / 53 k / 70 k 21.0 / 23.0 / 24.1 / 28.1 / 33.8 and 22.0 / 23.6 / 24.4 / 27.5 / 32.0,
+// indoor 21.1 / 23.7 / 25.0 / 28.8 / 34.4 and 21.6 / 23.5 / 24.6 / 27.4 / 31.7; K = 3, stride 2, sweeps 30.6 / 33.4 / 36.2 / 40.4 / 49.2 and 31.5 / 33.9 / 36.2 / 38.7 /
+// 48.4, indoor 28.4 / 31.1 / 32.8 / 34.1 / 40.8 and 30.1 / 32.5 / 34.0 / 35.4 / 41.9; fused sweeps 17.1 / 19.9 / 20.3 / 23.0 / 26.9 and 18.2 / 20.2 / 20.8 / 23.1 / 25.8;
+// 32 -> 128 sweeps 14 k / 20 k / 28 k 18.2 / 20.6 / 24.0 and 19.0 / 20.6 / 23.1, indoor 19.1 / 21.8 / 25.3 and 19.1 / 21.2 / 24.2.
+// Two offsets and one: 64 -> 64 sweeps 36 k / 46 k / 55 k / 60 k 26.2 / 28.0 / 32.6 / 34.3 and 27.9 / 29.7 / 33.2 / 34.9, indoor 27.4 / 29.3 / 34.7 / 35.6 and 27.5 / 29.1 / 33.4 /
+// 34.7; K = 3, stride 2, sweeps 36.3 / 40.3 / 46.0 / 49.0 and 37.5 / 40.5 / 44.6 / 46.9, indoor 33.7 / 35.5 / 37.3 / 38.0 and 36.9 / 39.0 / 40.2 / 40.9; 64 -> 128 sweeps
+// 18 k / 26 k / 30 k 23.0 / 26.7 / 28.2 and 25.5 / 27.2 / 28.3, indoor 25.4 / 30.1 / 31.2 and 25.4 / 28.9 / 30.5.
+constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return likely * ((CB + 3) / 4) <= 3 * cus; }
+
 }  // namespace sc

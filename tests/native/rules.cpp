@@ -25,3 +25,7 @@ static_assert(general_32_to_64(tiles(150000), false, 256) && !general_32_to_64(t
 static_assert(general_128_to_128(3, tiles(400000), false, 256) && !general_128_to_128(3, tiles(400000), true, 256), "part-filled rounds");
 static_assert(!general_128_to_128(3, tiles(500000), false, 256) && !general_128_to_128(2, tiles(400000), false, 256), "full rounds, K = 2");
 static_assert(general_128_to_128(3, 20 * 256, true, 256) && general_128_to_128(2, 20 * 256, true, 256), "up to 20 tiles per compute unit");
+
+// longer steps up to three workgroups per compute unit, one for 64 output channels: 32 -> 64 on 40 k rows too
+static_assert(few_workgroups(tiles(40000), 4, 256) && few_workgroups(768, 4, 256) && !few_workgroups(769, 4, 256), "64 output channels");
+static_assert(few_workgroups(384, 8, 256) && !few_workgroups(385, 8, 256) && few_workgroups(768, 1, 256), "128 and 16 output channels");

@@ -457,3 +457,29 @@ def test_streaming_kernel_strided_rows_known_to_the_caller(stride, C_in, C_out, 
     rows = np.unique(np.concatenate([np.random.default_rng(3).choice(n_out, 3000, replace=False), np.arange(200), np.arange(n_out - 200, n_out)]))
     err = rel_err(out.cpu().numpy()[rows], sampled_rows_reference(feat, weight, km, rows)[rows])
     assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("C_out,n", [(64, 512 * 64 + 1), (64, 768 * 64), (64, 768 * 64 + 1), (128, 384 * 64), (128, 384 * 64 + 1), (16, 33)])
+def test_32_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
+    """Steps of four offsets, with lists that do not fill the last one, and of two; with and without a map."""
+    say(f"32 -> {C_out}, n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import TOL, to_dev
+    side = max(4, int(round((n * 3) ** (1 / 3))))
+    coords = synth.uniform_cells(n, side, seed=C_out)
+    feat, weight = synth.features(n, 32, "f16", 1), synth.weights(27, 32, C_out, "f16", 1)
+    buf = sc.LayerBuffers(n, 3, 1, "subm", 32, C_out, "f16", device="cuda:0")
+    c, f, w = torch.from_numpy(coords).to("cuda:0"), to_dev(feat, "f16"), to_dev(weight, "f16")
+    buf.feat_out.fill_(float("nan"))
+    buf.layer(c, f, w)
+    pin, pout, start = (t.long() for t in buf.export())
+    ref = torch.zeros((n, C_out), device="cuda:0")
+    for k in range(27):
+        at = slice(int(start[k]), int(start[k + 1]))
+        ref.index_add_(0, pout[at], f[pin[at]].float() @ w[k].float())
+    assert float((buf.feat_out.float() - ref).abs().max() / ref.abs().max()) <= TOL["f16"]
+    if C_out == 64:
+        fused = sc.LayerBuffers(n, 3, 1, "subm", 32, C_out, "f16", device="cuda:0", grid_dims=(1, side, side, side))
+        fused.layer_fused(c, f, w)
+        assert torch.equal(fused.feat_out, buf.feat_out)
