@@ -630,9 +630,11 @@ static int launch_resident(int K3, int C_in, int C_out, int64_t tiles, int64_t l
     *handled = true;
 #define SC_ROWS16(K3V, KSV, CBV, NTV) \
     return launch_rows16<DT, K3V, KSV, CBV, NTV, FUSED, 0, WPACKED>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
-    // four tiles per workgroup once the likely tiles still give two CUs one (half the copies of the weights, and no CU with
-    // two workgroups while another has one: 53 k voxels 11.9 -> 10.6 us with raw weights).  The likely ones: by the bound, 512
-    // tiles or more, strided layers of 10 k ... 30 k voxels took four and left most CUs idle (7.6 ... 8.1 us, now 6.1 ... 6.5).
+    // four tiles per workgroup once the likely tiles still give two CUs one: half the copies of the weights, and no CU with
+    // two workgroups while another has one (us of whole layers on sweeps, two and four tiles: raw weights 16 k / 30 k / 34 k / 53 k 15.5 / 18.1 / 20.3 /
+    // 24.5 and 17.4 / 19.8 / 20.1 / 23.8, packed 16.0 / 18.7 / 19.9 / 24.0 and 16.8 / 19.2 / 19.8 / 23.5, fused 10.7 / 11.8 / 14.2 / 15.4 and 13.0 / 13.9 / 13.9 / 14.8; indoor
+    // sets cross at 34 k too).  The likely ones: by the bound, 512 tiles or more, strided layers of 10 k / 20 k / 30 k voxels took four and left
+    // most CUs idle (convolution 7.5 / 8.0 / 8.3, now 6.0 / 7.1 / 7.5).
     if (K3 == 27 && C_in == 32 && C_out == 32 && likely >= 512) SC_ROWS16(27, 1, 2, 4);
     if (K3 == 27 && C_in == 32 && C_out == 32) SC_ROWS16(27, 1, 2, 2);
     if constexpr (!FUSED) {

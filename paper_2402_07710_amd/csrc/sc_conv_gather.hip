@@ -36,14 +36,15 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 //    below); they go through LDS instead.  An fp32 multiply takes eight times as long per byte, so the
 //    wavefronts (eight) split rows as well as channels.
 //  * The steps are read from a list of the tile's offsets that is made once, in LDS: walking the mask words in every step was
-//    a third of a step's instructions, and scalar ones issue once per four cycles for all wavefronts of a SIMD (us, before and
-//    with the list: K = 5 32 -> 32 4 k / 53 k voxels 22.7 / 32.1 -> 16.0 / 25.3, K = 5 64 -> 64 20 k 44.5 -> 34.2, 64 -> 64 4 k
-//    12.6 -> 10.3, 128 -> 256 5 k 19.4 -> 17.8, fp32 64 -> 64 8 k 23.4 -> 21.3, 32 -> 64 80 k 58.3 -> 55.3; 110 k and more the same).
+//    a third of a step's instructions, and scalar ones issue once per four cycles for all wavefronts of a SIMD (us of whole layers, before
+//    and with the list: K = 5 32 -> 32 4 k / 53 k voxels 37.6 / 65.5 -> 31.1 / 58.8, K = 5 64 -> 64 20 k 64.6 -> 56.0, 64 -> 64 4 k / 110 k
+//    23.8 / 52.8 -> 22.5 / 51.6, 128 -> 256 5 k 28.8 -> 27.1, fp32 64 -> 64 8 k / 53 k 33.2 / 91.5 -> 31.1 / 88.2, 256 -> 256 14 k 62.6 -> 62.0; 32 -> 64
+//    80 k the same).
 //  * FROM_LINES (K <= 3, 16 bit): the tile's lines of the map are copied to LDS at the start, beside the
 //    masks' round trip.  Read from the map step by step, 32 bytes at a time, they were a third of the loads that the address unit
-//    serves at 17 cycles each, and the first gathers waited for them (us, before -> with: 64 -> 64 110 k / 262 k / 10^6 voxels
-//    30.7 / 58.0 / 326 -> 29.4 / 54.4 / 302, 128 -> 128 20 k / 53 k / 262 k 21.4 / 43.6 / 152 -> 20.2 / 42.2 / 147, 256 -> 256 14 k 45.7 ->
-//    43.5, 32 -> 64 2 k / 40 k 7.4 / 11.4 -> 7.1 / 11.1).  7 KB of LDS: fp32 would lose a workgroup per CU to them.
+//    serves at 17 cycles each, and the first gathers waited for them (us of whole layers, before -> with: 64 -> 64 110 k / 262 k / 10^6 voxels
+//    51.4 / 117.3 / 457 -> 50.6 / 114.4 / 429, 128 -> 128 20 k / 53 k / 262 k 32.6 / 56.4 / 205.6 -> 31.5 / 54.5 / 201, 256 -> 256 14 k 58.9 -> 56.9, 32 -> 64
+//    40 k 24.6 -> 23.7).  7 KB of LDS: fp32 would lose a workgroup per CU to them.
 //  * One wait for everything and one barrier per step.  What a step costs is issuing its loads (17
 //    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
 //  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
@@ -287,9 +288,9 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     auto compute = [&](const u32x4 (&a)[SL][CT], const uint32_t (&p)[OPS], int buf) {
         if constexpr (!F32 && (KP == 1 || KP == 8)) {
             // Operands are read a batch of groups ahead of its multiplies, also of a group without a neighbour: its products are
-            // left out.  Batches are all groups of an offset (32 channels) or one (256).  (us, before -> now: 256 -> 256 500 / 2 k /
-            // 5 k voxels 12.8 / 22.9 / 29.8 -> 11.2 / 20.8 / 26.0, K = 5 32 -> 32 4 k / 53 k 16.0 / 25.2 -> 15.3 / 24.4.  64 and 128
-            // channels, whose batches are short next to the latency, lose the registers: 110 k 64 -> 64 30.5 -> 32.3.)
+            // left out.  Batches are all groups of an offset (32 channels) or one (256).  (us of whole layers, before -> now: 256 -> 256 500 / 2 k /
+            // 5 k / 14 k voxels 25.9 / 33.6 / 37.8 / 62.3 -> 24.0 / 30.9 / 34.2 / 59.6; K = 5 32 -> 32 the same.  64 and 128
+            // channels, whose batches are short next to the latency, lose the registers: convolution of 110 k 64 -> 64 30.5 -> 32.3.)
             constexpr int GB = KP == 1 ? RG : 1, NB = RG / GB, BATCHES = OPS * NB;
             uint4 b[2][GB][KP];
             auto read = [&](uint4 (&b)[GB][KP], int i) __attribute__((always_inline)) {

@@ -638,7 +638,7 @@ k_strided_pairs(const int4* __restrict__ coords, int64_t n, Shape sh, const int3
 
 // The same for short builds with one candidate per input (K == stride), whose flag words the insert kernel has made: every
 // workgroup counts all words for itself, and there is no kernel between claiming and numbering (a launch of 4 us; whole layers K = 2
-// 32 -> 64, 2 k / 10 k / 53 k / 200 k voxels 18.3 / 19.8 / 21.7 / 33.9 -> 16.2 / 17.2 / 19.2 / 31.1 us).  Words and counts of the largest set that comes here are 48 KB of LDS.
+// 32 -> 64, 2 k / 10 k / 53 k / 200 k voxels 18.3 / 19.7 / 22.6 / 32.6 -> 16.0 / 17.2 / 20.1 / 30.3 us).  Words and counts of the largest set that comes here are 48 KB of LDS.
 template <class Shape>
 __global__ void __launch_bounds__(1024)
 k_strided_pairs_short(const int4* __restrict__ coords, int n, Shape sh, const int32_t* __restrict__ cand_slot, const int32_t* __restrict__ oslots,
@@ -809,7 +809,7 @@ k_write_starts(StartArg a, int count, int32_t* __restrict__ dst) {
 // Inverse layer (Section III-E): the pairs of a strided map with input and output swapped.  Every fine row has one parent
 // (K == stride); the strided build leaves (coarse row, offset) in one word per fine row, and this kernel expands the 64
 // words of a tile to its K^3 lines and group masks.  Finding the words again by scattering the strided table was a kernel of its
-// own, a launch of 4 us (transpose and 64 -> 32 convolution on 53 k rows 11.7 -> 9.2 us).
+// own, a launch of 4 us (transpose and 64 -> 32 convolution on 53 k rows 12.1 -> 9.5 us).
 // One wavefront per fine tile, lane = row.  A word counts only if the strided map confirms it: of inputs with the same
 // coordinate the map holds one.
 __global__ void __launch_bounds__(256)
