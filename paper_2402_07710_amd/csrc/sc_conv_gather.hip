@@ -40,7 +40,7 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 //    and with the list: K = 5 32 -> 32 4 k / 53 k voxels 37.6 / 65.5 -> 31.1 / 58.8, K = 5 64 -> 64 20 k 64.6 -> 56.0, 64 -> 64 4 k / 110 k
 //    23.8 / 52.8 -> 22.5 / 51.6, 128 -> 256 5 k 28.8 -> 27.1, fp32 64 -> 64 8 k / 53 k 33.2 / 91.5 -> 31.1 / 88.2, 256 -> 256 14 k 62.6 -> 62.0; 32 -> 64
 //    80 k the same).
-//  * FROM_LINES (K <= 3, 16 bit): the tile's lines of the map are copied to LDS at the start, beside the
+//  * FROM_LINES (K = 2 and 3, 16 bit): the tile's lines of the map are copied to LDS at the start, beside the
 //    masks' round trip.  Read from the map step by step, 32 bytes at a time, they were a third of the loads that the address unit
 //    serves at 17 cycles each, and the first gathers waited for them (us of whole layers, before -> with: 64 -> 64 110 k / 262 k / 10^6 voxels
 //    51.4 / 117.3 / 457 -> 50.6 / 114.4 / 429, 128 -> 128 20 k / 53 k / 262 k 32.6 / 56.4 / 205.6 -> 31.5 / 54.5 / 201, 256 -> 256 14 k 58.9 -> 56.9, 32 -> 64
@@ -497,7 +497,9 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
         return SC_EINVAL;
     }
     const bool few = few_workgroups(likely, CB, cus);
-    if (K3 <= 27) {
+    // K = 1 of 64 and more channels: one line, read once, is not worth holding (us of the convolution, held and read: 200 k voxels 64 -> 64
+    // 15.0 / 14.4, 128 -> 64 23.4 / 20.9, 256 -> 128 49.4 / 48.3, 53 k 128 -> 128 11.6 / 10.8; 32 -> 64, whose steps are shorter with it, 14.1 / 19.8)
+    if (K3 <= 27 && (K3 > 1 || C_in == 32)) {
         switch (C_in) {
             case 32:
                 if (few) SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
@@ -509,6 +511,7 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
             case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_LINES);
         }
     }
+    if (K3 == 1 && C_in == 64) SC_GATHER_KS(2, 2, 1, 6, 5, FROM_MAP);
     switch (C_in) {
         case 32: SC_GATHER_KS(1, 4, 0, 2, 2, FROM_MAP);
         case 64: SC_GATHER_KS(2, 4, 1, 5, 4, FROM_MAP);

@@ -483,3 +483,16 @@ def test_32_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
         fused = sc.LayerBuffers(n, 3, 1, "subm", 32, C_out, "f16", device="cuda:0", grid_dims=(1, side, side, side))
         fused.layer_fused(c, f, w)
         assert torch.equal(fused.feat_out, buf.feat_out)
+
+
+@pytest.mark.parametrize("C_in,C_out", [(64, 64), (64, 128), (128, 16), (256, 48)])
+@pytest.mark.parametrize("n,dtype", [(1, "f16"), (64, "bf16"), (65, "f16"), (34000, "f16")])
+def test_pointwise_layers(C_in, C_out, n, dtype):
+    """K = 1: a list of one offset, read from the map; whole tiles, a tile of one row, and two output blocks per wavefront (64 -> 128)."""
+    say(f"K=1 {C_in}->{C_out} {dtype} n={n}")
+    if n < 1000:
+        coords = synth.uniform_cells(n, 6, seed=n)
+    else:
+        coords = np.concatenate([synth.lidar_scene(4)[:n], synth.lidar_scene(5)[:n]])
+        coords[n:, 0] = 1
+    check_layer(np.ascontiguousarray(coords), 1, 1, "subm", C_in, C_out, dtype, seed=n, threads=16)
