@@ -93,7 +93,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     const int wr = wv / WC;
     const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
     // a tile's blocks of output channels follow each other on its XCD
-    const unsigned turn = blockIdx.x / NUM_XCD;
+    const unsigned turn = (blockIdx.y * (unsigned)GRID_COLUMNS + blockIdx.x) / NUM_XCD;
     const int by = (int)(turn % (unsigned)blocks_y);
     const int64_t tile = xcd_run_of(turn / (unsigned)blocks_y * NUM_XCD + blockIdx.x % NUM_XCD, (n_out + TILE - 1) / TILE);
     if (tile < 0) return;                              // the whole workgroup
@@ -432,8 +432,11 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s
         if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>, fixed + (343 + LIST_PAD + 3) / 4 * 16, allowed)) return rc;
     }
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
-    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>), dim3(xcd_run_grid(tiles) * blocks_y),
-              dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB, (int)blocks_y, n_out_ptr, n_out_cap);
+    static_assert(grid_fits(GRID_COLUMNS, 64 * NW) && GRID_COLUMNS % NUM_XCD == 0, "a row of the grid is whole turns of the XCDs");
+    const int64_t groups = (int64_t)xcd_run_grid(tiles) * blocks_y;
+    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>),
+              dim3((unsigned)grid_columns(groups), (unsigned)grid_rows(groups)), dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB,
+              (int)blocks_y, n_out_ptr, n_out_cap);
     return SC_OK;
 }
 

@@ -61,4 +61,11 @@ constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t c
 // 18 k / 26 k / 30 k 23.0 / 26.7 / 28.2 and 25.5 / 27.2 / 28.3, indoor 25.4 / 30.1 / 31.2 and 25.4 / 28.9 / 30.5.
 constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return likely * ((CB + 3) / 4) <= 3 * cus; }
 
+// Workgroups of the general kernel, tiles times blocks of output channels: a launch takes fewer than 2^32 threads along x, which 2^20
+// tiles (SC_N_MAX rows) of 8 blocks and 512 threads are not.  Past GRID_COLUMNS they go on in the next row of the grid, workgroup by workgroup.
+constexpr int64_t GRID_COLUMNS = 1 << 22;
+constexpr bool grid_fits(int64_t columns, int64_t threads) { return columns * threads < (int64_t)1 << 32; }
+constexpr int64_t grid_columns(int64_t groups) { return groups < GRID_COLUMNS ? groups : GRID_COLUMNS; }
+constexpr int64_t grid_rows(int64_t groups) { return (groups + GRID_COLUMNS - 1) / GRID_COLUMNS; }
+
 }  // namespace sc

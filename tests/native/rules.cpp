@@ -29,3 +29,10 @@ static_assert(general_128_to_128(3, 20 * 256, true, 256) && general_128_to_128(2
 // longer steps up to three workgroups per compute unit, one for 64 output channels: 32 -> 64 on 40 k rows too
 static_assert(few_workgroups(tiles(40000), 4, 256) && few_workgroups(768, 4, 256) && !few_workgroups(769, 4, 256), "64 output channels");
 static_assert(few_workgroups(384, 8, 256) && !few_workgroups(385, 8, 256) && few_workgroups(768, 1, 256), "128 and 16 output channels");
+
+// SC_N_MAX rows, fp32, 240 and 256 output channels: 8 blocks of 512 threads a tile, two rows of the grid, none left out; one row up to 2^22 workgroups
+constexpr int64_t most = tiles(67108864) * 8;
+static_assert(!grid_fits(most, 512) && grid_fits(grid_columns(most), 512) && grid_columns(most) * grid_rows(most) >= most && grid_rows(most) == 2, "largest launch");
+constexpr int64_t past = (int64_t)1 << 22;
+static_assert(grid_columns(past) == past && grid_rows(past) == 1 && grid_rows(past + 32) == 2 && grid_fits(grid_columns(past + 32), 512), "second row");
+static_assert(grid_columns(32) == 32 && grid_rows(32) == 1, "small launch");

@@ -496,3 +496,36 @@ def test_pointwise_layers(C_in, C_out, n, dtype):
         coords = np.concatenate([synth.lidar_scene(4)[:n], synth.lidar_scene(5)[:n]])
         coords[n:, 0] = 1
     check_layer(np.ascontiguousarray(coords), 1, 1, "subm", C_in, C_out, dtype, seed=n, threads=16)
+
+
+def test_more_workgroups_than_a_row_of_the_grid_holds():
+    """fp32, 240 output channels, room for SC_N_MAX rows: 2^20 tiles of 8 blocks of output channels, 2^23 workgroups of 512 threads.
+    A full 256 x 256 x 128 box, K = 3, stride 2: cell q has the inputs 2 q + d inside the box."""
+    say("2^26 rows of 240 channels")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    dev, X, Y, Z, C_in, C_out = "cuda:0", 256, 256, 128, 16, 240
+    n = X * Y * Z
+    lin = torch.arange(n, device=dev)
+    coords = torch.stack([torch.zeros_like(lin), lin // (Y * Z), lin // Z % Y, lin % Z], dim=1).int().contiguous()
+    feat = (lin[:, None] * 2654435761 + torch.arange(C_in, device=dev) * 40503).remainder(4093).float() / 2048 - 1
+    weight = torch.from_numpy(synth.weights(27, C_in, C_out, "f32", 9)).to(dev)
+    buf = sc.LayerBuffers(n, 3, 2, "strided", C_in, C_out, "f32", device=dev)
+    assert buf.feat_out.shape[0] == 1 << 26
+    buf.kmap_build(coords, standalone=True)
+    n_out = X // 2 * (Y // 2) * (Z // 2)
+    buf.feat_out[:n_out + 64] = float("nan")
+    buf.conv_fwd(feat, weight)
+    assert buf.read_counts().n_out == n_out
+    assert not bool(buf.feat_out[:n_out].isnan().any()) and bool(buf.feat_out[n_out:n_out + 64].isnan().all())
+    rows = torch.cat([torch.arange(128, device=dev), torch.arange(1, n_out, 509, device=dev), torch.arange(n_out - 128, n_out, device=dev)])
+    q = buf.out_coords[rows, 1:].long()
+    ref = torch.zeros((len(rows), C_out), dtype=torch.float64, device=dev)
+    for k in range(27):
+        p = 2 * q + torch.tensor([k // 9, k // 3 % 3, k % 3], device=dev)
+        inside = (p < torch.tensor([X, Y, Z], device=dev)).all(dim=1)
+        ref[inside] += feat[((p[:, 0] * Y + p[:, 1]) * Z + p[:, 2])[inside]].double() @ weight[k].double()
+    got = buf.feat_out[rows].double()
+    del buf, coords, feat
+    torch.cuda.empty_cache()
+    assert float((got - ref).abs().max() / ref.abs().max()) <= 1e-5
