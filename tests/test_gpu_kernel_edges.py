@@ -116,6 +116,27 @@ def test_packed_square_layers_beyond_the_resident_kernel(K, stride, C, n):
     assert err <= 1e-5, err
 
 
+@pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_packed_and_raw_weights_agree_bit_for_bit_across_kernels(K, stride, C, n, dtype):
+    """From 9 tiles per CU (of 256) packed weights take the general kernel and raw ones the resident kernel."""
+    say(f"packed and raw K={K} s={stride} {C}->{C} {dtype} n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import to_dev
+    coords = torch.from_numpy(synth.uniform_cells(n, 80, seed=6)).to("cuda:0")
+    feat, weight = to_dev(synth.features(n, C, dtype, 6), dtype), to_dev(synth.weights(K ** 3, C, C, dtype, 6), dtype)
+    for out in (dtype, "f32"):
+        buf = sc.LayerBuffers(n, K, stride, "subm" if stride == 1 else "strided", C, C, dtype, out_dtype=out, device="cuda:0")
+        buf.hash_build(coords)
+        buf.kmap_build(coords)
+        buf.conv_fwd(feat, weight)
+        raw = buf.feat_out[:buf.read_counts().n_out].clone()
+        buf.feat_out.fill_(float("nan"))
+        buf.conv_fwd_packed(feat, sc.sc_conv_weight_pack(weight, K))
+        assert len(raw) > 1000 and torch.equal(buf.feat_out[:len(raw)], raw)
+
+
 @pytest.mark.parametrize("C_in,C_out", [(32, 64), (64, 64), (64, 128), (128, 128)])
 @pytest.mark.parametrize("n", [64, 129, 66000])
 def test_fused_general_kernel(C_in, C_out, n):
