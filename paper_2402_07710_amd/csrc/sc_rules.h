@@ -39,14 +39,20 @@ constexpr bool general_32_to_64(int64_t likely, bool overlapping, int64_t cus) {
 // 128 -> 128, K = 2 and 3, 16 bit: general kernel or streaming kernel (false).  A workgroup of the streaming kernel is eight tiles and takes ~75 us
 // however few there are; full, it moves the weights once for them.  General up to 20 tiles per CU (us of the convolution, general / streaming:
 // 4 k voxels 17 / 71, 53 k 43 / 75, 262 k 127 / 157; denser sets 265 k 209 / 251, 320 k 259 / 276, 500 k 404 / 347, 10^6 854 / 714; K = 2 on 150 k 25 / 32, 900 k
-// 110 / 82).  Beyond, the streaming kernel takes 86 us a round of eight tiles per CU, full or not, the general one 0.05 us a tile of a
-// dense set and less of others: K = 3 layers whose rounds are less than four fifths full stay with it, where the rows are known to the caller
-// (whole layers: indoor 400 k, 0.76 full, 372 / 408, 500 k, 0.95, 464 / 427, 700 k, 0.89, 657 / 623; sweeps 400 k 282 / 366; inverse maps 400 k
-// sweeps 165 / 244, indoor 241 / 247).  Of strided layers only the inputs are known, and the rows decide how full the rounds are: stride 2 on 400 k
-// sweeps 396 / 386, indoor 270 / 267, stride 3 132 / 111 and 109.4 / 110.9.
+// 110 / 82).  Beyond, the streaming kernel takes about 86 us a round of eight tiles per CU, full or not, and the general one up to 0.05 us a tile, so
+// K = 3 layers whose rounds are less than five sixths full stay with it where the rows are known to the caller: 24 to 26 2/3 and 32 to 33 1/3
+// tiles per CU, from six rounds on none.  On sweeps, whose rows find fewer neighbours, it is ahead at every size; on dense sets there only, and how dense a
+// set is is not known here.  us of whole layers, general / streaming, sweep and indoor rows, and how full the rounds are: 330 k 0.84 233 / 286 and 314 / 322,
+// 394 k 0.75 267 / 359 and 353 / 390, 421 k 0.80 284 / 366 and 376 / 400, 440 k 0.84 296 / 372 and 394 / 406, 460 k 0.88 314 / 376 and 421 / 410, 500 k 0.95 327 / 391 and
+// 458 / 419, 530 k 0.81 354 / 466 and 501 / 508, 560 k 0.85 376 / 460 and 528 / 515, 600 k 0.92 399 / 468 and 569 / 527, 660 k 0.84 438 / 537 and 621 / 611, 790 k
+// 0.86 512 / 621 and 750 / 710, 10^6 0.95 651 / 738 and 945 / 825.  Fused: 262 k 157 / 195 and 206 / 192, 330 k 199 / 282 and 260 / 277, 394 k 244 / 376 and 312 / 371,
+// 440 k 275 / 388 and 361 / 384, 500 k 303 / 391 and 415 / 392, 530 k 322 / 477 and 452 / 484, 600 k 367 / 484 and 519 / 496, 10^6 614 / 775 and 884 / 795.  Convolution of
+// inverse maps, K = 3: 394 k 162 / 236 and 235 / 248, 419 k 147 / 227 and 217 / 237, 437 k 149 / 228 and 220 / 237, 545 k 183 / 279 and 255 / 296.  Of strided
+// layers only the inputs are known, and the rows decide how full the rounds are: stride 2 on 400 k sweeps 396 / 386, indoor 270 / 267, stride 3 132 / 111 and
+// 109.4 / 110.9.
 constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t cus) {
     const int64_t round = 8 * cus;
-    return likely <= 20 * cus || (K == 3 && !strided && 5 * likely < 4 * ((likely + round - 1) / round * round));
+    return likely <= 20 * cus || (K == 3 && !strided && 6 * likely < 5 * ((likely + round - 1) / round * round));
 }
 
 // The general kernel, K <= 3, up to three workgroups per CU: steps of four offsets of 32-channel rows and of two of 64-channel ones, the shorter walk; 39 KB of LDS,

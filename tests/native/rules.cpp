@@ -24,6 +24,9 @@ static_assert(general_32_to_64(tiles(150000), false, 256) && !general_32_to_64(t
 // 128 -> 128: the rounds of a layer that is not strided count, a strided one's are not known
 static_assert(general_128_to_128(3, tiles(400000), false, 256) && !general_128_to_128(3, tiles(400000), true, 256), "part-filled rounds");
 static_assert(!general_128_to_128(3, tiles(500000), false, 256) && !general_128_to_128(2, tiles(400000), false, 256), "full rounds, K = 2");
+static_assert(general_128_to_128(3, tiles(436864), false, 256) && !general_128_to_128(3, tiles(436865), false, 256), "fourth round five sixths full");
+static_assert(!general_128_to_128(3, 8192, false, 256) && general_128_to_128(3, 8193, false, 256) && general_128_to_128(3, 8533, false, 256) &&
+              !general_128_to_128(3, 8534, false, 256) && !general_128_to_128(3, 10241, false, 256), "a fifth round begun, a sixth");
 static_assert(general_128_to_128(3, 20 * 256, true, 256) && general_128_to_128(2, 20 * 256, true, 256), "up to 20 tiles per compute unit");
 
 // longer steps up to three workgroups per compute unit, one for 64 output channels: 32 -> 64 on 40 k rows too

@@ -480,6 +480,31 @@ def test_streaming_kernel_strided_rows_known_to_the_caller(stride, C_in, C_out, 
     assert err <= 1e-5, err
 
 
+@pytest.mark.parametrize("n", [400_000, 436_864, 436_865])
+def test_128_channels_on_both_sides_of_rounds_five_sixths_full(n):
+    """K = 3, 24 to 26 2/3 tiles per CU (of 256) and one tile more, with a map and fused."""
+    say(f"128 -> 128, n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import to_dev
+    coords = synth.uniform_cells(n, 110, seed=n)
+    feat, weight = synth.features(n, 128, "f16", 1), synth.weights(27, 128, 128, "f16", 1)
+    buf = sc.LayerBuffers(n, 3, 1, "subm", 128, 128, "f16", out_dtype="f32", device="cuda:0")
+    c, f, w = torch.from_numpy(coords).to("cuda:0"), to_dev(feat, "f16"), to_dev(weight, "f16")
+    buf.feat_out.fill_(float("nan"))
+    buf.layer(c, f, w)
+    pin, pout, start = (t.long() for t in buf.export())
+    ref = torch.zeros((n, 128), device="cuda:0")
+    for k in range(27):
+        at = slice(int(start[k]), int(start[k + 1]))
+        ref.index_add_(0, pout[at], f[pin[at]].float() @ w[k].float())
+    assert float((buf.feat_out - ref).abs().max() / ref.abs().max()) <= 1e-5
+    fused = sc.LayerBuffers(n, 3, 1, "subm", 128, 128, "f16", out_dtype="f32", device="cuda:0", grid_dims=(1, 110, 110, 110))
+    fused.feat_out.fill_(float("nan"))
+    fused.layer_fused(c, f, w)
+    assert float((fused.feat_out - ref).abs().max() / ref.abs().max()) <= 1e-5
+
+
 @pytest.mark.parametrize("C_out,n", [(64, 512 * 64 + 1), (64, 768 * 64), (64, 768 * 64 + 1), (128, 384 * 64), (128, 384 * 64 + 1), (16, 33)])
 def test_32_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
     """Steps of four offsets, with lists that do not fill the last one, and of two; with and without a map."""
