@@ -34,6 +34,24 @@ __device__ inline uint32_t line_pattern(int32_t entry) {
     for (int g = 0; g < 4; ++g) pat |= (((vote >> (16 * g)) & 0xffffull) != 0ull ? 1u : 0u) << g;
     return pat;
 }
+// Words OR-ed over the 16 lanes that hold a group's rows (a row of the data-parallel instructions).
+__device__ inline uint32_t or_of_group(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);      // rotated by 8, 4, 2 and 1 lanes
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, true);
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x122, 0xf, 0xf, true);
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xf, 0xf, true);
+    return v;
+}
+// The mask word of a lane's group from its row's entries, of maps without masks: an instruction an offset shifts the sign in.
+// Voting offset by offset (a compare and three scalar instructions each) was 0.3 us of a kernel.
+template <int N>
+__device__ inline uint32_t mask_of_entries(const int32_t (&e)[N]) {
+    static_assert(N < 32, "bits of a word");
+    uint32_t none = 0u;
+#pragma unroll
+    for (int k = N - 1; k >= 0; --k) none = __builtin_amdgcn_alignbit(none, (uint32_t)e[k], 31);
+    return or_of_group(~none & ((1u << N) - 1u));
+}
 // Workgroup barrier for data exchanged through LDS only.  __syncthreads() also waits until every
 // outstanding global load of the wavefront has returned (vmcnt(0)), which would drain the gathers
 // and weight fetches that were issued ahead on purpose; here only the wavefront's LDS operations

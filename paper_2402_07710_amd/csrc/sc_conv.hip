@@ -103,8 +103,7 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
         if (gmask != nullptr) {
             m = gmask[tile * 4 + q];
         } else {
-#pragma unroll
-            for (int k = 0; k < K3; ++k) m |= (__ballot(e[k] >= 0) != 0ull ? 1u : 0u) << k;
+            m = __builtin_amdgcn_readfirstlane(mask_of_entries(e));
         }
     } else {
 #pragma unroll
@@ -294,12 +293,9 @@ k_conv_stream(const uint16_t* __restrict__ feat, const uint4* wp, void* __restri
 #pragma unroll
             for (int g = 0; g < 4; ++g) mg[g] = gmask != nullptr ? gmask[tile * 4 + g] : 0u;
             if (gmask == nullptr) {
+                const uint32_t m = mask_of_entries(v);
 #pragma unroll
-                for (int k = 0; k < K3; ++k) {
-                    const uint32_t pat = line_pattern(v[k]);
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) mg[g] |= ((pat >> g) & 1u) << k;
-                }
+                for (int g = 0; g < 4; ++g) mg[g] = __builtin_amdgcn_readlane(m, 16 * g);
             }
         } else {
 #pragma unroll
@@ -411,17 +407,30 @@ k_conv_stream(const uint16_t* __restrict__ feat, const uint4* wp, void* __restri
 }
 
 constexpr int CB_MAX = 16;
-// The mask word of a 16-row group of a map without masks (K^3 <= 32): line = its first entry, at the lane's row.
-__device__ inline uint32_t vote_mask(const int32_t* line, int K3) {
-    uint32_t m = 0u;
-    for (int k = 0; k < K3; ++k) m |= (__ballot(line[(int64_t)k * TILE] >= 0) != 0ull ? 1u : 0u) << k;
-    return m;
+// The mask word of a 16-row group of a map without masks (K^3 <= 32): line = its first entry, at the lane's row.  The four lanes of a
+// row take every fourth offset each, so it is one round trip; offset after offset, each behind the one before, it was up to 27 (us of whole
+// strided fp32 layers, K = 3, stride 2: masks made by the build / offset after offset / now: 16 -> 16 2 k / 20 k / 100 k inputs 26.3 / 29.9 / 24.2, 30.8 / 34.3 /
+// 28.2, 69.5 / 71.1 / 65.7; 32 -> 32 2 k 32.9 / 35.8 / 30.4; 5 -> 7 100 k 90.1 / 107.1 / 89.5; K = stride = 3, 16 -> 16 100 k 33.7 / 35.9 / 29.8).
+__device__ inline uint32_t vote_mask(const int32_t* __restrict__ line, int K3, int qq) {
+    uint32_t found = 0u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int k = 4 * j + qq;
+        const int32_t e = k < K3 ? line[k * TILE] : -1;
+        found |= ((uint32_t)~e >> 31) << (4 * j);
+    }
+    found = or_of_group(found << qq);
+    return __builtin_amdgcn_readlane(found, 0) | __builtin_amdgcn_readlane(found, 16) | __builtin_amdgcn_readlane(found, 32) |
+           __builtin_amdgcn_readlane(found, 48);
 }
 // ---- fp32 features and weights -------------------------------------------------------------------
 // Same scheme with the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: true fp32 products and
 // sums): one wavefront per 16 output rows, offsets walked by mask bit, operands read straight from
 // the [K3][C_in][C_out] weights and the feature rows, four input channels per step.  Any C_in,
 // C_out <= 256 (edges are zero-filled).
+// MASKED: the map has masks.  The mask word is in a vector register either way: walked in a scalar one, the loop over channels took
+// 3 to 6 % longer (48 -> 48 on 100 k rows, submanifold 305 -> 318 us, K = 3, stride 3 131 -> 139).
+template <int MASKED>
 __global__ void __launch_bounds__(256)
 k_conv_f32(const float* __restrict__ feat, const float* __restrict__ w, float* __restrict__ out,
            const uint32_t* __restrict__ gmask, const int32_t* __restrict__ nbr, int K3, int mw, int C_in, int C_out,
@@ -439,7 +448,13 @@ k_conv_f32(const float* __restrict__ feat, const float* __restrict__ w, float* _
     for (int cb = 0; cb < CB_MAX; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int32_t* line = nbr + tile * (int64_t)K3 * TILE + q * 16 + r;
     for (int wi = 0; wi < mw; ++wi) {
-        uint32_t m = gmask != nullptr ? gmask[(tile * 4 + q) * mw + wi] : vote_mask(line, K3);
+        uint32_t m;
+        if constexpr (MASKED) {
+            m = gmask[(tile * 4 + q) * mw + wi];
+        } else {
+            m = vote_mask(line, K3, qq);
+            asm volatile("" : "+v"(m));
+        }
         while (m) {
             const int k = wi * 32 + __builtin_ctz(m);
             m &= m - 1;
@@ -505,8 +520,7 @@ k_conv_f32_first(const float* __restrict__ feat, const float* __restrict__ w, fl
     if (gmask != nullptr) {
         m = __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]);
     } else {
-#pragma unroll
-        for (int k = 0; k < K3; ++k) m |= (__ballot(e[k] >= 0) != 0ull ? 1u : 0u) << k;
+        m = __builtin_amdgcn_readfirstlane(mask_of_entries(e));
     }
     for (int i = threadIdx.x; i < K3 * C_out; i += 256) {           // 16 bytes each
         const int col = i % (C_out / 4), kc = i / (C_out / 4), ci = kc & 3;
@@ -559,7 +573,7 @@ k_conv_f32_small(const float* __restrict__ feat, const float* __restrict__ w, fl
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int32_t* line = nbr + tile * (int64_t)K3 * TILE + q * 16 + r;
-    uint32_t m = gmask != nullptr ? __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]) : vote_mask(line, K3);
+    uint32_t m = gmask != nullptr ? __builtin_amdgcn_readfirstlane(gmask[tile * 4 + q]) : vote_mask(line, K3, qq);
     while (m) {
         int kk[NB];
         int32_t e[NB];
@@ -862,7 +876,8 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
             SC_F32_SMALL(1, 1) SC_F32_SMALL(1, 2) SC_F32_SMALL(1, 4) SC_F32_SMALL(2, 1) SC_F32_SMALL(2, 2) SC_F32_SMALL(4, 1)
 #undef SC_F32_SMALL
         }
-        SC_LAUNCH(KID_CONV_F32, k_conv_f32, dim3((unsigned)tiles), dim3(256), 0, s, (const float*)d_feat_in,
+        const auto any = gmask != nullptr ? k_conv_f32<1> : k_conv_f32<0>;
+        SC_LAUNCH(KID_CONV_F32, any, dim3((unsigned)tiles), dim3(256), 0, s, (const float*)d_feat_in,
                   (const float*)d_weight, (float*)d_feat_out, gmask, nbr, L.K3, L.mw, C_in, C_out, n_out_ptr,
                   n_out_cap);
         return SC_OK;
