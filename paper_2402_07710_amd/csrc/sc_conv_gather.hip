@@ -1,5 +1,5 @@
-// The general convolution kernel: 16-bit layers of 64 and more channels (128 -> 128 up to 20 tiles per CU), every
-// shape without a kernel of its own in sc_conv.hip, and fp32 layers with enough work for it.
+// The general convolution kernel: 16-bit layers of 32, 64, 128 and 256 input channels without a kernel of their own in sc_conv.hip,
+// or on this kernel's side of the line to that one (sc_rules.h, conv_16bit), and fp32 layers with enough work for it.
 #include "sc_conv.h"
 #include "sc_rules.h"
 
@@ -50,8 +50,8 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 //  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
 //    65 us with 2, 51.5 with 4, 50 with 6).  That also decides the step length, 16 KB of LDS for 64 channels.
 // A group without a neighbour at an offset is not multiplied by its weights (a weight that is not finite stays out
-// of its sums).  SKIP: nor is it gathered and read (64 channels: 62 -> 50 us at that size).  32-channel rows are too short
-// for that: such groups read the row of zeros, and the places of the last step that have no offset are fetched
+// of its sums).  SKIP: nor is it gathered and read (64 channels: 62 -> 50 us at that size).  32-channel rows in steps of four
+// offsets (few workgroups, or K > 3; steps of two skip) are too short for that: such groups read the row of zeros, and the places of the last step that have no offset are fetched
 // like the others (of offset 0, rows of zeros); the operands of an offset are read together, then the
 // multiplies tested (whole layers K = 5 32 -> 32 on 2 k / 53 k voxels and 32 -> 64 on 110 k: 30.0 / 63.4 / 116 us; with SKIP
 // 31.0 / 64.5 / 121, with zeroed weights instead of the test 30.3 / 64.2 / 120, all of a step's operands first 29.4 / 63.2 / 120).
