@@ -18,6 +18,8 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
 // where a tile's table entries come from: the map's lines as they are needed, the same copied to LDS first, or look-ups
 enum { FROM_MAP, FROM_TABLE, FROM_LINES };
 constexpr int LIST_PAD = 12;                            // places of the list past the last offset: three steps of four, the longest
+// an instantiation whose pointwise layers (K = 1) gather once, into the first half of the rows' buffer: places without an offset are left out
+constexpr bool takes_one_step(int SRC, int SKIP, int KS, int SL) { return SRC == FROM_MAP && SKIP && KS <= SL; }
 
 // One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
 // input channel) is walked in steps of SL slices of 64 bytes of a row (32 16-bit or 16 fp32 channels):
@@ -77,6 +79,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     constexpr int OPS = SL / KP;                       // offsets per step
     // the two steps after the last are read too: up to 3 OPS - 1 places past the last offset, which have to be zeros
     static_assert(3 * OPS <= LIST_PAD, "the list's zeros reach as far as the steps read");
+    constexpr bool ONE_STEP = takes_one_step(SRC, SKIP, KS, SL);
     constexpr int CH = KP == 1 ? 1 : KP / 2;           // chunks per offset and step: 64 rows x 128 (64) bytes
     constexpr int CHB = KS == 1 ? 4096 : 8192;         // bytes per chunk
     constexpr int NI = KS == 1 || NW == 8 ? 1 : 2;     // gather instructions per wavefront and chunk
@@ -101,8 +104,11 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 
     // The offsets the tile takes part in, in increasing order, as a list in LDS: number and 4-bit pattern of groups, zeros past
     // the last.  Every wavefront makes it for itself (lane = offset), all with the same contents.
-    uint32_t* list = reinterpret_cast<uint32_t*>(smem + 2 * STEP_BYTES + 2 * W_BYTES);
-    int32_t* found = reinterpret_cast<int32_t*>(list + 40);
+    // ONE: of a pointwise layer whose step is the whole row the list lies in the half of the rows' buffer that is never filled: behind both buffers it
+    // would take the 16-channel workgroups of fp32, whose buffers are a quarter of the LDS, from four per CU to three.
+    const bool one = ONE_STEP && K3 == 1 && gmask != nullptr;
+    uint32_t* list = reinterpret_cast<uint32_t*>(smem + (one ? STEP_BYTES : 2 * STEP_BYTES + 2 * W_BYTES));
+    int32_t* found = reinterpret_cast<int32_t*>(smem + 2 * STEP_BYTES + 2 * W_BYTES) + 40;
     int listed = 0;
     auto add_to_list = [&](int k, uint32_t pat) __attribute__((always_inline)) {
         const uint64_t in = __ballot(pat != 0u);
@@ -139,13 +145,24 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
             for (int u = 0; u < 7; ++u) found[(wv + 4 * u) * TILE + lane] = part[u];
         };
         if (gmask != nullptr) {
-            for (int k = lane; k - lane < K3; k += WAVE) {
+            if (K3 == 1) {
+                // the masks are the list (us of whole pointwise layers, before there was a list / with it made as for other K / now: fp32 16 -> 80 on 20 k
+                // rows 17.1 / 17.2 / 16.2, 64 -> 16, 64 -> 64 and 128 -> 240 on 100 k 19.1, 30.9 and 102.4 / 20.1, 32.5 and 102.1 / 19.0, 31.3 and 94.4; f16 64 -> 128 23.97 /
+                // 24.02 / 23.8, 256 -> 256 50.1 / 47.1 / 45.0)
                 uint32_t pat = 0u;
-                if (k < K3) {
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
+                for (int g = 0; g < 4; ++g) pat |= (gmask[tile * 4 + g] & 1u) << g;
+                if (lane == 0) list[0] = pat;
+                listed = pat != 0u ? 1 : 0;
+            } else {
+                for (int k = lane; k - lane < K3; k += WAVE) {
+                    uint32_t pat = 0u;
+                    if (k < K3) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
+                    }
+                    add_to_list(k, pat);
                 }
-                add_to_list(k, pat);
             }
             if constexpr (HELD) {
                 hold();
@@ -426,7 +443,8 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (SRC != FROM_MAP ? 28 * TILE * 4 + 64 : 0);
     static_assert(fixed <= 65536 + 28 * TILE * 4 + 64, "loads into LDS land in the first 64 KB");
-    const size_t lds = fixed + (size_t)((SRC != FROM_MAP && K3 < 27 ? 27 : K3) + LIST_PAD + 3) / 4 * 16;     // entries lie behind a list of 27
+    const bool one = takes_one_step(SRC, SKIP, KS, SL) && K3 == 1 && ms.gmask != nullptr;
+    const size_t lds = fixed + (one ? 0 : (size_t)((SRC != FROM_MAP && K3 < 27 ? 27 : K3) + LIST_PAD + 3) / 4 * 16);     // entries lie behind a list of 27
     if constexpr (fixed + (343 + LIST_PAD + 3) / 4 * 16 > 65536) {
         static bool allowed[MAX_DEVICES] = {};
         if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>, fixed + (343 + LIST_PAD + 3) / 4 * 16, allowed)) return rc;

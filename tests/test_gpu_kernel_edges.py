@@ -159,7 +159,7 @@ def test_fused_general_kernel(C_in, C_out, n):
 
 
 @pytest.mark.parametrize("K,C_in,C_out,n", [(3, 16, 64, 17000), (3, 32, 32, 17000), (3, 64, 64, 1), (3, 64, 64, 65), (3, 64, 80, 1000),
-                                            (3, 128, 16, 700), (3, 256, 48, 300), (5, 16, 16, 700), (5, 32, 32, 65),
+                                            (3, 128, 16, 700), (3, 256, 48, 300), (5, 16, 16, 700), (5, 32, 32, 65), (1, 16, 80, 17000), (1, 64, 16, 24500),
                                             (3, 16, 64, 24500), (3, 32, 32, 16400), (3, 64, 64, 34000), (3, 64, 80, 5000),
                                             (3, 128, 64, 5000), (3, 256, 48, 8000), (5, 32, 32, 30000)])
 def test_general_kernel_fp32(K, C_in, C_out, n):
@@ -532,9 +532,10 @@ def test_32_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
 
 
 @pytest.mark.parametrize("C_in,C_out", [(64, 64), (64, 128), (128, 16), (256, 48)])
-@pytest.mark.parametrize("n,dtype", [(1, "f16"), (64, "bf16"), (65, "f16"), (34000, "f16")])
+@pytest.mark.parametrize("n,dtype", [(1, "f16"), (64, "bf16"), (65, "f16"), (34000, "f16"), (1, "f32"), (65, "f32"), (17000, "f32")])
 def test_pointwise_layers(C_in, C_out, n, dtype):
-    """K = 1: a list of one offset, read from the map; whole tiles, a tile of one row, and two output blocks per wavefront (64 -> 128)."""
+    """K = 1: a list of one offset, read from the map; whole tiles, a tile of one row, and two output blocks per wavefront (64 -> 128); in
+    fp32 a row of 128 and more channels is more than one step."""
     say(f"K=1 {C_in}->{C_out} {dtype} n={n}")
     if n < 1000:
         coords = synth.uniform_cells(n, 6, seed=n)
