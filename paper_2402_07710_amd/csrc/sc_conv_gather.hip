@@ -69,7 +69,7 @@ constexpr bool takes_one_step(int SRC, int SKIP, int KS, int SL) { return SRC ==
 template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int SRC>
 __global__ void __launch_bounds__(64 * NW, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
-              int blocks_y, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
+              int blocks_y, int64_t tiles_apart, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
     constexpr bool FUSED = SRC == FROM_TABLE, HELD = SRC != FROM_MAP;      // HELD: the tile's entries are in LDS
     static_assert(!HELD || (DT != SC_F32 && NW == 4), "a quarter of the 27 offsets per wavefront");
     const uint32_t* __restrict__ gmask = ms.gmask;
@@ -95,11 +95,16 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     const int r = lane & 15, qq = lane >> 4;
     const int wr = wv / WC;
     const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
-    // a tile's blocks of output channels follow each other on its XCD
+    // a tile's blocks of output channels follow each other on its XCD; from tiles_apart tiles on (CT == 2) block after block takes all
+    // tiles
+    const int64_t tiles = (n_out + TILE - 1) / TILE;
+    const bool apart = !F32 && CT == 2 && tiles >= tiles_apart;
     const unsigned turn = (blockIdx.y * (unsigned)GRID_COLUMNS + blockIdx.x) / NUM_XCD;
-    const int by = (int)(turn % (unsigned)blocks_y);
-    const int64_t tile = xcd_run_of(turn / (unsigned)blocks_y * NUM_XCD + blockIdx.x % NUM_XCD, (n_out + TILE - 1) / TILE);
-    if (tile < 0) return;                              // the whole workgroup
+    const unsigned divisor = apart ? xcd_run_grid(tiles) / NUM_XCD : (unsigned)blocks_y;
+    const unsigned quotient = turn / divisor, rest = turn - quotient * divisor;
+    const int by = (int)(apart ? quotient : rest);
+    const int64_t tile = xcd_run_of((apart ? rest : quotient) * NUM_XCD + blockIdx.x % NUM_XCD, tiles);
+    if (tile < 0 || by >= blocks_y) return;            // the whole workgroup
     const int cb0 = by * (WC * CT) + (wv % WC) * CT;
 
     // The offsets the tile takes part in, in increasing order, as a list in LDS: number and 4-bit pattern of groups, zeros past
@@ -439,7 +444,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 }
 
 template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int SRC>
-static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s, const void* feat, const void* wp, void* out,
+static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (SRC != FROM_MAP ? 28 * TILE * 4 + 64 : 0);
     static_assert(fixed <= 65536 + 28 * TILE * 4 + 64, "loads into LDS land in the first 64 KB");
@@ -454,7 +459,7 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, hipStream_t s
     const int64_t groups = (int64_t)xcd_run_grid(tiles) * blocks_y;
     SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>),
               dim3((unsigned)grid_columns(groups), (unsigned)grid_rows(groups)), dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB,
-              (int)blocks_y, n_out_ptr, n_out_cap);
+              (int)blocks_y, first_tiles_apart((int64_t)K3 * CB * KS * 1024, cus), n_out_ptr, n_out_cap);
     return SC_OK;
 }
 
@@ -463,7 +468,7 @@ template <int DT, int KS, int SL, int SKIP, int O1, int O2, int SRC = FROM_MAP>
 static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat, const void* wp,
                             void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
 #define SC_GATHER(NW, WR, CT, OCC) \
-    return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC, SRC>(K3, mw, CB, tiles, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+    return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC, SRC>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if constexpr (DT == SC_F32) {
         // 32 output channels per workgroup: gathering a tile's rows once more costs less than a workgroup of 64 channels
         // that others wait for (a tile near the sensor is 27 offsets x 2,048 cycles of multiplies per SIMD; us with

@@ -295,7 +295,7 @@ int compute_units();                       // of the current device
 // leave seven XCDs waiting for one (53 k voxels fp32 64 -> 64: 84 -> 80 us, 14 k voxels 256 -> 256 the same).
 constexpr int XCD_RUN = 4;
 template <int RUN = XCD_RUN>
-inline unsigned xcd_run_grid(int64_t units) {
+__host__ __device__ inline unsigned xcd_run_grid(int64_t units) {
     return (unsigned)((units + NUM_XCD * RUN - 1) / (NUM_XCD * RUN) * (NUM_XCD * RUN));
 }
 template <int RUN = XCD_RUN>

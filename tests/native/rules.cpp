@@ -39,3 +39,8 @@ static_assert(!grid_fits(most, 512) && grid_fits(grid_columns(most), 512) && gri
 constexpr int64_t past = (int64_t)1 << 22;
 static_assert(grid_columns(past) == past && grid_rows(past) == 1 && grid_rows(past + 32) == 2 && grid_fits(grid_columns(past + 32), 512), "second row");
 static_assert(grid_columns(32) == 32 && grid_rows(32) == 1, "small launch");
+
+// 16-bit weights beyond 6 MiB, more than 3 1/4 tiles per compute unit: blocks of output channels apart
+constexpr int64_t k5 = 125 * 128 * 256 * 2, k3 = 27 * 256 * 256 * 2;
+static_assert(first_tiles_apart(k5, 256) == 833 && first_tiles_apart(k5, 64) == 209 && first_tiles_apart(k5 / 2, 256) == INT64_MAX, "K = 5");
+static_assert(first_tiles_apart(k3, 256) == INT64_MAX, "K = 3");

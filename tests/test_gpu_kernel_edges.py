@@ -531,6 +531,32 @@ def test_32_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
         assert torch.equal(fused.feat_out, buf.feat_out)
 
 
+@pytest.mark.parametrize("K,stride,C_in,C_out,n", [(5, 1, 128, 256, 832 * 64), (5, 1, 128, 256, 832 * 64 + 1), (5, 1, 64, 256, 832 * 64 + 1), (5, 1, 256, 240, 900 * 64 - 7),
+                                                   (7, 1, 64, 256, 833 * 64), (4, 2, 256, 256, 60_000)])
+def test_blocks_of_output_channels_together_and_apart(K, stride, C_in, C_out, n):
+    """16 bit, two blocks per tile, on both sides of 3 1/4 tiles per CU (of 256) and of 6 MiB of weights; a last block that is not full, and
+    tiles that are known on the device only."""
+    say(f"blocks apart K={K} s={stride} {C_in}->{C_out} n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import to_dev
+    coords = synth.uniform_cells(n, 100, seed=K)
+    feat, weight = synth.features(n, C_in, "f16", 1), synth.weights(K ** 3, C_in, C_out, "f16", 1)
+    buf = sc.LayerBuffers(n, K, stride, "subm" if stride == 1 else "strided", C_in, C_out, "f16", out_dtype="f32", device="cuda:0")
+    c, f, w = torch.from_numpy(coords).to("cuda:0"), to_dev(feat, "f16"), to_dev(weight, "f16")
+    buf.feat_out.fill_(float("nan"))
+    buf.layer(c, f, w)
+    n_out = buf.read_counts().n_out
+    assert stride == 1 or n_out > 833 * 64
+    pin, pout, start = (t.long() for t in buf.export())
+    ref = torch.zeros((n_out, C_out), device="cuda:0")
+    for k in range(K ** 3):
+        at = slice(int(start[k]), int(start[k + 1]))
+        ref.index_add_(0, pout[at], f[pin[at]].float() @ w[k].float())
+    assert float((buf.feat_out[:n_out] - ref).abs().max() / ref.abs().max()) <= 1e-5
+    assert bool(buf.feat_out[n_out:].isnan().all())
+
+
 @pytest.mark.parametrize("C_in,C_out", [(64, 64), (64, 128), (128, 16), (256, 48)])
 @pytest.mark.parametrize("n,dtype", [(1, "f16"), (64, "bf16"), (65, "f16"), (34000, "f16"), (1, "f32"), (65, "f32"), (17000, "f32")])
 def test_pointwise_layers(C_in, C_out, n, dtype):
