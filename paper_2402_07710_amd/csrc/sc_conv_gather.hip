@@ -95,10 +95,10 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     const int r = lane & 15, qq = lane >> 4;
     const int wr = wv / WC;
     const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
-    // a tile's blocks of output channels follow each other on its XCD; from tiles_apart tiles on (CT == 2) block after block takes all
-    // tiles
+    // a tile's blocks of output channels follow each other on its XCD; from tiles_apart tiles on block after block takes all tiles (not where
+    // the lines are held: K <= 3, whose weights are never that large)
     const int64_t tiles = (n_out + TILE - 1) / TILE;
-    const bool apart = !F32 && CT == 2 && tiles >= tiles_apart;
+    const bool apart = !F32 && SRC == FROM_MAP && tiles >= tiles_apart;
     const unsigned turn = (blockIdx.y * (unsigned)GRID_COLUMNS + blockIdx.x) / NUM_XCD;
     const unsigned divisor = apart ? xcd_run_grid(tiles) / NUM_XCD : (unsigned)blocks_y;
     const unsigned quotient = turn / divisor, rest = turn - quotient * divisor;
@@ -459,7 +459,7 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, int cus, hipS
     const int64_t groups = (int64_t)xcd_run_grid(tiles) * blocks_y;
     SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>),
               dim3((unsigned)grid_columns(groups), (unsigned)grid_rows(groups)), dim3(64 * NW), lds, s, feat, wp, out, out_f32, ms, K3, mw, CB,
-              (int)blocks_y, first_tiles_apart((int64_t)K3 * CB * KS * 1024, cus), n_out_ptr, n_out_cap);
+              (int)blocks_y, first_tiles_apart((int64_t)K3 * CB * KS * 1024, CT, n_out_ptr != nullptr, cus), n_out_ptr, n_out_cap);
     return SC_OK;
 }
 

@@ -67,18 +67,25 @@ constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t c
 // 18 k / 26 k / 30 k 23.0 / 26.7 / 28.2 and 25.5 / 27.2 / 28.3, indoor 25.4 / 30.1 / 31.2 and 25.4 / 28.9 / 30.5.
 constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return likely * ((CB + 3) / 4) <= 3 * cus; }
 
-// The general kernel, 16 bit, two output blocks per wavefront: a tile's blocks of output channels one after the other on an XCD, whose L2 then holds the tile's rows for the second,
+// The general kernel, 16 bit: a tile's blocks of output channels one after the other on an XCD, whose L2 then holds the tile's rows for the second,
 // or all tiles' first blocks before any second one: the tile count from which it is the latter.  Where the weights are larger than an
-// L2 (4 MiB), workgroups of one block at a time share twice the weights of a few offsets.  Beyond 6 MiB and 3 1/4 tiles per CU (of the tiles that are
-// there; us of the convolution, one after the other / apart, sweep and indoor rows, 256 CUs.  K = 5, 64 -> 256, 3.9 MiB: 100 k 151 / 154 and 234 / 237; 128 -> 256, 7.8 MiB: 40 k
+// L2 (4 MiB), workgroups of one block at a time share half the weights of a few offsets.  Of the tiles that are there, with two output blocks per wavefront:
+// beyond 12 MiB from 2 1/4 per CU on, beyond 6 MiB from 3 1/4 (us of the convolution, one after the other / apart, sweep and indoor rows, 256 CUs.  K = 5,
+// 64 -> 256, 3.9 MiB: 100 k 151 / 154 and 234 / 237; 128 -> 256, 7.8 MiB: 40 k
 // 150 / 165 and 197 / 207, 55 k 196 / 200 and 254 / 252, 70 k 251 / 236 and 320 / 322, 100 k 317 / 291 and 489 / 471, 200 k 567 / 505 and 1004 / 912; 256 -> 256, 15.6 MiB:
-// 20 k 214 / 212 and 234 / 232, 40 k 347 / 339 and 412 / 420, 55 k 460 / 413 and 559 / 566, 100 k 775 / 658 and 1145 / 1089, 200 k 1549 / 1181 and 2480 / 2136; stride 2 80 k 1419 /
-// 1145 and 1151 / 1072.  K = 7, 64 -> 256, 10.7 MiB: 40 k 169 / 199 and 202 / 214, 55 k 232 / 232 and 262 / 262, 100 k 363 / 333 and 521 / 517; 128 -> 256, 21 MiB: 55 k 547 / 535 and
-// 616 / 589, 100 k 902 / 802 and 1361 / 1301.  K = 4, stride 2, 256 -> 256, 8 MiB: 2.8 tiles per CU 364 / 373, 3.2 429 / 426, 6.4 490 / 459, 15.4 1130 / 1045; K = stride = 4, 0.9
-// to 1.9 tiles per CU 75 / 90 and 105 / 111).  Of one output block per
-// wavefront, which is for fewer tiles, and in fp32, whose multiplies take the time, apart is slower at every size: K = 7, 128 -> 128 56 k 265 / 287, fp32 K = 5,
-// 256 -> 256 50 k 2317 / 2700.
-constexpr int64_t first_tiles_apart(int64_t weight_bytes, int64_t cus) { return weight_bytes > 6 << 20 ? 13 * cus / 4 + 1 : INT64_MAX; }
+// 100 k 775 / 658 and 1145 / 1089, 200 k 1549 / 1181 and 2480 / 2136; stride 2 80 k 1419 / 1145 and 1151 / 1072.  K = 7, 64 -> 256, 10.7 MiB: 40 k 169 / 199 and
+// 202 / 214, 55 k 232 / 232 and 262 / 262, 100 k 363 / 333 and 521 / 517; 128 -> 256, 21 MiB: 100 k 902 / 802 and 1361 / 1301.  K = 4, stride 2, 256 -> 256, 8 MiB:
+// 2.8 tiles per CU 364 / 373, 3.2 429 / 426, 6.4 490 / 459, 15.4 1130 / 1045.  Apart over one after the other, map and convolution, mean of five sweeps, of five
+// indoor sets, and random cells, whose groups of rows fetch weights for few neighbours: K = 5, 256 -> 256, 1.2 tiles per CU 1.06, 1.05, 0.90, 1.6 1.04, 1.01, 0.83, 2.1
+// 1.04, 1.01, 0.78, 2.4 0.97, 1.02, 0.78, 2.9 0.91, 1.03, 0.75; K = 7 1.2 1.13, 1.06, 0.86, 2.1 1.01, 0.99, 0.77, 2.9 0.96, 0.99, 0.80; K = 7, 128 -> 256, 2.1
+// 1.13, 0.99, 0.79, 2.4 1.01, 1.00, 0.83).  With one output block per wavefront, which is for few tiles to expect, only where a strided layer has many more rows than
+// inputs (256 -> 256 on random cells K = 6, stride 3, 3.8 tiles per CU 1257 / 650, 6.1 to 7 with K = 4, stride 2, 8 MiB 611 / 509; sweeps K = 6 2.7 604 / 493): in the others
+// apart is slower (K = 7, 128 -> 128 56 k 265 / 287, 256 -> 128 1.2 to 1.8 tiles per CU 1.04 to 1.19 of one after the other).  In fp32, whose multiplies take
+// the time, apart is slower at every size: K = 5, 256 -> 256 50 k 2317 / 2700.
+constexpr int64_t first_tiles_apart(int64_t weight_bytes, int blocks_per_wavefront, bool strided, int64_t cus) {
+    if (weight_bytes <= 6 << 20 || (blocks_per_wavefront == 1 && !strided)) return INT64_MAX;
+    return (weight_bytes > 12 << 20 ? 9 : 13) * cus / 4 + 1;
+}
 
 // Workgroups of the general kernel, tiles times blocks of output channels: a launch takes fewer than 2^32 threads along x, which 2^20
 // tiles (SC_N_MAX rows) of 8 blocks and 512 threads are not.  Past GRID_COLUMNS they go on in the next row of the grid, workgroup by workgroup.

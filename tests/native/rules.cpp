@@ -40,7 +40,8 @@ constexpr int64_t past = (int64_t)1 << 22;
 static_assert(grid_columns(past) == past && grid_rows(past) == 1 && grid_rows(past + 32) == 2 && grid_fits(grid_columns(past + 32), 512), "second row");
 static_assert(grid_columns(32) == 32 && grid_rows(32) == 1, "small launch");
 
-// 16-bit weights beyond 6 MiB, more than 3 1/4 tiles per compute unit: blocks of output channels apart
-constexpr int64_t k5 = 125 * 128 * 256 * 2, k3 = 27 * 256 * 256 * 2;
-static_assert(first_tiles_apart(k5, 256) == 833 && first_tiles_apart(k5, 64) == 209 && first_tiles_apart(k5 / 2, 256) == INT64_MAX, "K = 5");
-static_assert(first_tiles_apart(k3, 256) == INT64_MAX, "K = 3");
+// 16-bit weights beyond 12 MiB, more than 2 1/4 tiles per compute unit, beyond 6, more than 3 1/4: blocks of output channels apart
+constexpr int64_t k7 = 343 * 128 * 256 * 2, k5 = 125 * 128 * 256 * 2, k3 = 27 * 256 * 256 * 2;
+static_assert(first_tiles_apart(k5, 2, false, 256) == 833 && first_tiles_apart(k5, 2, true, 64) == 209 && first_tiles_apart(k5 / 2, 2, true, 256) == INT64_MAX, "K = 5");
+static_assert(first_tiles_apart(k7, 2, false, 256) == 577 && first_tiles_apart(2 * k5, 2, false, 256) == 577 && first_tiles_apart(k3, 2, true, 256) == INT64_MAX, "K = 7, 3");
+static_assert(first_tiles_apart(k7, 1, true, 256) == 577 && first_tiles_apart(k5, 1, true, 256) == 833 && first_tiles_apart(k7, 1, false, 256) == INT64_MAX, "one block");

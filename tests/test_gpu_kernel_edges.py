@@ -532,15 +532,16 @@ def test_32_channel_steps_on_both_sides_of_three_workgroups_per_cu(C_out, n):
 
 
 @pytest.mark.parametrize("K,stride,C_in,C_out,n", [(5, 1, 128, 256, 832 * 64), (5, 1, 128, 256, 832 * 64 + 1), (5, 1, 64, 256, 832 * 64 + 1), (5, 1, 256, 240, 900 * 64 - 7),
-                                                   (7, 1, 64, 256, 833 * 64), (4, 2, 256, 256, 60_000)])
+                                                   (7, 1, 64, 256, 833 * 64), (4, 2, 256, 256, 60_000), (7, 1, 128, 256, 576 * 64),
+                                                   (7, 1, 128, 256, 576 * 64 + 1), (6, 3, 256, 256, 8502), (6, 3, 256, 112, 9000), (7, 3, 128, 240, 8502)])
 def test_blocks_of_output_channels_together_and_apart(K, stride, C_in, C_out, n):
-    """16 bit, two blocks per tile, on both sides of 3 1/4 tiles per CU (of 256) and of 6 MiB of weights; a last block that is not full, and
-    tiles that are known on the device only."""
+    """16 bit, two to four blocks per tile, on both sides of 3 1/4 and 2 1/4 tiles per CU (of 256) and of 6 and 12 MiB of weights; a last block that is
+    not full, and tiles that are known on the device only, several times the inputs' (K = 6 and 7 with stride 3)."""
     say(f"blocks apart K={K} s={stride} {C_in}->{C_out} n={n}")
     import torch
     from paper_2402_07710_amd import binding as sc
     from tests.test_gpu_parity import to_dev
-    coords = synth.uniform_cells(n, 100, seed=K)
+    coords = synth.uniform_cells(n, 200 if stride == 3 else 100, seed=K)
     feat, weight = synth.features(n, C_in, "f16", 1), synth.weights(K ** 3, C_in, C_out, "f16", 1)
     buf = sc.LayerBuffers(n, K, stride, "subm" if stride == 1 else "strided", C_in, C_out, "f16", out_dtype="f32", device="cuda:0")
     c, f, w = torch.from_numpy(coords).to("cuda:0"), to_dev(feat, "f16"), to_dev(weight, "f16")
