@@ -558,7 +558,7 @@ def test_blocks_of_output_channels_together_and_apart(K, stride, C_in, C_out, n)
     assert bool(buf.feat_out[n_out:].isnan().all())
 
 
-@pytest.mark.parametrize("C_in,C_out", [(64, 64), (64, 128), (128, 16), (256, 48)])
+@pytest.mark.parametrize("C_in,C_out", [(32, 64), (64, 64), (64, 128), (128, 16), (256, 48)])
 @pytest.mark.parametrize("n,dtype", [(1, "f16"), (64, "bf16"), (65, "f16"), (34000, "f16"), (1, "f32"), (65, "f32"), (17000, "f32")])
 def test_pointwise_layers(C_in, C_out, n, dtype):
     """K = 1: a list of one offset, read from the map; whole tiles, a tile of one row, and two output blocks per wavefront (64 -> 128); in
