@@ -15,11 +15,10 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
 }
 
-// where a tile's table entries come from: the map's lines as they are needed, the same copied to LDS first, or look-ups
-enum { FROM_MAP, FROM_TABLE, FROM_LINES };
+// where a tile's table entries come from: the map's lines as they are needed, look-ups, the map's lines copied to LDS first, or the one line
+// of a pointwise layer
+enum { FROM_MAP, FROM_TABLE, FROM_LINES, FROM_LINE };
 constexpr int LIST_PAD = 12;                            // places of the list past the last offset: three steps of four, the longest
-// an instantiation whose pointwise layers (K = 1) gather once, into the first half of the rows' buffer: places without an offset are left out
-constexpr bool takes_one_step(int SRC, int SKIP, int KS, int SL) { return SRC == FROM_MAP && SKIP && KS <= SL; }
 
 // One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
 // input channel) is walked in steps of SL slices of 64 bytes of a row (32 16-bit or 16 fp32 channels):
@@ -70,7 +69,7 @@ template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int
 __global__ void __launch_bounds__(64 * NW, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
               int blocks_y, int64_t tiles_apart, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
-    constexpr bool FUSED = SRC == FROM_TABLE, HELD = SRC != FROM_MAP;      // HELD: the tile's entries are in LDS
+    constexpr bool FUSED = SRC == FROM_TABLE, HELD = FUSED || SRC == FROM_LINES, POINT = SRC == FROM_LINE;      // HELD: the tile's entries are in LDS
     static_assert(!HELD || (DT != SC_F32 && NW == 4), "a quarter of the 27 offsets per wavefront");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
@@ -79,7 +78,6 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     constexpr int OPS = SL / KP;                       // offsets per step
     // the two steps after the last are read too: up to 3 OPS - 1 places past the last offset, which have to be zeros
     static_assert(3 * OPS <= LIST_PAD, "the list's zeros reach as far as the steps read");
-    constexpr bool ONE_STEP = takes_one_step(SRC, SKIP, KS, SL);
     constexpr int CH = KP == 1 ? 1 : KP / 2;           // chunks per offset and step: 64 rows x 128 (64) bytes
     constexpr int CHB = KS == 1 ? 4096 : 8192;         // bytes per chunk
     constexpr int NI = KS == 1 || NW == 8 ? 1 : 2;     // gather instructions per wavefront and chunk
@@ -88,7 +86,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
     constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
     constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
-    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD] | HELD: entries[28][64], masks[4][4]
+    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD], but K = 1 | HELD: entries[28][64], masks[4][4]
     extern __shared__ __align__(16) char smem[];
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -109,18 +107,24 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 
     // The offsets the tile takes part in, in increasing order, as a list in LDS: number and 4-bit pattern of groups, zeros past
     // the last.  Every wavefront makes it for itself (lane = offset), all with the same contents.
-    // ONE: of a pointwise layer whose step is the whole row the list lies in the half of the rows' buffer that is never filled: behind both buffers it
-    // would take the 16-channel workgroups of fp32, whose buffers are a quarter of the LDS, from four per CU to three.
-    const bool one = ONE_STEP && K3 == 1 && gmask != nullptr;
-    uint32_t* list = reinterpret_cast<uint32_t*>(smem + (one ? STEP_BYTES : 2 * STEP_BYTES + 2 * W_BYTES));
-    int32_t* found = reinterpret_cast<int32_t*>(smem + 2 * STEP_BYTES + 2 * W_BYTES) + 40;
+    // A pointwise layer has one entry, `only`, and no list: making one of one entry in LDS and reading it there was a round trip
+    // before the first gather and one before the second (us of map and convolution, before there was a list / with it / now: fp32 32 -> 64 200 k rows 32.8 / 34.2 /
+    // 26.7, 300 k 46.6 / 48.5 / 37.5, 64 -> 128 90 k 34.0 / 34.9 / 30.3, 128 -> 128 200 k 96.1 / 91.6 / 86.1; 16 bit 32 -> 32 200 k 18.2 / 11.6 / 9.6, 256 -> 256 90 k
+    // 38.7 / 35.1 / 32.8).
+    uint32_t* list = reinterpret_cast<uint32_t*>(smem + 2 * STEP_BYTES + 2 * W_BYTES);
+    int32_t* found = reinterpret_cast<int32_t*>(list + 40);
+    uint32_t only = 0u;
     int listed = 0;
     auto add_to_list = [&](int k, uint32_t pat) __attribute__((always_inline)) {
         const uint64_t in = __ballot(pat != 0u);
         if (pat != 0u) list[listed + __popcll(in & ((1ull << lane) - 1ull))] = (uint32_t)k << 4 | pat;
         listed += __popcll(in);
     };
-    if constexpr (FUSED) {
+    if constexpr (POINT) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) only |= (gmask[tile * 4 + g] & 1u) << g;       // submanifold: the map has masks
+        only = __builtin_amdgcn_readfirstlane(only);
+    } else if constexpr (FUSED) {
         // lane = row; each wavefront looks up every fourth offset, its part of the masks is a vote
         uint32_t* votes = reinterpret_cast<uint32_t*>(found + 28 * TILE);
         int32_t part[7];
@@ -150,24 +154,13 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
             for (int u = 0; u < 7; ++u) found[(wv + 4 * u) * TILE + lane] = part[u];
         };
         if (gmask != nullptr) {
-            if (K3 == 1) {
-                // the masks are the list (us of whole pointwise layers, before there was a list / with it made as for other K / now: fp32 16 -> 80 on 20 k
-                // rows 17.1 / 17.2 / 16.2, 64 -> 16, 64 -> 64 and 128 -> 240 on 100 k 19.1, 30.9 and 102.4 / 20.1, 32.5 and 102.1 / 19.0, 31.3 and 94.4; f16 64 -> 128 23.97 /
-                // 24.02 / 23.8, 256 -> 256 50.1 / 47.1 / 45.0)
+            for (int k = lane; k - lane < K3; k += WAVE) {
                 uint32_t pat = 0u;
+                if (k < K3) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) pat |= (gmask[tile * 4 + g] & 1u) << g;
-                if (lane == 0) list[0] = pat;
-                listed = pat != 0u ? 1 : 0;
-            } else {
-                for (int k = lane; k - lane < K3; k += WAVE) {
-                    uint32_t pat = 0u;
-                    if (k < K3) {
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
-                    }
-                    add_to_list(k, pat);
+                    for (int g = 0; g < 4; ++g) pat |= ((gmask[tile * (4 * mw) + g * mw + (k >> 5)] >> (k & 31)) & 1u) << g;
                 }
+                add_to_list(k, pat);
             }
             if constexpr (HELD) {
                 hold();
@@ -190,7 +183,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
             add_to_list(lane, lane < K3 ? patterns[lane] : 0u);
         }
     }
-    if (lane < LIST_PAD) list[listed + lane] = 0u;
+    if (!POINT && lane < LIST_PAD) list[listed + lane] = 0u;
     const uint32_t* next = list;
     uint32_t fetched[OPS];                             // the list's entries of the next step, read a step before they are needed
     int part = 0;
@@ -198,20 +191,24 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
         for (int o = 0; o < OPS; ++o) fetched[o] = next[o];
     };
-    fetch();
+    if constexpr (!POINT) fetch();
     // numbers (times PARTS, plus the part; -1: none) and patterns of the next step's offsets
     auto next_step = [&](int (&k)[OPS], uint32_t (&p)[OPS]) __attribute__((always_inline)) {
 #pragma unroll
         for (int o = 0; o < OPS; ++o) {
-            const uint32_t e = __builtin_amdgcn_readfirstlane(fetched[o]);
+            const uint32_t e = POINT ? (o == 0 && part < PARTS ? only : 0u) : __builtin_amdgcn_readfirstlane(fetched[o]);
             p[o] = e & 15u;
             k[o] = e != 0u ? (int)(e >> 4) * PARTS + part : -1;
         }
-        if (PARTS == 1 || ++part == PARTS) {
-            part = 0;
-            next += OPS;
+        if constexpr (POINT) {
+            ++part;
+        } else {
+            if (PARTS == 1 || ++part == PARTS) {
+                part = 0;
+                next += OPS;
+            }
+            fetch();
         }
-        fetch();
     };
 
     // gathers: this wavefront fetches group gw (of eight wavefronts, two share a group: each takes every other
@@ -446,13 +443,14 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int SRC>
 static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-    constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (SRC != FROM_MAP ? 28 * TILE * 4 + 64 : 0);
+    constexpr bool held = SRC == FROM_TABLE || SRC == FROM_LINES;
+    constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (held ? 28 * TILE * 4 + 64 : 0);
     static_assert(fixed <= 65536 + 28 * TILE * 4 + 64, "loads into LDS land in the first 64 KB");
-    const bool one = takes_one_step(SRC, SKIP, KS, SL) && K3 == 1 && ms.gmask != nullptr;
-    const size_t lds = fixed + (one ? 0 : (size_t)((SRC != FROM_MAP && K3 < 27 ? 27 : K3) + LIST_PAD + 3) / 4 * 16);     // entries lie behind a list of 27
-    if constexpr (fixed + (343 + LIST_PAD + 3) / 4 * 16 > 65536) {
+    constexpr auto list_bytes = [](int K3) { return SRC == FROM_LINE ? (size_t)0 : (size_t)((held ? 27 : K3) + LIST_PAD + 3) / 4 * 16; };     // entries lie behind a list of 27
+    const size_t lds = fixed + list_bytes(K3);
+    if constexpr (fixed + list_bytes(343) > 65536) {
         static bool allowed[MAX_DEVICES] = {};
-        if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>, fixed + (343 + LIST_PAD + 3) / 4 * 16, allowed)) return rc;
+        if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>, fixed + list_bytes(343), allowed)) return rc;
     }
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
     static_assert(grid_fits(GRID_COLUMNS, 64 * NW) && GRID_COLUMNS % NUM_XCD == 0, "a row of the grid is whole turns of the XCDs");
@@ -510,8 +508,9 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
                : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if (dtype_in == SC_F32) {
-#define SC_GATHER_F32(KS) \
-    return launch_gather_ks<SC_F32, KS, 4, 1, 4, 4>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+#define SC_GATHER_F32(KS)                                                                                                              \
+    return K3 == 1 ? launch_gather_ks<SC_F32, KS, 4, 1, 4, 4, FROM_LINE>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap) \
+                   : launch_gather_ks<SC_F32, KS, 4, 1, 4, 4>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
         switch (C_in) {
             case 16: SC_GATHER_F32(1);
             case 32: SC_GATHER_F32(2);
@@ -522,15 +521,21 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
 #undef SC_GATHER_F32
         return SC_EINVAL;
     }
+    // K = 1: one offset, so the shortest steps, and the one line is read as it is needed
+    if (K3 == 1) {
+        switch (C_in) {
+            case 32: SC_GATHER_KS(1, 2, 1, 5, 4, FROM_LINE);
+            case 64: SC_GATHER_KS(2, 2, 1, 6, 5, FROM_LINE);
+            case 128: SC_GATHER_KS(4, 4, 1, 4, 3, FROM_LINE);
+            case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_LINE);
+        }
+        return SC_EINVAL;
+    }
     const bool few = few_workgroups(likely, CB, cus);
-    // K = 1 of 64 and more channels: one line, read once, is not worth holding (us of the convolution, held and read: 200 k voxels 64 -> 64
-    // 15.0 / 14.4, 128 -> 64 23.4 / 20.9, 256 -> 128 49.4 / 48.3, 53 k 128 -> 128 11.6 / 10.8; 32 -> 64, whose steps are shorter with it, 14.1 / 19.8)
-    if (K3 <= 27 && (K3 > 1 || C_in == 32)) {
+    if (K3 <= 27) {
         switch (C_in) {
             case 32:
-                // K = 1 has one offset: the longer step would only fetch three more rows of zeros each (us of the convolution, four and two places: 32 -> 64 2 k /
-                // 20 k / 46 k rows 3.9 / 4.5 / 6.0 and 3.4 / 4.1 / 5.1, 32 -> 16 3.2 / 3.4 / 4.2 and 2.9 / 3.0 / 3.5)
-                if (few && K3 > 1) SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
+                if (few) SC_GATHER_KS(1, 4, 0, 2, 2, FROM_LINES);
                 SC_GATHER_KS(1, 2, 1, 5, 4, FROM_LINES);
             case 64:
                 if (few) SC_GATHER_KS(2, 4, 1, 4, 4, FROM_LINES);
@@ -539,7 +544,6 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
             case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_LINES);
         }
     }
-    if (K3 == 1 && C_in == 64) SC_GATHER_KS(2, 2, 1, 6, 5, FROM_MAP);
     switch (C_in) {
         case 32: SC_GATHER_KS(1, 4, 0, 2, 2, FROM_MAP);
         case 64: SC_GATHER_KS(2, 4, 1, 5, 4, FROM_MAP);
