@@ -15,9 +15,9 @@ __device__ inline void load_to_lds(const void* src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
 }
 
-// where a tile's table entries come from: the map's lines as they are needed, look-ups, the map's lines copied to LDS first, or the one line
-// of a pointwise layer
-enum { FROM_MAP, FROM_TABLE, FROM_LINES, FROM_LINE };
+// where a tile's table entries come from: the map's lines as they are needed, look-ups, the map's lines copied to LDS first, the one line
+// of a pointwise layer, or the map's lines as they are needed by a list of offsets in registers
+enum { FROM_MAP, FROM_TABLE, FROM_LINES, FROM_LINE, FROM_MAP_BY_REGISTERS };
 constexpr int LIST_PAD = 12;                            // places of the list past the last offset: three steps of four, the longest
 
 // One workgroup of NW wavefronts per 64-row tile and block of output channels.  The sum over (offset,
@@ -69,7 +69,7 @@ template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int
 __global__ void __launch_bounds__(64 * NW, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
               int blocks_y, int64_t tiles_apart, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
-    constexpr bool FUSED = SRC == FROM_TABLE, HELD = FUSED || SRC == FROM_LINES, POINT = SRC == FROM_LINE;      // HELD: the tile's entries are in LDS
+    constexpr bool FUSED = SRC == FROM_TABLE, HELD = FUSED || SRC == FROM_LINES, POINT = SRC == FROM_LINE, REGS = SRC == FROM_MAP_BY_REGISTERS;      // HELD: the tile's entries are in LDS
     static_assert(!HELD || (DT != SC_F32 && NW == 4), "a quarter of the 27 offsets per wavefront");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
@@ -77,6 +77,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     constexpr int KP = KS < SL ? KS : SL, PARTS = KS / KP;     // slices of an offset taken in one step, steps per offset
     constexpr int OPS = SL / KP;                       // offsets per step
     // the two steps after the last are read too: up to 3 OPS - 1 places past the last offset, which have to be zeros
+    static_assert(!REGS || WAVE % OPS == 0, "a step's places are in one register");
     static_assert(3 * OPS <= LIST_PAD, "the list's zeros reach as far as the steps read");
     constexpr int CH = KP == 1 ? 1 : KP / 2;           // chunks per offset and step: 64 rows x 128 (64) bytes
     constexpr int CHB = KS == 1 ? 4096 : 8192;         // bytes per chunk
@@ -86,7 +87,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
     constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
     constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
-    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD], but K = 1 | HELD: entries[28][64], masks[4][4]
+    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD], but POINT and REGS | HELD: entries[28][64], masks[4][4]
     extern __shared__ __align__(16) char smem[];
 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -111,7 +112,11 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     // before the first gather and one before the second (us of map and convolution, before there was a list / with it / now: fp32 32 -> 64 200 k rows 32.8 / 34.2 /
     // 26.7, 300 k 46.6 / 48.5 / 37.5, 64 -> 128 90 k 34.0 / 34.9 / 30.3, 128 -> 128 200 k 96.1 / 91.6 / 86.1; 16 bit 32 -> 32 200 k 18.2 / 11.6 / 9.6, 256 -> 256 90 k
     // 38.7 / 35.1 / 32.8).
-    uint32_t* list = reinterpret_cast<uint32_t*>(smem + 2 * STEP_BYTES + 2 * W_BYTES);
+    // REGS: it is made in the half of the rows' buffer that is filled second and then lies in the lanes of PLACES registers: behind both buffers it takes
+    // the 16-channel workgroups of fp32, whose buffers are a quarter of the LDS, from four per CU to three (fewer_rounds_of_four).
+    constexpr int PLACES = REGS ? 6 : 1;               // 64 offsets each: K^3 <= 343 and what is read past them
+    uint32_t places[PLACES] = {};
+    uint32_t* list = reinterpret_cast<uint32_t*>(smem + (REGS ? STEP_BYTES + 128 : 2 * STEP_BYTES + 2 * W_BYTES));
     int32_t* found = reinterpret_cast<int32_t*>(list + 40);
     uint32_t only = 0u;
     int listed = 0;
@@ -183,20 +188,28 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
             add_to_list(lane, lane < K3 ? patterns[lane] : 0u);
         }
     }
-    if (!POINT && lane < LIST_PAD) list[listed + lane] = 0u;
+    if constexpr (REGS) {
+#pragma unroll
+        for (int j = 0; j < PLACES; ++j)
+            if (j * WAVE < listed) places[j] = j * WAVE + lane < listed ? list[j * WAVE + lane] : 0u;
+    } else if (!POINT && lane < LIST_PAD) {
+        list[listed + lane] = 0u;
+    }
     const uint32_t* next = list;
     uint32_t fetched[OPS];                             // the list's entries of the next step, read a step before they are needed
-    int part = 0;
+    int part = 0, at = 0;
     auto fetch = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int o = 0; o < OPS; ++o) fetched[o] = next[o];
     };
-    if constexpr (!POINT) fetch();
+    if constexpr (!POINT && !REGS) fetch();
     // numbers (times PARTS, plus the part; -1: none) and patterns of the next step's offsets
     auto next_step = [&](int (&k)[OPS], uint32_t (&p)[OPS]) __attribute__((always_inline)) {
 #pragma unroll
         for (int o = 0; o < OPS; ++o) {
-            const uint32_t e = POINT ? (o == 0 && part < PARTS ? only : 0u) : __builtin_amdgcn_readfirstlane(fetched[o]);
+            const uint32_t e = POINT  ? (o == 0 && part < PARTS ? only : 0u)
+                               : REGS ? __builtin_amdgcn_readlane(places[0], at + o)
+                                      : __builtin_amdgcn_readfirstlane(fetched[o]);
             p[o] = e & 15u;
             k[o] = e != 0u ? (int)(e >> 4) * PARTS + part : -1;
         }
@@ -206,8 +219,13 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
             if (PARTS == 1 || ++part == PARTS) {
                 part = 0;
                 next += OPS;
+                if (REGS && (at += OPS) == WAVE) {
+                    at = 0;
+#pragma unroll
+                    for (int j = 0; j < PLACES; ++j) places[j] = j + 1 < PLACES ? places[j + 1] : 0u;
+                }
             }
-            fetch();
+            if constexpr (!REGS) fetch();
         }
     };
 
@@ -446,7 +464,7 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, int cus, hipS
     constexpr bool held = SRC == FROM_TABLE || SRC == FROM_LINES;
     constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (held ? 28 * TILE * 4 + 64 : 0);
     static_assert(fixed <= 65536 + 28 * TILE * 4 + 64, "loads into LDS land in the first 64 KB");
-    constexpr auto list_bytes = [](int K3) { return SRC == FROM_LINE ? (size_t)0 : (size_t)((held ? 27 : K3) + LIST_PAD + 3) / 4 * 16; };     // entries lie behind a list of 27
+    constexpr auto list_bytes = [](int K3) { return SRC == FROM_LINE || SRC == FROM_MAP_BY_REGISTERS ? (size_t)0 : (size_t)((held ? 27 : K3) + LIST_PAD + 3) / 4 * 16; };     // entries lie behind a list of 27
     const size_t lds = fixed + list_bytes(K3);
     if constexpr (fixed + list_bytes(343) > 65536) {
         static bool allowed[MAX_DEVICES] = {};
@@ -475,6 +493,11 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
         // 8 k / 12 k 18.0 / 25.5 / 27.6 us against 20.3 / 23.6 / 34.3 with 32).
         const int64_t w = likely * CB;
         const bool narrow = w <= 8 * (int64_t)cus && (w + cus - 1) / cus < 2 * ((w + 2 * cus - 1) / (2 * cus));
+        if constexpr (SRC == FROM_MAP) {
+            if (CB == 1 && K3 >= 64 && fewer_rounds_of_four(w, cus))
+                return launch_gather_as<DT, KS, SL, SKIP, 4, 4, 1, 3, FROM_MAP_BY_REGISTERS>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms,
+                                                                                             n_out_ptr, n_out_cap);
+        }
         if (CB == 1 || narrow) SC_GATHER(4, 4, 1, 3);
         SC_GATHER(8, 4, 1, 4);
     } else {

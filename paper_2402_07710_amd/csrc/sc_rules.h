@@ -87,6 +87,17 @@ constexpr int64_t first_tiles_apart(int64_t weight_bytes, int blocks_per_wavefro
     return (weight_bytes > 12 << 20 ? 9 : 13) * cus / 4 + 1;
 }
 
+// The general kernel, fp32, 16 output channels, K >= 4: the list of offsets in registers instead of behind the buffers in LDS, which are a quarter of it.  A step takes
+// longer, but four workgroups are on a CU at a time instead of three; so where that is a round fewer, and not for less than half a workgroup per CU (us of map and
+// convolution, before there was a list / in LDS / in registers.  3.3 workgroups per CU, K = 5 and 7, sweeps 69 / 64 / 67 and 149 / 139 / 143.  3.8: 16 -> 16, K = 5, indoor
+// 76 / 85 / 75, K = 7, indoor 184 / 196 / 177, random 242 / 259 / 237, sweep 165 / 160 / 157, K = 5, stride 2, indoor 159 / 172 / 157; 32 -> 16, K = 5, sweep 79 / 75 / 75, random 90 /
+// 95 / 88, K = 7, stride 3, sweep 215 / 203 / 209.  7.9: K = 5, indoor 138 / 141 / 134, sweep 125 / 120 / 120, K = 4, stride 2, sweep 153 / 156 / 150; K = stride = 4, inverse, 14:
+// indoor 119 / 117 / 110; slower on surfaces with stride 3, K = 7, indoor 62 k rows 216 in LDS, 225 in registers).  K <= 3 and 16-channel blocks of wider layers: within 2 %, some
+// sets 5 % to 8 % slower.
+constexpr bool fewer_rounds_of_four(int64_t workgroups, int64_t cus) {
+    return (workgroups + 4 * cus - 1) / (4 * cus) < (workgroups - cus / 2 + 3 * cus - 1) / (3 * cus);
+}
+
 // Workgroups of the general kernel, tiles times blocks of output channels: a launch takes fewer than 2^32 threads along x, which 2^20
 // tiles (SC_N_MAX rows) of 8 blocks and 512 threads are not.  Past GRID_COLUMNS they go on in the next row of the grid, workgroup by workgroup.
 constexpr int64_t GRID_COLUMNS = 1 << 22;

@@ -45,3 +45,7 @@ constexpr int64_t k7 = 343 * 128 * 256 * 2, k5 = 125 * 128 * 256 * 2, k3 = 27 * 
 static_assert(first_tiles_apart(k5, 2, false, 256) == 833 && first_tiles_apart(k5, 2, true, 64) == 209 && first_tiles_apart(k5 / 2, 2, true, 256) == INT64_MAX, "K = 5");
 static_assert(first_tiles_apart(k7, 2, false, 256) == 577 && first_tiles_apart(2 * k5, 2, false, 256) == 577 && first_tiles_apart(k3, 2, true, 256) == INT64_MAX, "K = 7, 3");
 static_assert(first_tiles_apart(k7, 1, true, 256) == 577 && first_tiles_apart(k5, 1, true, 256) == 833 && first_tiles_apart(k7, 1, false, 256) == INT64_MAX, "one block");
+
+// fp32, 16 output channels: four workgroups per CU are a round fewer than three, by more than half a workgroup per CU
+static_assert(!fewer_rounds_of_four(1, 256) && !fewer_rounds_of_four(896, 256) && fewer_rounds_of_four(897, 256) && fewer_rounds_of_four(1024, 256) &&
+              !fewer_rounds_of_four(1025, 256) && fewer_rounds_of_four(1665, 256) && fewer_rounds_of_four(225, 64), "rounds");

@@ -558,6 +558,32 @@ def test_blocks_of_output_channels_together_and_apart(K, stride, C_in, C_out, n)
     assert bool(buf.feat_out[n_out:].isnan().all())
 
 
+@pytest.mark.parametrize("K,stride,C_in,C_out,n,grid", [(7, 1, 16, 16, 896 * 64, 40), (7, 1, 16, 16, 896 * 64 + 1, 40), (7, 1, 32, 16, 62_000, 120), (5, 1, 16, 16, 1024 * 64, 41),
+                                                        (5, 1, 64, 16, 1024 * 64 + 1, 41), (5, 1, 128, 16, 60_000, 60), (4, 1, 256, 16, 60_000, 50), (6, 2, 16, 16, 60_000, 60),
+                                                        (4, 4, 16, 16, 62_000, 60)])
+def test_list_of_offsets_in_registers(K, stride, C_in, C_out, n, grid):
+    """fp32, 16 output channels, K >= 4, on both sides of 3 1/2 and of 4 tiles per CU (of 256): tiles that take part in all of 343 offsets (the list goes on
+    in the next register every 64), in few, rows of more than one step; K > stride, and K == stride."""
+    say(f"list in registers K={K} s={stride} {C_in}->{C_out} n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import to_dev
+    coords = synth.uniform_cells(n, grid, seed=K)
+    feat, weight = synth.features(n, C_in, "f32", 1), synth.weights(K ** 3, C_in, C_out, "f32", 1)
+    buf = sc.LayerBuffers(n, K, stride, "subm" if K % 2 else "strided", C_in, C_out, "f32", device="cuda:0")
+    c, f, w = torch.from_numpy(coords).to("cuda:0"), to_dev(feat, "f32"), to_dev(weight, "f32")
+    buf.feat_out.fill_(float("nan"))
+    buf.layer(c, f, w)
+    n_out = buf.read_counts().n_out
+    pin, pout, start = (t.long() for t in buf.export())
+    ref = torch.zeros((n_out, C_out), dtype=torch.float64, device="cuda:0")
+    for k in range(K ** 3):
+        at = slice(int(start[k]), int(start[k + 1]))
+        ref.index_add_(0, pout[at], f[pin[at]].double() @ w[k].double())
+    assert float((buf.feat_out[:n_out] - ref).abs().max() / ref.abs().max()) <= 1e-5
+    assert bool(buf.feat_out[n_out:].isnan().all())
+
+
 @pytest.mark.parametrize("C_in,C_out", [(32, 64), (64, 64), (64, 128), (128, 16), (256, 48)])
 @pytest.mark.parametrize("n,dtype", [(1, "f16"), (64, "bf16"), (65, "f16"), (34000, "f16"), (1, "f32"), (65, "f32"), (17000, "f32")])
 def test_pointwise_layers(C_in, C_out, n, dtype):
