@@ -830,6 +830,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     const int64_t n_map_tiles = (n_map + TILE - 1) / TILE, likely = tiles < n_map_tiles ? tiles : n_map_tiles;
     const uint32_t* gmask = kmap_masked(mode, L.K3) ? (const uint32_t*)((const char*)d_kmap + L.off_mask) : nullptr;
     const int32_t* nbr = (const int32_t*)((const char*)d_kmap + L.off_nbr);
+    const uint32_t* density = L.off_density != 0 ? (const uint32_t*)((const char*)d_kmap + L.off_density) : nullptr;
     hipStream_t s = (hipStream_t)stream;
 
     if (dtype_in == SC_F32) {           // fp32 weights are used as they are: packed == raw
@@ -851,7 +852,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         const int64_t line_tiles = C_out == 16 || C_out == 32 || C_out == 64 ? likely : tiles;
         const bool slices = C_in == 16 || C_in == 32 || C_in == 64 || C_in == 128 || C_in == 256;
         if (slices && C_out % 16 == 0 && (C_in * C_out >= 2048 || (C_in * C_out >= 1024 && line_tiles >= compute_units()) || L.K3 > 32)) {
-            const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
+            const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u, density};
             return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, likely, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
                                  n_out_cap);
         }
@@ -888,7 +889,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         const size_t need = sc_conv_workspace_bytes(K, C_in, C_out, dtype_in);
         if (d_workspace == nullptr || workspace_bytes < need) return SC_ECAP;
     }
-    const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u};
+    const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u, density};
     const bool strided = mode == SC_STRIDED;
     return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, strided, strided && K != stride, s, d_feat_in, d_weight, packed,
                          d_workspace, d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap);
@@ -981,7 +982,7 @@ extern "C" int sc_conv_fwd_grid(const void* d_feat_in, const int32_t* d_coords, 
     const size_t need = sc_conv_workspace_bytes(K, C_in, C_out, dtype_in);
     if (d_workspace == nullptr || workspace_bytes < need) return SC_ECAP;
     if (n == 0) return SC_OK;
-    const MapSource ms{nullptr, nullptr, (const int4*)d_coords, (const unsigned long long*)d_grid, GridDims{B, X, Y, Z}, epoch};
+    const MapSource ms{nullptr, nullptr, (const int4*)d_coords, (const unsigned long long*)d_grid, GridDims{B, X, Y, Z}, epoch, nullptr};
     if (!mfma_channels_ok(C_in, C_out)) return SC_EINVAL;
     return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, false, false, (hipStream_t)stream, d_feat_in,
                          d_weight, false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n);

@@ -10,6 +10,7 @@
 // The linear index runs z fastest (the paper's eq. 6 runs x fastest; the order is free, and the
 // short vertical axis of LiDAR boxes keeps a 3x3x3 neighbourhood within a few cache lines this way).
 #include "sc_internal.h"
+#include "sc_rules.h"
 
 namespace sc {
 
@@ -70,7 +71,7 @@ k_grid_lookup(const unsigned long long* __restrict__ cells, GridDims dims, uint3
 template <int K, int WPT>
 __global__ void __launch_bounds__(64 * WPT)
 k_kmap_subm_grid(const int4* __restrict__ coords, int64_t n, const unsigned long long* __restrict__ cells, GridDims dims,
-                 uint32_t epoch, uint32_t* __restrict__ gmask, int32_t* __restrict__ nbr, sc_counts* counts,
+                 uint32_t epoch, uint32_t* __restrict__ gmask, int32_t* __restrict__ nbr, uint8_t* __restrict__ density, sc_counts* counts,
                  KmapHeader* hdr, KmapHeader hdr_value) {
     constexpr int K3 = K * K * K, pad = (K - 1) / 2, centre = (K3 - 1) / 2;
     constexpr int PER = (K3 + WPT - 1) / WPT;        // offsets per wavefront
@@ -124,7 +125,14 @@ k_kmap_subm_grid(const int4* __restrict__ coords, int64_t n, const unsigned long
         }
     }
     __syncthreads();
-    if (threadIdx.x < 4 * MW) gmask[tile * (4 * MW) + threadIdx.x] = mask_s[threadIdx.x];
+    if (threadIdx.x < 4 * MW) {
+        const uint32_t word = mask_s[threadIdx.x];
+        gmask[tile * (4 * MW) + threadIdx.x] = word;
+        if (density != nullptr) {
+            const uint8_t offsets = density_of<MW, K3>(word, mask_s);
+            if (threadIdx.x == 0) density[tile] = offsets;
+        }
+    }
 }
 
 static bool dims_ok(int32_t B, int32_t X, int32_t Y, int32_t Z) {
@@ -136,10 +144,10 @@ static bool dims_ok(int32_t B, int32_t X, int32_t Y, int32_t Z) {
 
 template <int K>
 static int launch_kmap_grid(int64_t tiles, hipStream_t s, const int4* coords, int64_t n, const unsigned long long* cells,
-                            GridDims dims, uint32_t epoch, uint32_t* gmask, int32_t* nbr, sc_counts* counts,
+                            GridDims dims, uint32_t epoch, uint32_t* gmask, int32_t* nbr, uint8_t* density, sc_counts* counts,
                             KmapHeader* hdr, KmapHeader hv) {
     SC_LAUNCH(KID_KMAP_GRID, (k_kmap_subm_grid<K, 8>), dim3(xcd_grid(tiles)), dim3(512), 0, s, coords, n, cells, dims, epoch,
-              gmask, nbr, counts, hdr, hv);
+              gmask, nbr, density, counts, hdr, hv);
     return SC_OK;
 }
 
@@ -208,13 +216,14 @@ extern "C" int sc_kmap_build_grid(const int32_t* d_coords, int64_t n, const void
     }
     uint32_t* gmask = (uint32_t*)((char*)d_kmap + L.off_mask);
     int32_t* nbr = (int32_t*)((char*)d_kmap + L.off_nbr);
+    uint8_t* density = density_wanted(L.tiles, compute_units()) ? (uint8_t*)d_kmap + L.off_density : nullptr;
     const unsigned long long* cells = (const unsigned long long*)d_grid;
     const GridDims dims{B, X, Y, Z};
     switch (K) {
-        case 1: return launch_kmap_grid<1>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, d_counts, hdr, hv);
-        case 3: return launch_kmap_grid<3>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, d_counts, hdr, hv);
-        case 5: return launch_kmap_grid<5>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, d_counts, hdr, hv);
-        case 7: return launch_kmap_grid<7>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, d_counts, hdr, hv);
+        case 1: return launch_kmap_grid<1>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, density, d_counts, hdr, hv);
+        case 3: return launch_kmap_grid<3>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, density, d_counts, hdr, hv);
+        case 5: return launch_kmap_grid<5>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, density, d_counts, hdr, hv);
+        case 7: return launch_kmap_grid<7>(L.tiles, s, (const int4*)d_coords, n, cells, dims, epoch, gmask, nbr, density, d_counts, hdr, hv);
     }
     return SC_EINVAL;
 }

@@ -168,6 +168,7 @@ struct MapSource {
     const unsigned long long* cells;
     GridDims dims;
     uint32_t epoch;
+    const uint32_t* density;      // per tile of a submanifold map, one byte (density_of); null: none
 };
 // The K^3 neighbours of `row` (its own index at the centre), straight from the dense table:
 // what k_kmap_subm_grid stores as the row's column of the offset table.
@@ -225,7 +226,8 @@ __device__ inline void grid_neighbours_quarter(const MapSource& ms, int64_t row,
 }
 
 // ---- kernel-map blob ------------------------------------------------------------------------
-// header | mask[T][4][mw] (uint32) | nbr[T][K3][TILE] (int32) | strided maps, K == stride <= 4: parent[n] (uint32)
+// header | mask[T][4][mw] (uint32) | nbr[T][K3][TILE] (int32) | strided maps, K == stride <= 4: parent[n] (uint32); submanifold maps:
+// density[T] (uint8, runs of XCD_RUN tiles whole)
 // Outputs are cut into tiles of 64 consecutive rows.  nbr[t][k][j] is the input row paired with
 // output row 64t+j at offset k, or -1: the paper's offset table (Section III-C.2), stored
 // offset-major inside a tile so that the 16 rows an MFMA group takes are 64 contiguous bytes.
@@ -247,6 +249,7 @@ struct KmapLayout {
     size_t off_mask;      // byte offsets inside the blob
     size_t off_nbr;
     size_t off_parent;    // 0: none
+    size_t off_density;   // 0: none
     size_t bytes;
 };
 // parent[i] = (output row << 6) | offset of input i, all ones where it has none: what sc_kmap_transpose makes the inverse map of.
@@ -265,7 +268,35 @@ inline KmapLayout kmap_layout(int64_t n_out_bound, int K, int stride, int mode) 
         L.off_parent = L.bytes;
         L.bytes = align_up(L.off_parent + (size_t)n_out_bound * sizeof(uint32_t), 256);
     }
+    L.off_density = 0;
+    if (mode == SC_SUBM) {
+        L.off_density = L.bytes;
+        L.bytes = align_up(L.off_density + (size_t)L.tiles, 256);
+    }
     return L;
+}
+// A tile's byte of `density`: the offsets it takes part in (halved where K^3 is more than a byte), from its masks.  Called by the
+// 4 MW lanes that hold them, [4][mw] words; lane 0's is the tile's.
+constexpr __host__ __device__ int density_full(int K3) { return K3 > 255 ? K3 / 2 : K3; }
+template <int MW, int K3>
+__device__ inline uint8_t density_of(uint32_t word, const uint32_t* masks) {
+    int offsets = 0;
+    if constexpr (MW == 1 || MW == 4) {                // words a group apart: a quad, or every fourth of 16 lanes
+        if (MW == 4) {
+            word |= (uint32_t)__builtin_amdgcn_mov_dpp((int)word, 0x128, 0xf, 0xf, true);         // rotated by 8 and 4 lanes of 16
+            word |= (uint32_t)__builtin_amdgcn_mov_dpp((int)word, 0x124, 0xf, 0xf, true);
+            offsets = __popc(word);
+            offsets += __builtin_amdgcn_mov_dpp(offsets, 0xb1, 0xf, 0xf, true);                   // the words of a quad of lanes
+            offsets += __builtin_amdgcn_mov_dpp(offsets, 0x4e, 0xf, 0xf, true);
+        } else {
+            word |= (uint32_t)__builtin_amdgcn_mov_dpp((int)word, 0xb1, 0xf, 0xf, true);
+            word |= (uint32_t)__builtin_amdgcn_mov_dpp((int)word, 0x4e, 0xf, 0xf, true);
+            offsets = __popc(word);
+        }
+    } else {
+        for (int w = 0; w < MW; ++w) offsets += __popc(masks[w] | masks[MW + w] | masks[2 * MW + w] | masks[3 * MW + w]);
+    }
+    return (uint8_t)(K3 > 255 ? offsets >> 1 : offsets);
 }
 
 // Workgroup -> work unit, XCD-aware.  MI355X hands consecutive workgroups to its 8 XCDs in turn
@@ -303,6 +334,39 @@ __device__ inline int64_t xcd_run_of(unsigned block, int64_t units) {    // need
     const unsigned i = block / NUM_XCD;
     const int64_t u = (int64_t)(i / RUN * NUM_XCD + block % NUM_XCD) * RUN + i % RUN;
     return u < units ? u : -1;
+}
+
+// The tiles of xcd_run_of, the dense ones first: workgroup i of an XCD takes the i-th of its tiles by `density`, in windows
+// of up to WAVE runs, whose words are one load.  Classes are quarters of the offsets, whichever of a class first.  Every wavefront finds the tile for itself; whatever the
+// bytes hold, every tile is some workgroup's.  Where it pays: dense_tiles_first.
+__device__ inline int64_t xcd_dense_first(unsigned block, int64_t tiles, const uint32_t* __restrict__ density, int K3) {
+    static_assert(XCD_RUN == 4, "a run is one word of bytes");
+    const unsigned lane = threadIdx.x & 63, xcd = block % NUM_XCD, i = block / NUM_XCD;
+    const unsigned runs = (unsigned)((tiles + NUM_XCD * XCD_RUN - 1) / (NUM_XCD * XCD_RUN)), windows = (runs + WAVE - 1) / WAVE;
+    const unsigned size = (runs + windows - 1) / windows, window = i / (size * XCD_RUN), run = window * size + lane;
+    int rank = (int)(i - window * size * XCD_RUN);
+    const int64_t first = (int64_t)(run * NUM_XCD + xcd) * XCD_RUN;
+    const int have = lane >= size || first >= tiles ? 0 : tiles - first < XCD_RUN ? (int)(tiles - first) : XCD_RUN;
+    const uint32_t word = have > 0 ? density[first / XCD_RUN] : 0u;
+    const uint32_t full = (uint32_t)density_full(K3);
+    uint32_t above = 256u;                             // of the class before
+#pragma unroll
+    for (int c = 3; c >= 0; --c) {
+        const uint32_t least = c == 0 ? 0u : c * full / 4u + 1u;
+#pragma unroll
+        for (int b = 0; b < XCD_RUN; ++b) {
+            const uint32_t offsets = (word >> (8 * b)) & 0xffu;
+            const uint64_t in = __ballot(b < have && offsets >= least && offsets < above);
+            const int n = __popcll(in);
+            if (rank < n) {                            // the lane of the rank-th bit
+                const uint64_t it = __ballot(((in >> lane) & 1ull) != 0ull && __popcll(in & ((1ull << lane) - 1ull)) == rank);
+                return (int64_t)((window * size + (unsigned)__builtin_ctzll(it)) * NUM_XCD + xcd) * XCD_RUN + b;
+            }
+            rank -= n;
+        }
+        above = least;
+    }
+    return -1;
 }
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }

@@ -41,7 +41,7 @@ template <int K, int WPT, int CH, int AT>
 __global__ void __launch_bounds__(64 * WPT)
 k_kmap_subm(const int4* __restrict__ coords, int64_t n, const uint4* __restrict__ slots,
             const TableHeader* __restrict__ th, uint32_t* __restrict__ gmask, int32_t* __restrict__ nbr,
-            sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
+            uint8_t* __restrict__ density, sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
     constexpr int K3 = K * K * K, pad = (K - 1) / 2, centre = (K3 - 1) / 2;
     constexpr int PER_PASS = WPT * CH;
     constexpr int PASSES = (K3 + PER_PASS - 1) / PER_PASS;
@@ -138,7 +138,14 @@ k_kmap_subm(const int4* __restrict__ coords, int64_t n, const uint4* __restrict_
     }
     __syncthreads();
     SC_MARK(4);
-    if (threadIdx.x < 4 * MW) gmask[tile * (4 * MW) + threadIdx.x] = mask_s[threadIdx.x];
+    if (threadIdx.x < 4 * MW) {
+        const uint32_t word = mask_s[threadIdx.x];
+        gmask[tile * (4 * MW) + threadIdx.x] = word;
+        if (density != nullptr) {
+            const uint8_t offsets = density_of<MW, K3>(word, mask_s);
+            if (threadIdx.x == 0) density[tile] = offsets;
+        }
+    }
     SC_MARK(5);
 }
 
@@ -157,7 +164,8 @@ constexpr int MAP_RUN = 16;
 template <int K, int YG, int YB, int RUNS>             // YG wavefronts share an x offset's y offsets, each takes YB of its at a time
 __global__ void __launch_bounds__(64 * K * YG)
 k_kmap_subm_blocks(const int4* __restrict__ coords, int64_t n, const uint4* __restrict__ slots, const TableHeader* __restrict__ th,
-                   uint32_t* __restrict__ gmask, int32_t* __restrict__ nbr, sc_counts* counts, KmapHeader* hdr, KmapHeader hdr_value) {
+                   uint32_t* __restrict__ gmask, int32_t* __restrict__ nbr, uint8_t* __restrict__ density, sc_counts* counts, KmapHeader* hdr,
+                   KmapHeader hdr_value) {
     static_assert(K == 3 || K == 5, "K cells in a row lie in at most two blocks of four");
     constexpr int K3 = K * K * K, pad = (K - 1) / 2, MW = (K3 + 31) / 32, YC = (K + YG - 1) / YG, U = YB * K;
     static_assert(YC % YB == 0, "the passes of a wavefront are whole");
@@ -254,7 +262,14 @@ k_kmap_subm_blocks(const int4* __restrict__ coords, int64_t n, const uint4* __re
         if (MW > 1 && (uint32_t)(placed >> 32) != 0u) atomicOr(&mask_s[lane * MW + (at >> 5) + 1], (uint32_t)(placed >> 32));
     }
     __syncthreads();
-    if (threadIdx.x < 4 * MW) gmask[tile * (4 * MW) + threadIdx.x] = mask_s[threadIdx.x];
+    if (threadIdx.x < 4 * MW) {
+        const uint32_t word = mask_s[threadIdx.x];
+        gmask[tile * (4 * MW) + threadIdx.x] = word;
+        if (density != nullptr) {
+            const uint8_t offsets = density_of<MW, K3>(word, mask_s);
+            if (threadIdx.x == 0) density[tile] = offsets;
+        }
+    }
 }
 
 // ---- strided layers ----------------------------------------------------------------------------
@@ -969,14 +984,15 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
     }
 
     if (mode == SC_SUBM) {
+        uint8_t* density = density_wanted(L.tiles, compute_units()) ? (uint8_t*)d_kmap + L.off_density : nullptr;
         HashTable t = table_view(const_cast<void*>(d_table), n);
 #define SC_SUBM_LAUNCH(KV, WPT, CH, AT)                                                                           \
     SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm<KV, WPT, CH, AT>), dim3(xcd_grid(L.tiles)), dim3(64 * WPT), 0, s,      \
-              (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, d_counts,          \
+              (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, density, d_counts,          \
               (KmapHeader*)d_kmap, h)
 #define SC_SUBM_BLOCKS_AS(KV, YG, YB, RUNS, GRID)                                                                  \
     SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm_blocks<KV, YG, YB, RUNS>), dim3(GRID), dim3(64 * KV * YG), 0, s,         \
-              (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, d_counts,    \
+              (const int4*)d_coords, n, (const uint4*)t.slots, (const TableHeader*)t.hdr, gmask, nbr, density, d_counts,    \
               (KmapHeader*)d_kmap, h)
 #define SC_SUBM_BLOCKS(KV, YG, YB)                                                                                 \
     do {                                                                                                           \

@@ -98,6 +98,22 @@ constexpr bool fewer_rounds_of_four(int64_t workgroups, int64_t cus) {
     return (workgroups + 4 * cus - 1) / (4 * cus) < (workgroups - cus / 2 + 3 * cus - 1) / (3 * cus);
 }
 
+// Maps that such a layer may follow hold how many offsets their tiles take part in.  (A tile has up to 16 workgroups: fp32, 256 output channels.)
+constexpr bool density_wanted(int64_t tiles, int64_t cus) { return 4 * tiles > cus && tiles <= 12 * cus; }
+// The general kernel on submanifold maps: the tiles with many offsets first (xcd_dense_first).  A workgroup of a tile with 27 offsets runs three
+// times as long as one with 9, which is what most tiles of a sweep have, and the dispatcher deals workgroups to the CUs in turn: in the order of the rows,
+// 110 k rows 64 -> 64, a CU gets 48 to 159 offsets (93 on average) and the last dense tile starts when most others are done.  Finding the tile is a round trip,
+// about 0.6 us a workgroup, in front of all others.  From two workgroups per CU on (1 1/4 where LDS holds no more than two at a time), up to
+// 12 tiles per CU; beyond, sweeps gain less than sets without sparse tiles lose, and how dense a set is is not known here.  us of whole layers, in the
+// order of the rows / dense first, sweeps: 64 -> 64 14 k 20.7 / 21.3, 30 k 24.1 / 24.2, 40 k 27.1 / 26.1, 53 k 32.6 / 32.5, 70 k 37.6 / 36.3, 110 k 51.7 / 48.5, 200 k 87.4 / 84.9,
+// 262 k 113 / 111.5, 400 k 163 / 161; 32 -> 64 53 k 27.7 / 26.9, 80 k 33.9 / 32.4; 128 -> 128 53 k 55.1 / 49.1, 262 k 200 / 191; 256 -> 256 4 k 32.9 / 33.8, 6 k 36.7 / 35.5,
+// 8 k 41.8 / 36.4, 14 k 58.0 / 49.3; fp32 64 -> 64 4 k 25.2 / 25.9, 8 k 31.3 / 31.7, 12 k 35.9 / 33.1, 53 k 88.7 / 76.9; K = 5 32 -> 32 30 k 42.8 / 43.4, 53 k 58.7 / 56.1, 64 -> 64
+// 60 k 81.9 / 76.9.  Indoor, 64 -> 64 50 k 31.5 / 31.7, 100 k 52.4 / 53.0, 200 k 92.5 / 93.3, 400 k 178 / 180, 10^6 430 / 438; 128 -> 128 100 k 104.3 / 105.4, 260 k 252 / 256; K = 5 32 -> 32
+// 53 k 56.9 / 56.5.  Random cells 64 -> 64 60 k 35.3 / 35.7.
+constexpr bool dense_tiles_first(int64_t tiles, int64_t workgroups, bool two_at_a_time, int64_t cus) {
+    return 4 * workgroups > (two_at_a_time ? 5 : 8) * cus && density_wanted(tiles, cus);
+}
+
 // Workgroups of the general kernel, tiles times blocks of output channels: a launch takes fewer than 2^32 threads along x, which 2^20
 // tiles (SC_N_MAX rows) of 8 blocks and 512 threads are not.  Past GRID_COLUMNS they go on in the next row of the grid, workgroup by workgroup.
 constexpr int64_t GRID_COLUMNS = 1 << 22;

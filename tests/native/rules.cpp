@@ -49,3 +49,10 @@ static_assert(first_tiles_apart(k7, 1, true, 256) == 577 && first_tiles_apart(k5
 // fp32, 16 output channels: four workgroups per CU are a round fewer than three, by more than half a workgroup per CU
 static_assert(!fewer_rounds_of_four(1, 256) && !fewer_rounds_of_four(896, 256) && fewer_rounds_of_four(897, 256) && fewer_rounds_of_four(1024, 256) &&
               !fewer_rounds_of_four(1025, 256) && fewer_rounds_of_four(1665, 256) && fewer_rounds_of_four(225, 64), "rounds");
+
+// tiles with many offsets first: from two workgroups per compute unit on, from 1 1/4 where no more than two fit, up to 12 tiles per compute unit
+static_assert(!dense_tiles_first(512, 512, false, 256) && dense_tiles_first(513, 513, false, 256) && dense_tiles_first(129, 516, false, 256), "two workgroups");
+static_assert(!dense_tiles_first(80, 320, true, 256) && dense_tiles_first(81, 324, true, 256), "two at a time");
+static_assert(dense_tiles_first(3072, 3072, false, 256) && !dense_tiles_first(3073, 6146, false, 256) && dense_tiles_first(768, 768, false, 64), "12 tiles");
+static_assert(density_wanted(65, 256) && !density_wanted(64, 256) && density_wanted(3072, 256) && !density_wanted(3073, 256), "of the maps, where a layer may ask");
+static_assert(!dense_tiles_first(64, 1024, false, 256), "what the map does not hold is not asked for");

@@ -629,3 +629,39 @@ def test_more_workgroups_than_a_row_of_the_grid_holds():
     del buf, coords, feat
     torch.cuda.empty_cache()
     assert float((got - ref).abs().max() / ref.abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("K,C_in,C_out,n,dtype", [(3, 64, 64, 64 * 513, "f16"), (3, 64, 64, 64 * 2048 + 1, "bf16"), (3, 32, 64, 64 * 3072, "f16"), (3, 256, 256, 64 * 81, "f16"),
+                                                  (5, 32, 32, 64 * 600 + 63, "bf16"), (3, 64, 64, 64 * 300 + 7, "f32"), (5, 32, 16, 64 * 1000 + 1, "f32"), (7, 32, 64, 64 * 520 + 5, "f16")])
+def test_tiles_in_the_order_of_their_density(K, C_in, C_out, n, dtype):
+    """First and last size of the rule, one window of 2,048 tiles and two, part-filled runs: every tile is computed whatever the map's
+    bytes say, with the same bits, and as the oracle has it."""
+    say(f"dense tiles first K={K} {C_in}->{C_out} {dtype} n={n}")
+    import torch
+    import oracle
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import rel_err, sampled_rows_reference
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    scenes = [synth.lidar_scene(s) for s in range(-(-n // 50000))]
+    for b, scene in enumerate(scenes):
+        scene[:, 0] = b
+    coords = np.ascontiguousarray(np.concatenate(scenes)[:n])
+    feat, weight = synth.features(n, C_in, dtype, 3), synth.weights(K ** 3, C_in, C_out, dtype, 3)
+    buf = sc.LayerBuffers(n, K, 1, "subm", C_in, C_out, dtype, "f32", device="cuda:0")
+    c, f, w = torch.from_numpy(coords).to("cuda:0"), torch.from_numpy(feat).to("cuda:0").to(tdt), torch.from_numpy(weight).to("cuda:0").to(tdt)
+    buf.layer(c, f, w)
+    want = buf.feat_out.clone()
+    tiles = -(-n // 64)
+    density = buf.kmap[buf.kmap.numel() - -(-tiles // 256) * 256:][:tiles]            # the last part of the map
+    masks = buf.kmap[256:256 + 16 * tiles * -(-K ** 3 // 32)].view(torch.int32).view(tiles, 4, -1).cpu().numpy().view(np.uint32)
+    offsets = np.unpackbits(np.bitwise_or.reduce(masks, axis=1).view(np.uint8), axis=1).sum(axis=1).astype(int)
+    assert np.array_equal(density.cpu().numpy(), offsets if K < 7 else offsets // 2)
+    rng = np.random.default_rng(n)
+    for fill in (rng.integers(0, 256, tiles), np.zeros(tiles), np.arange(tiles) % 4):
+        density.copy_(torch.from_numpy(fill.astype(np.uint8)))
+        buf.feat_out.fill_(float("nan"))
+        buf.conv_fwd(f, w)
+        assert torch.equal(buf.feat_out, want)
+    rows = np.unique(np.concatenate([rng.choice(n, 1000, replace=False), np.arange(n - 70, n)]))
+    err = rel_err(want.double().cpu().numpy()[rows], sampled_rows_reference(feat, weight, oracle.kmap(coords, K, 1, "subm"), rows)[rows])
+    assert err <= 1e-5, err
