@@ -85,7 +85,7 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
         __shared__ int32_t found_s[FUSED ? 4 * NT : 1][28][16];
         if (group_ok) {
             int32_t part[7];
-            grid_neighbours_quarter<3>(ms, row, n_out, qq, part);
+            grid_neighbours_part<3, 4>(ms, row, n_out, qq, part);
 #pragma unroll
             for (int u = 0; u < 7; ++u) found_s[wv][qq + 4 * u][r] = part[u];
 #pragma unroll

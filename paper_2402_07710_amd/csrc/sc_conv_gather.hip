@@ -50,6 +50,8 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 //    cycles of the CU's address unit per instruction) plus its multiplies; the waits are short.
 //  * What hides the latency of a step is other workgroups: OCC wavefronts per SIMD (64 -> 64, 262 k voxels:
 //    65 us with 2, 51.5 with 4, 50 with 6).  That also decides the step length, 16 KB of LDS for 64 channels.
+//  * HV = 2 (two_sets): few workgroups leave most of a CU idle, and two sets of NW wavefronts walk alternate steps of the list, each with its own
+//    buffers.  In the end a set hands the sums of half of its groups to the other through LDS.
 // A group without a neighbour at an offset is not multiplied by its weights (a weight that is not finite stays out
 // of its sums).  SKIP: nor is it gathered and read (64 channels: 62 -> 50 us at that size).  32-channel rows in steps of four
 // offsets (few workgroups, or K > 3; steps of two skip) are too short for that: such groups read the row of zeros, and the places of the last step that have no offset are fetched
@@ -65,12 +67,13 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 // fp32 118 -> 72 us.  Against the kernels that shared W[k] in LDS or gave a wavefront 64 rows: 64 -> 64 2 k /
 // 20 k / 110 k / 262 k voxels 14.8 / 15.8 / 29.4 / 58.2 -> 10.7 / 14.1 / 28.6 / 50.3 us; 64 -> 128 4 k / 110 k 27.4 /
 // 47.1 -> 11.7 / 40.7; 128 -> 128 4 k / 53 k / 262 k 70.8 / 75.5 / 157 -> 16.8 / 43 / 127.5.
-template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int SRC>
-__global__ void __launch_bounds__(64 * NW, OCC)
+template <int DT, int KS, int NW, int WR, int CT, int SL, int SKIP, int OCC, int SRC, int HV>
+__global__ void __launch_bounds__(64 * NW * HV, OCC)
 k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_f32, const MapSource ms, int K3, int mw, int CB,
               int blocks_y, int64_t tiles_apart, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
     constexpr bool FUSED = SRC == FROM_TABLE, HELD = FUSED || SRC == FROM_LINES, POINT = SRC == FROM_LINE, REGS = SRC == FROM_MAP_BY_REGISTERS;      // HELD: the tile's entries are in LDS
     static_assert(!HELD || (DT != SC_F32 && NW == 4), "a quarter of the 27 offsets per wavefront");
+    static_assert(HV == 1 || (HV == 2 && HELD), "two sets of wavefronts: layers with the lines in LDS");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
     constexpr bool F32 = DT == SC_F32;
@@ -79,6 +82,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     // the two steps after the last are read too: up to 3 OPS - 1 places past the last offset, which have to be zeros
     static_assert(!REGS || WAVE % OPS == 0, "a step's places are in one register");
     static_assert(3 * OPS <= LIST_PAD, "the list's zeros reach as far as the steps read");
+    constexpr int PAD = LIST_PAD * HV;
     constexpr int CH = KP == 1 ? 1 : KP / 2;           // chunks per offset and step: 64 rows x 128 (64) bytes
     constexpr int CHB = KS == 1 ? 4096 : 8192;         // bytes per chunk
     constexpr int NI = KS == 1 || NW == 8 ? 1 : 2;     // gather instructions per wavefront and chunk
@@ -87,10 +91,12 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     static_assert(SL % KP == 0 && KS % KP == 0, "a step is whole offsets, or an offset whole steps");
     constexpr int NC = 16 * WC * CT;                   // output channels of the workgroup
     constexpr int W_BYTES = F32 ? SL * 16 * NC * 4 : 0;        // fp32 weights of a step, in LDS behind the rows
-    // rows[2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + LIST_PAD], but POINT and REGS | HELD: entries[28][64], masks[4][4]
-    extern __shared__ __align__(16) char smem[];
+    // rows[HV][2][STEP_BYTES] | weights[2][W_BYTES] | list[K3 + PAD], but POINT and REGS | HELD: entries[28 or 32][64], masks[4 HV][4]
+    extern __shared__ __align__(16) char smem_all[];
 
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wv = HV == 1 ? wave : wave % NW, set = HV == 1 ? 0 : wave / NW;
+    char* const smem = smem_all + set * (2 * STEP_BYTES);
     const int r = lane & 15, qq = lane >> 4;
     const int wr = wv / WC;
     const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
@@ -115,10 +121,11 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     // 38.7 / 35.1 / 32.8).
     // REGS: it is made in the half of the rows' buffer that is filled second and then lies in the lanes of PLACES registers: behind both buffers it takes
     // the 16-channel workgroups of fp32, whose buffers are a quarter of the LDS, from four per CU to three (fewer_rounds_of_four).
+    constexpr int WAVES = NW * HV, LINES = (27 + WAVES - 1) / WAVES;       // HELD: lines of the map a wavefront copies or looks up
     constexpr int PLACES = REGS ? 6 : 1;               // 64 offsets each: K^3 <= 343 and what is read past them
     uint32_t places[PLACES] = {};
-    uint32_t* list = reinterpret_cast<uint32_t*>(smem + (REGS ? STEP_BYTES + 128 : 2 * STEP_BYTES + 2 * W_BYTES));
-    int32_t* found = reinterpret_cast<int32_t*>(list + 40);
+    uint32_t* list = reinterpret_cast<uint32_t*>(smem_all + (REGS ? STEP_BYTES + 128 : HV * 2 * STEP_BYTES + 2 * W_BYTES));
+    int32_t* found = reinterpret_cast<int32_t*>(list + (28 + PAD));
     uint32_t only = 0u;
     int listed = 0;
     auto add_to_list = [&](int k, uint32_t pat) __attribute__((always_inline)) {
@@ -132,32 +139,37 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         only = __builtin_amdgcn_readfirstlane(only);
     } else if constexpr (FUSED) {
         // lane = row; each wavefront looks up every fourth offset, its part of the masks is a vote
-        uint32_t* votes = reinterpret_cast<uint32_t*>(found + 28 * TILE);
-        int32_t part[7];
-        grid_neighbours_quarter<3>(ms, tile * TILE + lane, n_out, wv, part);
+        uint32_t* votes = reinterpret_cast<uint32_t*>(found + LINES * WAVES * TILE);
+        int32_t part[LINES];
+        grid_neighbours_part<3, WAVES>(ms, tile * TILE + lane, n_out, wave, part);
         uint32_t vg[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int u = 0; u < 7; ++u) {
-            found[(wv + 4 * u) * TILE + lane] = part[u];
+        for (int u = 0; u < LINES; ++u) {
+            found[(wave + WAVES * u) * TILE + lane] = part[u];
             const uint64_t vote = __ballot(part[u] >= 0);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) vg[g] |= (((vote >> (16 * g)) & 0xffffull) != 0ull ? 1u : 0u) << (wv + 4 * u);
+            for (int g = 0; g < 4; ++g) vg[g] |= (((vote >> (16 * g)) & 0xffffull) != 0ull ? 1u : 0u) << (wave + WAVES * u);
         }
-        if (lane == 0) *reinterpret_cast<uint4*>(votes + 4 * wv) = make_uint4(vg[0], vg[1], vg[2], vg[3]);
+        if (lane == 0) *reinterpret_cast<uint4*>(votes + 4 * wave) = make_uint4(vg[0], vg[1], vg[2], vg[3]);
         __syncthreads();
         uint32_t pat = 0u;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) pat |= (((votes[g] | votes[4 + g] | votes[8 + g] | votes[12 + g]) >> (lane & 31)) & 1u) << g;
+        for (int g = 0; g < 4; ++g) {
+            uint32_t any = 0u;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) any |= votes[4 * w + g];
+            pat |= ((any >> (lane & 31)) & 1u) << g;
+        }
         add_to_list(lane, lane < 27 ? pat : 0u);
     } else {
-        int32_t part[7];
+        int32_t part[LINES];
         if constexpr (HELD) {
 #pragma unroll
-            for (int u = 0; u < 7; ++u) part[u] = wv + 4 * u < K3 ? nbr[(tile * K3 + wv + 4 * u) * TILE + lane] : -1;
+            for (int u = 0; u < LINES; ++u) part[u] = wave + WAVES * u < K3 ? nbr[(tile * K3 + wave + WAVES * u) * TILE + lane] : -1;
         }
         auto hold = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < 7; ++u) found[(wv + 4 * u) * TILE + lane] = part[u];
+            for (int u = 0; u < LINES; ++u) found[(wave + WAVES * u) * TILE + lane] = part[u];
         };
         if (gmask != nullptr) {
             for (int k = lane; k - lane < K3; k += WAVE) {
@@ -175,13 +187,13 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         } else {
             // a map without masks (K^3 <= 32): its lines are voted on, every NWth by a wavefront, and the patterns traded through
             // LDS, in the half of the rows' buffer that is filled second
-            uint32_t* patterns = reinterpret_cast<uint32_t*>(smem + STEP_BYTES);
+            uint32_t* patterns = reinterpret_cast<uint32_t*>(smem_all + STEP_BYTES);
             if constexpr (HELD) hold();
 #pragma unroll
-            for (int u = 0; u < 32 / NW; ++u) {
-                const int k = wv + NW * u;
+            for (int u = 0; u < 32 / WAVES; ++u) {
+                const int k = wave + WAVES * u;
                 if (k < K3) {
-                    const uint32_t pat = line_pattern(HELD && u < 7 ? part[u] : nbr[(tile * K3 + k) * TILE + lane]);
+                    const uint32_t pat = line_pattern(HELD && u < LINES ? part[u] : nbr[(tile * K3 + k) * TILE + lane]);
                     if (lane == 0) patterns[k] = pat;
                 }
             }
@@ -193,10 +205,10 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
 #pragma unroll
         for (int j = 0; j < PLACES; ++j)
             if (j * WAVE < listed) places[j] = j * WAVE + lane < listed ? list[j * WAVE + lane] : 0u;
-    } else if (!POINT && lane < LIST_PAD) {
+    } else if (!POINT && lane < PAD) {
         list[listed + lane] = 0u;
     }
-    const uint32_t* next = list;
+    const uint32_t* next = list + set * OPS;
     uint32_t fetched[OPS];                             // the list's entries of the next step, read a step before they are needed
     int part = 0, at = 0;
     auto fetch = [&]() __attribute__((always_inline)) {
@@ -219,7 +231,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         } else {
             if (PARTS == 1 || ++part == PARTS) {
                 part = 0;
-                next += OPS;
+                next += HV * OPS;
                 if (REGS && (at += OPS) == WAVE) {
                     at = 0;
 #pragma unroll
@@ -442,11 +454,46 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         compute(a, p0, buf);
         step_end();
     };
+    if constexpr (HV == 1) {
 #pragma unroll 1
-    while (p1[0] != 0u) {
-        step(a0, a1, 0);
-        if (p1[0] == 0u) break;
-        step(a1, a0, 1);
+        while (p1[0] != 0u) {
+            step(a0, a1, 0);
+            if (p1[0] == 0u) break;
+            step(a1, a0, 1);
+        }
+    } else {
+        // as many steps for both sets; then each gives the other its sums of two groups and stores the other two
+#pragma unroll 1
+        for (int left = (listed + HV * OPS - 1) / (HV * OPS) * PARTS; left > 0; --left) {
+            step(a0, a1, 0);
+            if (--left <= 0) break;
+            step(a1, a0, 1);
+        }
+        constexpr int G = RG / 2;
+        f32x4* sums = reinterpret_cast<f32x4*>(smem_all) + (size_t)wave * (G * CT * 64) + lane;
+        const f32x4* theirs = reinterpret_cast<const f32x4*>(smem_all) + (size_t)(wave ^ NW) * (G * CT * 64) + lane;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) sums[(g * CT + ct) * 64] = set == 0 ? acc[G + g][ct] : acc[g][ct];
+        lds_barrier();
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const f32x4 other = theirs[(g * CT + ct) * 64];
+                acc[g][ct] = set == 0 ? acc[g][ct] + other : other + acc[G + g][ct];
+            }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int64_t row = tile * TILE + (wr * RG + set * G + g) * 16 + r;
+            if (row < n_out) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+                    if (cb0 + ct < CB) store_acc<DT>(out, out_f32, row, CB * 16, (cb0 + ct) * 16 + qq * 4, acc[g][ct]);
+            }
+        }
+        return;
     }
 #pragma unroll
     for (int g = 0; g < RG; ++g) {
@@ -459,25 +506,26 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     }
 }
 
-template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int SRC>
+template <int DT, int KS, int SL, int SKIP, int NW, int WR, int CT, int OCC, int SRC, int HV = 1>
 static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out,
                             int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     constexpr bool held = SRC == FROM_TABLE || SRC == FROM_LINES;
-    constexpr size_t fixed = 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + (held ? 28 * TILE * 4 + 64 : 0);
-    static_assert(fixed <= 65536 + 28 * TILE * 4 + 64, "loads into LDS land in the first 64 KB");
-    constexpr auto list_bytes = [](int K3) { return SRC == FROM_LINE || SRC == FROM_MAP_BY_REGISTERS ? (size_t)0 : (size_t)((held ? 27 : K3) + LIST_PAD + 3) / 4 * 16; };     // entries lie behind a list of 27
+    constexpr size_t entries = held ? (HV == 1 ? 28 : 32) * TILE * 4 + 64 * HV : 0;
+    constexpr size_t fixed = HV * 2 * SL * 4096 + (DT == SC_F32 ? 2 * SL * 1024 * (NW / WR * CT) : 0) + entries;
+    static_assert(fixed <= 65536 + entries, "loads into LDS land in the first 64 KB");
+    constexpr auto list_bytes = [](int K3) { return SRC == FROM_LINE || SRC == FROM_MAP_BY_REGISTERS ? (size_t)0 : (size_t)((held ? 28 : K3) + LIST_PAD * HV + 3) / 4 * 16; };     // entries lie behind a list of 28
     const size_t lds = fixed + list_bytes(K3);
     if constexpr (fixed + list_bytes(343) > 65536) {
         static bool allowed[MAX_DEVICES] = {};
-        if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>, fixed + list_bytes(343), allowed)) return rc;
+        if (int rc = allow_lds((const void*)k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC, HV>, fixed + list_bytes(343), allowed)) return rc;
     }
     const unsigned blocks_y = (unsigned)((CB + NW / WR * CT - 1) / (NW / WR * CT));
-    static_assert(grid_fits(GRID_COLUMNS, 64 * NW) && GRID_COLUMNS % NUM_XCD == 0, "a row of the grid is whole turns of the XCDs");
+    static_assert(grid_fits(GRID_COLUMNS, 64 * NW * HV) && GRID_COLUMNS % NUM_XCD == 0, "a row of the grid is whole turns of the XCDs");
     const int64_t groups = (int64_t)xcd_run_grid(tiles) * blocks_y;
     MapSource source = ms;
     if (SRC == FROM_LINE || !dense_tiles_first(tiles, tiles * blocks_y, 3 * fixed > 160 * 1024, cus)) source.density = nullptr;
-    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC>),
-              dim3((unsigned)grid_columns(groups), (unsigned)grid_rows(groups)), dim3(64 * NW), lds, s, feat, wp, out, out_f32, source, K3, mw, CB,
+    SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC, HV>),
+              dim3((unsigned)grid_columns(groups), (unsigned)grid_rows(groups)), dim3(64 * NW * HV), lds, s, feat, wp, out, out_f32, source, K3, mw, CB,
               (int)blocks_y, first_tiles_apart((int64_t)K3 * CB * KS * 1024, CT, n_out_ptr != nullptr, cus), n_out_ptr, n_out_cap);
     return SC_OK;
 }
@@ -525,6 +573,16 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
 #undef SC_GATHER
 }
 
+// Two sets of wavefronts (two_sets), one output block per wavefront.
+template <int DT, int KS, int SL, int SKIP, int O1, int SRC>
+static int launch_gather_sets(int K3, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out, int out_f32,
+                              const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
+    if constexpr (SRC != FROM_TABLE) {
+        if (CB == 2) return launch_gather_as<DT, KS, SL, SKIP, 4, 2, 1, O1, SRC, 2>(K3, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
+    }
+    return launch_gather_as<DT, KS, SL, SKIP, 4, 1, 1, O1, SRC, 2>(K3, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
+}
+
 int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const int CB = C_out / 16;
@@ -532,6 +590,10 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
     // with more workgroups: 128 -> 64 at 53 k voxels 36.7 us instead of 28.8).  64: an offset; two for K = 5 and 7, whose
     // tiles walk many more offsets (K = 3 -> 64 at 262 k voxels 50.3 us with one, 56.5 with two; K = 5 -> 64 at 53 k 55.1
     // and 50.7).  32: four (K = 5 -> 32 at 53 k: 30.4 us; two 32.1, eight with half the workgroups 36).
+#define SC_GATHER_SETS(KS, SL, SKIP, O1)                                                                                                      \
+    return dtype_in == SC_F16                                                                                                     \
+               ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, FROM_LINES>(K3, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
+               : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, FROM_LINES>(K3, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
 #define SC_GATHER_KS(KS, SL, SKIP, O1, O2, SRC)                                                                                      \
     return dtype_in == SC_F16                                                                                                     \
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
@@ -561,6 +623,13 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
         return SC_EINVAL;
     }
     const bool few = few_workgroups(likely, CB, cus);
+    if (K3 <= 27 && two_sets(likely, CB, C_in, cus)) {
+        switch (C_in) {
+            case 32: SC_GATHER_SETS(1, 2, 1, 4);
+            case 64: SC_GATHER_SETS(2, 2, 1, 6);
+            case 128: SC_GATHER_SETS(4, 4, 1, 4);
+        }
+    }
     if (K3 <= 27) {
         switch (C_in) {
             case 32:
@@ -580,6 +649,7 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
         case 256: SC_GATHER_KS(8, 8, 1, 2, 2, FROM_MAP);
     }
 #undef SC_GATHER_KS
+#undef SC_GATHER_SETS
     return SC_EINVAL;
 }
 
@@ -592,6 +662,15 @@ int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cu
     return dtype_in == SC_F16                                                                                                                \
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
                : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+#define SC_GATHER_FUSED_SETS(KS, SL, SKIP, O1)                                                                                                    \
+    return dtype_in == SC_F16 ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, FROM_TABLE>(27, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
+                              : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, FROM_TABLE>(27, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+    if (two_sets(tiles, CB, C_in, cus)) {
+        if (C_in == 32) SC_GATHER_FUSED_SETS(1, 2, 1, 4);
+        if (C_in == 64) SC_GATHER_FUSED_SETS(2, 2, 1, 6);
+        if (C_in == 128) SC_GATHER_FUSED_SETS(4, 4, 1, 4);
+    }
+#undef SC_GATHER_FUSED_SETS
     const bool few = few_workgroups(tiles, CB, cus);
     if (C_in == 32 && few) SC_GATHER_FUSED(1, 4, 0, 2, 2);
     if (C_in == 32) SC_GATHER_FUSED(1, 2, 1, 5, 4);

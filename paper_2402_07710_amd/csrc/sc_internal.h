@@ -196,12 +196,12 @@ __device__ inline void grid_neighbours(const MapSource& ms, int64_t row, int64_t
     }
 }
 
-// The same for every fourth offset only, k = first + 4u (u = 0..ceil(K^3/4)-1; entries past K^3 are
-// -1): four lanes that serve one row share the look-ups instead of repeating them.
-template <int K>
-__device__ inline void grid_neighbours_quarter(const MapSource& ms, int64_t row, int64_t n, int first,
-                                               int32_t (&e)[(K * K * K + 3) / 4]) {
-    constexpr int K3 = K * K * K, pad = (K - 1) / 2, centre = (K3 - 1) / 2, NQ = (K3 + 3) / 4;
+// The same for every STEPth offset only, k = first + STEP u (u = 0..ceil(K^3/STEP)-1; entries past K^3 are
+// -1): four lanes or wavefronts (or eight) that serve one row share the look-ups instead of repeating them.
+template <int K, int STEP>
+__device__ inline void grid_neighbours_part(const MapSource& ms, int64_t row, int64_t n, int first,
+                                            int32_t (&e)[(K * K * K + STEP - 1) / STEP]) {
+    constexpr int K3 = K * K * K, pad = (K - 1) / 2, centre = (K3 - 1) / 2, NQ = (K3 + STEP - 1) / STEP;
     const bool valid = row < n;
     int4 c = make_int4(-1, 0, 0, 0);
     if (valid) c = ms.coords[row];
@@ -211,7 +211,7 @@ __device__ inline void grid_neighbours_quarter(const MapSource& ms, int64_t row,
     bool look[NQ];
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
-        const int k = first + 4 * u;
+        const int k = first + STEP * u;
         const int dx = k / (K * K) - pad, dy = (k / K) % K - pad, dz = k % K - pad;
         look[u] = ok && k < K3 && k != centre && (unsigned)(c.y + dx) < (unsigned)ms.dims.X &&
                   (unsigned)(c.z + dy) < (unsigned)ms.dims.Y && (unsigned)(c.w + dz) < (unsigned)ms.dims.Z;
@@ -219,7 +219,7 @@ __device__ inline void grid_neighbours_quarter(const MapSource& ms, int64_t row,
     }
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
-        const int k = first + 4 * u;
+        const int k = first + STEP * u;
         if (k == centre) e[u] = valid ? (int32_t)row : -1;
         else e[u] = (look[u] && (uint32_t)(got[u] >> 32) == ms.epoch) ? (int32_t)(uint32_t)got[u] : -1;
     }

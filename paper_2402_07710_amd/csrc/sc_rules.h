@@ -67,6 +67,17 @@ constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t c
 // 18 k / 26 k / 30 k 23.0 / 26.7 / 28.2 and 25.5 / 27.2 / 28.3, indoor 25.4 / 30.1 / 31.2 and 25.4 / 28.9 / 30.5.
 constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return likely * ((CB + 3) / 4) <= 3 * cus; }
 
+// The general kernel, K <= 3, 16 bit, up to 128 input channels: two sets of four wavefronts walk alternate offsets of the tile and add up their sums in the end.  Up to
+// two workgroups per CU (32 input channels 1 1/4) a layer takes as long as the workgroup of a dense tile walks its offsets, one wavefront per SIMD, and of 27
+// offsets each set walks 14; beyond, the CUs have enough wavefronts and the sums are traded for nothing.  us of whole layers, one set / two, sweeps: 64 -> 64 500 15.5 /
+// 14.5, 2 k 18.0 / 16.0, 10 k 19.9 / 18.9, 14 k 20.8 / 20.2, 25 k 23.1 / 22.4, 30 k 23.8 / 22.9, 42 k 26.5 / 26.1, 53 k 32.4 / 32.0, 80 k 38.1 / 41.2; indoor 3 k 18.6 / 16.7, 10 k 19.2 / 17.5, 30 k 23.9 / 23.2, 40 k 28.4 /
+// 29.1; stride 2 2 k 26.1 / 23.9, 20 k 30.1 / 29.3; 64 -> 128 5 k 19.3 / 17.6, 20 k 23.6 / 23.1, 40 k 30.3 / 34.3; 128 -> 128 500 18.9 / 17.3, 2 k 23.1 / 20.3, 8 k 27.6 / 24.4, 14 k 29.6 / 25.8, 20 k 31.1 /
+// 31.6, 26 k 32.4 / 35.3; indoor 5 k 26.4 / 23.8, 15 k 29.6 / 30.2; 128 -> 256 1 k 22.4 / 20.0, 8 k 29.1 / 25.3, 12 k 30.4 / 32.9; 128 -> 32 30 k 29.3 / 26.4; 32 -> 64 1 k 15.3 / 14.6, 10 k 16.5 / 16.1, 14 k 17.5 / 17.0, 20 k 18.7 /
+// 18.7, 53 k 26.8 / 30.4.  256 input channels, whose offsets take 64 KB through the L1 of a CU, as fast as that goes, are the same with two sets (1 k 27.8 / 28.0, 14 k 49.1 / 50.8).
+constexpr bool two_sets(int64_t likely, int CB, int C_in, int64_t cus) {
+    return CB > 1 && C_in <= 128 && likely * ((CB + 3) / 4) * 4 <= (C_in == 32 ? 5 : 8) * cus;
+}
+
 // The general kernel, 16 bit: a tile's blocks of output channels one after the other on an XCD, whose L2 then holds the tile's rows for the second,
 // or all tiles' first blocks before any second one: the tile count from which it is the latter.  Where the weights are larger than an
 // L2 (4 MiB), workgroups of one block at a time share half the weights of a few offsets.  Of the tiles that are there, with two output blocks per wavefront:

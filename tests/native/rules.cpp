@@ -56,3 +56,8 @@ static_assert(!dense_tiles_first(80, 320, true, 256) && dense_tiles_first(81, 32
 static_assert(dense_tiles_first(3072, 3072, false, 256) && !dense_tiles_first(3073, 6146, false, 256) && dense_tiles_first(768, 768, false, 64), "12 tiles");
 static_assert(density_wanted(65, 256) && !density_wanted(64, 256) && density_wanted(3072, 256) && !density_wanted(3073, 256), "of the maps, where a layer may ask");
 static_assert(!dense_tiles_first(64, 1024, false, 256), "what the map does not hold is not asked for");
+
+// two sets of wavefronts up to two workgroups per compute unit, with 32 input channels 1 1/4; not for 16 output channels, nor for 256 input channels
+static_assert(two_sets(512, 4, 64, 256) && !two_sets(513, 4, 64, 256) && two_sets(256, 8, 128, 256) && !two_sets(257, 8, 128, 256), "two");
+static_assert(two_sets(320, 4, 32, 256) && !two_sets(321, 4, 32, 256) && two_sets(512, 2, 128, 256) && two_sets(128, 4, 64, 64), "1 1/4");
+static_assert(!two_sets(1, 1, 64, 256) && !two_sets(1, 4, 256, 256), "one set");

@@ -665,3 +665,29 @@ def test_tiles_in_the_order_of_their_density(K, C_in, C_out, n, dtype):
     rows = np.unique(np.concatenate([rng.choice(n, 1000, replace=False), np.arange(n - 70, n)]))
     err = rel_err(want.double().cpu().numpy()[rows], sampled_rows_reference(feat, weight, oracle.kmap(coords, K, 1, "subm"), rows)[rows])
     assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("C_in,C_out,n", [(32, 64, 320 * 64), (32, 64, 320 * 64 + 1), (64, 64, 512 * 64 - 1), (64, 64, 512 * 64 + 1), (128, 128, 256 * 64), (128, 128, 256 * 64 + 1),
+                                          (128, 32, 1000), (64, 80, 77), (128, 256, 64)])
+def test_two_sets_of_wavefronts(C_in, C_out, n):
+    """Both sides of the lines, two wavefronts across the rows (32 output channels), a part-filled block of output channels; tiles with
+    odd and even numbers of offsets; the fused layer, which walks the same steps, gives the same bits."""
+    say(f"two sets {C_in} -> {C_out}, n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import to_dev
+    side = max(4, int(round((n * 8) ** (1 / 3))))
+    coords = synth.uniform_cells(n, side, seed=C_in)
+    coords = np.ascontiguousarray(coords[np.lexsort((coords[:, 3], coords[:, 2], coords[:, 1]))])
+    check_layer(coords, 3, 1, "subm", C_in, C_out, "bf16", seed=n, out_dtype="f32", threads=16)
+    check_layer(coords, 2, 2, "strided", C_in, C_out, "f16", seed=n, out_dtype="f32", threads=16)
+    if C_out in (64, 128):
+        c, f = torch.from_numpy(coords).to("cuda:0"), to_dev(synth.features(n, C_in, "f16", 1), "f16")
+        w = to_dev(synth.weights(27, C_in, C_out, "f16", 1), "f16")
+        outs = []
+        for dims in (None, (1, side, side, side)):
+            buf = sc.LayerBuffers(n, 3, 1, "subm", C_in, C_out, "f16", "f32", device="cuda:0", grid_dims=dims)
+            buf.feat_out.fill_(float("nan"))
+            (buf.layer if dims is None else buf.layer_fused)(c, f, w)
+            outs.append(buf.feat_out)
+        assert torch.equal(*outs)
