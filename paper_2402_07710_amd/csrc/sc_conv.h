@@ -94,6 +94,13 @@ __device__ inline void store_acc(void* __restrict__ out, int out_f32, int64_t ro
     }
 }
 
+// 16 bytes per lane from global memory straight into LDS: lane l's land at byte lds + 16 l.  The
+// instruction takes its LDS address from M0 and needs one wait state after a write of it (s_nop).  Inline
+// assembly, because the compiler would put a wait for all loads in front of every later LDS read.
+__device__ inline void load_to_lds(const void* src, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
+}
+
 // Large dynamic LDS has to be allowed per kernel, once on every device the kernel runs on: a flag
 // per device (a repeated call would be harmless, so a race between host threads is too).
 constexpr int MAX_DEVICES = 64;

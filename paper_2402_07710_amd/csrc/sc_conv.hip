@@ -44,6 +44,9 @@ k_weight_pack(const uint16_t* __restrict__ w, uint4* __restrict__ wp, int K3, in
 // copies the weights of all K3 offsets into LDS once, re-laying them out as MFMA operand tiles on
 // the way, so no separate packing pass is needed; meanwhile every wavefront has its K3 offset-table lines and then all its feature
 // gathers in flight.  KS = C_in/32, CB = C_out/16.
+// Packed weights go straight to LDS, requested before the lines and waited for with them.  Through registers they were a loop of round
+// trips between the lines and the gathers (us of whole layers on sweeps 2 k / 10 k / 30 k / 53 k, before and now: 13.2 / 14.4 / 18.4 / 23.3 and 12.8 / 14.0 /
+// 17.3 / 23.2; two layers and the strided one 10 k / 53 k 40.0 / 51.5 and 37.5 / 50.4).
 // FUSED: there is no kernel map; the K^3 neighbours of a row are looked up in the dense location
 // table right here (one index computation and one 8-byte load each, all in flight together), and
 // the group's mask is a vote over what was found.  n_out_cap is then the number of rows.
@@ -76,6 +79,16 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
     const int64_t row = tile * TILE + q * 16 + r;
     const bool group_ok = tile * TILE + q * 16 < n_out;             // uniform per wavefront
 
+    // packed weights land in LDS beside everything up to the gathers, which wait for the lines behind them
+    constexpr bool DIRECT = WPACKED && K3 * CB * KS <= 64;
+    if constexpr (DIRECT) {
+        const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)w_lds;
+#pragma unroll
+        for (int i = 0; i < (K3 * CB * KS + 4 * NT - 1) / (4 * NT); ++i) {
+            const int t = __builtin_amdgcn_readfirstlane(wv) + i * 4 * NT;
+            if (t < K3 * CB * KS) load_to_lds(wraw + t * 64 + lane, base + t * 1024);
+        }
+    }
     // the group's offset-table lines (all K3 of them) and its mask word: one round trip
     int32_t e[K3];
     uint32_t m = 0;
@@ -113,7 +126,9 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
     // channels of 8 input channels (8-byte loads) and writes four lanes' 16 bytes.  With a thread per lane, 2-byte loads, they were
     // four times as many loads of 17 cycles each (us: up-sampling from the strided map 64 -> 32 53 k 6.1 -> 5.4, 64 -> 64 200 k 22.8 ->
     // 20.8, 128 -> 64 53 k 12.8 -> 11.4; layers K = 2 64 -> 64 200 k 40.7 -> 38.6, fused 32 -> 32 53 k 15.1 -> 14.8)
-    if constexpr (WPACKED) {
+    if constexpr (DIRECT) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0)
+    } else if constexpr (WPACKED) {
         // the caller packed the weights once (sc_conv_weight_pack): the tiles are copied as they are
         for (int i = threadIdx.x; i < K3 * CB * KS * 64; i += 256 * NT) w_lds[i] = wraw[i];
     } else {

@@ -8,13 +8,6 @@ namespace sc {
 // A row of zeros that stands in for "no neighbour": 512 bytes, up to 256 16-bit channels.
 static __device__ __align__(512) uint4 g_zero_row[32];
 
-// 16 bytes per lane from global memory straight into LDS: lane l's land at byte lds + 16 l.  The
-// instruction takes its LDS address from M0 and needs one wait state after a write of it (s_nop).  Inline
-// assembly, because the compiler would put a wait for all loads in front of every later LDS read.
-__device__ inline void load_to_lds(const void* src, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
-}
-
 // where a tile's table entries come from: the map's lines as they are needed, look-ups, the map's lines copied to LDS first, the one line
 // of a pointwise layer, or the map's lines as they are needed by a list of offsets in registers
 enum { FROM_MAP, FROM_TABLE, FROM_LINES, FROM_LINE, FROM_MAP_BY_REGISTERS };
