@@ -40,13 +40,19 @@ k_weight_pack(const uint16_t* __restrict__ w, uint4* __restrict__ wp, int K3, in
 }
 
 // ---- small layers: all of W resident in LDS ----------------------------------------------------
-// One wavefront per 16 output rows, NT tiles (4*NT wavefronts) per workgroup.  The workgroup
-// copies the weights of all K3 offsets into LDS once, re-laying them out as MFMA operand tiles on
+// One wavefront per 16 output rows, up to NT tiles (4*NT wavefronts) per workgroup at a time.  The workgroup
+// copies the weights of all K3 offsets into LDS once, raw ones re-laid out as MFMA operand tiles on
 // the way, so no separate packing pass is needed; meanwhile every wavefront has its K3 offset-table lines and then all its feature
 // gathers in flight.  KS = C_in/32, CB = C_out/16.
 // Packed weights go straight to LDS, requested before the lines and waited for with them.  Through registers they were a loop of round
 // trips between the lines and the gathers (us of whole layers on sweeps 2 k / 10 k / 30 k / 53 k, before and now: 13.2 / 14.4 / 18.4 / 23.3 and 12.8 / 14.0 /
 // 17.3 / 23.2; two layers and the strided one 10 k / 53 k 40.0 / 51.5 and 37.5 / 50.4).
+// Which tiles a workgroup takes is decided here, by the rows there are (of a coarse map they are known on the device only): a round is a workgroup per
+// compute unit with at most NT tiles each, and as few as give all of them their share.  A workgroup per two tiles, however many there were, came to
+// two for some CUs and one for the others, and to a copy of the weights for every two tiles.  With the loop (resident_loop) the weights are copied once per CU.  us, before and
+// now, sweeps: up-sampling by the transposed map 64 -> 32 53 k / 110 k / 260 k 9.2 / 14.9 / 26.4 and 8.5 / 11.6 / 17.6, 64 -> 64 12.2 / 19.8 / 34.7 and 11.4 / 15.4 /
+// 24.3; from the strided map 128 -> 64 20 k / 80 k / 110 k / 260 k 9.8 / 19.2 / 20.3 / 36.7 and 9.0 / 14.2 / 17.1 / 24.9, 64 -> 64 8.0 / 12.6 / 13.5 / 22.3 and 6.9 / 11.1 /
+// 13.9 / 20.5, 64 -> 32 5.3 / 7.1 / 7.8 / 12.7 and 4.8 / 6.5 / 8.1 / 12.6; layers K = 2, 64 -> 64 20 k / 53 k / 120 k 20.3 / 23.4 / 27.4 and 17.9 / 21.0 / 26.3.
 // FUSED: there is no kernel map; the K^3 neighbours of a row are looked up in the dense location
 // table right here (one index computation and one 8-byte load each, all in flight together), and
 // the group's mask is a vote over what was found.  n_out_cap is then the number of rows.
@@ -55,29 +61,36 @@ k_weight_pack(const uint16_t* __restrict__ w, uint4* __restrict__ wp, int K3, in
 // coarse rows, read in place; entry k of a row's table column names the fine row that receives
 // row . W[k].  Every fine row has exactly one parent, so results are stored, not accumulated, and
 // nothing needs to be transposed first.
+// Round after round in one workgroup, or every workgroup one: the loop pays from 32 KB of weights on (K = 2 32 -> 32, 16 KB, 200 k inputs 27.8 us with it, 26.9
+// without), and with 27 gathers in flight its registers are too many (sweep 53 k 37 with it, 23.3 without).
+constexpr bool resident_loop(int K3, int KS, int CB, int UP) { return (K3 < 27 || UP) && K3 * KS * CB >= 32; }
 template <int DT, int K3, int KS, int CB, int NT, int FUSED, int UP = 0, int WPACKED = 0>
 __global__ void __launch_bounds__(256 * NT)
 k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw, void* __restrict__ out, int out_f32,
-              const MapSource ms, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
+              const MapSource ms, int team, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
     static_assert(K3 <= 32, "one mask word per group");
     static_assert(!FUSED || K3 == 27, "fused look-ups: 3x3x3 layers");
     static_assert(!(FUSED && UP), "one or the other");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
     constexpr int C_in = KS * 32, C_out = CB * 16;
+    constexpr bool LOOP = resident_loop(K3, KS, CB, UP);
     extern __shared__ __align__(16) uint4 w_lds[];                   // [K3][CB][KS][64]
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int r = lane & 15, qq = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int q = wv & 3;
     SC_MARK(0);
     const int64_t n_out = FUSED ? n_out_cap : output_rows(n_out_ptr, n_out_cap);
-    // the grid covers the caller's row capacity; the rows that exist are spread over all XCDs and
-    // a workgroup that gets none leaves at once (the whole workgroup, before any barrier)
-    const int64_t unit = xcd_unit_of(blockIdx.x, (n_out + NT * TILE - 1) / (NT * TILE));
-    if (unit < 0) return;
-    const int64_t tile = unit * NT + (wv >> 2);
-    const int64_t row = tile * TILE + q * 16 + r;
-    const bool group_ok = tile * TILE + q * 16 < n_out;             // uniform per wavefront
+    // an XCD's workgroups share a contiguous eighth of the tiles, so that neighbours meet in its L2
+    const int tiles = (int)((n_out + TILE - 1) / TILE), eighth = (tiles + NUM_XCD - 1) / NUM_XCD;
+    const int first = (int)(blockIdx.x % NUM_XCD) * eighth, share = tiles - first < eighth ? tiles - first : eighth;
+    const int turn = (int)(blockIdx.x / NUM_XCD);
+    // tiles per workgroup of the round that starts with `done` of the share
+    auto per_workgroup = [&](int done) -> int {
+        const int each = (share - done + team - 1) / team;
+        return each < NT ? each : NT;
+    };
+    int done = 0, each = share > 0 ? per_workgroup(0) : 0;
+    if (turn * each >= share) return;                  // no tile: the whole workgroup, before any barrier
 
     // packed weights land in LDS beside everything up to the gathers, which wait for the lines behind them
     constexpr bool DIRECT = WPACKED && K3 * CB * KS <= 64;
@@ -85,135 +98,150 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
         const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)w_lds;
 #pragma unroll
         for (int i = 0; i < (K3 * CB * KS + 4 * NT - 1) / (4 * NT); ++i) {
-            const int t = __builtin_amdgcn_readfirstlane(wv) + i * 4 * NT;
-            if (t < K3 * CB * KS) load_to_lds(wraw + t * 64 + lane, base + t * 1024);
+            const int t = wv + i * 4 * NT;
+            if (t < K3 * CB * KS) load_to_lds(wraw + t * 64 + (threadIdx.x & 63), base + t * 1024);
         }
     }
-    // the group's offset-table lines (all K3 of them) and its mask word: one round trip
-    int32_t e[K3];
-    uint32_t m = 0;
-    if constexpr (FUSED) {
-        // the four lanes that serve a row look up every fourth offset each and trade the results
-        // through LDS (a wavefront's LDS operations execute in order: no barrier needed)
-        __shared__ int32_t found_s[FUSED ? 4 * NT : 1][28][16];
-        if (group_ok) {
-            int32_t part[7];
-            grid_neighbours_part<3, 4>(ms, row, n_out, qq, part);
+#pragma unroll 1
+    for (;;) {
+        // what depends on the lane is made anew for each round: kept over the rounds it costs the registers that the gathers need
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int r = lane & 15, qq = lane >> 4;
+        const int at = done + turn * each + (wv >> 2);
+        const bool mine = (wv >> 2) < each && at < share;
+        const int64_t tile = mine ? first + at : 0;
+        const int64_t row = tile * TILE + q * 16 + r;
+        const bool group_ok = mine && tile * TILE + q * 16 < n_out;     // uniform per wavefront
+
+        // the group's offset-table lines (all K3 of them) and its mask word: one round trip
+        int32_t e[K3];
+        uint32_t m = 0;
+        if constexpr (FUSED) {
+            // the four lanes that serve a row look up every fourth offset each and trade the results
+            // through LDS (a wavefront's LDS operations execute in order: no barrier needed)
+            __shared__ int32_t found_s[FUSED ? 4 * NT : 1][28][16];
+            if (group_ok) {
+                int32_t part[7];
+                grid_neighbours_part<3, 4>(ms, row, n_out, qq, part);
 #pragma unroll
-            for (int u = 0; u < 7; ++u) found_s[wv][qq + 4 * u][r] = part[u];
+                for (int u = 0; u < 7; ++u) found_s[wv][qq + 4 * u][r] = part[u];
 #pragma unroll
-            for (int k = 0; k < K3; ++k) e[k] = found_s[wv][k][r];
+                for (int k = 0; k < K3; ++k) e[k] = found_s[wv][k][r];
 #pragma unroll
-            for (int k = 0; k < K3; ++k) m |= (__ballot(e[k] >= 0) != 0ull ? 1u : 0u) << k;
+                for (int k = 0; k < K3; ++k) m |= (__ballot(e[k] >= 0) != 0ull ? 1u : 0u) << k;
+            } else {
+#pragma unroll
+                for (int k = 0; k < K3; ++k) e[k] = -1;
+            }
+        } else if (group_ok) {
+            const int32_t* line = nbr + tile * (int64_t)(K3 * TILE) + q * 16 + r;
+#pragma unroll
+            for (int k = 0; k < K3; ++k) e[k] = line[k * TILE];
+            if (gmask != nullptr) {
+                m = gmask[tile * 4 + q];
+            } else {
+                m = __builtin_amdgcn_readfirstlane(mask_of_entries(e));
+            }
         } else {
 #pragma unroll
             for (int k = 0; k < K3; ++k) e[k] = -1;
         }
-    } else if (group_ok) {
-        const int32_t* line = nbr + tile * (int64_t)(K3 * TILE) + q * 16 + r;
+        // weights -> LDS as operand tiles (every thread helps, also wavefronts without rows): a thread reads four output
+        // channels of 8 input channels (8-byte loads) and writes four lanes' 16 bytes.  With a thread per lane, 2-byte loads, they were
+        // four times as many loads of 17 cycles each (us: up-sampling from the strided map 64 -> 32 53 k 6.1 -> 5.4, 64 -> 64 200 k 22.8 ->
+        // 20.8, 128 -> 64 53 k 12.8 -> 11.4; layers K = 2 64 -> 64 200 k 40.7 -> 38.6, fused 32 -> 32 53 k 15.1 -> 14.8)
+        if (done == 0) {
+            if constexpr (DIRECT) {
+                __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0)
+            } else if constexpr (WPACKED) {
+                // the caller packed the weights once (sc_conv_weight_pack): the tiles are copied as they are
+                for (int i = threadIdx.x; i < K3 * CB * KS * 64; i += 256 * NT) w_lds[i] = wraw[i];
+            } else {
+                const uint16_t* w16 = reinterpret_cast<const uint16_t*>(wraw);
+                for (int i = threadIdx.x; i < K3 * CB * KS * 16; i += 256 * NT) {
+                    const int col = (i & 3) * 4, oct = (i >> 2) & 3;
+                    int rest = i >> 4;
+                    const int ks = rest % KS; rest /= KS;
+                    const int cb = rest % CB;
+                    const int k = rest / CB;
+                    const uint16_t* src = w16 + ((int64_t)k * C_in + ks * 32 + 8 * oct) * C_out + cb * 16 + col;
+                    uint2 v[8];
 #pragma unroll
-        for (int k = 0; k < K3; ++k) e[k] = line[k * TILE];
-        if (gmask != nullptr) {
-            m = gmask[tile * 4 + q];
-        } else {
-            m = __builtin_amdgcn_readfirstlane(mask_of_entries(e));
-        }
-    } else {
+                    for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const uint2*>(src + j * C_out);
+                    uint4* dst = w_lds + ((k * CB + cb) * KS + ks) * 64 + oct * 16 + col;
 #pragma unroll
-        for (int k = 0; k < K3; ++k) e[k] = -1;
-    }
-    // weights -> LDS as operand tiles (every thread helps, also wavefronts without rows): a thread reads four output
-    // channels of 8 input channels (8-byte loads) and writes four lanes' 16 bytes.  With a thread per lane, 2-byte loads, they were
-    // four times as many loads of 17 cycles each (us: up-sampling from the strided map 64 -> 32 53 k 6.1 -> 5.4, 64 -> 64 200 k 22.8 ->
-    // 20.8, 128 -> 64 53 k 12.8 -> 11.4; layers K = 2 64 -> 64 200 k 40.7 -> 38.6, fused 32 -> 32 53 k 15.1 -> 14.8)
-    if constexpr (DIRECT) {
-        __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0)
-    } else if constexpr (WPACKED) {
-        // the caller packed the weights once (sc_conv_weight_pack): the tiles are copied as they are
-        for (int i = threadIdx.x; i < K3 * CB * KS * 64; i += 256 * NT) w_lds[i] = wraw[i];
-    } else {
-        const uint16_t* w16 = reinterpret_cast<const uint16_t*>(wraw);
-        for (int i = threadIdx.x; i < K3 * CB * KS * 16; i += 256 * NT) {
-            const int col = (i & 3) * 4, oct = (i >> 2) & 3;
-            int rest = i >> 4;
-            const int ks = rest % KS; rest /= KS;
-            const int cb = rest % CB;
-            const int k = rest / CB;
-            const uint16_t* src = w16 + ((int64_t)k * C_in + ks * 32 + 8 * oct) * C_out + cb * 16 + col;
-            uint2 v[8];
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t take = (c & 1) ? 0x07060302u : 0x05040100u;     // the upper or the lower halves of two words
+                        uint32_t o[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const uint2*>(src + j * C_out);
-            uint4* dst = w_lds + ((k * CB + cb) * KS + ks) * 64 + oct * 16 + col;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t take = (c & 1) ? 0x07060302u : 0x05040100u;     // the upper or the lower halves of two words
-                uint32_t o[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    o[j] = c < 2 ? __builtin_amdgcn_perm(v[2 * j + 1].x, v[2 * j].x, take) : __builtin_amdgcn_perm(v[2 * j + 1].y, v[2 * j].y, take);
-                dst[c] = make_uint4(o[0], o[1], o[2], o[3]);
-            }
-        }
-    }
-    SC_MARK(1);
-    m = __builtin_amdgcn_readfirstlane(m);
-
-    if constexpr (UP) {
-        uint4 own[KS];                       // the coarse row itself: no gather
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            own[ks] = (group_ok && row < n_out) ? reinterpret_cast<const uint4*>(feat + row * C_in)[qq + ks * 4]
-                                                : make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        SC_MARK(2);
-#pragma unroll
-        for (int k = 0; k < K3; ++k) {
-            if (m & (1u << k)) {
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    f32x4 d = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-                        d = mfma16x16x32<DT>(w_lds[((k * CB + cb) * KS + ks) * 64 + lane], own[ks], d);
-                    if (e[k] >= 0) store_acc<DT>(out, out_f32, e[k], C_out, cb * 16 + qq * 4, d);
+                        for (int j = 0; j < 4; ++j)
+                            o[j] = c < 2 ? __builtin_amdgcn_perm(v[2 * j + 1].x, v[2 * j].x, take) : __builtin_amdgcn_perm(v[2 * j + 1].y, v[2 * j].y, take);
+                        dst[c] = make_uint4(o[0], o[1], o[2], o[3]);
+                    }
                 }
             }
         }
-        SC_MARK(3);
-        SC_MARK(4);
-        SC_MARK(5);
-        return;
-    }
-    // every gather of the group in flight at once
-    uint4 fb[K3][KS];
-#pragma unroll
-    for (int k = 0; k < K3; ++k) {
-        if (m & (1u << k)) {
-            const uint4* frow = reinterpret_cast<const uint4*>(feat + (int64_t)(e[k] < 0 ? 0 : e[k]) * C_in) + qq;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) fb[k][ks] = e[k] >= 0 ? frow[ks * 4] : make_uint4(0, 0, 0, 0);
-        }
-    }
-    __syncthreads();
-    SC_MARK(2);
+        SC_MARK(1);
+        m = __builtin_amdgcn_readfirstlane(m);
 
-    f32x4 acc[CB];
+        if constexpr (UP) {
+            uint4 own[KS];                       // the coarse row itself: no gather
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < KS; ++ks)
+                own[ks] = (group_ok && row < n_out) ? reinterpret_cast<const uint4*>(feat + row * C_in)[qq + ks * 4]
+                                                    : make_uint4(0, 0, 0, 0);
+            if (done == 0) __syncthreads();
+            SC_MARK(2);
 #pragma unroll
-    for (int k = 0; k < K3; ++k) {
-        if (m & (1u << k)) {
+            for (int k = 0; k < K3; ++k) {
+                if (m & (1u << k)) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+                    for (int cb = 0; cb < CB; ++cb) {
+                        f32x4 d = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    acc[cb] = mfma16x16x32<DT>(w_lds[((k * CB + cb) * KS + ks) * 64 + lane], fb[k][ks], acc[cb]);
+                        for (int ks = 0; ks < KS; ++ks)
+                            d = mfma16x16x32<DT>(w_lds[((k * CB + cb) * KS + ks) * 64 + lane], own[ks], d);
+                        if (e[k] >= 0) store_acc<DT>(out, out_f32, e[k], C_out, cb * 16 + qq * 4, d);
+                    }
+                }
+            }
+        } else {
+            // every gather of the group in flight at once
+            uint4 fb[K3][KS];
+#pragma unroll
+            for (int k = 0; k < K3; ++k) {
+                if (m & (1u << k)) {
+                    const uint4* frow = reinterpret_cast<const uint4*>(feat + (int64_t)(e[k] < 0 ? 0 : e[k]) * C_in) + qq;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) fb[k][ks] = e[k] >= 0 ? frow[ks * 4] : make_uint4(0, 0, 0, 0);
+                }
+            }
+            if (done == 0) __syncthreads();
+            SC_MARK(2);
+
+            f32x4 acc[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < K3; ++k) {
+                if (m & (1u << k)) {
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int ks = 0; ks < KS; ++ks)
+                            acc[cb] = mfma16x16x32<DT>(w_lds[((k * CB + cb) * KS + ks) * 64 + lane], fb[k][ks], acc[cb]);
+                }
+            }
+            SC_MARK(3);
+            if (group_ok && row < n_out) {
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) store_acc<DT>(out, out_f32, row, C_out, cb * 16 + qq * 4, acc[cb]);
+            }
         }
-    }
-    SC_MARK(3);
-    if (group_ok && row < n_out) {
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) store_acc<DT>(out, out_f32, row, C_out, cb * 16 + qq * 4, acc[cb]);
+        done += team * each;
+        if (!LOOP || done >= share) break;
+        each = per_workgroup(done);
     }
     SC_MARK(4);
     SC_MARK(5);
@@ -638,8 +666,11 @@ static int launch_rows16(int64_t tiles, hipStream_t s, const uint16_t* feat, con
     const size_t lds = (size_t)K3 * CB * KS * 64 * sizeof(uint4);
     static bool allowed[MAX_DEVICES] = {};  // per instantiation
     if (int rc = allow_lds((const void*)fn, lds, allowed)) return rc;
-    const dim3 grid(xcd_grid((tiles + NT - 1) / NT));
-    SC_LAUNCH(KID_CONV_MFMA, fn, grid, dim3(256 * NT), lds, s, feat, wp, out, out_f32, ms, counts, n_out_cap);
+    // workgroups per XCD and round: one per compute unit; without the loop as many as there are at NT tiles each
+    const int team = (compute_units() + NUM_XCD - 1) / NUM_XCD;
+    const int64_t share = (tiles + NUM_XCD - 1) / NUM_XCD, all = resident_loop(K3, KS, CB, UP) ? 0 : (share + NT - 1) / NT;
+    const int64_t most = all > team ? all : team, turns = share < most ? share : most;
+    SC_LAUNCH(KID_CONV_MFMA, fn, dim3((unsigned)(turns * NUM_XCD)), dim3(256 * NT), lds, s, feat, wp, out, out_f32, ms, team, counts, n_out_cap);
     return SC_OK;
 }
 
@@ -657,20 +688,20 @@ static int launch_resident(int K3, int C_in, int C_out, int64_t tiles, int64_t l
                            const uint4* wp, void* out, int out_f32, const MapSource& ms, const int64_t* counts,
                            int64_t n_out_cap, bool* handled) {
     *handled = true;
+    const int64_t cus = compute_units();
 #define SC_ROWS16(K3V, KSV, CBV, NTV) \
     return launch_rows16<DT, K3V, KSV, CBV, NTV, FUSED, 0, WPACKED>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
-    // four tiles per workgroup once the likely tiles still give two CUs one: half the copies of the weights, and no CU with
-    // two workgroups while another has one (us of whole layers on sweeps, two and four tiles: raw weights 16 k / 30 k / 34 k / 53 k 15.5 / 18.1 / 20.3 /
-    // 24.5 and 17.4 / 19.8 / 20.1 / 23.8, packed 16.0 / 18.7 / 19.9 / 24.0 and 16.8 / 19.2 / 19.8 / 23.5, fused 10.7 / 11.8 / 14.2 / 15.4 and 13.0 / 13.9 / 13.9 / 14.8; indoor
-    // sets cross at 34 k too).  The likely ones: by the bound, 512 tiles or more, strided layers of 10 k / 20 k / 30 k voxels took four and left
-    // most CUs idle (convolution 7.5 / 8.0 / 8.3, now 6.0 / 7.1 / 7.5).
-    if (K3 == 27 && C_in == 32 && C_out == 32 && likely >= 512) SC_ROWS16(27, 1, 2, 4);
+    // 3x3x3: up to four tiles per workgroup where that is one workgroup per CU for the likely tiles, and two where two do that or there are more than one
+    // round of four: with 16 wavefronts of 124 registers a CU has no second workgroup to go on with (us of whole layers, four and two tiles, sweeps: packed
+    // 36 k / 48 k / 53 k / 60 k 19.4 / 20.8 / 23.4 / 25.0 and 20.4 / 21.7 / 23.6 / 25.2, 70 k / 80 k / 110 k / 130 k 30.2 / 31.8 / 38.2 / 42.0 and 28.3 / 29.7 / 37.2 / 40.9; fused 36 k / 53 k 12.7 / 14.8
+    // and 14.3 / 15.5, 80 k / 200 k 23.4 / 51.0 and 20.5 / 46.0; indoor 80 k 34.4 and 30.1).  The likely ones: the bound of a strided layer is up to eight times what there is.
+    if (K3 == 27 && C_in == 32 && C_out == 32 && likely > 2 * cus && likely <= 4 * cus) SC_ROWS16(27, 1, 2, 4);
     if (K3 == 27 && C_in == 32 && C_out == 32) SC_ROWS16(27, 1, 2, 2);
     if constexpr (!FUSED) {
-        if (K3 == 8 && C_in == 32 && C_out == 64) SC_ROWS16(8, 1, 4, 2);
+        if (K3 == 8 && C_in == 32 && C_out == 64) SC_ROWS16(8, 1, 4, 4);
         if (K3 == 8 && C_in == 32 && C_out == 32) SC_ROWS16(8, 1, 2, 2);
-        if (K3 == 8 && C_in == 64 && C_out == 64) SC_ROWS16(8, 2, 4, 2);
-        if (K3 == 8 && C_in == 64 && C_out == 32) SC_ROWS16(8, 2, 2, 2);      // the up-sampling twin of 32 -> 64
+        if (K3 == 8 && C_in == 64 && C_out == 64) SC_ROWS16(8, 2, 4, 4);
+        if (K3 == 8 && C_in == 64 && C_out == 32) SC_ROWS16(8, 2, 2, 4);      // the up-sampling twin of 32 -> 64
     }
 #undef SC_ROWS16
     *handled = false;
@@ -708,13 +739,13 @@ static int launch_up(int K3, int C_in, int C_out, int64_t tiles, hipStream_t s, 
                      void* out, int out_f32, const MapSource& ms, const int64_t* counts, int64_t n_out_cap,
                      bool* handled) {
     *handled = true;
-#define SC_UP16(K3V, KSV, CBV) \
-    return launch_rows16<DT, K3V, KSV, CBV, 2, 0, 1>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
-    if (K3 == 8 && C_in == 64 && C_out == 32) SC_UP16(8, 2, 2);
-    if (K3 == 8 && C_in == 32 && C_out == 32) SC_UP16(8, 1, 2);
-    if (K3 == 8 && C_in == 64 && C_out == 64) SC_UP16(8, 2, 4);
-    if (K3 == 8 && C_in == 128 && C_out == 64) SC_UP16(8, 4, 4);
-    if (K3 == 27 && C_in == 32 && C_out == 32) SC_UP16(27, 1, 2);
+#define SC_UP16(K3V, KSV, CBV, NTV) \
+    return launch_rows16<DT, K3V, KSV, CBV, NTV, 0, 1>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
+    if (K3 == 8 && C_in == 64 && C_out == 32) SC_UP16(8, 2, 2, 4);
+    if (K3 == 8 && C_in == 32 && C_out == 32) SC_UP16(8, 1, 2, 2);
+    if (K3 == 8 && C_in == 64 && C_out == 64) SC_UP16(8, 2, 4, 4);
+    if (K3 == 8 && C_in == 128 && C_out == 64) SC_UP16(8, 4, 4, 4);
+    if (K3 == 27 && C_in == 32 && C_out == 32) SC_UP16(27, 1, 2, 4);
 #undef SC_UP16
     *handled = false;
     return SC_OK;

@@ -691,3 +691,70 @@ def test_two_sets_of_wavefronts(C_in, C_out, n):
             (buf.layer if dims is None else buf.layer_fused)(c, f, w)
             outs.append(buf.feat_out)
         assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("way,K,C_in,C_out", [("down", 2, 32, 32), ("down", 2, 32, 64), ("down", 2, 64, 64), ("up", 2, 64, 32), ("up", 2, 128, 64), ("up", 3, 32, 32),
+                                              ("transposed", 2, 64, 32), ("transposed", 2, 64, 64)])
+@pytest.mark.parametrize("n", [1, 64 * 8 + 1, 64 * 256 - 15, 64 * 256 + 1, 64 * 768 + 16, 64 * 1024 + 1, 64 * 1280 + 49, 64 * 2048 + 17])
+def test_resident_kernels_deal_their_tiles(way, K, C_in, C_out, n):
+    """Less than a tile per workgroup, one to four, and further rounds with fewer: one input per coarse cell, so that input and
+    output rows are the same and a row is its input times the weights of its one offset."""
+    say(f"resident kernel {way} K={K} {C_in}->{C_out} n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    i, k = np.arange(n), np.arange(n) % K ** 3
+    cells = np.stack([i % 50, i // 50 % 50, i // 2500], axis=1)
+    xyz = cells * K + np.stack([k // (K * K), k // K % K, k % K], axis=1)
+    coords = torch.from_numpy(np.concatenate([np.zeros((n, 1), dtype=np.int64), xyz], axis=1).astype(np.int32)).to("cuda:0")
+    f = torch.from_numpy(synth.features(n, C_in, "f16", n)).to("cuda:0").half()
+    w = torch.from_numpy(synth.weights(K ** 3, C_in, C_out, "f16", n)).to("cuda:0").half()
+    want = torch.empty((n, C_out), dtype=torch.float64, device="cuda:0")
+    for o in range(K ** 3):
+        want[o::K ** 3] = f[o::K ** 3].double() @ w[o].double()
+    down = sc.LayerBuffers(n, K, K, "strided", C_in, C_out, "f16", "f32", device="cuda:0")
+    down.kmap_build(coords, standalone=True)
+    outs = []
+    if way == "down":
+        for packed in (False, True):
+            down.feat_out.fill_(float("nan"))
+            (down.conv_fwd_packed if packed else down.conv_fwd)(f, sc.sc_conv_weight_pack(w, K) if packed else w)
+            outs.append(down.feat_out[:n].clone())
+    else:
+        out = torch.full((n, C_out), float("nan"), dtype=torch.float32, device="cuda:0")
+        if way == "up":
+            sc.sc_conv_up_fwd(f, n, w, out, down.kmap, down.counts, K)
+        else:
+            inverse = torch.empty(sc.sc_kmap_bytes(n, K, K, "inverse"), dtype=torch.uint8, device="cuda:0")
+            workspace = torch.empty(sc.sc_conv_workspace_bytes(K, C_in, C_out, "f16"), dtype=torch.uint8, device="cuda:0")
+            sc.sc_kmap_transpose(down.kmap, n, K, K, down.counts, inverse)
+            sc.sc_conv_fwd(f, w, out, inverse, down.counts, K, K, "inverse", workspace, n_map=n)
+        outs.append(out)
+    for got in outs:            # sums of up to 128 products in 32 bits
+        assert float((got.double() - want).abs().max() / want.abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("n", [64 * 256, 64 * 256 + 1, 64 * 512, 64 * 512 + 1, 64 * 768 + 33, 64 * 1024, 64 * 1024 + 1])
+def test_resident_3x3x3_kernel_deals_its_tiles(n):
+    """Both numbers of tiles per workgroup at their ends, packed and raw weights and the fused form: the same bits, as the oracle has them."""
+    say(f"resident kernel 3x3x3 n={n}")
+    import torch
+    import oracle
+    from paper_2402_07710_amd import binding as sc
+    from tests.test_gpu_parity import rel_err, sampled_rows_reference
+    scenes = [synth.lidar_scene(s) for s in range(-(-n // 50000))]
+    for b, scene in enumerate(scenes):
+        scene[:, 0] = b
+    coords = np.ascontiguousarray(np.concatenate(scenes)[:n])
+    feat, weight = synth.features(n, 32, "bf16", 3), synth.weights(27, 32, 32, "bf16", 3)
+    c, f, w = torch.from_numpy(coords).to("cuda:0"), torch.from_numpy(feat).to("cuda:0").bfloat16(), torch.from_numpy(weight).to("cuda:0").bfloat16()
+    buf = sc.LayerBuffers(n, 3, 1, "subm", 32, 32, "bf16", "f32", device="cuda:0", grid_dims=(len(scenes), 1408, 1600, 41))
+    outs = []
+    for run in (lambda: buf.layer(c, f, w), lambda: buf.conv_fwd_packed(f, sc.sc_conv_weight_pack(w, 3)), lambda: buf.layer_fused(c, f, w)):
+        buf.feat_out.fill_(float("nan"))
+        run()
+        outs.append(buf.feat_out.clone())
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    rng = np.random.default_rng(n)
+    rows = np.unique(np.concatenate([rng.choice(n, 1000, replace=False), np.arange(n - 70, n)]))
+    err = rel_err(outs[0].double().cpu().numpy()[rows], sampled_rows_reference(feat, weight, oracle.kmap(coords, 3, 1, "subm"), rows)[rows])
+    assert err <= 1e-5, err
