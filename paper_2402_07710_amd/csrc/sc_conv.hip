@@ -792,14 +792,12 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     const uint16_t* feat = (const uint16_t*)d_feat_in;
     bool handled = false;
     int rc;
-    // From 9 tiles per CU the general kernel takes the square layers: by then the CUs run its workgroups in several rounds,
-    // one tile each, while the resident kernel's large workgroups end unevenly.  Packed weights only: raw ones would need a launch to pack
-    // them (us, resident and general kernel: 32 -> 32, K = 3: lidar 110 k 15.9 / 15.8, 131 k 16.3 / 17.7, 150 k 20.6 / 19.7, 200 k
-    // 24.8 / 24.2, indoor 200 k 34.7 / 31.1, 400 k 59.1 / 54.1, 800 k 108 / 104, strided 300 k 45.2 / 44.7; 64 -> 64, K = 2: 110 k
-    // 9.8 / 9.75, 150 k 15.0 / 11.6, 200 k 16.9 / 14.1, indoor 400 k 20.9 / 19.2, 500 k 27.8 / 21.1.  The other K = 2 shapes stay:
-    // 32 -> 32 200 k 6.3 / 8.1, 32 -> 64 9.7 / 12.3, indoor 500 k 16.0 / 17.05).
-    const bool outgrown = packed && !FUSED && likely > 9 * (int64_t)compute_units() &&
-                          ((K3 == 27 && C_in == 32 && C_out == 32) || (K3 == 8 && C_in == 64 && C_out == 64));
+    // Packed 64 -> 64 layers, K = 2, from 9 to 12 tiles per CU through the general kernel: their rows are a few more than the resident kernel's first round (us of whole
+    // layers, stride 2, general and resident, sweeps 110 k / 150 k / 160 k / 175 k / 190 k / 200 k / 300 k 26.9 / 29.6 / 30.2 / 31.7 / 33.3 / 34.0 / 50.1 and 25.9 / 30.7 / 31.1 / 32.1 / 33.4 /
+    // 33.7 / 46.9; indoor 150 k / 175 k / 400 k / 800 k 25.9 / 27.8 / 52.2 / 86.0 and 26.1 / 27.9 / 48.5 / 81.3).  32 -> 32, K = 3, is ahead on the resident kernel at every
+    // size (150 k / 200 k / 400 k 46.7 / 61.9 / 124.0 and 45.2 / 60.2 / 121.2, indoor 50.2 / 62.3 / 124.3 and 46.5 / 59.9 / 116.9).
+    const int64_t cus = compute_units();
+    const bool outgrown = packed && !FUSED && K3 == 8 && C_in == 64 && C_out == 64 && likely > 9 * cus && likely <= 12 * cus;
     if (resident_shape(K3, C_in, C_out, FUSED) && !outgrown) {
         if (packed)
             rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,

@@ -547,7 +547,8 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
     } else {
         if constexpr (SRC != FROM_TABLE) {
             if (CB == 1) SC_GATHER(4, 4, 1, O1);
-            if (CB == 2) SC_GATHER(4, 2, 1, O1);
+            if constexpr (KS > 1 || SRC != FROM_LINES)        // K = 2 and 3, 32 -> 32 are the resident kernel's
+                if (CB == 2) SC_GATHER(4, 2, 1, O1);
         }
         // two output blocks per wavefront halve how often a tile's rows are gathered; one, where that leaves CUs
         // idle or, up to 128 channels either way, with few wavefronts (us with one and with two blocks: 256 -> 128 at
@@ -570,7 +571,7 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
 template <int DT, int KS, int SL, int SKIP, int O1, int SRC>
 static int launch_gather_sets(int K3, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out, int out_f32,
                               const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-    if constexpr (SRC != FROM_TABLE) {
+    if constexpr (SRC != FROM_TABLE && KS > 1) {
         if (CB == 2) return launch_gather_as<DT, KS, SL, SKIP, 4, 2, 1, O1, SRC, 2>(K3, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
     }
     return launch_gather_as<DT, KS, SL, SKIP, 4, 1, 1, O1, SRC, 2>(K3, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);

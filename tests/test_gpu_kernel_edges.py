@@ -93,8 +93,8 @@ def test_streaming_kernel_32_to_64_channels(stride, n):
 @pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457),
                                           (3, 2, 32, 32_640), (3, 2, 32, 32_705)])
 def test_packed_square_layers_beyond_the_resident_kernel(K, stride, C, n):
-    """Packed weights, the fewest tiles (9 per CU of 256, one row more) that go through the general kernel; strided
-    layers at 510 and 512 likely tiles, where the resident kernel takes two and four tiles per workgroup."""
+    """Packed weights, the fewest tiles (9 per CU of 256, one row more) that go through the general kernel (64 -> 64); strided
+    layers at 510 and 512 likely tiles."""
     say(f"packed K={K} s={stride} {C}->{C} n={n}")
     import oracle
     import torch
@@ -119,7 +119,7 @@ def test_packed_square_layers_beyond_the_resident_kernel(K, stride, C, n):
 @pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_packed_and_raw_weights_agree_bit_for_bit_across_kernels(K, stride, C, n, dtype):
-    """From 9 tiles per CU (of 256) packed weights take the general kernel and raw ones the resident kernel."""
+    """From 9 to 12 tiles per CU (of 256) packed weights of 64 -> 64 layers take the general kernel and raw ones the resident kernel."""
     say(f"packed and raw K={K} s={stride} {C}->{C} {dtype} n={n}")
     import torch
     from paper_2402_07710_amd import binding as sc
