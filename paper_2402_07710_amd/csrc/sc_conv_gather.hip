@@ -66,7 +66,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
               int blocks_y, int64_t tiles_apart, const int64_t* __restrict__ n_out_ptr, int64_t n_out_cap) {
     constexpr bool FUSED = SRC == FROM_TABLE, HELD = FUSED || SRC == FROM_LINES, POINT = SRC == FROM_LINE, REGS = SRC == FROM_MAP_BY_REGISTERS;      // HELD: the tile's entries are in LDS
     static_assert(!HELD || (DT != SC_F32 && NW == 4), "a quarter of the 27 offsets per wavefront");
-    static_assert(HV == 1 || (HV == 2 && HELD), "two sets of wavefronts: layers with the lines in LDS");
+    static_assert(HV == 1 || (HV == 2 && DT != SC_F32 && !POINT && !REGS), "two sets of wavefronts: 16 bit, a list of offsets in LDS");
     const uint32_t* __restrict__ gmask = ms.gmask;
     const int32_t* __restrict__ nbr = ms.nbr;
     constexpr bool F32 = DT == SC_F32;
@@ -569,12 +569,12 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
 
 // Two sets of wavefronts (two_sets), one output block per wavefront.
 template <int DT, int KS, int SL, int SKIP, int O1, int SRC>
-static int launch_gather_sets(int K3, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out, int out_f32,
+static int launch_gather_sets(int K3, int mw, int CB, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp, void* out, int out_f32,
                               const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
-    if constexpr (SRC != FROM_TABLE && KS > 1) {
-        if (CB == 2) return launch_gather_as<DT, KS, SL, SKIP, 4, 2, 1, O1, SRC, 2>(K3, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
+    if constexpr (SRC == FROM_MAP || (SRC == FROM_LINES && KS > 1)) {
+        if (CB == 2) return launch_gather_as<DT, KS, SL, SKIP, 4, 2, 1, O1, SRC, 2>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
     }
-    return launch_gather_as<DT, KS, SL, SKIP, 4, 1, 1, O1, SRC, 2>(K3, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
+    return launch_gather_as<DT, KS, SL, SKIP, 4, 1, 1, O1, SRC, 2>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
 }
 
 int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat,
@@ -584,10 +584,10 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
     // with more workgroups: 128 -> 64 at 53 k voxels 36.7 us instead of 28.8).  64: an offset; two for K = 5 and 7, whose
     // tiles walk many more offsets (K = 3 -> 64 at 262 k voxels 50.3 us with one, 56.5 with two; K = 5 -> 64 at 53 k 55.1
     // and 50.7).  32: four (K = 5 -> 32 at 53 k: 30.4 us; two 32.1, eight with half the workgroups 36).
-#define SC_GATHER_SETS(KS, SL, SKIP, O1)                                                                                                      \
+#define SC_GATHER_SETS(KS, SL, SKIP, O1, SRC)                                                                                                      \
     return dtype_in == SC_F16                                                                                                     \
-               ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, FROM_LINES>(K3, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
-               : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, FROM_LINES>(K3, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+               ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, SRC>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
+               : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, SRC>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
 #define SC_GATHER_KS(KS, SL, SKIP, O1, O2, SRC)                                                                                      \
     return dtype_in == SC_F16                                                                                                     \
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
@@ -617,11 +617,18 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
         return SC_EINVAL;
     }
     const bool few = few_workgroups(likely, CB, cus);
-    if (K3 <= 27 && two_sets(likely, CB, C_in, cus)) {
+    if (two_sets(likely, K3, CB, C_in, cus)) {
+        if (K3 <= 27) {
+            switch (C_in) {
+                case 32: SC_GATHER_SETS(1, 2, 1, 4, FROM_LINES);
+                case 64: SC_GATHER_SETS(2, 2, 1, 6, FROM_LINES);
+                case 128: SC_GATHER_SETS(4, 4, 1, 4, FROM_LINES);
+            }
+        }
         switch (C_in) {
-            case 32: SC_GATHER_SETS(1, 2, 1, 4);
-            case 64: SC_GATHER_SETS(2, 2, 1, 6);
-            case 128: SC_GATHER_SETS(4, 4, 1, 4);
+            case 32: SC_GATHER_SETS(1, 4, 0, 2, FROM_MAP);
+            case 64: SC_GATHER_SETS(2, 4, 1, 4, FROM_MAP);
+            case 128: SC_GATHER_SETS(4, 4, 1, 4, FROM_MAP);
         }
     }
     if (K3 <= 27) {
@@ -657,9 +664,9 @@ int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cu
                ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
                : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
 #define SC_GATHER_FUSED_SETS(KS, SL, SKIP, O1)                                                                                                    \
-    return dtype_in == SC_F16 ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, FROM_TABLE>(27, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
-                              : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, FROM_TABLE>(27, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
-    if (two_sets(tiles, CB, C_in, cus)) {
+    return dtype_in == SC_F16 ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, FROM_TABLE>(27, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
+                              : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, FROM_TABLE>(27, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+    if (two_sets(tiles, 27, CB, C_in, cus)) {
         if (C_in == 32) SC_GATHER_FUSED_SETS(1, 2, 1, 4);
         if (C_in == 64) SC_GATHER_FUSED_SETS(2, 2, 1, 6);
         if (C_in == 128) SC_GATHER_FUSED_SETS(4, 4, 1, 4);

@@ -67,15 +67,20 @@ constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t c
 // 18 k / 26 k / 30 k 23.0 / 26.7 / 28.2 and 25.5 / 27.2 / 28.3, indoor 25.4 / 30.1 / 31.2 and 25.4 / 28.9 / 30.5.
 constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return likely * ((CB + 3) / 4) <= 3 * cus; }
 
-// The general kernel, K <= 3, 16 bit, up to 128 input channels: two sets of four wavefronts walk alternate offsets of the tile and add up their sums in the end.  Up to
-// two workgroups per CU (32 input channels 1 1/4) a layer takes as long as the workgroup of a dense tile walks its offsets, one wavefront per SIMD, and of 27
+// The general kernel, 16 bit, up to 128 input channels: two sets of four wavefronts walk alternate offsets of the tile and add up their sums in the end.  Up to
+// two workgroups per CU (32 input channels, K <= 3, 1 1/4) a layer takes as long as the workgroup of a dense tile walks its offsets, one wavefront per SIMD, and of 27
 // offsets each set walks 14; beyond, the CUs have enough wavefronts and the sums are traded for nothing.  us of whole layers, one set / two, sweeps: 64 -> 64 500 15.5 /
 // 14.5, 2 k 18.0 / 16.0, 10 k 19.9 / 18.9, 14 k 20.8 / 20.2, 25 k 23.1 / 22.4, 30 k 23.8 / 22.9, 42 k 26.5 / 26.1, 53 k 32.4 / 32.0, 80 k 38.1 / 41.2; indoor 3 k 18.6 / 16.7, 10 k 19.2 / 17.5, 30 k 23.9 / 23.2, 40 k 28.4 /
 // 29.1; stride 2 2 k 26.1 / 23.9, 20 k 30.1 / 29.3; 64 -> 128 5 k 19.3 / 17.6, 20 k 23.6 / 23.1, 40 k 30.3 / 34.3; 128 -> 128 500 18.9 / 17.3, 2 k 23.1 / 20.3, 8 k 27.6 / 24.4, 14 k 29.6 / 25.8, 20 k 31.1 /
 // 31.6, 26 k 32.4 / 35.3; indoor 5 k 26.4 / 23.8, 15 k 29.6 / 30.2; 128 -> 256 1 k 22.4 / 20.0, 8 k 29.1 / 25.3, 12 k 30.4 / 32.9; 128 -> 32 30 k 29.3 / 26.4; 32 -> 64 1 k 15.3 / 14.6, 10 k 16.5 / 16.1, 14 k 17.5 / 17.0, 20 k 18.7 /
 // 18.7, 53 k 26.8 / 30.4.  256 input channels, whose offsets take 64 KB through the L1 of a CU, as fast as that goes, are the same with two sets (1 k 27.8 / 28.0, 14 k 49.1 / 50.8).
-constexpr bool two_sets(int64_t likely, int CB, int C_in, int64_t cus) {
-    return CB > 1 && C_in <= 128 && likely * ((CB + 3) / 4) * 4 <= (C_in == 32 ? 5 : 8) * cus;
+// K > 3, whose walks are longer: two workgroups per CU, sweeps gain up to four and dense sets lose from one and a half (32 input channels) or two on (one set / two,
+// K = 5, sweeps: 32 -> 32 2 k 24.2 / 22.2, 6 k 34.2 / 29.1, 20 k 40.3 / 36.3, 35 k 46.8 / 43.0, 46 k 49.7 / 49.7, 53 k 56.1 / 57.9; 32 -> 64 2 k 27.2 / 23.8, 20 k 41.7 / 37.6, 53 k 58.1 / 60.0; 64 -> 64 2 k
+// 34.0 / 29.1, 12 k 50.9 / 41.5, 35 k 62.6 / 53.4, 53 k 73.0 / 66.7, 75 k 87.3 / 89.8; 128 -> 128 2 k 51.8 / 42.0, 12 k 78.8 / 64.1, 25 k 87.3 / 75.6, 53 k 118.5 / 128.4; 64 -> 32 30 k 59.7 / 48.3;
+// indoor 32 -> 32 5 k 30.5 / 26.8, 20 k 36.8 / 35.8, 30 k 38.8 / 40.0, 36 k 46.1 / 49.8; 64 -> 64 5 k 42.5 / 35.3, 30 k 52.2 / 51.7, 40 k 65.2 / 71.0; 128 -> 128 15 k 70.9 / 71.7, 20 k 87.6 / 94.9; random
+// cells 64 -> 64 5 k 36.5 / 32.0, 20 k 53.4 / 48.1; stride 2 32 -> 64 10 k 59.4 / 53.6, 30 k 84.9 / 86.3; K = 7 64 -> 64 10 k 118 / 94.5, 30 k 138 / 113).
+constexpr bool two_sets(int64_t likely, int K3, int CB, int C_in, int64_t cus) {
+    return CB > 1 && C_in <= 128 && likely * ((CB + 3) / 4) * 4 <= (C_in == 32 && K3 <= 27 ? 5 : 8) * cus;
 }
 
 // The general kernel, 16 bit: a tile's blocks of output channels one after the other on an XCD, whose L2 then holds the tile's rows for the second,

@@ -758,3 +758,15 @@ def test_resident_3x3x3_kernel_deals_its_tiles(n):
     rows = np.unique(np.concatenate([rng.choice(n, 1000, replace=False), np.arange(n - 70, n)]))
     err = rel_err(outs[0].double().cpu().numpy()[rows], sampled_rows_reference(feat, weight, oracle.kmap(coords, 3, 1, "subm"), rows)[rows])
     assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("K,stride,C_in,C_out,n", [(5, 1, 32, 32, 512 * 64), (5, 1, 32, 32, 512 * 64 + 1), (5, 1, 64, 64, 512 * 64 - 1), (5, 1, 128, 128, 256 * 64 + 1), (5, 1, 128, 32, 77),
+                                                   (5, 1, 64, 80, 1000), (7, 1, 32, 48, 300), (7, 1, 64, 32, 65), (4, 2, 32, 64, 3000), (4, 4, 64, 32, 3000), (5, 2, 128, 64, 1)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_two_sets_of_wavefronts_beyond_27_offsets(K, stride, C_in, C_out, n, dtype):
+    """Both sides of the line; lists of one entry to all K^3, odd numbers of steps among them, two wavefronts across the rows, a part-filled block."""
+    say(f"two sets K={K} s={stride} {C_in} -> {C_out}, n={n} {dtype}")
+    side = max(4, int(round((n * (2 if n < 5000 else 8)) ** (1 / 3))))
+    coords = synth.uniform_cells(n, side, seed=C_in)
+    coords = np.ascontiguousarray(coords[np.lexsort((coords[:, 3], coords[:, 2], coords[:, 1]))])
+    check_layer(coords, K, stride, "subm" if stride == 1 else "strided", C_in, C_out, dtype, seed=n, out_dtype="f32", threads=16)
