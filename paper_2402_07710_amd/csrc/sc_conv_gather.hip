@@ -554,13 +554,12 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
         // idle or, up to 128 channels either way, with few wavefronts (us with one and with two blocks: 256 -> 128 at
         // 219 tiles 29.0, 34.2; 256 -> 256 49.1, 44.1; 64 -> 256 at 157 tiles 17.6, 19.3, at 250 22.9, 20.9; 128 -> 128 at
         // 625 tiles 36.0, 38.2, at 4,088 132, 127.5; 64 -> 128 at 469 tiles 20.2, 21.4, at 834 26.9, 26.7; and with 256 input
-        // channels, whose step is the longest, up to four workgroups of one block per CU: sweeps gain there, dense sets cross at three already, and
-        // how dense a set is is not known here (map and convolution, one and two blocks, means of eight sweeps and of eight indoor sets: 256 -> 256 at 172
-        // tiles 42.0, 47.1 and 56.4, 52.9, at 193 44.0, 48.8 and 57.6, 53.4, at 219 49.3, 50.5 and 63.6, 55.3, at 255 53.1, 52.6 and 66.9, 58.8; 256 -> 128 at 386 48.8,
-        // 52.8 and 61.9, 56.5, at 511 57.5, 58.4 and 69.4, 61.9; K = 5, 256 -> 256 at 219 155, 174 and 196, 179, 256 -> 128 at 438 152, 178 and 202, 182; K = 3,
-        // stride 2 the other way round, 256 -> 256 at 219 64.5, 61.5 and 54.8, 57.5))
+        // channels, whose step is the longest, up to four workgroups of one block per CU, three and a half with K <= 3: sweeps gain there, dense sets cross before, and
+        // how dense a set is is not known here (whole layers, one and two blocks, sweep and indoor rows: 256 -> 256 at 172 tiles 43.4, 49.1 and 61.0, 57.4, at 204 46.7, 49.3 and 67.0, 59.3, at
+        // 219 49.2, 49.7 and 69.7, 60.8, at 229 50.7, 51.4 and 72.3, 61.7, at 255 53.1, 50.7 and 74.6, 64.0; 256 -> 128 at 407 48.3, 51.5 and 70.5, 63.1, at 500 55.2, 53.6; random cells at 229
+        // 40.0, 36.3; stride 2 at 229 65.4, 62.4 and 53.3, 56.9; K = 5 at 229 138, 161 and 203, 187, at 255 149, 178 and 216, 190))
         const int64_t pairs = likely * ((CB + 7) / 8);
-        if (CB <= 4 || (CB <= 8 && KS <= 4 ? likely <= 4 * (int64_t)cus : KS == 8 ? pairs <= 2 * (int64_t)cus : 2 * pairs < 3 * (int64_t)cus))
+        if (CB <= 4 || (CB <= 8 && KS <= 4 ? likely <= 4 * (int64_t)cus : KS == 8 ? 4 * pairs <= (K3 <= 27 ? 7 : 8) * (int64_t)cus : 2 * pairs < 3 * (int64_t)cus))
             SC_GATHER(4, 1, 1, O1);
         SC_GATHER(4, 1, 2, O2);
     }
