@@ -389,13 +389,10 @@ __device__ inline int32_t claim_cell(int32_t* oslots, uint32_t omask, const int4
     ousted = -1;
     for (uint32_t t = 0; t <= omask + REHASH_MAX; ++t) {
         const uint32_t slot = probe_slot(key, t, omask);
-        int32_t cur = *const_cast<const volatile int32_t*>(&oslots[slot]);
+        const int32_t cur = atomicCAS(&oslots[slot], CELL_EMPTY, id);
         if (cur == CELL_EMPTY) {
-            cur = atomicCAS(&oslots[slot], CELL_EMPTY, id);
-            if (cur == CELL_EMPTY) {
-                fresh = true;
-                return (int32_t)slot;
-            }
+            fresh = true;
+            return (int32_t)slot;
         }
         if (candidate_key(coords, sh, cur) == key) {
             if (id < cur) {
