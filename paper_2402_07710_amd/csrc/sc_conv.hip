@@ -93,14 +93,52 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
     if (turn * each >= share) return;                  // no tile: the whole workgroup, before any barrier
 
     // packed weights land in LDS beside everything up to the gathers, which wait for the lines behind them
-    constexpr bool DIRECT = WPACKED && K3 * CB * KS <= 64;
-    if constexpr (DIRECT) {
+    static_assert(!WPACKED || K3 * CB * KS <= 64, "loads into LDS land in the first 64 KB");
+    if constexpr (WPACKED) {
         const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)w_lds;
 #pragma unroll
         for (int i = 0; i < (K3 * CB * KS + 4 * NT - 1) / (4 * NT); ++i) {
             const int t = wv + i * 4 * NT;
             if (t < K3 * CB * KS) load_to_lds(wraw + t * 64 + (threadIdx.x & 63), base + t * 1024);
         }
+    }
+    // raw weights -> LDS as operand tiles (every thread helps, also wavefronts without rows): a thread reads four output
+    // channels of 8 input channels (8-byte loads) and writes four lanes' 16 bytes.  With a thread per lane, 2-byte loads, they were
+    // four times as many loads of 17 cycles each (us: up-sampling from the strided map 64 -> 32 53 k 6.1 -> 5.4, 64 -> 64 200 k 22.8 ->
+    // 20.8, 128 -> 64 53 k 12.8 -> 11.4; layers K = 2 64 -> 64 200 k 40.7 -> 38.6, fused 32 -> 32 53 k 15.1 -> 14.8)
+    constexpr int ITEMS = K3 * CB * KS * 16, PASSES = WPACKED ? 1 : (ITEMS + 256 * NT - 1) / (256 * NT);
+    auto raw_weights = [&](int pass, uint2 (&v)[8]) __attribute__((always_inline)) {
+        const int i = pass * (256 * NT) + threadIdx.x;
+        const int col = (i & 3) * 4, oct = (i >> 2) & 3, ks = (i >> 4) % KS, cb = (i >> 4) / KS % CB, k = (i >> 4) / KS / CB;
+        const uint16_t* src = reinterpret_cast<const uint16_t*>(wraw) + ((int64_t)k * C_in + ks * 32 + 8 * oct) * C_out + cb * 16 + col;
+        if (i < ITEMS) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const uint2*>(src + j * C_out);
+        }
+    };
+    auto weights_to_lds = [&](int pass, const uint2 (&v)[8]) __attribute__((always_inline)) {
+        const int i = pass * (256 * NT) + threadIdx.x;
+        if (i >= ITEMS) return;
+        const int col = (i & 3) * 4, oct = (i >> 2) & 3;
+        uint4* dst = w_lds + (i >> 4) * 64 + oct * 16 + col;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t take = (c & 1) ? 0x07060302u : 0x05040100u;     // the upper or the lower halves of two words
+            uint32_t o[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                o[j] = c < 2 ? __builtin_amdgcn_perm(v[2 * j + 1].x, v[2 * j].x, take) : __builtin_amdgcn_perm(v[2 * j + 1].y, v[2 * j].y, take);
+            dst[c] = make_uint4(o[0], o[1], o[2], o[3]);
+        }
+    };
+    // Look-ups have to be back before anything behind them is asked for, so the weights are asked for before them (us of fused layers, behind and before,
+    // sweeps 36 k / 53 k / 110 k / 200 k 13.0 / 15.0 / 25.7 / 45.8 and 12.9 / 14.6 / 25.0 / 44.7, indoor 53 k / 110 k 15.8 / 26.2 and 15.3 / 25.0; 16 k 10.3 and 10.7).
+    constexpr bool AHEAD = FUSED && !WPACKED;
+    uint2 ahead[AHEAD ? PASSES : 1][8];
+    if constexpr (AHEAD) {
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) raw_weights(i, ahead[i]);
+        __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll 1
     for (;;) {
@@ -147,38 +185,15 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
 #pragma unroll
             for (int k = 0; k < K3; ++k) e[k] = -1;
         }
-        // weights -> LDS as operand tiles (every thread helps, also wavefronts without rows): a thread reads four output
-        // channels of 8 input channels (8-byte loads) and writes four lanes' 16 bytes.  With a thread per lane, 2-byte loads, they were
-        // four times as many loads of 17 cycles each (us: up-sampling from the strided map 64 -> 32 53 k 6.1 -> 5.4, 64 -> 64 200 k 22.8 ->
-        // 20.8, 128 -> 64 53 k 12.8 -> 11.4; layers K = 2 64 -> 64 200 k 40.7 -> 38.6, fused 32 -> 32 53 k 15.1 -> 14.8)
         if (done == 0) {
-            if constexpr (DIRECT) {
+            if constexpr (WPACKED) {
                 __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0)
-            } else if constexpr (WPACKED) {
-                // the caller packed the weights once (sc_conv_weight_pack): the tiles are copied as they are
-                for (int i = threadIdx.x; i < K3 * CB * KS * 64; i += 256 * NT) w_lds[i] = wraw[i];
             } else {
-                const uint16_t* w16 = reinterpret_cast<const uint16_t*>(wraw);
-                for (int i = threadIdx.x; i < K3 * CB * KS * 16; i += 256 * NT) {
-                    const int col = (i & 3) * 4, oct = (i >> 2) & 3;
-                    int rest = i >> 4;
-                    const int ks = rest % KS; rest /= KS;
-                    const int cb = rest % CB;
-                    const int k = rest / CB;
-                    const uint16_t* src = w16 + ((int64_t)k * C_in + ks * 32 + 8 * oct) * C_out + cb * 16 + col;
+#pragma unroll
+                for (int i = 0; i < PASSES; ++i) {
                     uint2 v[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const uint2*>(src + j * C_out);
-                    uint4* dst = w_lds + ((k * CB + cb) * KS + ks) * 64 + oct * 16 + col;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const uint32_t take = (c & 1) ? 0x07060302u : 0x05040100u;     // the upper or the lower halves of two words
-                        uint32_t o[4];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            o[j] = c < 2 ? __builtin_amdgcn_perm(v[2 * j + 1].x, v[2 * j].x, take) : __builtin_amdgcn_perm(v[2 * j + 1].y, v[2 * j].y, take);
-                        dst[c] = make_uint4(o[0], o[1], o[2], o[3]);
-                    }
+                    if constexpr (!AHEAD) raw_weights(i, v);
+                    weights_to_lds(i, AHEAD ? ahead[AHEAD ? i : 0] : v);
                 }
             }
         }
