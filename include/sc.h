@@ -267,6 +267,12 @@ size_t sc_conv_workspace_bytes(int K, int C_in, int C_out, int dtype_in);
  *   dtype_out   SC_F32 or the same as dtype_in (one round-to-nearest-even at the end)
  *   channels    SC_F32: any C_in >= 1, 1 <= C_out <= 256.  SC_F16 / SC_BF16: C_in one of 32, 64,
  *               128, 256 and C_out a multiple of 16, 16 <= C_out <= 256.
+ *   Order of the sums: for one (n_map, K, stride, mode, channels, dtypes) it is fixed, so a call
+ *               repeated, with packed weights or (16-bit layers) with another n_out_cap gives the same bits.  Layers of
+ *               other n_map may take another kernel: 16-bit ones sum a row's offsets in increasing
+ *               order, or, where there are few rows, alternate groups of them apart and the two sums in the end; equal
+ *               rows of a small and a large layer, such as a scene alone and in a batch, can then differ in the
+ *               last bits of their 32-bit sums.
  *   Not finite: an infinity or NaN in W[k] reaches the output rows that have a pair at offset k and may
  *               reach other rows of the same 16 (rows 16g .. 16g + 15) if one of them has; no row outside.
  *               One in a feature row reaches the rows it is paired with.

@@ -576,7 +576,7 @@ static int launch_gather_sets(int K3, int mw, int CB, int64_t tiles, int cus, hi
     return launch_gather_as<DT, KS, SL, SKIP, 4, 1, 1, O1, SRC, 2>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
 }
 
-int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat,
+int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, bool sets, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const int CB = C_out / 16;
     // Slices per step, skipping, wavefronts per SIMD.  256 channels: a whole offset.  128: an offset (half of one,
@@ -616,7 +616,7 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
         return SC_EINVAL;
     }
     const bool few = few_workgroups(likely, CB, cus);
-    if (two_sets(likely, K3, CB, C_in, cus)) {
+    if (sets) {
         if (K3 <= 27) {
             switch (C_in) {
                 case 32: SC_GATHER_SETS(1, 2, 1, 4, FROM_LINES);
@@ -654,7 +654,7 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
 }
 
 // 3x3x3 layers that look their neighbours up in the dense table themselves: 32, 64 and 128 channels, at least 64 out.
-int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cus, hipStream_t s, const void* feat, const void* wp,
+int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, bool sets, int cus, hipStream_t s, const void* feat, const void* wp,
                         void* out, int out_f32, const MapSource& ms, int64_t n) {
     const int CB = C_out / 16;
     if (CB < 4) return SC_EINVAL;
@@ -665,7 +665,7 @@ int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, int cu
 #define SC_GATHER_FUSED_SETS(KS, SL, SKIP, O1)                                                                                                    \
     return dtype_in == SC_F16 ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, FROM_TABLE>(27, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
                               : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, FROM_TABLE>(27, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
-    if (two_sets(tiles, 27, CB, C_in, cus)) {
+    if (sets) {
         if (C_in == 32) SC_GATHER_FUSED_SETS(1, 2, 1, 4);
         if (C_in == 64) SC_GATHER_FUSED_SETS(2, 2, 1, 6);
         if (C_in == 128) SC_GATHER_FUSED_SETS(4, 4, 1, 4);

@@ -1,4 +1,4 @@
-// Lines between kernels that give the same result, as functions of sizes alone: a host compiler can read them, so a test
+// Lines between kernels that give the same result (two_sets: the same up to the order of a row's sums), as functions of sizes alone: a host compiler can read them, so a test
 // holds them without a GPU.  Tiles are 64 rows, `cus` the compute units of the device.
 #pragma once
 
@@ -67,7 +67,9 @@ constexpr bool general_128_to_128(int K, int64_t likely, bool strided, int64_t c
 // 18 k / 26 k / 30 k 23.0 / 26.7 / 28.2 and 25.5 / 27.2 / 28.3, indoor 25.4 / 30.1 / 31.2 and 25.4 / 28.9 / 30.5.
 constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return likely * ((CB + 3) / 4) <= 3 * cus; }
 
-// The general kernel, 16 bit, up to 128 input channels: two sets of four wavefronts walk alternate offsets of the tile and add up their sums in the end.  Up to
+// The general kernel, 16 bit, up to 128 input channels: two sets of four wavefronts walk alternate offsets of the tile and add up their sums in the end.  The other
+// 16-bit kernels, and this one beyond the line, add the offsets up in increasing order, so a row's last bits differ between the sides; `tiles` are
+// those of the rows the map was built from (strided layers: the inputs), which a caller's capacity does not move.  Up to
 // two workgroups per CU (32 input channels, K <= 3, 1 1/4) a layer takes as long as the workgroup of a dense tile walks its offsets, one wavefront per SIMD, and of 27
 // offsets each set walks 14; beyond, the CUs have enough wavefronts and the sums are traded for nothing.  us of whole layers, one set / two, sweeps: 64 -> 64 500 15.5 /
 // 14.5, 2 k 18.0 / 16.0, 10 k 19.9 / 18.9, 14 k 20.8 / 20.2, 25 k 23.1 / 22.4, 30 k 23.8 / 22.9, 42 k 26.5 / 26.1, 53 k 32.4 / 32.0, 80 k 38.1 / 41.2; indoor 3 k 18.6 / 16.7, 10 k 19.2 / 17.5, 30 k 23.9 / 23.2, 40 k 28.4 /
@@ -79,8 +81,8 @@ constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return like
 // 34.0 / 29.1, 12 k 50.9 / 41.5, 35 k 62.6 / 53.4, 53 k 73.0 / 66.7, 75 k 87.3 / 89.8; 128 -> 128 2 k 51.8 / 42.0, 12 k 78.8 / 64.1, 25 k 87.3 / 75.6, 53 k 118.5 / 128.4; 64 -> 32 30 k 59.7 / 48.3;
 // indoor 32 -> 32 5 k 30.5 / 26.8, 20 k 36.8 / 35.8, 30 k 38.8 / 40.0, 36 k 46.1 / 49.8; 64 -> 64 5 k 42.5 / 35.3, 30 k 52.2 / 51.7, 40 k 65.2 / 71.0; 128 -> 128 15 k 70.9 / 71.7, 20 k 87.6 / 94.9; random
 // cells 64 -> 64 5 k 36.5 / 32.0, 20 k 53.4 / 48.1; stride 2 32 -> 64 10 k 59.4 / 53.6, 30 k 84.9 / 86.3; K = 7 64 -> 64 10 k 118 / 94.5, 30 k 138 / 113).
-constexpr bool two_sets(int64_t likely, int K3, int CB, int C_in, int64_t cus) {
-    return CB > 1 && C_in <= 128 && likely * ((CB + 3) / 4) * 4 <= (C_in == 32 && K3 <= 27 ? 5 : 8) * cus;
+constexpr bool two_sets(int64_t tiles, int K3, int CB, int C_in, int64_t cus) {
+    return CB > 1 && C_in <= 128 && tiles * ((CB + 3) / 4) * 4 <= (C_in == 32 && K3 <= 27 ? 5 : 8) * cus;
 }
 
 // The general kernel, 16 bit: a tile's blocks of output channels one after the other on an XCD, whose L2 then holds the tile's rows for the second,
