@@ -951,7 +951,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u, density};
     const bool strided = mode == SC_STRIDED;
     // by the rows of the map, not by the caller's capacity: the order of a row's sums is not to depend on how large a buffer is
-    const bool sets = two_sets(n_map_tiles, L.K3, C_out / 16, C_in, compute_units());
+    const bool sets = two_sets(n_map_tiles, L.K3, C_out / 16, C_in, strided && K >= 2 * stride, compute_units());
     return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, strided, strided && K != stride, sets, s, d_feat_in, d_weight, packed,
                          d_workspace, d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap);
 }
@@ -1045,6 +1045,6 @@ extern "C" int sc_conv_fwd_grid(const void* d_feat_in, const int32_t* d_coords, 
     if (n == 0) return SC_OK;
     const MapSource ms{nullptr, nullptr, (const int4*)d_coords, (const unsigned long long*)d_grid, GridDims{B, X, Y, Z}, epoch, nullptr};
     if (!mfma_channels_ok(C_in, C_out)) return SC_EINVAL;
-    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, false, false, two_sets((n + TILE - 1) / TILE, 27, C_out / 16, C_in, compute_units()), (hipStream_t)stream, d_feat_in,
+    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, false, false, two_sets((n + TILE - 1) / TILE, 27, C_out / 16, C_in, false, compute_units()), (hipStream_t)stream, d_feat_in,
                          d_weight, false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n);
 }

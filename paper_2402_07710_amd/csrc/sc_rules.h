@@ -80,9 +80,16 @@ constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return like
 // K = 5, sweeps: 32 -> 32 2 k 24.2 / 22.2, 6 k 34.2 / 29.1, 20 k 40.3 / 36.3, 35 k 46.8 / 43.0, 46 k 49.7 / 49.7, 53 k 56.1 / 57.9; 32 -> 64 2 k 27.2 / 23.8, 20 k 41.7 / 37.6, 53 k 58.1 / 60.0; 64 -> 64 2 k
 // 34.0 / 29.1, 12 k 50.9 / 41.5, 35 k 62.6 / 53.4, 53 k 73.0 / 66.7, 75 k 87.3 / 89.8; 128 -> 128 2 k 51.8 / 42.0, 12 k 78.8 / 64.1, 25 k 87.3 / 75.6, 53 k 118.5 / 128.4; 64 -> 32 30 k 59.7 / 48.3;
 // indoor 32 -> 32 5 k 30.5 / 26.8, 20 k 36.8 / 35.8, 30 k 38.8 / 40.0, 36 k 46.1 / 49.8; 64 -> 64 5 k 42.5 / 35.3, 30 k 52.2 / 51.7, 40 k 65.2 / 71.0; 128 -> 128 15 k 70.9 / 71.7, 20 k 87.6 / 94.9; random
-// cells 64 -> 64 5 k 36.5 / 32.0, 20 k 53.4 / 48.1; stride 2 32 -> 64 10 k 59.4 / 53.6, 30 k 84.9 / 86.3; K = 7 64 -> 64 10 k 118 / 94.5, 30 k 138 / 113).
-constexpr bool two_sets(int64_t tiles, int K3, int CB, int C_in, int64_t cus) {
-    return CB > 1 && C_in <= 128 && tiles * ((CB + 3) / 4) * 4 <= (C_in == 32 && K3 <= 27 ? 5 : 8) * cus;
+// cells 64 -> 64 5 k 36.5 / 32.0, 20 k 53.4 / 48.1; K = 7 64 -> 64 10 k 118 / 94.5, 30 k 138 / 113).
+// `many_rows`: strided with K >= 2 stride, where an input is in eight cells and more, and even on surfaces more rows than inputs come: 1 1/4 too (us of the convolution, one
+// set / two, sweep, indoor and random rows: K = 4, stride 2, 64 -> 64 8 k 20.3 / 16.0, 22.1 / 17.2 and 27.2 / 30.1, 16 k 21.1 / 16.5, 22.2 / 17.3 and 45.7 / 51.4, 24 k 22.1 / 20.9,
+// 22.3 / 17.4 and 62.7 / 71.4, 32 k 28.6 / 28.5, 25.2 / 25.6 and 79.4 / 93.1; K = 5, stride 2, 32 -> 64 8 k 23.4 / 17.6, 24.2 / 18.3 and 38.9 / 42.4, 16 k 24.1 / 18.1, 24.4 / 18.7 and 62.9 / 78.6, 21 k
+// 24.4 / 19.5, 26.2 / 26.5 and 80 / 101, 24 k 24.6 / 22.8, 26.8 / 26.8 and 90.7 / 115.6, 32 k 33.6 / 33.8, 27.3 / 33.0 and 117 / 154; K = 7, 64 -> 64 16 k 102 / 74, 118 / 107 and 232 / 271, 30 k 117 / 101, 156 / 175 and 506 / 591).  Random cells, which have up to eight times the rows, lose below the line as well; how many rows
+// there are is not known here.  The other overlapping strides keep two: K = 3, stride 2, 64 -> 64 16 k 11.7 / 9.4, 11.8 / 9.5 and 16.8 / 16.5, 32 k 13.5 / 13.3, 11.8 / 9.5 and 28.0 / 26.6, 64 -> 128 16 k
+// 12.9 / 11.3, 11.9 / 9.6 and 27.7 / 26.4, 128 -> 128 8 k 17.3 / 14.1, 19.0 / 15.2 and 24.0 / 27.2, 16 k 19.3 / 17.6, 19.1 / 15.3 and 40.4 / 44.0; K = 5, stride 3, 64 -> 64 16 k 31.8 / 24.8, 39.7 / 30.1
+// and 33.9 / 38.6, 32 k 32.7 / 25.2, 39.8 / 30.2 and 59.4 / 59.7.
+constexpr bool two_sets(int64_t tiles, int K3, int CB, int C_in, bool many_rows, int64_t cus) {
+    return CB > 1 && C_in <= 128 && tiles * ((CB + 3) / 4) * 4 <= ((C_in == 32 && K3 <= 27) || many_rows ? 5 : 8) * cus;
 }
 
 // The general kernel, 16 bit: a tile's blocks of output channels one after the other on an XCD, whose L2 then holds the tile's rows for the second,

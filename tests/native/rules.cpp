@@ -58,7 +58,10 @@ static_assert(density_wanted(65, 256) && !density_wanted(64, 256) && density_wan
 static_assert(!dense_tiles_first(64, 1024, false, 256), "what the map does not hold is not asked for");
 
 // two sets of wavefronts up to two workgroups per compute unit, with 32 input channels 1 1/4; not for 16 output channels, nor for 256 input channels
-static_assert(two_sets(512, 27, 4, 64, 256) && !two_sets(513, 27, 4, 64, 256) && two_sets(256, 8, 8, 128, 256) && !two_sets(257, 8, 8, 128, 256), "two");
-static_assert(two_sets(320, 27, 4, 32, 256) && !two_sets(321, 27, 4, 32, 256) && two_sets(512, 27, 2, 128, 256) && two_sets(128, 27, 4, 64, 64), "1 1/4");
-static_assert(two_sets(512, 125, 2, 32, 256) && !two_sets(513, 125, 2, 32, 256) && two_sets(512, 64, 4, 32, 256) && !two_sets(257, 343, 8, 64, 256), "K > 3: two");
-static_assert(!two_sets(1, 27, 1, 64, 256) && !two_sets(1, 27, 4, 256, 256) && !two_sets(1, 125, 1, 32, 256) && !two_sets(1, 125, 4, 256, 256), "one set");
+static_assert(two_sets(512, 27, 4, 64, false, 256) && !two_sets(513, 27, 4, 64, false, 256) && two_sets(256, 8, 8, 128, false, 256) && !two_sets(257, 8, 8, 128, false, 256), "two");
+static_assert(two_sets(320, 27, 4, 32, false, 256) && !two_sets(321, 27, 4, 32, false, 256) && two_sets(512, 27, 2, 128, false, 256) && two_sets(128, 27, 4, 64, false, 64), "1 1/4");
+static_assert(two_sets(512, 125, 2, 32, false, 256) && !two_sets(513, 125, 2, 32, false, 256) && two_sets(512, 64, 4, 32, false, 256) && !two_sets(257, 343, 8, 64, false, 256), "K > 3: two");
+static_assert(!two_sets(1, 27, 1, 64, false, 256) && !two_sets(1, 27, 4, 256, false, 256) && !two_sets(1, 125, 1, 32, false, 256) && !two_sets(1, 125, 4, 256, false, 256), "one set");
+// strided with K >= 2 stride: 1 1/4, whatever the channels
+static_assert(two_sets(320, 125, 4, 64, true, 256) && !two_sets(321, 125, 4, 64, true, 256) && two_sets(160, 8, 8, 128, true, 256) && !two_sets(161, 8, 8, 128, true, 256), "many rows");
+static_assert(two_sets(320, 27, 4, 32, true, 256) && !two_sets(321, 27, 4, 32, true, 256) && two_sets(80, 64, 4, 64, true, 64), "many rows, 32 input channels");

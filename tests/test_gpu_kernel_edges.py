@@ -773,7 +773,7 @@ def test_two_sets_of_wavefronts_beyond_27_offsets(K, stride, C_in, C_out, n, dty
 
 
 @pytest.mark.parametrize("K,stride,C_in,C_out,n", [(3, 2, 64, 64, 64 * 600), (3, 1, 64, 64, 64 * 600), (5, 1, 32, 32, 64 * 600), (3, 2, 128, 128, 64 * 300), (2, 2, 64, 128, 64 * 300),
-                                                   (5, 2, 32, 64, 64 * 600), (3, 1, 64, 64, 64 * 300)])
+                                                   (5, 2, 32, 64, 64 * 600), (4, 2, 64, 64, 64 * 321), (3, 1, 64, 64, 64 * 300)])
 def test_capacity_of_the_output_leaves_the_bits_of_a_row(K, stride, C_in, C_out, n):
     """Layers on both sides of the line for two sets of wavefronts: the first rows alone, in a buffer small enough for the other
     side, are the whole layer's rows bit for bit, with raw and with packed weights."""
