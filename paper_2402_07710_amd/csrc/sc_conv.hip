@@ -807,13 +807,12 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     const uint16_t* feat = (const uint16_t*)d_feat_in;
     bool handled = false;
     int rc;
-    // Packed 64 -> 64 layers, K = 2, from 9 to 12 tiles per CU through the general kernel: their rows are a few more than the resident kernel's first round (us of whole
-    // layers, stride 2, general and resident, sweeps 110 k / 150 k / 160 k / 175 k / 190 k / 200 k / 300 k 26.9 / 29.6 / 30.2 / 31.7 / 33.3 / 34.0 / 50.1 and 25.9 / 30.7 / 31.1 / 32.1 / 33.4 /
-    // 33.7 / 46.9; indoor 150 k / 175 k / 400 k / 800 k 25.9 / 27.8 / 52.2 / 86.0 and 26.1 / 27.9 / 48.5 / 81.3).  32 -> 32, K = 3, is ahead on the resident kernel at every
-    // size (150 k / 200 k / 400 k 46.7 / 61.9 / 124.0 and 45.2 / 60.2 / 121.2, indoor 50.2 / 62.3 / 124.3 and 46.5 / 59.9 / 116.9).
-    const int64_t cus = compute_units();
-    const bool outgrown = packed && !FUSED && K3 == 8 && C_in == 64 && C_out == 64 && likely > 9 * cus && likely <= 12 * cus;
-    if (resident_shape(K3, C_in, C_out, FUSED) && !outgrown) {
+    // The resident kernel takes its shapes at every size (us of whole layers, general and resident, packed weights, sweeps: 64 -> 64, K = 2, 110 k / 148 k / 160 k / 175 k /
+    // 196 k / 300 k 26.9 / 29.7 / 29.8 / 31.5 / 32.9 / 50.1 and 25.9 / 30.3 / 30.5 / 31.5 / 32.8 / 46.9, indoor 148 k / 196 k / 400 k / 800 k 25.0 / 28.1 / 52.2 / 86.0 and 24.7 / 28.3 / 48.5 / 81.3, random
+    // cells 148 k / 175 k / 196 k 45.7 / 50.0 / 53.6 and 43.4 / 46.9 / 49.5; convolutions of inverse maps,
+    // sweeps 110 k / 148 k / 196 k / 300 k 14.1 / 18.0 / 20.3 / 28.8 and 12.3 / 14.8 / 16.4 / 23.1, indoor 16.1 / 19.2 / 23.4 / 34.2 and 14.3 / 17.6 / 19.6 / 27.6; 32 -> 32, K = 3, 150 k / 200 k / 400 k 46.7 / 61.9 / 124.0 and 45.2 / 60.2 / 121.2, indoor 50.2 / 62.3 / 124.3 and
+    // 46.5 / 59.9 / 116.9).
+    if (resident_shape(K3, C_in, C_out, FUSED)) {
         if (packed)
             rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
                                                                        d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled)

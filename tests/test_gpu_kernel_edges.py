@@ -92,9 +92,9 @@ def test_streaming_kernel_32_to_64_channels(stride, n):
 
 @pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457),
                                           (3, 2, 32, 32_640), (3, 2, 32, 32_705)])
-def test_packed_square_layers_beyond_the_resident_kernel(K, stride, C, n):
-    """Packed weights, the fewest tiles (9 per CU of 256, one row more) that go through the general kernel (64 -> 64); strided
-    layers at 510 and 512 likely tiles."""
+def test_packed_square_layers_of_the_resident_kernel(K, stride, C, n):
+    """Packed weights: 9 tiles per CU of 256 and one row more; 510 and 512 tiles of strided layers, the
+    last that take two tiles per workgroup."""
     say(f"packed K={K} s={stride} {C}->{C} n={n}")
     import oracle
     import torch
@@ -118,8 +118,8 @@ def test_packed_square_layers_beyond_the_resident_kernel(K, stride, C, n):
 
 @pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-def test_packed_and_raw_weights_agree_bit_for_bit_across_kernels(K, stride, C, n, dtype):
-    """From 9 to 12 tiles per CU (of 256) packed weights of 64 -> 64 layers take the general kernel and raw ones the resident kernel."""
+def test_packed_and_raw_weights_agree_bit_for_bit(K, stride, C, n, dtype):
+    """The resident kernel with packed weights and with raw ones, which it lays out itself, 9 tiles per CU (of 256) and more."""
     say(f"packed and raw K={K} s={stride} {C}->{C} {dtype} n={n}")
     import torch
     from paper_2402_07710_amd import binding as sc
@@ -728,6 +728,8 @@ def test_resident_kernels_deal_their_tiles(way, K, C_in, C_out, n):
             workspace = torch.empty(sc.sc_conv_workspace_bytes(K, C_in, C_out, "f16"), dtype=torch.uint8, device="cuda:0")
             sc.sc_kmap_transpose(down.kmap, n, K, K, down.counts, inverse)
             sc.sc_conv_fwd(f, w, out, inverse, down.counts, K, K, "inverse", workspace, n_map=n)
+            outs.append(torch.full_like(out, float("nan")))
+            sc.sc_conv_fwd_packed(f, sc.sc_conv_weight_pack(w, K), C_out, outs[0], inverse, down.counts, K, K, "inverse", n_map=n)
         outs.append(out)
     for got in outs:            # sums of up to 128 products in 32 bits
         assert float((got.double() - want).abs().max() / want.abs().max()) <= 1e-5
