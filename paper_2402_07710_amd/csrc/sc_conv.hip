@@ -888,7 +888,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     const int64_t n_map_tiles = (n_map + TILE - 1) / TILE, likely = tiles < n_map_tiles ? tiles : n_map_tiles;
     const uint32_t* gmask = kmap_masked(mode, L.K3) ? (const uint32_t*)((const char*)d_kmap + L.off_mask) : nullptr;
     const int32_t* nbr = (const int32_t*)((const char*)d_kmap + L.off_nbr);
-    const uint32_t* density = L.off_density != 0 ? (const uint32_t*)((const char*)d_kmap + L.off_density) : nullptr;
+    const uint32_t* density = (const uint32_t*)map_density(d_kmap, L);
     hipStream_t s = (hipStream_t)stream;
 
     if (dtype_in == SC_F32) {           // fp32 weights are used as they are: packed == raw

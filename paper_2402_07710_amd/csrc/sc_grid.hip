@@ -216,7 +216,7 @@ extern "C" int sc_kmap_build_grid(const int32_t* d_coords, int64_t n, const void
     }
     uint32_t* gmask = (uint32_t*)((char*)d_kmap + L.off_mask);
     int32_t* nbr = (int32_t*)((char*)d_kmap + L.off_nbr);
-    uint8_t* density = density_wanted(L.tiles, compute_units()) ? (uint8_t*)d_kmap + L.off_density : nullptr;
+    uint8_t* density = map_density(d_kmap, L);
     const unsigned long long* cells = (const unsigned long long*)d_grid;
     const GridDims dims{B, X, Y, Z};
     switch (K) {

@@ -8,6 +8,7 @@
 #include <stdlib.h>
 
 #include "sc.h"
+#include "sc_rules.h"
 
 namespace sc {
 
@@ -275,6 +276,13 @@ inline KmapLayout kmap_layout(int64_t n_out_bound, int K, int stride, int mode) 
     }
     return L;
 }
+int compute_units();                       // of the current device
+
+// Where a map's `density` bytes are, null if it holds none: the builds write by it and the layers that follow read by it, whatever part of
+// the rows they compute.
+inline uint8_t* map_density(const void* d_kmap, const KmapLayout& L) {
+    return L.off_density != 0 && density_wanted(L.tiles, compute_units()) ? (uint8_t*)const_cast<void*>(d_kmap) + L.off_density : nullptr;
+}
 // A tile's byte of `density`: the offsets it takes part in (halved where K^3 is more than a byte), from its masks.  Called by the
 // 4 MW lanes that hold them, [4][mw] words; lane 0's is the tile's.
 constexpr __host__ __device__ int density_full(int K3) { return K3 > 255 ? K3 / 2 : K3; }
@@ -319,7 +327,6 @@ __device__ inline int64_t xcd_unit_of(unsigned block, int64_t units) {
     return (block / NUM_XCD < chunk && u < units) ? u : -1;
 }
 
-int compute_units();                       // of the current device
 // The same in short runs: an XCD takes every eighth run of XCD_RUN consecutive units.  For kernels
 // whose time follows the neighbours of their rows: rows come in scan order, the first eighth of a
 // sweep (near the sensor) has several times the neighbours of the last, and contiguous eighths

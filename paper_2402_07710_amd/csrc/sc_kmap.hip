@@ -982,7 +982,7 @@ static int kmap_build(const int32_t* d_coords, int64_t n, const void* d_table, i
     }
 
     if (mode == SC_SUBM) {
-        uint8_t* density = density_wanted(L.tiles, compute_units()) ? (uint8_t*)d_kmap + L.off_density : nullptr;
+        uint8_t* density = map_density(d_kmap, L);
         HashTable t = table_view(const_cast<void*>(d_table), n);
 #define SC_SUBM_LAUNCH(KV, WPT, CH, AT)                                                                           \
     SC_LAUNCH(KID_KMAP_SUBM, (k_kmap_subm<KV, WPT, CH, AT>), dim3(xcd_grid(L.tiles)), dim3(64 * WPT), 0, s,      \
