@@ -93,7 +93,7 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
     if (turn * each >= share) return;                  // no tile: the whole workgroup, before any barrier
 
     // packed weights land in LDS beside everything up to the gathers, which wait for the lines behind them
-    static_assert(!WPACKED || K3 * CB * KS <= 64, "loads into LDS land in the first 64 KB");
+    static_assert(!WPACKED || (!FUSED && K3 * CB * KS <= 64), "loads into LDS land in its first 64 KB, which the weights have to themselves");
     if constexpr (WPACKED) {
         const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)w_lds;
 #pragma unroll
@@ -806,24 +806,23 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
                       int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const uint16_t* feat = (const uint16_t*)d_feat_in;
     bool handled = false;
-    int rc;
     // The resident kernel takes its shapes at every size (us of whole layers, general and resident, packed weights, sweeps: 64 -> 64, K = 2, 110 k / 148 k / 160 k / 175 k /
     // 196 k / 300 k 26.9 / 29.7 / 29.8 / 31.5 / 32.9 / 50.1 and 25.9 / 30.3 / 30.5 / 31.5 / 32.8 / 46.9, indoor 148 k / 196 k / 400 k / 800 k 25.0 / 28.1 / 52.2 / 86.0 and 24.7 / 28.3 / 48.5 / 81.3, random
     // cells 148 k / 175 k / 196 k 45.7 / 50.0 / 53.6 and 43.4 / 46.9 / 49.5; convolutions of inverse maps,
     // sweeps 110 k / 148 k / 196 k / 300 k 14.1 / 18.0 / 20.3 / 28.8 and 12.3 / 14.8 / 16.4 / 23.1, indoor 16.1 / 19.2 / 23.4 / 34.2 and 14.3 / 17.6 / 19.6 / 27.6; 32 -> 32, K = 3, 150 k / 200 k / 400 k 46.7 / 61.9 / 124.0 and 45.2 / 60.2 / 121.2, indoor 50.2 / 62.3 / 124.3 and
     // 46.5 / 59.9 / 116.9).
     if (resident_shape(K3, C_in, C_out, FUSED)) {
-        if (packed)
-            rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
-                                                                       d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled)
-                                    : launch_resident<SC_BF16, FUSED, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
-                                                                        d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled);
-        else
-            rc = dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 0>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
-                                                                       d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled)
-                                    : launch_resident<SC_BF16, FUSED, 0>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight,
-                                                                        d_feat_out, out_f32, ms, n_out_ptr, n_out_cap, &handled);
-        return rc;
+        if constexpr (!FUSED) {
+            if (packed)
+                return dtype_in == SC_F16 ? launch_resident<SC_F16, 0, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight, d_feat_out,
+                                                                          out_f32, ms, n_out_ptr, n_out_cap, &handled)
+                                          : launch_resident<SC_BF16, 0, 1>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight, d_feat_out,
+                                                                           out_f32, ms, n_out_ptr, n_out_cap, &handled);
+        }
+        return dtype_in == SC_F16 ? launch_resident<SC_F16, FUSED, 0>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight, d_feat_out,
+                                                                      out_f32, ms, n_out_ptr, n_out_cap, &handled)
+                                  : launch_resident<SC_BF16, FUSED, 0>(K3, C_in, C_out, tiles, likely, s, feat, (const uint4*)d_weight, d_feat_out,
+                                                                       out_f32, ms, n_out_ptr, n_out_cap, &handled);
     }
     const bool fused_gather = (C_in == 32 && C_out == 64) || (C_in == 64 && (C_out == 64 || C_out == 128)), wide = C_in == 128 && C_out == 128;
     if (FUSED && !fused_gather && !wide) return SC_EINVAL;     // no fused kernel for this shape: use the three calls
@@ -843,10 +842,10 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
         return launch_gather_fused(dtype_in, C_in, C_out, tiles, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
     if (general)
         return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
-    rc = dtype_in == SC_F16 ? launch_streamed<SC_F16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
-                                                            n_out_ptr, n_out_cap, &handled)
-                            : launch_streamed<SC_BF16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
-                                                             n_out_ptr, n_out_cap, &handled);
+    const int rc = dtype_in == SC_F16 ? launch_streamed<SC_F16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
+                                                                       n_out_ptr, n_out_cap, &handled)
+                                      : launch_streamed<SC_BF16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
+                                                                        n_out_ptr, n_out_cap, &handled);
     if (handled || rc != SC_OK) return rc;
     if (FUSED) return SC_EINVAL;
     return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
