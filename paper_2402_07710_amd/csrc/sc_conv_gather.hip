@@ -102,7 +102,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
     const unsigned quotient = turn / divisor, rest = turn - quotient * divisor;
     const int by = (int)(apart ? quotient : rest);
     const unsigned place = (apart ? rest : quotient) * NUM_XCD + blockIdx.x % NUM_XCD;
-    const int64_t tile = SRC != FROM_TABLE && ms.density != nullptr ? xcd_dense_first(place, tiles, ms.density, K3) : xcd_run_of(place, tiles);
+    const int64_t tile = SRC != FROM_TABLE && !POINT && ms.density != nullptr ? xcd_dense_first(place, tiles, ms.density, K3) : xcd_run_of(place, tiles);
     if (tile < 0 || by >= blocks_y) return;            // the whole workgroup
     const int cb0 = by * (WC * CT) + (wv % WC) * CT;
 
@@ -516,7 +516,7 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, int cus, hipS
     static_assert(grid_fits(GRID_COLUMNS, 64 * NW * HV) && GRID_COLUMNS % NUM_XCD == 0, "a row of the grid is whole turns of the XCDs");
     const int64_t groups = (int64_t)xcd_run_grid(tiles) * blocks_y;
     MapSource source = ms;
-    if (SRC == FROM_LINE || !dense_tiles_first(tiles, tiles * blocks_y, 3 * fixed > 160 * 1024, cus)) source.density = nullptr;
+    if (!dense_tiles_first(tiles, tiles * blocks_y, 3 * fixed > 160 * 1024, cus)) source.density = nullptr;
     SC_LAUNCH(DT == SC_F32 ? KID_CONV_F32 : KID_CONV_MFMA, (k_conv_gather<DT, KS, NW, WR, CT, SL, SKIP, OCC, SRC, HV>),
               dim3((unsigned)grid_columns(groups), (unsigned)grid_rows(groups)), dim3(64 * NW * HV), lds, s, feat, wp, out, out_f32, source, K3, mw, CB,
               (int)blocks_y, first_tiles_apart((int64_t)K3 * CB * KS * 1024, CT, n_out_ptr != nullptr, cus), n_out_ptr, n_out_cap);

@@ -128,7 +128,7 @@ k_kmap_subm_grid(const int4* __restrict__ coords, int64_t n, const unsigned long
     if (threadIdx.x < 4 * MW) {
         const uint32_t word = mask_s[threadIdx.x];
         gmask[tile * (4 * MW) + threadIdx.x] = word;
-        if (density != nullptr) {
+        if (K > 1 && density != nullptr) {
             const uint8_t offsets = density_of<MW, K3>(word, mask_s);
             if (threadIdx.x == 0) density[tile] = offsets;
         }

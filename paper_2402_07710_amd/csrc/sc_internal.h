@@ -227,7 +227,7 @@ __device__ inline void grid_neighbours_part(const MapSource& ms, int64_t row, in
 }
 
 // ---- kernel-map blob ------------------------------------------------------------------------
-// header | mask[T][4][mw] (uint32) | nbr[T][K3][TILE] (int32) | strided maps, K == stride <= 4: parent[n] (uint32); submanifold maps:
+// header | mask[T][4][mw] (uint32) | nbr[T][K3][TILE] (int32) | strided maps, K == stride <= 4: parent[n] (uint32); submanifold maps, K > 1:
 // density[T] (uint8, runs of XCD_RUN tiles whole)
 // Outputs are cut into tiles of 64 consecutive rows.  nbr[t][k][j] is the input row paired with
 // output row 64t+j at offset k, or -1: the paper's offset table (Section III-C.2), stored
@@ -270,7 +270,7 @@ inline KmapLayout kmap_layout(int64_t n_out_bound, int K, int stride, int mode) 
         L.bytes = align_up(L.off_parent + (size_t)n_out_bound * sizeof(uint32_t), 256);
     }
     L.off_density = 0;
-    if (mode == SC_SUBM) {
+    if (mode == SC_SUBM && K > 1) {                    // a pointwise layer's tiles are all alike
         L.off_density = L.bytes;
         L.bytes = align_up(L.off_density + (size_t)L.tiles, 256);
     }

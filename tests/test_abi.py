@@ -64,6 +64,9 @@ def test_size_queries(lib):
     # tile-major offset table: header + 4 mask words per tile + one int32 per (row, offset)
     b = lib.sc_kmap_bytes(6400, 3, 1, binding.SC_SUBM)
     assert b >= 100 * 64 * 27 * 4 + 100 * 16 and b < 100 * 64 * 27 * 4 + 100 * 16 + 1024
+    # a pointwise map ends with its table: nothing says how dense its tiles are (a byte per tile of the others)
+    assert lib.sc_kmap_bytes(64 * 1024, 1, 1, binding.SC_SUBM) == 256 + 1024 * 16 + 1024 * 64 * 4
+    assert lib.sc_kmap_bytes(64 * 1024, 3, 1, binding.SC_SUBM) == 256 + 1024 * 16 + 1024 * 64 * 27 * 4 + 1024
     assert lib.sc_kmap_scratch_bytes(6400, 2, 2, binding.SC_STRIDED) > 32768 * 16 + 6400 * 4
     assert lib.sc_conv_workspace_bytes(3, 64, 64, binding.SC_F16) == 27 * 64 * 64 * 2
     assert lib.sc_conv_workspace_bytes(3, 16, 16, binding.SC_F32) == 0
