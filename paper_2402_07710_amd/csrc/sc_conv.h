@@ -118,7 +118,7 @@ inline int allow_lds(const void* fn, size_t lds, bool (&done)[MAX_DEVICES]) {
 // 128 or 256 and packed weights, fp32 layers with C_in 16, 32, 64, 128 or 256 and weights as they are.  `tiles` covers the
 // caller's row capacity, `likely` is how many of them to expect (the input's, where the output count is known on the device only).
 // `sets`: two sets of wavefronts (two_sets).
-int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, bool sets, int cus, hipStream_t s, const void* feat,
+int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, LayerKind kind, bool sets, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap);
 int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, bool sets, int cus, hipStream_t s, const void* feat, const void* wp,
                         void* out, int out_f32, const MapSource& ms, int64_t n);

@@ -798,10 +798,10 @@ static int pack_weights(int K3, int C_in, int C_out, const void* d_weight, void*
 
 // A 16-bit layer.  `packed`: d_weight is what sc_conv_weight_pack made; otherwise the raw weights,
 // which the resident kernels re-lay out themselves and the others have packed into the workspace
-// first.  FUSED (dense table, no map) always takes raw weights.  `strided`: the number of output rows is known on the device only;
-// `overlapping`: strided with K != stride; `sets`: two sets of wavefronts where the general kernel takes it.
+// first.  FUSED (dense table, no map) always takes raw weights.  Of strided
+// layers the number of output rows is known on the device only.  `sets`: two sets of wavefronts where the general kernel takes it.
 template <int FUSED>
-static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, bool strided, bool overlapping, bool sets, hipStream_t s,
+static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, LayerKind kind, bool sets, hipStream_t s,
                       const void* d_feat_in, const void* d_weight, bool packed, void* d_workspace, void* d_feat_out,
                       int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const uint16_t* feat = (const uint16_t*)d_feat_in;
@@ -835,20 +835,20 @@ static int conv_16bit(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t
     // the general one at every size (whole layers, us, general and streaming: 2 k 13.1 / 22.3, 53 k 22.5 / 27.0, 200 k 60.3 / 77.6, 400 k 114 / 142, 10^6 257 /
     // 309; indoor 200 k 50.2 / 58.2, 400 k 104 / 115, 800 k 213.6 / 216.9, 10^6 266.9 / 269.0)
     const bool general = FUSED && fused_gather ? true
-                         : wide                ? general_128_to_128(K3 == 27 ? 3 : 2, likely, strided, compute_units())
+                         : wide                ? general_128_to_128(K3 == 27 ? 3 : 2, likely, kind == CELLS || kind == OVERLAPPING, compute_units())
                                                : !FUSED && K3 == 27 && C_in == 32 && C_out == 64 &&
-                                                     general_32_to_64(likely, overlapping, compute_units());
+                                                     general_32_to_64(likely, kind == OVERLAPPING, compute_units());
     if (general && FUSED)
         return launch_gather_fused(dtype_in, C_in, C_out, tiles, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_cap);
     if (general)
-        return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
+        return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, kind, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
     const int rc = dtype_in == SC_F16 ? launch_streamed<SC_F16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
                                                                        n_out_ptr, n_out_cap, &handled)
                                       : launch_streamed<SC_BF16, FUSED>(K3, C_in, C_out, tiles, s, feat, wp, d_feat_out, out_f32, ms,
                                                                         n_out_ptr, n_out_cap, &handled);
     if (handled || rc != SC_OK) return rc;
     if (FUSED) return SC_EINVAL;
-    return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
+    return launch_gather(dtype_in, K3, mw, C_in, C_out, tiles, likely, kind, sets, compute_units(), s, feat, wp, d_feat_out, out_f32, ms, n_out_ptr, n_out_cap);
 }
 
 }  // namespace sc
@@ -888,6 +888,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
     const uint32_t* gmask = kmap_masked(mode, L.K3) ? (const uint32_t*)((const char*)d_kmap + L.off_mask) : nullptr;
     const int32_t* nbr = (const int32_t*)((const char*)d_kmap + L.off_nbr);
     const uint32_t* density = (const uint32_t*)map_density(d_kmap, L);
+    const LayerKind kind = mode == SC_SUBM ? SUBMANIFOLD : mode == SC_INVERSE ? INVERSE : K == stride ? CELLS : OVERLAPPING;
     hipStream_t s = (hipStream_t)stream;
 
     if (dtype_in == SC_F32) {           // fp32 weights are used as they are: packed == raw
@@ -910,7 +911,7 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         const bool slices = C_in == 16 || C_in == 32 || C_in == 64 || C_in == 128 || C_in == 256;
         if (slices && C_out % 16 == 0 && (C_in * C_out >= 2048 || (C_in * C_out >= 1024 && line_tiles >= compute_units()) || L.K3 > 32)) {
             const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u, density};
-            return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, likely, false, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
+            return launch_gather(SC_F32, L.K3, L.mw, C_in, C_out, tiles, likely, kind, false, compute_units(), s, d_feat_in, d_weight, d_feat_out, 1, ms, n_out_ptr,
                                  n_out_cap);
         }
         if (C_in <= 4) {
@@ -947,10 +948,9 @@ static int conv_fwd(const void* d_feat_in, int64_t n_map, const void* d_weight, 
         if (d_workspace == nullptr || workspace_bytes < need) return SC_ECAP;
     }
     const MapSource ms{gmask, nbr, nullptr, nullptr, GridDims{0, 0, 0, 0}, 0u, density};
-    const bool strided = mode == SC_STRIDED;
     // by the rows of the map, not by the caller's capacity: the order of a row's sums is not to depend on how large a buffer is
-    const bool sets = two_sets(n_map_tiles, L.K3, C_out / 16, C_in, strided && K >= 2 * stride, compute_units());
-    return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, strided, strided && K != stride, sets, s, d_feat_in, d_weight, packed,
+    const bool sets = two_sets(n_map_tiles, L.K3, C_out / 16, C_in, mode == SC_STRIDED && K >= 2 * stride, compute_units());
+    return conv_16bit<0>(dtype_in, L.K3, L.mw, C_in, C_out, tiles, likely, kind, sets, s, d_feat_in, d_weight, packed,
                          d_workspace, d_feat_out, dtype_out == SC_F32, ms, n_out_ptr, n_out_cap);
 }
 
@@ -1043,6 +1043,6 @@ extern "C" int sc_conv_fwd_grid(const void* d_feat_in, const int32_t* d_coords, 
     if (n == 0) return SC_OK;
     const MapSource ms{nullptr, nullptr, (const int4*)d_coords, (const unsigned long long*)d_grid, GridDims{B, X, Y, Z}, epoch, nullptr};
     if (!mfma_channels_ok(C_in, C_out)) return SC_EINVAL;
-    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, false, false, two_sets((n + TILE - 1) / TILE, 27, C_out / 16, C_in, false, compute_units()), (hipStream_t)stream, d_feat_in,
+    return conv_16bit<1>(dtype_in, 27, 1, C_in, C_out, (n + TILE - 1) / TILE, (n + TILE - 1) / TILE, SUBMANIFOLD, two_sets((n + TILE - 1) / TILE, 27, C_out / 16, C_in, false, compute_units()), (hipStream_t)stream, d_feat_in,
                          d_weight, false, d_workspace, d_feat_out, dtype_out == SC_F32, ms, nullptr, n);
 }

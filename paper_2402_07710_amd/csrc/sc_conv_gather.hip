@@ -525,7 +525,7 @@ static int launch_gather_as(int K3, int mw, int CB, int64_t tiles, int cus, hipS
 
 // O1, O2: wavefronts per SIMD with one and with two output blocks per wavefront
 template <int DT, int KS, int SL, int SKIP, int O1, int O2, int SRC = FROM_MAP>
-static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likely, int cus, hipStream_t s, const void* feat, const void* wp,
+static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likely, LayerKind kind, int cus, hipStream_t s, const void* feat, const void* wp,
                             void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
 #define SC_GATHER(NW, WR, CT, OCC) \
     return launch_gather_as<DT, KS, SL, SKIP, NW, WR, CT, OCC, SRC>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
@@ -553,13 +553,11 @@ static int launch_gather_ks(int K3, int mw, int CB, int64_t tiles, int64_t likel
         // two output blocks per wavefront halve how often a tile's rows are gathered; one, where that leaves CUs
         // idle or, up to 128 channels either way, with few wavefronts (us with one and with two blocks: 256 -> 128 at
         // 219 tiles 29.0, 34.2; 256 -> 256 49.1, 44.1; 64 -> 256 at 157 tiles 17.6, 19.3, at 250 22.9, 20.9; 128 -> 128 at
-        // 625 tiles 36.0, 38.2, at 4,088 132, 127.5; 64 -> 128 at 469 tiles 20.2, 21.4, at 834 26.9, 26.7; and with 256 input
-        // channels, whose step is the longest, up to four workgroups of one block per CU, three and a half with K <= 3: sweeps gain there, dense sets cross before, and
-        // how dense a set is is not known here (whole layers, one and two blocks, sweep and indoor rows: 256 -> 256 at 172 tiles 43.4, 49.1 and 61.0, 57.4, at 204 46.7, 49.3 and 67.0, 59.3, at
-        // 219 49.2, 49.7 and 69.7, 60.8, at 229 50.7, 51.4 and 72.3, 61.7, at 255 53.1, 50.7 and 74.6, 64.0; 256 -> 128 at 407 48.3, 51.5 and 70.5, 63.1, at 500 55.2, 53.6; random cells at 229
-        // 40.0, 36.3; stride 2 at 229 65.4, 62.4 and 53.3, 56.9; K = 5 at 229 138, 161 and 203, 187, at 255 149, 178 and 216, 190))
+        // 625 tiles 36.0, 38.2, at 4,088 132, 127.5; 64 -> 128 at 469 tiles 20.2, 21.4, at 834 26.9, 26.7; 256 input channels: one_block_of_256)
         const int64_t pairs = likely * ((CB + 7) / 8);
-        if (CB <= 4 || (CB <= 8 && KS <= 4 ? likely <= 4 * (int64_t)cus : KS == 8 ? 4 * pairs <= (K3 <= 27 ? 7 : 8) * (int64_t)cus : 2 * pairs < 3 * (int64_t)cus))
+        if (CB <= 4 || (CB <= 8 && KS <= 4 ? likely <= 4 * (int64_t)cus
+                        : KS == 8          ? one_block_of_256(pairs, K3, kind, cus)
+                                           : 2 * pairs < 3 * (int64_t)cus))
             SC_GATHER(4, 1, 1, O1);
         SC_GATHER(4, 1, 2, O2);
     }
@@ -576,7 +574,7 @@ static int launch_gather_sets(int K3, int mw, int CB, int64_t tiles, int cus, hi
     return launch_gather_as<DT, KS, SL, SKIP, 4, 1, 1, O1, SRC, 2>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap);
 }
 
-int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, bool sets, int cus, hipStream_t s, const void* feat,
+int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t tiles, int64_t likely, LayerKind kind, bool sets, int cus, hipStream_t s, const void* feat,
                   const void* wp, void* out, int out_f32, const MapSource& ms, const int64_t* n_out_ptr, int64_t n_out_cap) {
     const int CB = C_out / 16;
     // Slices per step, skipping, wavefronts per SIMD.  256 channels: a whole offset.  128: an offset (half of one,
@@ -589,12 +587,12 @@ int launch_gather(int dtype_in, int K3, int mw, int C_in, int C_out, int64_t til
                : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, SRC>(K3, mw, CB, tiles, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
 #define SC_GATHER_KS(KS, SL, SKIP, O1, O2, SRC)                                                                                      \
     return dtype_in == SC_F16                                                                                                     \
-               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
-               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, kind, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)    \
+               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, SRC>(K3, mw, CB, tiles, likely, kind, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
     if (dtype_in == SC_F32) {
 #define SC_GATHER_F32(KS)                                                                                                              \
-    return K3 == 1 ? launch_gather_ks<SC_F32, KS, 4, 1, 4, 4, FROM_LINE>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap) \
-                   : launch_gather_ks<SC_F32, KS, 4, 1, 4, 4>(K3, mw, CB, tiles, likely, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
+    return K3 == 1 ? launch_gather_ks<SC_F32, KS, 4, 1, 4, 4, FROM_LINE>(K3, mw, CB, tiles, likely, kind, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap) \
+                   : launch_gather_ks<SC_F32, KS, 4, 1, 4, 4>(K3, mw, CB, tiles, likely, kind, cus, s, feat, wp, out, out_f32, ms, n_out_ptr, n_out_cap)
         switch (C_in) {
             case 16: SC_GATHER_F32(1);
             case 32: SC_GATHER_F32(2);
@@ -660,8 +658,8 @@ int launch_gather_fused(int dtype_in, int C_in, int C_out, int64_t tiles, bool s
     if (CB < 4) return SC_EINVAL;
 #define SC_GATHER_FUSED(KS, SL, SKIP, O1, O2)                                                                                                    \
     return dtype_in == SC_F16                                                                                                                \
-               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
-               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
+               ? launch_gather_ks<SC_F16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, SUBMANIFOLD, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
+               : launch_gather_ks<SC_BF16, KS, SL, SKIP, O1, O2, FROM_TABLE>(27, 1, CB, tiles, tiles, SUBMANIFOLD, cus, s, feat, wp, out, out_f32, ms, nullptr, n)
 #define SC_GATHER_FUSED_SETS(KS, SL, SKIP, O1)                                                                                                    \
     return dtype_in == SC_F16 ? launch_gather_sets<SC_F16, KS, SL, SKIP, O1, FROM_TABLE>(27, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)    \
                               : launch_gather_sets<SC_BF16, KS, SL, SKIP, O1, FROM_TABLE>(27, 1, CB, tiles, cus, s, feat, wp, out, out_f32, ms, nullptr, n)

@@ -6,6 +6,9 @@
 
 namespace sc {
 
+// Kinds of layers, as far as lines differ between them: submanifold, over an inverse map, strided with K == stride and with K != stride (an input in several cells).
+enum LayerKind { SUBMANIFOLD, INVERSE, CELLS, OVERLAPPING };
+
 // Submanifold maps, K = 3 and 5: tiles to the XCDs in runs instead of contiguous eighths, of which the one nearest the sensor, whose
 // rows find more, ends last.  K = 3 beyond 6 tiles per CU, K = 5 beyond 3.5 (us of the whole 32 -> 32 layer, eighths / runs, 256 CUs.  K = 3:
 // sweeps 53 k 23.3 / 23.8, 80 k 32.0 / 31.9, 98 k 36.3 / 35.8, 110 k 38.6 / 38.2, 147 k 47.7 / 47.1, 170 k 53.6 / 52.6; indoor 64 k 26.0 / 26.2, 100 k 38.0 /
@@ -90,6 +93,22 @@ constexpr bool few_workgroups(int64_t likely, int CB, int64_t cus) { return like
 // and 33.9 / 38.6, 32 k 32.7 / 25.2, 39.8 / 30.2 and 59.4 / 59.7.
 constexpr bool two_sets(int64_t tiles, int K3, int CB, int C_in, bool many_rows, int64_t cus) {
     return CB > 1 && C_in <= 128 && tiles * ((CB + 3) / 4) * 4 <= ((C_in == 32 && K3 <= 27) || many_rows ? 5 : 8) * cus;
+}
+
+// The general kernel, 16 bit, 256 input channels, whose step is the longest: one or two output blocks per wavefront.  `pairs` are tiles times pairs of blocks of 64
+// channels.  Two halve how often a tile's rows are gathered and leave CUs idle where there are few.  us of the convolution, one / two blocks, sweep, indoor and random rows (256 CUs: 1 pair per CU is 128
+// tiles of 256 -> 256 and 256 of 256 -> 128).
+// Submanifold layers, K = 3, 1 3/4 pairs per CU: sweeps gain up to there and, from 1 5/8 on, less than the others lose; how dense a set is is not known here (means of five sets): 256 -> 256 12.4 k 30.9 / 38.9, 56.1 / 48.1 and 26.6 / 24.1, 13 k
+// 32.7 / 39.0, 58.4 / 49.6 and 27.5 / 24.4, 14 k 36.2 / 39.5, 59.4 / 51.0 and 27.7 / 24.1, 16 k 41.5 / 41.7, 66.4 / 56.8 and 29.2 / 24.4; 256 -> 128 24 k 33.7 / 41.1, 55.8 / 52.1 and 26.6 / 24.2, 26 k 38.2 / 41.2, 58.5 / 51.1 and
+// 27.3 / 24.3, 31 k 43.7 / 42.8, 65.6 / 57.7 and 28.7 / 24.9.  K > 3 2 (whole layers, 229 tiles 138 / 161 and 203 / 187, 255 tiles 149 / 178 and 216 / 190).
+// Inverse maps, 1 1/2: K = 2 256 -> 256 9 k 16.9 / 17.8, 21.1 / 20.5 and 21.2 / 20.9, 12.4 k 18.4 / 18.3, 22.8 / 20.6 and 22.7 / 20.2, 16 k 20.2 / 18.3, 24.9 / 20.6 and 24.9 / 20.4; K = 3 12.4 k 30.8 / 31.3, 47.1 / 42.8 and 46.0 / 42.0, 16 k
+// 35.2 / 31.9, 52.1 / 43.6 and 49.9 / 42.9; 256 -> 128 K = 2 18 k 15.5 / 16.8, 19.9 / 19.6 and 19.9 / 19.8, 24 k 18.4 / 17.5, 20.8 / 20.3 and 21.0 / 20.2.
+// Strided layers with K == stride, whose rows are fewer than the inputs that are counted, 2 (beyond not tried): K = 2 256 -> 256 12 k 9.7 / 12.7, 10.5 / 14.3 and 21.4 / 21.0, 16 k 11.7 / 12.9, 12.8 / 14.4 and
+// 25.1 / 21.9; K = 3 12 k 19.4 / 27.8, 26.5 / 39.5 and 46.3 / 44.3, 16 k 20.7 / 29.4, 26.7 / 39.8 and 52.5 / 45.7; 256 -> 128 K = 2 24 k 11.3 / 13.0, 10.4 / 14.4 and 21.5 / 21.0, K = 3 31 k 20.8 / 29.9, 26.5 / 39.5 and 51.4 / 46.2.
+// Overlapping ones, 1 3/4: K = 3, stride 2, 256 -> 256 9 k 30.2 / 36.4, 31.5 / 39.1 and 91.5 / 82.0, 12 k 41.5 / 38.8, 34.3 / 39.3 and 116 / 103, 14 k 47.3 / 43.8, 37.5 / 39.5 and 136 / 119, 16 k 52.4 / 46.3,
+// 38.9 / 39.8 and 150 / 124; 256 -> 128 24 k 48.4 / 47.3, 33.1 / 38.9 and 116 / 103, 31 k 57.0 / 52.1, 36.5 / 39.3 and 148 / 123.
+constexpr bool one_block_of_256(int64_t pairs, int K3, LayerKind kind, int64_t cus) {
+    return 4 * pairs <= (K3 > 27 || kind == CELLS ? 8 : kind == INVERSE ? 6 : 7) * cus;
 }
 
 // The general kernel, 16 bit: a tile's blocks of output channels one after the other on an XCD, whose L2 then holds the tile's rows for the second,

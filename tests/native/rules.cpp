@@ -65,3 +65,10 @@ static_assert(!two_sets(1, 27, 1, 64, false, 256) && !two_sets(1, 27, 4, 256, fa
 // strided with K >= 2 stride: 1 1/4, whatever the channels
 static_assert(two_sets(320, 125, 4, 64, true, 256) && !two_sets(321, 125, 4, 64, true, 256) && two_sets(160, 8, 8, 128, true, 256) && !two_sets(161, 8, 8, 128, true, 256), "many rows");
 static_assert(two_sets(320, 27, 4, 32, true, 256) && !two_sets(321, 27, 4, 32, true, 256) && two_sets(80, 64, 4, 64, true, 64), "many rows, 32 input channels");
+
+// 256 input channels, one output block per wavefront: 1 3/4 pairs of blocks per compute unit, inverse maps 1 1/2, K == stride and K > 3 2
+static_assert(one_block_of_256(448, 27, SUBMANIFOLD, 256) && !one_block_of_256(449, 27, SUBMANIFOLD, 256) && one_block_of_256(448, 27, OVERLAPPING, 256) &&
+              !one_block_of_256(449, 27, OVERLAPPING, 256), "submanifold, overlapping");
+static_assert(one_block_of_256(384, 8, INVERSE, 256) && !one_block_of_256(385, 27, INVERSE, 256) && one_block_of_256(96, 8, INVERSE, 64), "inverse maps");
+static_assert(one_block_of_256(512, 27, CELLS, 256) && !one_block_of_256(513, 27, CELLS, 256) && one_block_of_256(512, 8, CELLS, 256), "K == stride");
+static_assert(one_block_of_256(512, 125, SUBMANIFOLD, 256) && !one_block_of_256(513, 125, OVERLAPPING, 256) && one_block_of_256(512, 64, INVERSE, 256), "K > 3");

@@ -795,3 +795,32 @@ def test_capacity_of_the_output_leaves_the_bits_of_a_row(K, stride, C_in, C_out,
     some.fill_(float("nan"))
     sc.sc_conv_fwd_packed(feat, sc.sc_conv_weight_pack(weight, K), C_out, some, buf.kmap, buf.counts, K, stride, mode)
     assert torch.equal(some, buf.feat_out[:len(some)])
+
+
+@pytest.mark.parametrize("way,n", [("down", 64 * 256), ("down", 64 * 256 + 1), ("up", 64 * 192), ("up", 64 * 192 + 1), ("up", 64 * 224)])
+def test_256_channels_with_one_and_two_output_blocks_per_wavefront(way, n):
+    """Both sides of the lines for K == stride and for inverse maps: one input per coarse cell, so that a row is its input
+    times the weights of its one offset."""
+    say(f"256 -> 256 {way} n={n}")
+    import torch
+    from paper_2402_07710_amd import binding as sc
+    i, k = np.arange(n), np.arange(n) % 8
+    xyz = np.stack([i % 50, i // 50 % 50, i // 2500], axis=1) * 2 + np.stack([k // 4, k // 2 % 2, k % 2], axis=1)
+    coords = torch.from_numpy(np.concatenate([np.zeros((n, 1), dtype=np.int64), xyz], axis=1).astype(np.int32)).to("cuda:0")
+    f = torch.from_numpy(synth.features(n, 256, "f16", n)).to("cuda:0").half()
+    w = torch.from_numpy(synth.weights(8, 256, 256, "f16", n)).to("cuda:0").half()
+    want = torch.empty((n, 256), dtype=torch.float64, device="cuda:0")
+    for o in range(8):
+        want[o::8] = f[o::8].double() @ w[o].double()
+    down = sc.LayerBuffers(n, 2, 2, "strided", 256, 256, "f16", "f32", device="cuda:0")
+    down.kmap_build(coords, standalone=True)
+    got = torch.full((n, 256), float("nan"), dtype=torch.float32, device="cuda:0")
+    if way == "down":
+        down.feat_out.fill_(float("nan"))
+        down.conv_fwd(f, w)
+        got = down.feat_out[:n]
+    else:
+        inverse = torch.empty(sc.sc_kmap_bytes(n, 2, 2, "inverse"), dtype=torch.uint8, device="cuda:0")
+        sc.sc_kmap_transpose(down.kmap, n, 2, 2, down.counts, inverse)
+        sc.sc_conv_fwd(f, w, got, inverse, down.counts, 2, 2, "inverse", down.workspace, n_map=n)
+    assert float((got.double() - want).abs().max() / want.abs().max()) <= 1e-5            # sums of 256 products in 32 bits
