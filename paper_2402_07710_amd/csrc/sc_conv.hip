@@ -84,12 +84,7 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
     const int tiles = (int)((n_out + TILE - 1) / TILE), eighth = (tiles + NUM_XCD - 1) / NUM_XCD;
     const int first = (int)(blockIdx.x % NUM_XCD) * eighth, share = tiles - first < eighth ? tiles - first : eighth;
     const int turn = (int)(blockIdx.x / NUM_XCD);
-    // tiles per workgroup of the round that starts with `done` of the share
-    auto per_workgroup = [&](int done) -> int {
-        const int each = (share - done + team - 1) / team;
-        return each < NT ? each : NT;
-    };
-    int done = 0, each = share > 0 ? per_workgroup(0) : 0;
+    int done = 0, each = share > 0 ? tiles_per_workgroup(share, team, NT) : 0;
     if (turn * each >= share) return;                  // no tile: the whole workgroup, before any barrier
 
     // packed weights land in LDS beside everything up to the gathers, which wait for the lines behind them
@@ -256,7 +251,7 @@ k_conv_rows16(const uint16_t* __restrict__ feat, const uint4* __restrict__ wraw,
         }
         done += team * each;
         if (!LOOP || done >= share) break;
-        each = per_workgroup(done);
+        each = tiles_per_workgroup(share - done, team, NT);
     }
     SC_MARK(4);
     SC_MARK(5);

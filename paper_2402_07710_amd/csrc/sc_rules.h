@@ -158,6 +158,15 @@ constexpr bool dense_tiles_first(int64_t tiles, int64_t workgroups, bool two_at_
     return 4 * workgroups > (two_at_a_time ? 5 : 8) * cus && density_wanted(tiles, cus);
 }
 
+// The resident kernels: tiles that a workgroup of a round takes when `left` (at least one) are left for `team` workgroups: as few as give all their share, `most` at most.  A
+// division, in front of everything a workgroup does, cost 0.15 us (us of the convolution, K = 2, packed weights, with it and without: 32 -> 32 sweeps 80 k / 110 k 4.44 / 4.70 and 4.23 / 4.52, indoor
+// 200 k 5.15 and 4.99, random cells 100 k 5.85 and 5.60; 32 -> 64 30 k / 110 k / 200 k 4.02 / 6.81 / 9.20 and 3.89 / 6.65 / 8.95).
+constexpr int tiles_per_workgroup(int left, int team, int most) {
+    int each = 1;
+    for (int t = 1; t < most; ++t) each += left > t * team ? 1 : 0;
+    return each;
+}
+
 // Workgroups of the general kernel, tiles times blocks of output channels: a launch takes fewer than 2^32 threads along x, which 2^20
 // tiles (SC_N_MAX rows) of 8 blocks and 512 threads are not.  Past GRID_COLUMNS they go on in the next row of the grid, workgroup by workgroup.
 constexpr int64_t GRID_COLUMNS = 1 << 22;

@@ -72,3 +72,16 @@ static_assert(one_block_of_256(448, 27, SUBMANIFOLD, 256) && !one_block_of_256(4
 static_assert(one_block_of_256(384, 8, INVERSE, 256) && !one_block_of_256(385, 27, INVERSE, 256) && one_block_of_256(96, 8, INVERSE, 64), "inverse maps");
 static_assert(one_block_of_256(512, 27, CELLS, 256) && !one_block_of_256(513, 27, CELLS, 256) && one_block_of_256(512, 8, CELLS, 256), "K == stride");
 static_assert(one_block_of_256(512, 125, SUBMANIFOLD, 256) && !one_block_of_256(513, 125, OVERLAPPING, 256) && one_block_of_256(512, 64, INVERSE, 256), "K > 3");
+
+// the resident kernels' shares: a division rounded up, up to the most that a workgroup takes
+constexpr bool shares_are_quotients() {
+    const int teams[] = {1, 8, 31, 32, 38};
+    for (int most = 2; most <= 4; most += 2)
+        for (int team : teams)
+            for (int left = 1; left <= 6 * team; ++left) {
+                const int quotient = (left + team - 1) / team;
+                if (tiles_per_workgroup(left, team, most) != (quotient < most ? quotient : most)) return false;
+            }
+    return true;
+}
+static_assert(shares_are_quotients(), "tiles per workgroup");
