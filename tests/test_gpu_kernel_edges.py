@@ -91,10 +91,10 @@ def test_streaming_kernel_32_to_64_channels(stride, n):
 
 
 @pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457),
-                                          (3, 2, 32, 32_640), (3, 2, 32, 32_705)])
+                                          (3, 2, 32, 32_640), (3, 2, 32, 32_705), (3, 2, 32, 64 * 512 + 1), (3, 2, 32, 64 * 1024), (3, 2, 32, 64 * 1024 + 1)])
 def test_packed_square_layers_of_the_resident_kernel(K, stride, C, n):
-    """Packed weights: 9 tiles per CU of 256 and one row more; 510 and 512 tiles of strided layers, the
-    last that take two tiles per workgroup."""
+    """Packed weights: 9 tiles per CU of 256 and one row more; strided layers up to 512 tiles and beyond 1,024, which take up to two tiles per
+    workgroup, and between, up to four."""
     say(f"packed K={K} s={stride} {C}->{C} n={n}")
     import oracle
     import torch
@@ -116,10 +116,12 @@ def test_packed_square_layers_of_the_resident_kernel(K, stride, C, n):
     assert err <= 1e-5, err
 
 
-@pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457)])
+@pytest.mark.parametrize("K,stride,C,n", [(3, 1, 32, 147_457), (3, 2, 32, 147_457), (2, 2, 64, 147_457),
+                                          (3, 2, 32, 64 * 512), (3, 2, 32, 64 * 512 + 1), (3, 2, 32, 64 * 1024), (3, 2, 32, 64 * 1024 + 1)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_packed_and_raw_weights_agree_bit_for_bit(K, stride, C, n, dtype):
-    """The resident kernel with packed weights and with raw ones, which it lays out itself, 9 tiles per CU (of 256) and more."""
+    """The resident kernel with packed weights and with raw ones, which it lays out itself: 9 tiles per CU (of 256) and more, and
+    strided layers at the ends of the range that takes four tiles per workgroup."""
     say(f"packed and raw K={K} s={stride} {C}->{C} {dtype} n={n}")
     import torch
     from paper_2402_07710_amd import binding as sc
@@ -775,10 +777,12 @@ def test_two_sets_of_wavefronts_beyond_27_offsets(K, stride, C_in, C_out, n, dty
 
 
 @pytest.mark.parametrize("K,stride,C_in,C_out,n", [(3, 2, 64, 64, 64 * 600), (3, 1, 64, 64, 64 * 600), (5, 1, 32, 32, 64 * 600), (3, 2, 128, 128, 64 * 300), (2, 2, 64, 128, 64 * 300),
-                                                   (5, 2, 32, 64, 64 * 600), (4, 2, 64, 64, 64 * 321), (3, 1, 64, 64, 64 * 300), (3, 1, 64, 64, 64 * 3073)])
+                                                   (5, 2, 32, 64, 64 * 600), (4, 2, 64, 64, 64 * 321), (3, 1, 64, 64, 64 * 300), (3, 1, 64, 64, 64 * 3073),
+                                                   (3, 1, 32, 64, 64 * 3329), (3, 2, 32, 64, 64 * 1793), (3, 1, 128, 128, 64 * 5121), (2, 2, 128, 128, 64 * 5121)])
 def test_capacity_of_the_output_leaves_the_bits_of_a_row(K, stride, C_in, C_out, n):
     """Layers on both sides of the line for two sets of wavefronts: the first rows alone, in a buffer small enough for the other
-    side, are the whole layer's rows bit for bit, with raw and with packed weights.  The last map is too large to say how dense its tiles are."""
+    side, are the whole layer's rows bit for bit, with raw and with packed weights.  A map too large to say how dense its tiles are; and the
+    sizes from which the streaming kernel takes the whole layer and the general one its first rows."""
     say(f"capacity K={K} s={stride} {C_in}->{C_out} n={n}")
     import torch
     from paper_2402_07710_amd import binding as sc
@@ -788,7 +792,7 @@ def test_capacity_of_the_output_leaves_the_bits_of_a_row(K, stride, C_in, C_out,
     feat, weight = to_dev(synth.features(n, C_in, "f16", 4), "f16"), to_dev(synth.weights(K ** 3, C_in, C_out, "f16", 4), "f16")
     buf = sc.LayerBuffers(n, K, stride, mode, C_in, C_out, "f16", "f32", device="cuda:0")
     buf.layer(coords, feat, weight)
-    some = torch.full((64 * (100 if n < 100_000 else 1000) + 5, C_out), float("nan"), dtype=torch.float32, device="cuda:0")
+    some = torch.full((64 * (100 if n < 100_000 else 900) + 5, C_out), float("nan"), dtype=torch.float32, device="cuda:0")
     assert int(buf.read_counts().n_out) >= len(some)
     sc.sc_conv_fwd(feat, weight, some, buf.kmap, buf.counts, K, stride, mode, buf.workspace)
     assert torch.equal(some, buf.feat_out[:len(some)])
