@@ -192,7 +192,9 @@ size_t sc_kmap_scratch_bytes(int64_t n, int K, int stride, int mode);
  *                 tile-major: 64 consecutive output rows per tile, offset-major inside a tile,
  *                 plus one bit per (16-row group, offset) that tells whether the group has any
  *                 neighbour there (strided maps: K^3 > 32 only) and, K == stride <= 4, every
- *                 input's output row and offset.  Read it with sc_kmap_export; feed it to sc_conv_fwd (any
+ *                 input's output row and offset; submanifold maps, K > 1, have a byte per tile for how
+ *                 many offsets it takes part in (only the order in which a layer takes its tiles
+ *                 follows from it).  Read it with sc_kmap_export; feed it to sc_conv_fwd (any
  *                 number of times: layers that share coordinates share the map).
  *   d_scratch     scratch_bytes >= sc_kmap_scratch_bytes(...); contents undefined afterwards.
  *   d_counts      n_out is written here (device side); errors are latched into status. */

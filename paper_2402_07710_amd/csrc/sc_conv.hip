@@ -708,6 +708,9 @@ static int launch_resident(int K3, int C_in, int C_out, int64_t tiles, int64_t l
     if (K3 == 27 && C_in == 32 && C_out == 32 && likely > 2 * cus && likely <= 4 * cus) SC_ROWS16(27, 1, 2, 4);
     if (K3 == 27 && C_in == 32 && C_out == 32) SC_ROWS16(27, 1, 2, 2);
     if constexpr (!FUSED) {
+        // 32 -> 64: up to four tiles and all rounds in one workgroup against a workgroup per two tiles (us of the convolution, packed weights, sweeps 2 k / 30 k / 53 k / 80 k / 110 k / 150 k / 200 k 4.3 /
+        // 4.6 / 4.9 / 6.0 / 6.3 / 8.2 / 9.0 with two, now 3.8 / 3.9 / 4.5 / 5.4 / 6.6 / 8.1 / 8.9, indoor 53 k / 200 k / 600 k 5.0 / 6.9 / 17.3 and 4.1 / 7.3 / 15.9, random cells 20 k / 100 k 4.9 / 8.9 and 4.6 / 9.0): shares of three
+        // tiles, as 110 k sweep and 200 k indoor rows give, leave a quarter of the CUs without any.  Two tiles and the loop 6.1 at 80 k and 18.2 indoor, four without it 9.7 at 150 k.
         if (K3 == 8 && C_in == 32 && C_out == 64) SC_ROWS16(8, 1, 4, 4);
         if (K3 == 8 && C_in == 32 && C_out == 32) SC_ROWS16(8, 1, 2, 2);
         if (K3 == 8 && C_in == 64 && C_out == 64) SC_ROWS16(8, 2, 4, 4);
@@ -751,6 +754,8 @@ static int launch_up(int K3, int C_in, int C_out, int64_t tiles, hipStream_t s, 
     *handled = true;
 #define SC_UP16(K3V, KSV, CBV, NTV) \
     return launch_rows16<DT, K3V, KSV, CBV, NTV, 0, 1>(tiles, s, feat, wp, out, out_f32, ms, counts, n_out_cap)
+    // 64 -> 32, a workgroup per two tiles and now: 30 k / 80 k / 110 k / 150 k / 200 k / 260 k 5.1 / 7.0 / 7.5 / 9.8 / 10.6 / 13.0 and 4.9 / 6.4 / 7.9 / 9.4 / 10.2 / 12.5, indoor 200 k / 600 k 8.9 / 20.5 and 9.3 / 18.0, random
+    // cells 100 k 8.7 and 8.9; four tiles without the loop 7.4 at 110 k, but 10.9 at 150 k
     if (K3 == 8 && C_in == 64 && C_out == 32) SC_UP16(8, 2, 2, 4);
     if (K3 == 8 && C_in == 32 && C_out == 32) SC_UP16(8, 1, 2, 2);
     if (K3 == 8 && C_in == 64 && C_out == 64) SC_UP16(8, 2, 4, 4);

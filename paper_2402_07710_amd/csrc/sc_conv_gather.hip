@@ -51,7 +51,7 @@ constexpr int LIST_PAD = 12;                            // places of the list pa
 // like the others (of offset 0, rows of zeros); the operands of an offset are read together, then the
 // multiplies tested (whole layers K = 5 32 -> 32 on 2 k / 53 k voxels and 32 -> 64 on 110 k: 30.0 / 63.4 / 116 us; with SKIP
 // 31.0 / 64.5 / 121, with zeroed weights instead of the test 30.3 / 64.2 / 120, all of a step's operands first 29.4 / 63.2 / 120).
-// FROM_TABLE (fused layers): there is no kernel map; the four wavefronts look up every fourth of the 27 offsets of the tile's rows in the
+// FROM_TABLE (fused layers): there is no kernel map; the four (two sets: eight) wavefronts look up every fourth (eighth) of the 27 offsets of the tile's rows in the
 // dense location table and leave entries and votes in LDS (7 KB).  Whole fused layers on 2 k / 53 k / 262 k voxels, against
 // the kernels that gave a wavefront 64 rows: 64 -> 64 21.2 / 33.6 / 95 -> 17.6 / 30.0 / 81 us, 64 -> 128 38.9 / 46.6 / 124 ->
 // 17.8 / 40.0 / 108, 128 -> 128 88.7 / 93.9 / 193 -> 22.4 / 55.3 / 160.
@@ -131,7 +131,7 @@ k_conv_gather(const void* feat, const void* wp, void* __restrict__ out, int out_
         for (int g = 0; g < 4; ++g) only |= (gmask[tile * 4 + g] & 1u) << g;       // submanifold: the map has masks
         only = __builtin_amdgcn_readfirstlane(only);
     } else if constexpr (FUSED) {
-        // lane = row; each wavefront looks up every fourth offset, its part of the masks is a vote
+        // lane = row; each wavefront looks up every fourth offset (two sets: every eighth), its part of the masks is a vote
         uint32_t* votes = reinterpret_cast<uint32_t*>(found + LINES * WAVES * TILE);
         int32_t part[LINES];
         grid_neighbours_part<3, WAVES>(ms, tile * TILE + lane, n_out, wave, part);

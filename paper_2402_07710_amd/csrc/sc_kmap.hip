@@ -382,7 +382,9 @@ __device__ inline uint64_t candidate_key(const int4* __restrict__ coords, const 
 // full.  `fresh`: this call claimed it; `ousted`: the id that stood there until this call's smaller one took its place, or -1.  A slot is one word, the smallest id seen of its cell: which cell
 // that is follows from the id's coordinates, so claiming a cell is a single compare-and-swap.  It is not preceded by a read: most entries that
 // come here, merged by workgroup, are their cell's first, and for them that was a round trip more (us of whole layers on sweeps, with the read and without:
-// K = 3, stride 2 2 k / 53 k / 120 k / 200 k 21.9 / 38.8 / 63.5 / 92.0 and 21.2 / 37.8 / 61.6 / 88.6, K = 2 10 k / 200 k 16.3 / 30.0 and 15.6 / 28.9; indoor 200 k 73.9 and 72.2).
+// K = 3, stride 2 2 k / 53 k / 120 k / 200 k 21.9 / 38.8 / 63.5 / 92.0 and 21.2 / 37.8 / 61.6 / 88.6, K = 2 10 k / 200 k 16.3 / 30.0 and 15.6 / 28.9; indoor 200 k 73.9 and 72.2;
+// builds alone, sweep 53 k, indoor 53 k and random 20 k: K = 4, stride 2 44.8, 38.6, 49.3 and 44.2, 37.2, 47.9; K = 5, stride 2 80.2, 82.2, 77.4 and 79.9, 78.9, 76.9, stride 3 43.6, 42.6, 47.6 and 43.0, 41.4, 45.6;
+// K = 7, stride 2 198, 194, 306 and 197, 175, 306, stride 3 93.9, 102, 87.6 and 93.7, 96.0, 86.8).
 template <class Shape>
 __device__ inline int32_t claim_cell(int32_t* oslots, uint32_t omask, const int4* __restrict__ coords, const Shape& sh, uint64_t key,
                                      int32_t id, bool& fresh, int32_t& ousted) {

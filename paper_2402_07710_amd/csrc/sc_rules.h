@@ -148,12 +148,14 @@ constexpr bool density_wanted(int64_t tiles, int64_t cus) { return 4 * tiles > c
 // times as long as one with 9, which is what most tiles of a sweep have, and the dispatcher deals workgroups to the CUs in turn: in the order of the rows,
 // 110 k rows 64 -> 64, a CU gets 48 to 159 offsets (93 on average) and the last dense tile starts when most others are done.  Finding the tile is a round trip,
 // about 0.6 us a workgroup, in front of all others.  From two workgroups per CU on (1 1/4 where LDS holds no more than two at a time), up to
-// 12 tiles per CU; beyond, sweeps gain less than sets without sparse tiles lose, and how dense a set is is not known here.  us of whole layers, in the
-// order of the rows / dense first, sweeps: 64 -> 64 14 k 20.7 / 21.3, 30 k 24.1 / 24.2, 40 k 27.1 / 26.1, 53 k 32.6 / 32.5, 70 k 37.6 / 36.3, 110 k 51.7 / 48.5, 200 k 87.4 / 84.9,
-// 262 k 113 / 111.5, 400 k 163 / 161; 32 -> 64 53 k 27.7 / 26.9, 80 k 33.9 / 32.4; 128 -> 128 53 k 55.1 / 49.1, 262 k 200 / 191; 256 -> 256 4 k 32.9 / 33.8, 6 k 36.7 / 35.5,
-// 8 k 41.8 / 36.4, 14 k 58.0 / 49.3; fp32 64 -> 64 4 k 25.2 / 25.9, 8 k 31.3 / 31.7, 12 k 35.9 / 33.1, 53 k 88.7 / 76.9; K = 5 32 -> 32 30 k 42.8 / 43.4, 53 k 58.7 / 56.1, 64 -> 64
-// 60 k 81.9 / 76.9.  Indoor, 64 -> 64 50 k 31.5 / 31.7, 100 k 52.4 / 53.0, 200 k 92.5 / 93.3, 400 k 178 / 180, 10^6 430 / 438; 128 -> 128 100 k 104.3 / 105.4, 260 k 252 / 256; K = 5 32 -> 32
-// 53 k 56.9 / 56.5.  Random cells 64 -> 64 60 k 35.3 / 35.7.
+// 12 tiles per CU; beyond, sweeps gain less than sets without sparse tiles lose, and how dense a set is is not known here.  Sets whose tiles are all alike
+// pay for the look-up and gain nothing: up to 4 % of a layer, 1 % to 11 % of the convolution.  us of whole layers, in the order of the rows / dense first, sweep, indoor and random rows (means of three
+// sets): 64 -> 64 36 k 26.7 / 25.8 and 28.4 / 29.0, 53 k 32.5 / 31.7, 33.9 / 34.8 and 33.9 / 34.3, 70 k 37.8 / 36.3 and 39.8 / 40.8, 100 k 45.3 / 42.1 and 51.9 / 52.3, 150 k 60.9 / 58.9 and 67.2 / 68.4, 190 k 72.5 / 70.2 and
+// 82.6 / 83.4; 32 -> 64 36 k 22.3 / 21.8 and 23.4 / 23.8, 53 k 27.4 / 26.6, 28.0 / 28.8 and 30.7 / 31.6, 150 k 52.1 / 50.8 and 54.1 / 55.6; 64 -> 128 20 k 23.9 / 23.0, 25.7 / 26.4 and 22.7 / 23.1, 53 k 39.8 / 37.4, 46.9 / 48.1 and
+// 39.4 / 40.2; 128 -> 128 20 k 31.8 / 30.4, 35.8 / 36.5 and 26.9 / 27.2, 53 k 54.2 / 48.0, 68.1 / 69.4 and 46.3 / 47.4, 100 k 85.3 / 73.5 and 102.6 / 104.3, 150 k 110.7 / 106.1 and 144.2 / 145.8; 128 -> 256 53 k 75.9 / 64.4 and
+// 98.9 / 100.6; 256 -> 256 6 k 36.4 / 35.1 and 40.3 / 40.4, 8 k 42.0 / 36.9 and 43.0 / 42.9, 14 k 60.2 / 48.9, 67.1 / 69.7 and 38.6 / 40.3, 53 k 121.7 / 104.3 and 177.5 / 182.4; fp32 64 -> 64 12 k 34.3 / 32.2 and 39.4 / 40.0, 53 k
+// 86.8 / 73.7 and 121.8 / 122.4, 110 k 154.2 / 144.3 and 226.7 / 227.7; K = 5 32 -> 32 40 k 46.2 / 46.6 and 48.1 / 49.4, 53 k 56.9 / 56.0 and 56.9 / 56.5, 100 k 87.9 / 81.7 and 88.4 / 88.1, 64 -> 64 53 k 72.3 / 71.6 and 79.7 / 77.8, 100 k
+// 113.3 / 98.2 and 127.2 / 125.2.  Below the line, one set of rows: 64 -> 64 14 k 20.7 / 21.3, 30 k 24.1 / 24.2, 256 -> 256 4 k 32.9 / 33.8; above it 262 k 113 / 111.5 and, indoor, 400 k 178 / 180.
 constexpr bool dense_tiles_first(int64_t tiles, int64_t workgroups, bool two_at_a_time, int64_t cus) {
     return 4 * workgroups > (two_at_a_time ? 5 : 8) * cus && density_wanted(tiles, cus);
 }
