@@ -636,9 +636,9 @@ def test_shifted_delta_weights(dtype, C_in, C_out, n):
 
 
 def test_resident_kernel_with_four_tiles_per_workgroup_fp32_output():
-    """32 -> 32 channels on >= 512 tiles takes the NT = 4 form of the resident kernel: held to
+    """32 -> 32 channels on 513 to 1,024 tiles (256 CUs) take the NT = 4 form of the resident kernel: held to
     the oracle with fp32 output (only the order of summation differs: 1e-5)."""
-    say("32->32, 512+ tiles, fp32 output")
+    say("32->32, 625 tiles, fp32 output")
     coords = synth.lidar_scene(4)[:40000]
     err = check_layer(coords, 3, 1, "subm", 32, 32, "f16", seed=4, out_dtype="f32", threads=16)
     assert err <= 1e-5
